@@ -560,6 +560,27 @@ static void add_f32(Pool& pool, DCsr& a, hipStream_t s) {
   setup::cast_f32(a.nnz, a.v, a.vf, s);
 }
 
+// The layout that the solve phase reads a matrix in: diagonal slices where
+// the pattern keeps to diagonals, else packed columns and the operand tiles
+// of its row blocks of rb rows.  Slices replace row blocks of 32 rows up
+// only: their order of summation follows the row-block form, and below
+// 32768 rows that form has fewer rows than that in a block (one row per
+// thread would leave most of the chip idle there).  try_slices is false for
+// matrices that have no diagonals by construction (transfer operators,
+// Galerkin products), which saves looking.
+static void solve_layout(Pool& pool, DCsr& a, int cap, bool try_slices, bool f32, hipStream_t s) {
+  const int rb = solve::rows_per_block(a, cap, true);
+  if (try_slices && rb >= 32 && solve::rows_per_block(a, solve::ROWS_CAP_F64, true) >= 32) {
+    setup::build_slices(pool, a, s);
+    if (a.dia_w) {
+      setup::alloc_slice_values(pool, a, f32);
+      return;
+    }
+  }
+  setup::pack_columns(pool, a, s);
+  setup::build_tiles(pool, a, rb, s);
+}
+
 static solve::ChebCoef cheb_coef(const hbgs_options& o, double lam) {
   solve::ChebCoef c{};
   c.degree = o.cheb_degree;
@@ -753,21 +774,19 @@ static void build_hierarchy(hbgs_ctx* c, Field& F, hipStream_t s) {
     Level& L = F.lv[l];
     add_f32(pool, L.A, s);
     setup::row_stats(L.A, s);
-    setup::pack_columns(pool, L.A, s);
-    setup::build_tiles(pool, L.A, solve::rows_per_block(L.A, solve::ROWS_CAP_F32, true), s);
+    solve_layout(pool, L.A, solve::ROWS_CAP_F32, l == 0, true, s);
+    setup::fill_slices(L.A, s);
     if (l + 1 < F.lv.size()) {
       add_f32(pool, L.P, s);
       add_f32(pool, L.R, s);
       setup::row_stats(L.P, s);
       setup::row_stats(L.R, s);
-      setup::pack_columns(pool, L.P, s);
+      solve_layout(pool, L.P, solve::ROWS_CAP_F32, false, true, s);
       setup::pack_columns(pool, L.R, s);
-      setup::build_tiles(pool, L.P, solve::rows_per_block(L.P, solve::ROWS_CAP_F32, true), s);
       if (L.Q.n) {
         add_f32(pool, L.Q, s);
         setup::row_stats(L.Q, s);
-        setup::pack_columns(pool, L.Q, s);
-        setup::build_tiles(pool, L.Q, solve::rows_per_block(L.Q, solve::ROWS_CAP_F32, true), s);
+        solve_layout(pool, L.Q, solve::ROWS_CAP_F32, false, true, s);
       }
     }
     const int n = L.A.n;
@@ -895,8 +914,8 @@ static void build_field_T(hbgs_ctx* c, Field& F, hipStream_t s) {
   F.upperT = extract(pool, c->ApT, F.lo, F.hi, bj ? ghi : F.hi, ghi, glo, ghi - glo, s);
   add_f32(pool, F.upperT, s);
   setup::row_stats(F.upperT, s);
-  setup::pack_columns(pool, F.upperT, s);
-  setup::build_tiles(pool, F.upperT, solve::rows_per_block(F.upperT, solve::ROWS_CAP_F32, true), s);
+  solve_layout(pool, F.upperT, solve::ROWS_CAP_F32, true, true, s);
+  setup::fill_slices(F.upperT, s);
   if (F.leaf == 2) setup::ilu_transpose(pool, F.ilu, s);
   if (F.leaf == 0) {
     for (size_t l = 0; l < F.lv.size(); ++l) {
@@ -905,6 +924,8 @@ static void build_field_T(hbgs_ctx* c, Field& F, hipStream_t s) {
       L.AT.v = pool.make<double>(L.A.nnz);
       setup::transpose_symmetric(L.A, L.AT.v, s);
       add_f32(pool, L.AT, s);
+      setup::alloc_slice_values(pool, L.AT, true);  // the pattern's slices, values of its own
+      setup::fill_slices(L.AT, s);
       if (L.Q.n) {  // A_l^T P_l for the adjoint's fused prolongation (same pattern as A_l P_l)
         DCsr ATP;
         Pool tmp_pool{Pool::FromScratch{}};
@@ -947,8 +968,8 @@ static void build_field(hbgs_ctx* c, Field& F, hipStream_t s) {
   F.lower = extract(c->hier, c->Ap, F.lo, F.hi, glo, bj ? glo : F.lo, glo, ghi - glo, s);
   add_f32(c->hier, F.lower, s);
   setup::row_stats(F.lower, s);
-  setup::pack_columns(c->hier, F.lower, s);
-  setup::build_tiles(c->hier, F.lower, solve::rows_per_block(F.lower, solve::ROWS_CAP_F32, true), s);
+  solve_layout(c->hier, F.lower, solve::ROWS_CAP_F32, true, true, s);
+  setup::fill_slices(F.lower, s);
   F.td = c->hier.make<double>(F.n());
   F.tf = c->hier.make<float>(F.n());
   HBGS_HIP(hipStreamSynchronize(s));
@@ -996,7 +1017,8 @@ static void build_rest_T(hbgs_ctx* c, hipStream_t s) {
     g.upperT = extract(c->hier, c->ApT, g.lo, g.hi, bj ? c->n : g.hi, c->n, 0, c->n, s);
     for (DCsr* a : {&g.AT, &g.upperT}) {
       setup::row_stats(*a, s);
-      setup::pack_columns(c->hier, *a, s);
+      solve_layout(c->hier, *a, solve::ROWS_CAP_F64, true, false, s);
+      setup::fill_slices(*a, s);
     }
   }
   field_deps(c, 1, s);
@@ -1095,7 +1117,8 @@ static void build_values(hbgs_ctx* c, hipStream_t s) {
     g.lower = extract(c->hier, c->Ap, g.lo, g.hi, 0, bj ? 0 : g.lo, 0, c->n, s);
     for (DCsr* a : {&g.A, &g.lower}) {
       setup::row_stats(*a, s);
-      setup::pack_columns(c->hier, *a, s);
+      solve_layout(c->hier, *a, solve::ROWS_CAP_F64, true, false, s);
+      setup::fill_slices(*a, s);
     }
   }
   field_deps(c, 0, s);
@@ -1581,6 +1604,7 @@ __global__ void k_pos_int(int64_t nnz, const double* pos, int* posT) {
 static void gather_apt(hbgs_ctx* c, hipStream_t s) {
   k_gather_vals<<<grid_for(c->nnz, 256), 256, 0, s>>>(c->nnz, c->Ap.v, c->posT, c->ApT.v);
   HBGS_HIP(hipGetLastError());
+  setup::fill_slices(c->ApT, s);
   c->apt_fresh = true;
 }
 
@@ -1750,13 +1774,13 @@ hbgs_status hbgs_setup(hbgs_ctx** out, int32_t n, int64_t nnz, const int32_t* ro
     c->posT = c->pool.make<int>(nnz);
     k_pos_int<<<grid_for(nnz, 256), 256, 0, s>>>(nnz, c->ApT.v, c->posT);
     HBGS_HIP(hipGetLastError());
-    if (c->o.build_transpose) gather_apt(c, s);  // else on first use
   }
-  setup::row_stats(c->Ap, s);
-  setup::row_stats(c->ApT, s);
-  setup::pack_columns(c->pool, c->Ap, s);
-  setup::pack_columns(c->pool, c->ApT, s);
-  for (DCsr* a : {&c->Ap, &c->ApT}) setup::build_tiles(c->pool, *a, solve::rows_per_block(*a, solve::ROWS_CAP_F64, true), s);
+  for (DCsr* a : {&c->Ap, &c->ApT}) {
+    setup::row_stats(*a, s);
+    solve_layout(c->pool, *a, solve::ROWS_CAP_F64, true, false, s);
+  }
+  setup::fill_slices(c->Ap, s);
+  if (c->o.build_transpose) gather_apt(c, s);  // else on first use
   build_values(c, s);
   c->stats.setup_seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
   *out = c;
@@ -1787,6 +1811,7 @@ hbgs_status hbgs_set_values(hbgs_ctx* c, const double* val, int32_t rebuild_hier
   if (!rebuild_hierarchy && !c->hier_t) ensure_transpose(c, s);
   k_gather_vals<<<grid_for(c->nnz, 256), 256, 0, s>>>(c->nnz, val, c->src, c->Ap.v);
   HBGS_HIP(hipGetLastError());
+  setup::fill_slices(c->Ap, s);
   c->apt_fresh = false;
   if (c->o.build_transpose) gather_apt(c, s);
   if (rebuild_hierarchy) {

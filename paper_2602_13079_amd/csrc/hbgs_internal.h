@@ -217,10 +217,27 @@ struct DCsr {
   int tile_rb = 0, tile_cnt = 0;
   int* tiles = nullptr;
   uint16_t* lc = nullptr;
+  // diagonal slices (dia_w = 0: not built), for matrices whose rows keep to
+  // a few diagonals, as grid stencils and their couplings do: slice q is the
+  // DIA_ROWS rows from DIA_ROWS q on; dia_tab[q * DIA_TS] is its number of
+  // diagonals (at most dia_w) and the entries after it their column - row,
+  // ascending; bit j of a row's mask says that the row has an entry on its
+  // slice's diagonal j (16-bit masks where dia_w <= 16).  That entry's value
+  // is dv / dvf[(q * dia_w + j) * DIA_ROWS + row % DIA_ROWS]; the places of
+  // absent entries hold 0
+  int dia_w = 0;
+  int* dia_tab = nullptr;
+  uint16_t* dia_m16 = nullptr;
+  uint32_t* dia_m32 = nullptr;
+  double* dv = nullptr;
+  float* dvf = nullptr;
   float avg_row() const { return n ? (float)nnz / (float)n : 0.f; }
 };
 constexpr int TILE_W = 64;    // operand entries per tile
 constexpr int TILE_MAX = 48;  // tiles per row block at most
+constexpr int DIA_ROWS = 64;  // rows per diagonal slice: one wavefront
+constexpr int DIA_MAX = 32;   // diagonals per slice at most (the mask's bits)
+constexpr int DIA_TS = 36;    // table entries per slice (count, diagonals, 16-byte multiple)
 
 
 // DD(0)-ILU(0) leaf of one field: factors on the subdomain-block pattern of
@@ -319,6 +336,13 @@ void row_stats(DCsr& a, hipStream_t s);
 // a.tile_rb = rb), or none (a.tile_rb = 0) where a block has more than
 // TILE_MAX tiles or more entries than one block's LDS staging holds
 void build_tiles(Pool& pool, DCsr& a, int rb, hipStream_t s);
+// the diagonal slices of a's pattern (a.dia_w, table and masks), or none
+// (a.dia_w = 0) where a slice has more than DIA_MAX diagonals or the slices
+// would hold more than 1.25 places per entry
+void build_slices(Pool& pool, DCsr& a, hipStream_t s);
+// the slices' values (new arrays) from a.v: FP64 always, FP32 when asked
+void alloc_slice_values(Pool& pool, DCsr& a, bool f32);
+void fill_slices(const DCsr& a, hipStream_t s);
 // DD(0)-ILU(0) of the n x n block a with subdomains of `sub` rows (factors,
 // transposed factors, schedules, FP32 copies); returns -4 on a zero pivot
 int ilu_setup(Pool& pool, const DCsr& a, int sub, IluLeaf& out, hipStream_t s);

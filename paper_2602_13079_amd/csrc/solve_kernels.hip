@@ -294,6 +294,74 @@ __global__ __launch_bounds__(SBLK) void k_csr_rows_tiled(int n, int m, const int
   }
 }
 
+// Diagonal slices, one row per thread: the slice's table (wave-uniform,
+// scalar loads) gives the columns, so the values and the operand are read
+// with unit-stride loads that wait on nothing but the table and the row's
+// mask, and neither column indices (2-4 B per entry) nor LDS passes are
+// left.  The sums are those of the row-block kernels: products rounded
+// before they are added (no contraction), and NACC = lanes per row of the
+// row-block form partial sums that take the row's entries in turn; they are
+// kept in rotation, which pairs them as that form's shuffles do, since the
+// sums of a pair commute.  Absent places are skipped by the mask: their
+// operand may be out of range or not finite.
+// Bound by memory: at 1,048,576 rows a finest FP32 pass moves 31-48 MB
+// against 43-62 MB for the tiled row blocks (no columns, no row pointers) in
+// 8.8-10.7 us against 12.7-15.1; the outer product of the 4.2M-row system
+// 340 MB against 479 MB in 63 us (5.4 TB/s; a plain copy reaches 6.1)
+// against 81; at 262,144 rows 3.6-4.7 us against 4.8-6.4.
+template <int NACC, class TM, class TV, class TACC, class TX, class Epi>
+__global__ __launch_bounds__(BLK) void k_slices(int n, int w, const int* __restrict__ tab,
+                                                const TM* __restrict__ mask, const TV* __restrict__ v,
+                                                const TX* __restrict__ x, Epi epi) {
+#pragma clang fp contract(off)
+  constexpr int CH = 8;  // places whose loads are issued together
+  const int row = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+  if (row >= n) return;
+  const int q = __builtin_amdgcn_readfirstlane(row / DIA_ROWS);
+  const int* t = tab + (size_t)q * DIA_TS;
+  const typename Epi::Pre pre = epi.load(row);
+  const uint32_t m = mask[row];
+  const int cnt = t[0];
+  const TV* vs = v + (size_t)q * w * DIA_ROWS + (row & (DIA_ROWS - 1));
+  TACC acc[NACC];
+#pragma unroll
+  for (int a = 0; a < NACC; ++a) acc[a] = 0;
+  for (int j0 = 0; j0 < cnt; j0 += CH) {
+    TV a[CH];
+    TX b[CH];
+#pragma unroll
+    for (int u = 0; u < CH; ++u) {
+      const int j = j0 + u;
+      if (j < cnt) {
+        a[u] = vs[(size_t)j * DIA_ROWS];
+        b[u] = x[m >> j & 1u ? row + t[1 + j] : 0];
+      } else {
+        a[u] = TV(0);
+        b[u] = TX(0);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < CH; ++u) {
+      const int j = j0 + u;
+      const bool on = j < DIA_MAX && (m >> (j & (DIA_MAX - 1)) & 1u);
+      const TACC p = (TACC)a[u] * (TACC)b[u];
+      if constexpr (NACC == 1) {
+        acc[0] = acc[0] + (on ? p : TACC(0));
+      } else {
+        const TACC s = acc[0] + p;
+#pragma unroll
+        for (int c = 0; c + 1 < NACC; ++c) acc[c] = on ? acc[c + 1] : acc[c];
+        acc[NACC - 1] = on ? s : acc[NACC - 1];
+      }
+    }
+  }
+#pragma unroll
+  for (int off = NACC / 2; off > 0; off >>= 1)
+#pragma unroll
+    for (int c = 0; c < off; ++c) acc[c] = acc[c] + acc[c + off];
+  epi.store(row, acc[0], pre);
+}
+
 template <class T>
 struct LoadArr;
 template <class L>
@@ -304,7 +372,7 @@ template <class T>
 struct load_arr_elem<LoadArr<T>> {
   using type = T;
 };
-static bool g_tiles_on = true;  // the LDS-staged operand where a matrix has tiles
+static bool g_tiles_on = true;  // slices, and the LDS-staged operand, where a matrix has them
 void set_tiles(bool on) { g_tiles_on = on; }
 
 int rows_per_block(const DCsr& a, int cap, bool vec) {
@@ -410,10 +478,53 @@ static void launch_csr_cols(const DCsr& a, Col col, const TV* v, LoadX lx, Epi e
   HBGS_HIP(hipGetLastError());
 }
 
+template <class TV>
+static const TV* slice_vals(const DCsr& a);
+template <>
+const double* slice_vals<double>(const DCsr& a) {
+  return a.dv;
+}
+template <>
+const float* slice_vals<float>(const DCsr& a) {
+  return a.dvf;
+}
+
+template <int NACC, class TM, class TV, class TACC, class TX, class Epi>
+static void launch_slices(const DCsr& a, const TM* mask, const TX* x, Epi epi, hipStream_t s, hipEvent_t e0,
+                          hipEvent_t e1) {
+  const unsigned grid = (unsigned)(((int64_t)a.n + BLK - 1) / BLK);
+  const TV* v = slice_vals<TV>(a);
+  if (e0)
+    hipExtLaunchKernelGGL(k_slices<NACC, TM, TV, TACC, TX, Epi>, dim3(grid), dim3(BLK), 0, s, e0, e1, 0, a.n, a.dia_w,
+                          a.dia_tab, mask, v, x, epi);
+  else
+    k_slices<NACC, TM, TV, TACC, TX, Epi><<<grid, BLK, 0, s>>>(a.n, a.dia_w, a.dia_tab, mask, v, x, epi);
+  HBGS_HIP(hipGetLastError());
+}
+
 template <class TV, class TACC, class LoadX, class Epi>
 static void launch_csr(const DCsr& a, const TV* v, LoadX lx, Epi epi, hipStream_t s, hipEvent_t e0 = nullptr,
                        hipEvent_t e1 = nullptr) {
   if (a.n == 0) return;
+  using TX = typename load_arr_elem<LoadX>::type;
+  if constexpr (!std::is_void<TX>::value) {
+    if (a.dia_w && g_tiles_on && slice_vals<TV>(a)) {
+      const int rb = rows_per_block(a, ROWS_LDS_BYTES / (int)sizeof(TACC), true);
+#define HBGS_SLICES(RB)                                                                            \
+  if (rb == RB) {                                                                                  \
+    if (a.dia_m16)                                                                                 \
+      launch_slices<SBLK / RB, uint16_t, TV, TACC>(a, a.dia_m16, lx.x, epi, s, e0, e1);            \
+    else                                                                                           \
+      launch_slices<SBLK / RB, uint32_t, TV, TACC>(a, a.dia_m32, lx.x, epi, s, e0, e1);            \
+    return;                                                                                        \
+  }
+      HBGS_SLICES(256)
+      HBGS_SLICES(128)
+      HBGS_SLICES(64)
+      HBGS_SLICES(32)
+#undef HBGS_SLICES
+    }
+  }
   if (a.nnz == 0) {  // rows without entries: epilogue of an empty sum
     if (e0) HBGS_HIP(hipEventRecord(e0, s));
     k_empty<TACC, Epi><<<grid_for(a.n, 256), 256, 0, s>>>(a.n, epi);
