@@ -328,15 +328,13 @@ struct Field {
   int n() const { return hi - lo; }
 };
 
-// Concurrent field V-cycles: a field's sweep step (coupling + V-cycle) only
-// reads the z of the fields its coupling rows reference, so independent
-// fields run on separate streams; events carry the dependencies.
+// The sweep's stages: a field's step (coupling + V-cycle) only reads the z of
+// the fields its coupling rows reference, so the fields whose couplings are
+// all satisfied by earlier stages form one stage.  A stage's fields advance
+// together in the same launches on one stream.
 struct SweepPlan {
-  std::vector<int> order;   // fields in visiting order
-  std::vector<int> stream;  // stream slot per position
-  int nstreams = 1;
+  std::vector<std::vector<int>> stage;  // fields, in visiting order within a stage
 };
-constexpr int MAX_SWEEP_STREAMS = 4;
 
 // one captured GMRES iteration (key: precision, transpose, column j)
 struct IterGraph {
@@ -440,11 +438,10 @@ struct hbgs_ctx {
   std::vector<hbgs::Group> G;
   hbgs::Profiler prof;
   hbgs_stats_t stats{};
-  // concurrent sweep
   hbgs::SweepPlan plan[2];
-  hipStream_t fstream[hbgs::MAX_SWEEP_STREAMS] = {};
-  hipEvent_t fdone[HBGS_MAX_FIELDS] = {};
-  hipEvent_t fork = nullptr;
+  // ILU leaves run on a stream of their own beside a stage's V-cycles
+  hipStream_t side = nullptr;
+  hipEvent_t fork = nullptr, side_done = nullptr;
   // concurrent setup: one stream per field
   hipStream_t sstream[HBGS_MAX_FIELDS] = {};
   hipEvent_t setup_in = nullptr;
@@ -462,11 +459,9 @@ struct hbgs_ctx {
     if (sm) (void)hipStreamDestroy(sm);
     if (join_in) (void)hipEventDestroy(join_in);
     if (join_out) (void)hipEventDestroy(join_out);
-    for (auto& st : fstream)
-      if (st) (void)hipStreamDestroy(st);
-    for (auto& e : fdone)
-      if (e) (void)hipEventDestroy(e);
+    if (side) (void)hipStreamDestroy(side);
     if (fork) (void)hipEventDestroy(fork);
+    if (side_done) (void)hipEventDestroy(side_done);
     for (auto& st : sstream)
       if (st) (void)hipStreamDestroy(st);
     if (setup_in) (void)hipEventDestroy(setup_in);
@@ -862,31 +857,23 @@ static void compute_stats(hbgs_ctx* c) {
   }
 }
 
-// Stream slots for the sweep: a field continues the stream of the latest
-// field (in visiting order) it depends on; a field without dependencies
-// starts the next free slot.
+// The stages of a sweep over `leaves` (reversed for the adjoint).
 static void plan_sweep(hbgs_ctx* c, const std::vector<int>& leaves, int tr, SweepPlan& p) {
   const int nl = (int)leaves.size();
-  p.order.clear();
-  p.stream.clear();
-  p.nstreams = 0;
-  std::vector<int> slot_of(c->nf, -1);
+  p.stage.clear();
+  std::vector<int> at(c->nf, -1);
   for (int q = 0; q < nl; ++q) {
-    int f = leaves[tr ? nl - 1 - q : q];
-    int slot = -1;
-    for (int k = q - 1; k >= 0 && slot < 0; --k)
-      if (c->F[f].deps[tr] >> p.order[k] & 1u) slot = slot_of[p.order[k]];
-    if (slot < 0) slot = p.nstreams < MAX_SWEEP_STREAMS ? p.nstreams++ : q % MAX_SWEEP_STREAMS;
-    slot_of[f] = slot;
-    p.order.push_back(f);
-    p.stream.push_back(slot);
+    const int f = leaves[tr ? nl - 1 - q : q];
+    int k = 0;
+    for (int g = 0; g < c->nf; ++g)
+      if ((c->F[f].deps[tr] >> g & 1u) && at[g] >= 0) k = std::max(k, at[g] + 1);
+    at[f] = k;
+    if ((int)p.stage.size() <= k) p.stage.resize(k + 1);
+    p.stage[k].push_back(f);
   }
-  if (p.nstreams == 0) p.nstreams = 1;
-  for (int k = 0; k < MAX_SWEEP_STREAMS; ++k)
-    if (!c->fstream[k]) HBGS_HIP(hipStreamCreateWithFlags(&c->fstream[k], hipStreamNonBlocking));
-  for (int f = 0; f < c->nf; ++f)
-    if (!c->fdone[f]) HBGS_HIP(hipEventCreateWithFlags(&c->fdone[f], hipEventDisableTiming));
+  if (!c->side) HBGS_HIP(hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking));
   if (!c->fork) HBGS_HIP(hipEventCreateWithFlags(&c->fork, hipEventDisableTiming));
+  if (!c->side_done) HBGS_HIP(hipEventCreateWithFlags(&c->side_done, hipEventDisableTiming));
   if (!c->sm) HBGS_HIP(hipStreamCreateWithFlags(&c->sm, hipStreamNonBlocking));
   if (!c->join_in) HBGS_HIP(hipEventCreateWithFlags(&c->join_in, hipEventDisableTiming));
   if (!c->join_out) HBGS_HIP(hipEventCreateWithFlags(&c->join_out, hipEventDisableTiming));
@@ -1168,77 +1155,159 @@ static int lk(int kind, int l) {
   }
 }
 
+// one field's V-cycle: z = V(t)
 template <class T>
-static void vcycle(hbgs_ctx* c, Field& F, int l, int tr, const T* b, T* x, hipStream_t s) {
+struct VcField {
+  Field* F;
+  const T* b;
+  T* x;
+};
+
+// Kernel-class bytes of a step over several jobs
+template <class T, class F>
+static double sum_bytes(const solve::LevelJob<T>* j, int nj, F f) {
+  double b = 0;
+  for (int q = 0; q < nj; ++q) b += f(j[q]);
+  return b;
+}
+
+// The V-cycles of independent fields from level l down and back, every step
+// in shared launches.  Fields may differ in depth, degree and coarsest
+// solver: the dense coarsest solves that a level meets are collected in
+// `dense` and launched with those of the deepest level.
+template <class T>
+static void vcycle(hbgs_ctx* c, const VcField<T>* v, int nv, int l, int tr, solve::DenseJob<T>* dense, int* nd,
+                   hipStream_t s) {
   using B = Buf<T>;
+  using J = solve::LevelJob<T>;
+  using Ops = VcOps<T>;
   const int TS = (int)sizeof(T);
-  Level& L = F.lv[l];
-  const int n = L.A.n;
-  const bool coarsest = l + 1 == (int)F.lv.size();
-  if (coarsest && F.inv) {
-    Prof p(c->prof, s, solve::K_COARSE, 8.0 * n * n + 2.0 * n * TS);
-    VcOps<T>::coarse(n, tr ? F.invT : F.inv, 0, b, x, s);
-    return;
-  }
-  const DCsr& A = tr ? L.AT : L.A;
-  const T* dinv = B::dinv(L);
-  const solve::ChebCoef& cc = L.cc;
-  T *r = B::r(L), *d = B::d(L), *dn = B::dn(L);
+  J j[HBGS_MAX_FIELDS];
+  VcField<T> next[HBGS_MAX_FIELDS];
+  int nj = 0, nn = 0;  // levels smoothed here; of those, the first nn have a next level
+  for (int pass = 0; pass < 2; ++pass)
+    for (int q = 0; q < nv; ++q) {
+      Field& F = *v[q].F;
+      Level& L = F.lv[l];
+      const bool coarsest = l + 1 == (int)F.lv.size();
+      if (coarsest != (pass == 1)) continue;
+      if (coarsest && F.inv) {
+        dense[(*nd)++] = {L.A.n, tr ? F.invT : F.inv, v[q].b, v[q].x};
+        continue;
+      }
+      J& k = j[nj++];
+      k = {};
+      k.A = tr ? &L.AT : &L.A;
+      k.dinv = B::dinv(L);
+      k.cc = &L.cc;
+      k.b = v[q].b;
+      k.x = v[q].x;
+      k.r = B::r(L);
+      k.d = B::d(L);
+      k.dn = B::dn(L);
+      if (coarsest) continue;
+      Level& C = F.lv[l + 1];
+      const bool d0c = smoothed_level(F, l + 1) && C.cc.degree == 2;
+      const DCsr& Q = tr ? L.QT : L.Q;
+      k.P = &L.P;
+      k.R = &L.R;
+      k.Q = Q.n ? &Q : nullptr;
+      k.bc = B::b(C);
+      k.xc = B::x(C);
+      k.dinv_c = d0c ? B::dinv(C) : nullptr;
+      k.c0_c = C.cc.c0;
+      k.d0_c = d0c ? B::d(C) : nullptr;
+      next[nn++] = {&F, k.bc, k.xc};
+    }
+  // the first m jobs for which pred holds, in one call
+  auto select = [&](int m, auto&& pred, auto&& f) {
+    J sel[HBGS_MAX_FIELDS];
+    int ns = 0;
+    for (int k = 0; k < m; ++k)
+      if (pred(j[k])) sel[ns++] = j[k];
+    if (ns) f((const J*)sel, ns);
+  };
+  int most = 0;
+  for (int q = 0; q < nj; ++q) most = std::max(most, j[q].cc->degree);
+  // Chebyshev steps of the first m jobs: before (every degree but 2, whose
+  // one step pre2 includes) or after the coarse correction
+  auto steps = [&](int m, bool post) {
+    for (int k = 1; k < most; ++k) {
+      auto has = [&](const J& w) { return w.cc->degree > k && (post || w.cc->degree != 2); };
+      for (int keep = 1; keep >= 0; --keep)
+        select(m, [&](const J& w) { return has(w) && (k + 1 < w.cc->degree) == (keep != 0); },
+               [&](const J* w, int n) {
+                 Prof p(c->prof, s, lk(keep || !post ? solve::K_CHEB_OTHER : solve::K_CHEB_POST_B, l),
+                        sum_bytes(w, n, [&](const J& x) {
+                          return spmv_bytes(*x.A, TS, TS, post ? TS : 3 * TS, post ? 3 : 2);
+                        }));
+                 Ops::step(w, n, k, post && k == 1, keep != 0, s);
+               });
+      for (int t = 0; t < m; ++t)
+        if (has(j[t])) std::swap(j[t].d, j[t].dn);
+    }
+  };
   // pre-smoothing from a zero guess (degree 2: d0 was written by the
   // producer of b into this level's d buffer)
-  if (cc.degree == 2) {
-    Prof p(c->prof, s, lk(solve::K_CHEB_PRE, l), spmv_bytes(A, TS, TS, TS, 2));
-    VcOps<T>::pre2(A, dinv, cc, b, d, x, s);
-  } else {
+  select(nj, [](const J& k) { return k.cc->degree == 2; }, [&](const J* w, int n) {
+    Prof p(c->prof, s, lk(solve::K_CHEB_PRE, l),
+           sum_bytes(w, n, [&](const J& x) { return spmv_bytes(*x.A, TS, TS, TS, 2); }));
+    Ops::pre2(w, n, s);
+  });
+  select(nj, [](const J& k) { return k.cc->degree != 2; }, [&](const J* w, int n) {
+    Prof p(c->prof, s, lk(solve::K_CHEB_OTHER, l), 4.0 * TS * sum_bytes(w, n, [](const J& x) { return (double)x.A->n; }));
+    Ops::init0(w, n, s);
+  });
+  steps(nj, false);
+  if (nn > 0) {  // a smoothed coarsest level: the polynomial from zero only
     {
-      Prof p(c->prof, s, lk(solve::K_CHEB_OTHER, l), 4.0 * n * TS);
-      VcOps<T>::init0(n, dinv, cc, b, r, d, x, s);
+      Prof p(c->prof, s, lk(solve::K_RESID, l),
+             sum_bytes(j, nn, [&](const J& x) { return spmv_bytes(*x.A, TS, TS, TS, 1); }));
+      Ops::resid(j, nn, s);
     }
-    for (int k = 1; k < cc.degree; ++k) {
-      Prof p(c->prof, s, lk(solve::K_CHEB_OTHER, l), spmv_bytes(A, TS, TS, 3 * TS, 2));
-      VcOps<T>::step(A, dinv, cc, k, false, k + 1 < cc.degree, r, d, dn, x, s);
-      std::swap(d, dn);
+    {
+      Prof p(c->prof, s, lk(solve::K_RESTRICT, l),
+             sum_bytes(j, nn, [&](const J& x) { return spmv_bytes(*x.R, TS, TS, TS, x.d0_c ? 2 : 0); }));
+      Ops::restrict_(j, nn, s);
     }
+    vcycle<T>(c, next, nn, l + 1, tr, dense, nd, s);
+  } else if (*nd > 0) {  // no field goes deeper: the coarsest solves met so far
+    double b = 0;
+    for (int q = 0; q < *nd; ++q) b += 8.0 * dense[q].n * dense[q].n + 2.0 * dense[q].n * TS;
+    Prof p(c->prof, s, solve::K_COARSE, b);
+    Ops::coarse(dense, *nd, s);
+    *nd = 0;
   }
-  if (coarsest) return;  // a smoothed coarsest level: the polynomial from zero only
-  {
-    Prof p(c->prof, s, lk(solve::K_RESID, l), spmv_bytes(A, TS, TS, TS, 1));
-    VcOps<T>::resid(A, b, x, r, s);
-  }
-  Level& C = F.lv[l + 1];
-  {
-    const bool d0c = smoothed_level(F, l + 1) && C.cc.degree == 2;
-    Prof p(c->prof, s, lk(solve::K_RESTRICT, l), spmv_bytes(L.R, TS, TS, TS, d0c ? 2 : 0));
-    VcOps<T>::restrict_(L.R, r, B::b(C), d0c ? B::dinv(C) : nullptr, C.cc.c0, d0c ? B::d(C) : nullptr, s);
-  }
-  vcycle<T>(c, F, l + 1, tr, B::b(C), B::x(C), s);
+  if (nn == 0) return;
   // coarse correction and the post-smoother's start: x += P xc, r = b - A x,
   // d = D^-1 r / theta, in one pass over [A P; P] from the residual r of
   // before the correction (r - A P xc = b - A (x + P xc))
-  d = B::d(L);
-  dn = B::dn(L);
-  const DCsr& Q = tr ? L.QT : L.Q;
-  if (Q.n) {
-    Prof p(c->prof, s, lk(solve::K_CHEB_POST_A, l), spmv_bytes(Q, TS, TS, TS, 2));
-    VcOps<T>::post_q(Q, dinv, cc, B::x(C), r, x, d, s);
-  } else {
+  for (int t = 0; t < nn; ++t) {
+    Level& L = next[t].F->lv[l];
+    j[t].d = B::d(L);
+    j[t].dn = B::dn(L);
+  }
+  select(nn, [](const J& k) { return k.Q != nullptr; }, [&](const J* w, int n) {
+    Prof p(c->prof, s, lk(solve::K_CHEB_POST_A, l),
+           sum_bytes(w, n, [&](const J& x) { return spmv_bytes(*x.Q, TS, TS, TS, 2); }));
+    Ops::post_q(w, n, s);
+  });
+  select(nn, [](const J& k) { return k.Q == nullptr; }, [&](const J* w, int n) {
     {
-      Prof p(c->prof, s, lk(solve::K_PROLONG, l), spmv_bytes(L.P, TS, TS, TS, 1));
-      VcOps<T>::prolong(L.P, B::x(C), x, s);
+      Prof p(c->prof, s, lk(solve::K_PROLONG, l),
+             sum_bytes(w, n, [&](const J& x) { return spmv_bytes(*x.P, TS, TS, TS, 1); }));
+      Ops::prolong(w, n, s);
     }
-    Prof p(c->prof, s, lk(solve::K_CHEB_POST_A, l), spmv_bytes(A, TS, TS, 2 * TS, 2));
-    VcOps<T>::post_start(A, dinv, cc, b, x, r, d, s);
-  }
-  if (cc.degree == 1) {
-    Prof p(c->prof, s, lk(solve::K_CHEB_OTHER, l), 3.0 * n * TS);
-    VcOps<T>::add(n, d, x, s);
-  }
-  for (int k = 1; k < cc.degree; ++k) {
-    bool keep = k + 1 < cc.degree;
-    Prof p(c->prof, s, lk(keep ? solve::K_CHEB_OTHER : solve::K_CHEB_POST_B, l), spmv_bytes(A, TS, TS, TS, 3));
-    VcOps<T>::step(A, dinv, cc, k, k == 1, keep, r, d, dn, x, s);
-    std::swap(d, dn);
-  }
+    Prof p(c->prof, s, lk(solve::K_CHEB_POST_A, l),
+           sum_bytes(w, n, [&](const J& x) { return spmv_bytes(*x.A, TS, TS, 2 * TS, 2); }));
+    Ops::post_start(w, n, s);
+  });
+  for (int t = 0; t < nn; ++t)
+    if (j[t].cc->degree == 1) {
+      Prof p(c->prof, s, lk(solve::K_CHEB_OTHER, l), 3.0 * j[t].A->n * TS);
+      Ops::add(j[t].A->n, j[t].d, j[t].x, s);
+    }
+  steps(nn, true);
 }
 
 // z = M^-1 (v / vs) (tr = 0) or M^-T (v / vs) (tr = 1) over the fields of
@@ -1246,70 +1315,89 @@ static void vcycle(hbgs_ctx* c, Field& F, int l, int tr, const T* b, T* x, hipSt
 // v[F.lo - base ..]); z has type T; vs is a device scalar (null: 1)
 template <class T>
 static void sweep(hbgs_ctx* c, const SweepPlan& plan, int tr, const double* v, T* z, int base, const double* vs,
-                  hipStream_t s0) {
-  const int nl = (int)plan.order.size();
+                  hipStream_t s) {
   const int TS = (int)sizeof(T);
   double plan_bytes = 0;
-  for (int f : plan.order) plan_bytes += c->F[f].bytes[TS == 4 ? 1 : 0];
-  Prof whole(c->prof, s0, solve::K_SWEEP, plan_bytes);
-  HBGS_HIP(hipEventRecord(c->fork, s0));
-  for (int k = 0; k < plan.nstreams; ++k) HBGS_HIP(hipStreamWaitEvent(c->fstream[k], c->fork, 0));
-  std::vector<int> slot_of(c->nf, -1);
-  for (int q = 0; q < nl; ++q) {
-    Field& F = c->F[plan.order[q]];
-    const int slot = plan.stream[q];
-    hipStream_t s = c->fstream[slot];
-    for (int k = 0; k < q; ++k) {
-      int g = plan.order[k];
-      if ((F.deps[tr] >> g & 1u) && slot_of[g] != slot) HBGS_HIP(hipStreamWaitEvent(s, c->fdone[g], 0));
-    }
-    slot_of[F.id] = slot;
-    const DCsr& cpl = tr ? F.upperT : F.lower;
-    const int off = F.lo - base;
-    Level& L0 = F.lv[0];
-    // the finest level's first Chebyshev direction is formed with its rhs
-    const bool d0 = F.leaf == 0 && smoothed_level(F, 0) && L0.cc.degree == 2;
-    const T* dinv0 = d0 ? Buf<T>::dinv(L0) : nullptr;
-    T* d00 = d0 ? Buf<T>::d(L0) : nullptr;
-    if (F.leaf == 1) {  // z = D^-1 t straight from the coupling / cast epilogue
-      const T* dinv = Buf<T>::dinv(L0);
-      T* zf = z + off;
-      Prof p(c->prof, s, solve::K_COUPLE, (cpl.nnz ? spmv_bytes(cpl, TS, 0, TS, 2) : 0.0) + (8.0 + 2 * TS) * F.n());
-      if (cpl.nnz > 0)
-        VcOps<T>::couple(cpl, v + off, z, Buf<T>::t(F), dinv, 1.0, zf, vs, s);
-      else if (sizeof(T) == sizeof(double) && !vs)
-        VcOps<T>::make_d0(F.n(), reinterpret_cast<const T*>(v + off), dinv, 1.0, zf, s);
-      else
-        VcOps<T>::cast_in(F.n(), v + off, Buf<T>::t(F), dinv, 1.0, zf, vs, s);
-      HBGS_HIP(hipEventRecord(c->fdone[F.id], s));
-      continue;
-    }
-    const T* t;
-    if (cpl.nnz > 0) {
-      Prof p(c->prof, s, solve::K_COUPLE,
-             spmv_bytes(cpl, TS, 0, TS, d0 ? 2 : 0) + 8.0 * F.n() + (double)std::min<int64_t>(cpl.nnz, c->n) * TS);
-      VcOps<T>::couple(cpl, v + off, z, Buf<T>::t(F), dinv0, L0.cc.c0, d00, vs, s);
-      t = Buf<T>::t(F);
-    } else if (sizeof(T) == sizeof(double) && !vs) {
-      t = reinterpret_cast<const T*>(v + off);
-      if (d0) {
-        Prof p(c->prof, s, solve::K_COUPLE, 3.0 * F.n() * TS);
-        VcOps<T>::make_d0(F.n(), t, dinv0, L0.cc.c0, d00, s);
+  for (auto& st : plan.stage)
+    for (int f : st) plan_bytes += c->F[f].bytes[TS == 4 ? 1 : 0];
+  Prof whole(c->prof, s, solve::K_SWEEP, plan_bytes);
+  for (auto& st : plan.stage) {
+    // right-hand sides; the finest level's first Chebyshev direction is
+    // formed with its rhs, a Jacobi leaf's z = D^-1 t likewise
+    solve::RhsJob<T> cpl[HBGS_MAX_FIELDS], cast[HBGS_MAX_FIELDS];
+    VcField<T> amg[HBGS_MAX_FIELDS];
+    solve::IluJob<T> ilu[HBGS_MAX_FIELDS];
+    int nc = 0, nk = 0, na = 0, ni = 0;
+    double cpl_bytes = 0, cast_bytes = 0, ilu_bytes = 0;
+    for (int f : st) {
+      Field& F = c->F[f];
+      const DCsr& a = tr ? F.upperT : F.lower;
+      const int off = F.lo - base;
+      Level& L0 = F.lv[0];
+      const bool d0 = F.leaf == 0 && smoothed_level(F, 0) && L0.cc.degree == 2;
+      solve::RhsJob<T> r{F.n(), nullptr, v + off, Buf<T>::t(F), nullptr, 0.0, nullptr};
+      if (F.leaf == 1) {
+        r.dinv = Buf<T>::dinv(L0);
+        r.c0 = 1.0;
+        r.d0 = z + off;
+      } else if (d0) {
+        r.dinv = Buf<T>::dinv(L0);
+        r.c0 = L0.cc.c0;
+        r.d0 = Buf<T>::d(L0);
       }
-    } else {
-      Prof p(c->prof, s, solve::K_COUPLE, (8.0 + TS * (d0 ? 3 : 1)) * F.n());
-      VcOps<T>::cast_in(F.n(), v + off, Buf<T>::t(F), dinv0, L0.cc.c0, d00, vs, s);
-      t = Buf<T>::t(F);
+      const T* t = r.t;
+      if (a.nnz > 0) {
+        r.cpl = &a;
+        cpl_bytes += spmv_bytes(a, TS, 0, TS, r.d0 ? 2 : 0) + 8.0 * F.n() + (double)std::min<int64_t>(a.nnz, c->n) * TS;
+        cpl[nc++] = r;
+      } else {
+        bool want = true;
+        if (sizeof(T) == sizeof(double) && !vs) {  // v itself is the right-hand side
+          t = reinterpret_cast<const T*>(v + off);
+          r.t = nullptr;
+          want = r.d0 != nullptr;
+        }
+        if (want) {
+          cast_bytes += (8.0 + TS * (r.d0 ? 3 : 1)) * F.n();
+          cast[nk++] = r;
+        }
+      }
+      if (F.leaf == 0) amg[na++] = {&F, t, z + off};
+      if (F.leaf == 2) {
+        ilu_bytes += 2.0 * spmv_bytes(F.ilu.F, TS, TS, TS, 1);
+        ilu[ni++] = {&F.ilu, t, z + off};
+      }
     }
-    if (F.leaf == 2) {
-      Prof p(c->prof, s, solve::K_COARSE, 2.0 * spmv_bytes(F.ilu.F, TS, TS, TS, 1));
-      VcOps<T>::ilu(F.ilu, tr, t, z + off, s);
-    } else {
-      vcycle<T>(c, F, 0, tr, t, z + off, s);
+    if (nc) {
+      Prof p(c->prof, s, solve::K_COUPLE, cpl_bytes);
+      VcOps<T>::couple(cpl, nc, z, vs, s);
     }
-    HBGS_HIP(hipEventRecord(c->fdone[F.id], s));
+    if (nk) {
+      Prof p(c->prof, s, solve::K_COUPLE, cast_bytes);
+      VcOps<T>::cast_in(cast, nk, vs, s);
+    }
+    // ILU sweeps take one workgroup per subdomain: they leave room for the
+    // stage's V-cycles beside them
+    const bool beside = ni > 0 && na > 0;
+    if (ni) {
+      hipStream_t si = beside ? c->side : s;
+      if (beside) {
+        HBGS_HIP(hipEventRecord(c->fork, s));
+        HBGS_HIP(hipStreamWaitEvent(si, c->fork, 0));
+      }
+      {
+        Prof p(c->prof, si, solve::K_COARSE, ilu_bytes);
+        VcOps<T>::ilu(ilu, ni, tr, si);
+      }
+      if (beside) HBGS_HIP(hipEventRecord(c->side_done, si));
+    }
+    if (na) {
+      solve::DenseJob<T> dense[HBGS_MAX_FIELDS];
+      int nd = 0;
+      vcycle<T>(c, amg, na, 0, tr, dense, &nd, s);
+    }
+    if (beside) HBGS_HIP(hipStreamWaitEvent(s, c->side_done, 0));
   }
-  for (int q = 0; q < nl; ++q) HBGS_HIP(hipStreamWaitEvent(s0, c->fdone[plan.order[q]], 0));
 }
 
 // ------------------------------------------------------------------ GMRES
@@ -1559,7 +1647,8 @@ static void nested_apply(hbgs_ctx* c, int tr, const double* v, int j, const doub
       else
         solve::couple_f64<double>(cpl, v + g.lo, K.Zd + (size_t)j * K.ld, KG.bp, vs, s);
     } else if (vs) {
-      VcOps<double>::cast_in(g.n(), v + g.lo, KG.bp, nullptr, 0.0, nullptr, vs, s);
+      const solve::RhsJob<double> in{g.n(), nullptr, v + g.lo, KG.bp, nullptr, 0.0, nullptr};
+      VcOps<double>::cast_in(&in, 1, vs, s);
     } else {
       HBGS_HIP(hipMemcpyAsync(KG.bp, v + g.lo, sizeof(double) * g.n(), hipMemcpyDeviceToDevice, s));
     }
@@ -1572,9 +1661,10 @@ static void nested_apply(hbgs_ctx* c, int tr, const double* v, int j, const doub
     int32_t it = 0, hl = 0;
     (void)fgmres(c, KG, tr ? g.AT : g.A, prec, c->o.inner_rtol, c->o.inner_max_iters, 0, &it, nullptr, 0, &hl, -1,
                  s);
-    if (c->precision == 1)
-      VcOps<float>::cast_in(g.n(), KG.xp, K.Zf + (size_t)j * K.ld + g.lo, nullptr, 0.0, nullptr, nullptr, s);
-    else
+    if (c->precision == 1) {
+      const solve::RhsJob<float> out{g.n(), nullptr, KG.xp, K.Zf + (size_t)j * K.ld + g.lo, nullptr, 0.0, nullptr};
+      VcOps<float>::cast_in(&out, 1, nullptr, s);
+    } else
       HBGS_HIP(hipMemcpyAsync(K.Zd + (size_t)j * K.ld + g.lo, KG.xp, sizeof(double) * g.n(),
                               hipMemcpyDeviceToDevice, s));
   }

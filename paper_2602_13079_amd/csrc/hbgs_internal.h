@@ -223,9 +223,10 @@ struct DCsr {
   // diagonals (at most dia_w) and the entries after it their column - row,
   // ascending; bit j of a row's mask says that the row has an entry on its
   // slice's diagonal j (16-bit masks where dia_w <= 16).  That entry's value
-  // is dv / dvf[(q * dia_w + j) * DIA_ROWS + row % DIA_ROWS]; the places of
-  // absent entries hold 0
+  // is dv / dvf[(dia_tab[q * DIA_TS + DIA_BASE] + j) * DIA_ROWS + row %
+  // DIA_ROWS]; the places of absent entries hold 0; dia_places of them in all
   int dia_w = 0;
+  int64_t dia_places = 0;
   int* dia_tab = nullptr;
   uint16_t* dia_m16 = nullptr;
   uint32_t* dia_m32 = nullptr;
@@ -237,7 +238,9 @@ constexpr int TILE_W = 64;    // operand entries per tile
 constexpr int TILE_MAX = 48;  // tiles per row block at most
 constexpr int DIA_ROWS = 64;  // rows per diagonal slice: one wavefront
 constexpr int DIA_MAX = 32;   // diagonals per slice at most (the mask's bits)
-constexpr int DIA_TS = 36;    // table entries per slice (count, diagonals, 16-byte multiple)
+constexpr int DIA_TS = 36;    // table entries per slice (a 16-byte multiple)
+constexpr int DIA_BASE = 1;   // entry 0: count, DIA_BASE: first place / DIA_ROWS, DIA_DIAG on: diagonals
+constexpr int DIA_DIAG = 2;
 
 
 // DD(0)-ILU(0) leaf of one field: factors on the subdomain-block pattern of
@@ -417,46 +420,79 @@ template <class TZ>
 void couple_f64(const DCsr& a, const double* v, const TZ* z, double* t, const double* vs, hipStream_t s);
 void spmv_resid_f64(const DCsr& a, const double* x, const double* b, double* r, hipStream_t s);
 
+// What the passes of one field's level read and write.  The operations below
+// take several jobs (at most HBGS_MAX_FIELDS): the same step of independent
+// fields, put into as few launches as the matrices' kernel shapes allow.
+template <class T>
+struct LevelJob {
+  const DCsr *A, *P, *R, *Q;  // P, R, Q: null on the coarsest level; Q null where it was not built
+  const T* dinv;
+  const ChebCoef* cc;
+  const T* b;
+  T *x, *r, *d, *dn;
+  // the next level's right-hand side, solution and (degree 2) first direction
+  T *bc, *xc;
+  const T* dinv_c;
+  double c0_c;
+  T* d0_c;
+};
+// dense coarsest solve: x = inv b
+template <class T>
+struct DenseJob {
+  int n;
+  const double* inv;
+  const T* b;
+  T* x;
+};
+// right-hand side of a field: t = (T)(v / vs) - sum over coupling columns of
+// a * z (cpl null: no couplings); with d0 given also d0 = (D^-1 t) * c0 for
+// the field's finest level.  vs is a device scalar (null: 1) by which the
+// sweep's input is divided; t null: not wanted (no couplings only)
+template <class T>
+struct RhsJob {
+  int n;
+  const DCsr* cpl;
+  const double* v;
+  T* t;
+  const T* dinv;
+  double c0;
+  T* d0;
+};
+template <class T>
+struct IluJob {
+  const IluLeaf* f;
+  const T* t;
+  T* z;
+};
 template <class T>
 struct VcOps {
   // degree-2 pre-smoothing from a zero guess, one fused kernel, with the
-  // first direction d0 = D^-1 b / theta precomputed by the rhs producer:
-  // x = d0 + c1 d0 + c2 D^-1 (b - A d0)
-  static void pre2(const DCsr& a, const T* dinv, const ChebCoef& c, const T* b, const T* d0, T* x, hipStream_t s);
-  // d0 = (D^-1 b) / theta
-  static void make_d0(int n, const T* b, const T* dinv, double c0, T* d0, hipStream_t s);
+  // first direction d0 = D^-1 b / theta precomputed (in d) by the rhs
+  // producer: x = d0 + c1 d0 + c2 D^-1 (b - A d0)
+  static void pre2(const LevelJob<T>* j, int nj, hipStream_t s);
   // general degree, zero guess: r = b, d = D^-1 b / theta, x = d
-  static void init0(int n, const T* dinv, const ChebCoef& c, const T* b, T* r, T* d, T* x, hipStream_t s);
+  static void init0(const LevelJob<T>* j, int nj, hipStream_t s);
   // post-smoothing start from x: r = b - A x, d = D^-1 r / theta (x not yet updated)
-  static void post_start(const DCsr& a, const T* dinv, const ChebCoef& c, const T* b, const T* x, T* r, T* d,
-                         hipStream_t s);
+  static void post_start(const LevelJob<T>* j, int nj, hipStream_t s);
   // Chebyshev step k >= 1: r -= A d; dn = c1 d + c2 D^-1 r; x (+ d when add_d) += dn;
   // r and dn are stored only when keep
-  static void step(const DCsr& a, const T* dinv, const ChebCoef& c, int k, bool add_d, bool keep, T* r,
-                   const T* d, T* dn, T* x, hipStream_t s);
+  static void step(const LevelJob<T>* j, int nj, int k, bool add_d, bool keep, hipStream_t s);
   static void add(int n, const T* d, T* x, hipStream_t s);
-  static void resid(const DCsr& a, const T* b, const T* x, T* r, hipStream_t s);
+  static void resid(const LevelJob<T>* j, int nj, hipStream_t s);
   // bc = R r; when d0_c is given also d0_c = (Dc^-1 bc) * c0_c for the coarse level
-  static void restrict_(const DCsr& rmat, const T* r, T* bc, const T* dinv_c, double c0_c, T* d0_c,
-                        hipStream_t s);
-  static void prolong(const DCsr& p, const T* xc, T* x, hipStream_t s);
+  static void restrict_(const LevelJob<T>* j, int nj, hipStream_t s);
+  static void prolong(const LevelJob<T>* j, int nj, hipStream_t s);
   // prolongation fused with the post-smoother's start: with Q the rows of
   // A P (even) and P (odd) interleaved and r the residual b - A x from
   // before the coarse correction, one pass forms r = r - (A P) xc,
   // d = D^-1 r / theta and x = x + P xc, i.e. the residual and first
   // direction of the corrected x without re-reading A
-  static void post_q(const DCsr& q, const T* dinv, const ChebCoef& c, const T* xc, T* r, T* x, T* d,
-                     hipStream_t s);
-  static void coarse(int n, const double* inv, int transpose, const T* b, T* x, hipStream_t s);
-  static void ilu(const IluLeaf& f, int transpose, const T* t, T* z, hipStream_t s);
-  // t = (T)(v / vs) - sum over coupling columns of a * z, rows of one field;
-  // with d0 given also d0 = (D^-1 t) * c0 for the field's finest level.  vs
-  // is a device scalar (null: 1) by which the sweep's input is divided
-  static void couple(const DCsr& c, const double* v, const T* z, T* t, const T* dinv, double c0, T* d0,
-                     const double* vs, hipStream_t s);
-  // t = (T)(v / vs), and d0 as in couple
-  static void cast_in(int n, const double* v, T* t, const T* dinv, double c0, T* d0, const double* vs,
-                      hipStream_t s);
+  static void post_q(const LevelJob<T>* j, int nj, hipStream_t s);
+  static void coarse(const DenseJob<T>* j, int nj, hipStream_t s);
+  static void ilu(const IluJob<T>* j, int nj, int transpose, hipStream_t s);
+  // right-hand sides with couplings to z, and without
+  static void couple(const RhsJob<T>* j, int nj, const T* z, const double* vs, hipStream_t s);
+  static void cast_in(const RhsJob<T>* j, int nj, const double* vs, hipStream_t s);
 };
 
 // GMRES pieces (FP64)

@@ -2445,14 +2445,14 @@ void build_tiles(Pool& pool, DCsr& a, int rb, hipStream_t s) {
 // One wavefront per slice of 64 rows, one row per lane: the lanes walk their
 // rows' ascending entries together, each step taking the smallest pending
 // column - row of the slice as its next diagonal.  stat[0]: largest count,
-// stat[1]: a slice with more than DIA_MAX diagonals, stat[2]: places in all
-// (counted in slices of 64, at most n / 64 * DIA_MAX).
+// stat[1]: a slice with more than DIA_MAX diagonals.
 __global__ __launch_bounds__(256) void k_slice_diags(int n, const int* __restrict__ rp, const int* __restrict__ ci,
-                                                     int* __restrict__ tab, uint16_t* __restrict__ m16,
-                                                     uint32_t* __restrict__ m32, int* stat) {
+                                                     int* __restrict__ tab, int* __restrict__ count,
+                                                     uint16_t* __restrict__ m16, uint32_t* __restrict__ m32,
+                                                     int* stat) {
   const int nsl = (n + DIA_ROWS - 1) / DIA_ROWS;
   const int lane = threadIdx.x & 63;
-  int most = 0, places = 0, bad = 0;
+  int most = 0, bad = 0;
   for (int q = (int)blockIdx.x * 4 + (threadIdx.x >> 6); q < nsl; q += (int)gridDim.x * 4) {
     const int row = q * DIA_ROWS + lane;
     int k = row < n ? rp[row] : 0;
@@ -2472,23 +2472,24 @@ __global__ __launch_bounds__(256) void k_slice_diags(int n, const int* __restric
         mask |= 1u << cnt;
         ++k;
       }
-      if (lane == 0) t[1 + cnt] = lo;
+      if (lane == 0) t[DIA_DIAG + cnt] = lo;
       ++cnt;
     }
     if (bad) break;
-    if (lane == 0) t[0] = cnt;
+    if (lane == 0) t[0] = count[q] = cnt;
     if (row < n) {
       m16[row] = (uint16_t)mask;
       m32[row] = mask;
     }
     most = max(most, cnt);
-    places += cnt;
   }
   if (lane == 0) {
     if (bad) atomicOr(&stat[1], 1);
     if (most) atomicMax(&stat[0], most);
-    if (places) atomicAdd(&stat[2], places);
   }
+}
+__global__ void k_slice_base(int nsl, const int* __restrict__ base, int* __restrict__ tab) {
+  GRID_STRIDE(q, nsl) tab[(size_t)q * DIA_TS + DIA_BASE] = base[q];
 }
 void build_slices(Pool& pool, DCsr& a, hipStream_t s) {
   a.dia_w = 0;
@@ -2502,20 +2503,26 @@ void build_slices(Pool& pool, DCsr& a, hipStream_t s) {
   int* tab = pool.make<int>((size_t)nsl * DIA_TS);
   uint16_t* m16 = pool.make<uint16_t>(a.n);
   uint32_t* m32 = pool.make<uint32_t>(a.n);
-  Tmp<int> stat(3);
-  HBGS_HIP(hipMemsetAsync(stat.p, 0, 3 * sizeof(int), s));
-  k_slice_diags<<<grid_for((nsl + 3) / 4, 1, 2048), 256, 0, s>>>(a.n, a.rp, a.ci, tab, m16, m32, stat.p);
+  Tmp<int> stat(2), count(nsl), base(nsl + 1);
+  HBGS_HIP(hipMemsetAsync(stat.p, 0, 2 * sizeof(int), s));
+  k_slice_diags<<<grid_for((nsl + 3) / 4, 1, 2048), 256, 0, s>>>(a.n, a.rp, a.ci, tab, count.p, m16, m32, stat.p);
   HBGS_HIP(hipGetLastError());
-  int h[3] = {0, 0, 0};
+  int h[2] = {0, 0};
   HBGS_HIP(hipMemcpyAsync(h, stat.p, sizeof(h), hipMemcpyDeviceToHost, s));
   HBGS_HIP(hipStreamSynchronize(s));
-  const bool use = !h[1] && h[0] > 0 && (double)h[2] * DIA_ROWS <= 1.25 * (double)a.nnz;
+  bool use = !h[1] && h[0] > 0;
+  if (use) {
+    a.dia_places = counts_to_rowptr(count.p, base.p, nsl, s) * DIA_ROWS;
+    use = (double)a.dia_places <= 1.25 * (double)a.nnz;
+  }
   if (!use || h[0] <= 16) pool.release(m32);
   if (!use || h[0] > 16) pool.release(m16);
   if (!use) {
     pool.release(tab);
     return;
   }
+  k_slice_base<<<grid_for(nsl, 256), 256, 0, s>>>(nsl, base.p, tab);
+  HBGS_HIP(hipGetLastError());
   a.dia_w = h[0];
   a.dia_tab = tab;
   if (h[0] <= 16)
@@ -2526,12 +2533,11 @@ void build_slices(Pool& pool, DCsr& a, hipStream_t s) {
 
 void alloc_slice_values(Pool& pool, DCsr& a, bool f32) {
   if (!a.dia_w) return;
-  const size_t places = (size_t)((a.n + DIA_ROWS - 1) / DIA_ROWS) * a.dia_w * DIA_ROWS;
-  a.dv = pool.make<double>(places);
-  a.dvf = f32 ? pool.make<float>(places) : nullptr;
+  a.dv = pool.make<double>(a.dia_places);
+  a.dvf = f32 ? pool.make<float>(a.dia_places) : nullptr;
 }
 template <class TM>
-__global__ __launch_bounds__(256) void k_slice_fill(int n, int w, const int* __restrict__ rp,
+__global__ __launch_bounds__(256) void k_slice_fill(int n, const int* __restrict__ rp,
                                                     const double* __restrict__ v, const int* __restrict__ tab,
                                                     const TM* __restrict__ mask, double* __restrict__ dv,
                                                     float* __restrict__ dvf) {
@@ -2541,7 +2547,7 @@ __global__ __launch_bounds__(256) void k_slice_fill(int n, int w, const int* __r
   const int cnt = tab[(size_t)q * DIA_TS];
   const uint32_t m = row < n ? (uint32_t)mask[row] : 0u;
   int k = row < n ? rp[row] : 0;
-  const size_t base = (size_t)q * w * DIA_ROWS + row % DIA_ROWS;
+  const size_t base = (size_t)tab[(size_t)q * DIA_TS + DIA_BASE] * DIA_ROWS + row % DIA_ROWS;
   for (int j = 0; j < cnt; ++j) {
     const double x = m >> j & 1u ? v[k++] : 0.0;
     dv[base + (size_t)j * DIA_ROWS] = x;
@@ -2552,9 +2558,9 @@ void fill_slices(const DCsr& a, hipStream_t s) {
   if (!a.dia_w) return;
   const unsigned g = (unsigned)(((int64_t)a.n + 255) / 256);
   if (a.dia_m16)
-    k_slice_fill<uint16_t><<<g, 256, 0, s>>>(a.n, a.dia_w, a.rp, a.v, a.dia_tab, a.dia_m16, a.dv, a.dvf);
+    k_slice_fill<uint16_t><<<g, 256, 0, s>>>(a.n, a.rp, a.v, a.dia_tab, a.dia_m16, a.dv, a.dvf);
   else
-    k_slice_fill<uint32_t><<<g, 256, 0, s>>>(a.n, a.dia_w, a.rp, a.v, a.dia_tab, a.dia_m32, a.dv, a.dvf);
+    k_slice_fill<uint32_t><<<g, 256, 0, s>>>(a.n, a.rp, a.v, a.dia_tab, a.dia_m32, a.dv, a.dvf);
   HBGS_HIP(hipGetLastError());
 }
 

@@ -10,8 +10,8 @@
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
-#include <type_traits>
 
 #include "hbgs_internal.h"
 
@@ -80,16 +80,62 @@ __device__ __forceinline__ void load4(const double* p, double* w) {
   w[3] = b.y;
 }
 
-// acc = sum_k v[k] * X(ci[k]) over row `row`, then epi(row, acc)
-template <int LPR, class TV, class TACC, class Col, class LoadX, class Epi>
-__global__ __launch_bounds__(BLK) void k_csr(int n, const int* __restrict__ rp, Col ci, const TV* __restrict__ v,
-                                             LoadX lx, Epi epi) {
+// Up to MAXB jobs (the same operation on several fields' matrices) share one
+// launch: job q owns the blocks from first[q] on (UINT_MAX: no such job).
+// Independent fields' V-cycles advance together this way, in one stream:
+// their small levels fill the chip side by side, and neither events nor a
+// second stream's launches stand between a stage and the next.  Against one
+// stream per independent chain: the 1M-row mixed solve 5.27 -> 4.57 ms, the
+// 4,096-row apply 98 -> 60 us and FP64 solve 1.10 -> 0.67 ms, the 4.2M-row
+// solve 11.93 -> 11.82 ms.  Large levels share launches too: fields one after
+// the other on levels above 200 MB (so that a pass finds the previous one's
+// matrix in the last-level cache) ran 1% slower at 25M rows and for FP64
+// applies at 5.3M.
+constexpr int MAXB = 4;
+template <class D>
+struct Batch {
+  unsigned first[MAXB];
+  D d[MAXB];
+};
+// the job of this block (uniform) and the block's index within it
+template <class D>
+__device__ __forceinline__ const D& batch_job(const Batch<D>& b, int* blk) {
+  int q = 0;
+#pragma unroll
+  for (int k = 1; k < MAXB; ++k)
+    if (blockIdx.x >= b.first[k]) q = k;
+  *blk = (int)(blockIdx.x - b.first[q]);
+  return b.d[q];
+}
+
+// a CSR pass of one job: a's rows, the operand x and the rows' epilogue
+template <class Col, class TV, class TX, class Epi>
+struct CsrJob {
+  int n, vec;
+  const int* rp;
+  Col ci;
+  const TV* v;
+  const TX* x;
+  Epi epi;
+};
+
+// acc = sum_k v[k] * x[ci[k]] over row `row`, then epi(row, acc)
+template <int LPR, class TV, class TACC, class Col, class TX, class Epi>
+__global__ __launch_bounds__(BLK) void k_csr(const Batch<CsrJob<Col, TV, TX, Epi>> batch) {
+  int blk;
+  const auto& job = batch_job(batch, &blk);
+  const int n = job.n;
+  const int* __restrict__ rp = job.rp;
+  const Col ci = job.ci;
+  const TV* __restrict__ v = job.v;
+  const TX* __restrict__ x = job.x;
+  const Epi epi = job.epi;
   const int lane = threadIdx.x & (LPR - 1);
-  const int row = (int)(((int64_t)blockIdx.x * BLK + threadIdx.x) / LPR);
+  const int row = (int)(((int64_t)blk * BLK + threadIdx.x) / LPR);
   if (row >= n) return;
   const int s = rp[row], e = rp[row + 1];
   TACC acc = 0;
-  for (int k = s + lane; k < e; k += LPR) acc += (TACC)v[k] * (TACC)lx(ci(k));
+  for (int k = s + lane; k < e; k += LPR) acc += (TACC)v[k] * (TACC)x[ci(k)];
   if (LPR > 1) acc = lanes_sum<TACC>(acc, LPR);
   if (lane == 0) epi.store(row, acc, epi.load(row));
 }
@@ -114,13 +160,20 @@ static bool g_vec_entries = true;  // grouped entry loads where the arrays are a
 // column loads) over the block's 4-aligned entries, two groups per step,
 // single entries at the two ends; else two single entries per step.  The
 // products and their summation order are the same either way.
-template <int RB, class TV, class TACC, class Col, class LoadX, class Epi>
-__global__ __launch_bounds__(SBLK) void k_csr_rows(int n, const int* __restrict__ rp, Col ci,
-                                                   const TV* __restrict__ v, LoadX lx, Epi epi, int vec) {
+template <int RB, class TV, class TACC, class Col, class TX, class Epi>
+__global__ __launch_bounds__(SBLK) void k_csr_rows(const Batch<CsrJob<Col, TV, TX, Epi>> batch) {
+  int blk;
+  const auto& job = batch_job(batch, &blk);
+  const int n = job.n, vec = job.vec;
+  const int* __restrict__ rp = job.rp;
+  const Col ci = job.ci;
+  const TV* __restrict__ v = job.v;
+  const TX* __restrict__ x = job.x;
+  const Epi epi = job.epi;
   constexpr int LPR = RB >= SBLK ? 1 : SBLK / RB;  // lanes per row in the row sums
   constexpr int RPT = RB >= SBLK ? RB / SBLK : 1;  // rows per thread
   __shared__ TACC prod[ROWS_LDS_BYTES / sizeof(TACC)];
-  const int r0 = blockIdx.x * RB;
+  const int r0 = blk * RB;
   const int r1 = min(n, r0 + RB);
   const int lane = threadIdx.x & (LPR - 1);
   const int rbase = r0 + (int)threadIdx.x / LPR;
@@ -158,16 +211,16 @@ __global__ __launch_bounds__(SBLK) void k_csr_rows(int n, const int* __restrict_
       ci.load4(kb, c1);
       TACC x0[4], x1[4];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) x0[q] = (TACC)lx(c0[q]);
+      for (int q = 0; q < 4; ++q) x0[q] = (TACC)x[c0[q]];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) x1[q] = (TACC)lx(c1[q]);
+      for (int q = 0; q < 4; ++q) x1[q] = (TACC)x[c1[q]];
 #pragma unroll
       for (int q = 0; q < 4; ++q) prod[k4 + q - s0] = (TACC)w0[q] * x0[q];
       if (two)
 #pragma unroll
         for (int q = 0; q < 4; ++q) prod[k4b + q - s0] = (TACC)w1[q] * x1[q];
     }
-    const TACC xh = (TACC)lx(ch), xt = (TACC)lx(ct);
+    const TACC xh = (TACC)x[ch], xt = (TACC)x[ct];
     if (hh) prod[kh - s0] = (TACC)vh * xh;
     if (ht) prod[kt - s0] = (TACC)vt * xt;
   } else {
@@ -176,11 +229,11 @@ __global__ __launch_bounds__(SBLK) void k_csr_rows(int n, const int* __restrict_
     for (; k + SBLK < s1; k += 2 * SBLK) {
       const int c0 = ci(k), c1 = ci(k + SBLK);
       const TV w0 = v[k], w1 = v[k + SBLK];
-      const TACC x0 = (TACC)lx(c0), x1 = (TACC)lx(c1);
+      const TACC x0 = (TACC)x[c0], x1 = (TACC)x[c1];
       prod[k - s0] = (TACC)w0 * x0;
       prod[k + SBLK - s0] = (TACC)w1 * x1;
     }
-    if (k < s1) prod[k - s0] = (TACC)v[k] * (TACC)lx(ci(k));
+    if (k < s1) prod[k - s0] = (TACC)v[k] * (TACC)x[ci(k)];
   }
   __syncthreads();
 #pragma unroll
@@ -203,12 +256,27 @@ __global__ __launch_bounds__(SBLK) void k_csr_rows(int n, const int* __restrict_
 // column index.  The block's entries (at most 4 * SBLK * NG) are held in
 // registers across the barrier that publishes the tiles.  Same products,
 // LDS positions and row sums as k_csr_rows: bitwise the same result.
+template <class TV, class TX, class Epi>
+struct TiledJob {
+  int n, m, tcnt, prod_bytes;
+  const int* rp;
+  const uint16_t* lc;
+  const int* tiles;
+  const TV* v;
+  const TX* x;
+  Epi epi;
+};
 template <int RB, class TV, class TACC, class TX, class Epi>
-__global__ __launch_bounds__(SBLK) void k_csr_rows_tiled(int n, int m, const int* __restrict__ rp,
-                                                         const uint16_t* __restrict__ lc,
-                                                         const int* __restrict__ tiles, int tcnt,
-                                                         const TV* __restrict__ v, const TX* __restrict__ x,
-                                                         Epi epi, int prod_bytes) {
+__global__ __launch_bounds__(SBLK) void k_csr_rows_tiled(const Batch<TiledJob<TV, TX, Epi>> batch) {
+  int blk;
+  const auto& job = batch_job(batch, &blk);
+  const int n = job.n, m = job.m, tcnt = job.tcnt, prod_bytes = job.prod_bytes;
+  const int* __restrict__ rp = job.rp;
+  const uint16_t* __restrict__ lc = job.lc;
+  const int* __restrict__ tiles = job.tiles;
+  const TV* __restrict__ v = job.v;
+  const TX* __restrict__ x = job.x;
+  const Epi epi = job.epi;
   constexpr int LPR = RB >= SBLK ? 1 : SBLK / RB;
   constexpr int RPT = RB >= SBLK ? RB / SBLK : 1;
   constexpr int NG = (ROWS_LDS_BYTES / (int)sizeof(TACC)) / (4 * SBLK);  // groups of four per thread
@@ -217,7 +285,7 @@ __global__ __launch_bounds__(SBLK) void k_csr_rows_tiled(int n, int m, const int
   TACC* prod = reinterpret_cast<TACC*>(smem);
   TX* xs = reinterpret_cast<TX*>(smem + prod_bytes);
   const int t = (int)threadIdx.x;
-  const int b = (int)blockIdx.x;
+  const int b = blk;
   const int r0 = b * RB, r1 = min(n, r0 + RB);
   const int lane = t & (LPR - 1);
   const int rbase = r0 + t / LPR;
@@ -309,20 +377,35 @@ __global__ __launch_bounds__(SBLK) void k_csr_rows_tiled(int n, int m, const int
 // 8.8-10.7 us against 12.7-15.1; the outer product of the 4.2M-row system
 // 340 MB against 479 MB in 63 us (5.4 TB/s; a plain copy reaches 6.1)
 // against 81; at 262,144 rows 3.6-4.7 us against 4.8-6.4.
+template <class TM, class TV, class TX, class Epi>
+struct SliceJob {
+  int n;
+  const int* tab;
+  const TM* mask;
+  const TV* v;
+  const TX* x;
+  Epi epi;
+};
 template <int NACC, class TM, class TV, class TACC, class TX, class Epi>
-__global__ __launch_bounds__(BLK) void k_slices(int n, int w, const int* __restrict__ tab,
-                                                const TM* __restrict__ mask, const TV* __restrict__ v,
-                                                const TX* __restrict__ x, Epi epi) {
+__global__ __launch_bounds__(BLK) void k_slices(const Batch<SliceJob<TM, TV, TX, Epi>> batch) {
 #pragma clang fp contract(off)
   constexpr int CH = 8;  // places whose loads are issued together
-  const int row = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+  int blk;
+  const auto& job = batch_job(batch, &blk);
+  const int n = job.n;
+  const int* __restrict__ tab = job.tab;
+  const TM* __restrict__ mask = job.mask;
+  const TV* __restrict__ v = job.v;
+  const TX* __restrict__ x = job.x;
+  const Epi epi = job.epi;
+  const int row = blk * BLK + (int)threadIdx.x;
   if (row >= n) return;
   const int q = __builtin_amdgcn_readfirstlane(row / DIA_ROWS);
   const int* t = tab + (size_t)q * DIA_TS;
   const typename Epi::Pre pre = epi.load(row);
   const uint32_t m = mask[row];
   const int cnt = t[0];
-  const TV* vs = v + (size_t)q * w * DIA_ROWS + (row & (DIA_ROWS - 1));
+  const TV* vs = v + (size_t)t[DIA_BASE] * DIA_ROWS + (row & (DIA_ROWS - 1));
   TACC acc[NACC];
 #pragma unroll
   for (int a = 0; a < NACC; ++a) acc[a] = 0;
@@ -334,7 +417,7 @@ __global__ __launch_bounds__(BLK) void k_slices(int n, int w, const int* __restr
       const int j = j0 + u;
       if (j < cnt) {
         a[u] = vs[(size_t)j * DIA_ROWS];
-        b[u] = x[m >> j & 1u ? row + t[1 + j] : 0];
+        b[u] = x[m >> j & 1u ? row + t[DIA_DIAG + j] : 0];
       } else {
         a[u] = TV(0);
         b[u] = TX(0);
@@ -362,16 +445,6 @@ __global__ __launch_bounds__(BLK) void k_slices(int n, int w, const int* __restr
   epi.store(row, acc[0], pre);
 }
 
-template <class T>
-struct LoadArr;
-template <class L>
-struct load_arr_elem {
-  using type = void;
-};
-template <class T>
-struct load_arr_elem<LoadArr<T>> {
-  using type = T;
-};
 static bool g_tiles_on = true;  // slices, and the LDS-staged operand, where a matrix has them
 void set_tiles(bool on) { g_tiles_on = on; }
 
@@ -393,157 +466,229 @@ int rows_per_block(const DCsr& a, int cap, bool vec) {
   return rb;
 }
 
-// e0/e1 (optional): events that the dispatch itself stamps with the
-// kernel's start and end (no extra packets in the stream), for timing one
-// class of launches inside a timed run
-template <class TV, class TACC, class Col, class LoadX, class Epi>
-static void launch_csr_cols(const DCsr& a, Col col, const TV* v, LoadX lx, Epi epi, hipStream_t s,
-                            hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr) {
+// one job of a CSR launch: the matrix, the operand, the rows' epilogue
+template <class TX, class Epi>
+struct Pass {
+  const DCsr* a;
+  const TX* x;
+  Epi epi;
+};
+// the kernel a matrix takes: passes of one shape can share a launch
+struct Shape {
+  enum Kind { EMPTY, SLICES, TILED, ROWS, LANES } kind = EMPTY;
+  int par = 0;        // rows per block (LANES: lanes per row)
+  bool flag = false;  // SLICES: 16-bit masks; ROWS, LANES: packed columns
+  int vec = 0;        // ROWS: grouped entry loads
+  bool operator==(const Shape& o) const { return kind == o.kind && par == o.par && flag == o.flag && vec == o.vec; }
+};
+template <class TV>
+static const TV* csr_vals(const DCsr& a) {
+  if constexpr (sizeof(TV) == sizeof(double))
+    return a.v;
+  else
+    return a.vf;
+}
+template <class TV>
+static const TV* slice_vals(const DCsr& a) {
+  if constexpr (sizeof(TV) == sizeof(double))
+    return a.dv;
+  else
+    return a.dvf;
+}
+static int tile_prod_bytes(const DCsr& a, int rb, int acc_bytes) {
+  int q = 0;
+  while (row_block(q) != rb) ++q;
+  return (a.blkmax[q] * acc_bytes + 15) / 16 * 16;
+}
+template <class TV, class TACC, class TX>
+static Shape shape_of(const DCsr& a) {
+  Shape sh;
+  if (a.nnz == 0) return sh;  // rows without entries: the epilogue of an empty sum
   constexpr int cap = ROWS_LDS_BYTES / (int)sizeof(TACC);
-  const int vec = g_vec_entries && reinterpret_cast<uintptr_t>(v) % 16 == 0 && col.aligned();
-  const int rb = rows_per_block(a, cap, vec != 0);
+  if (a.dia_w && g_tiles_on && slice_vals<TV>(a)) {
+    const int rb = rows_per_block(a, cap, true);
+    if (rb >= 32 && rb <= SBLK) {
+      sh.kind = Shape::SLICES;
+      sh.par = rb;
+      sh.flag = a.dia_m16 != nullptr;
+      return sh;
+    }
+  }
+  sh.flag = a.cd != nullptr;
+  const bool col_ok = a.cd ? reinterpret_cast<uintptr_t>(a.cd) % 8 == 0 : reinterpret_cast<uintptr_t>(a.ci) % 16 == 0;
+  sh.vec = g_vec_entries && reinterpret_cast<uintptr_t>(csr_vals<TV>(a)) % 16 == 0 && col_ok;
+  sh.par = rows_per_block(a, cap, sh.vec != 0);
   // the LDS-staged operand where the matrix has tiles for this block size
   // and the staging (products and tiles) takes at most 32 KiB, 5 blocks per
   // CU (at 4.2M DOF the outer SpMV's 21-27 KiB still run faster staged: 95
   // -> 83 us mixed, 102 -> 93 us FP64)
-  using TX = typename load_arr_elem<LoadX>::type;
-  if constexpr (!std::is_void<TX>::value) {
-    if (g_tiles_on && vec && a.tile_rb == rb && a.lc && (rb == 256 || rb == 128 || rb == 64)) {
-      int q = 0;
-      while (row_block(q) != rb) ++q;
-      const int pb = (a.blkmax[q] * (int)sizeof(TACC) + 15) / 16 * 16;
-      const int lds = pb + a.tile_cnt * TILE_W * (int)sizeof(TX);
-      if (lds <= 32768) {
-        const unsigned grid = (unsigned)(((int64_t)a.n + rb - 1) / rb);
-#define HBGS_TILED(RB)                                                                                     \
-  if (rb == RB) {                                                                                          \
-    if (e0)                                                                                                \
-      hipExtLaunchKernelGGL(k_csr_rows_tiled<RB, TV, TACC, TX, Epi>, dim3(grid), dim3(SBLK), lds, s, e0, e1, 0, \
-                            a.n, a.m, a.rp, a.lc, a.tiles, a.tile_cnt, v, lx.x, epi, pb);                  \
-    else                                                                                                   \
-      k_csr_rows_tiled<RB, TV, TACC, TX, Epi><<<grid, SBLK, lds, s>>>(a.n, a.m, a.rp, a.lc, a.tiles,       \
-                                                                      a.tile_cnt, v, lx.x, epi, pb);       \
-    HBGS_HIP(hipGetLastError());                                                                           \
-    return;                                                                                                \
+  if (g_tiles_on && sh.vec && a.tile_rb == sh.par && a.lc && (sh.par == 256 || sh.par == 128 || sh.par == 64) &&
+      tile_prod_bytes(a, sh.par, (int)sizeof(TACC)) + a.tile_cnt * TILE_W * (int)sizeof(TX) <= 32768) {
+    sh.kind = Shape::TILED;
+    sh.flag = false;
+    return sh;
   }
-        HBGS_TILED(256)
-        HBGS_TILED(128)
-        HBGS_TILED(64)
-#undef HBGS_TILED
-      }
-    }
+  if (sh.par) {
+    sh.kind = Shape::ROWS;
+    return sh;
   }
-#define HBGS_ROWS(RB)                                                                                      \
-  case RB:                                                                                                 \
-    if (e0)                                                                                                \
-      hipExtLaunchKernelGGL(k_csr_rows<RB, TV, TACC, Col, LoadX, Epi>, dim3((a.n + RB - 1) / RB), dim3(SBLK), \
-                            0, s, e0, e1, 0, a.n, a.rp, col, v, lx, epi, vec);                             \
-    else                                                                                                   \
-      k_csr_rows<RB, TV, TACC, Col, LoadX, Epi><<<(a.n + RB - 1) / RB, SBLK, 0, s>>>(a.n, a.rp, col, v, lx, epi, vec); \
-    HBGS_HIP(hipGetLastError());                                                                           \
-    return;
-  switch (rb) {
-    HBGS_ROWS(512)
-    HBGS_ROWS(256)
-    HBGS_ROWS(128)
-    HBGS_ROWS(64)
-    HBGS_ROWS(32)
-    HBGS_ROWS(16)
-    HBGS_ROWS(8)
-    HBGS_ROWS(4)
-    default: break;
-  }
-#undef HBGS_ROWS
-  float avg = a.avg_row();
-  int lpr = avg <= 1.5f ? 1 : avg <= 3.f ? 2 : avg <= 6.f ? 4 : avg <= 16.f ? 8 : avg <= 64.f ? 16 : avg <= 128.f ? 32 : 64;
-  unsigned grid = (unsigned)(((int64_t)a.n * lpr + BLK - 1) / BLK);
-#define HBGS_CASE(L)                                                                                       \
-  case L:                                                                                                  \
-    if (e0)                                                                                                \
-      hipExtLaunchKernelGGL(k_csr<L, TV, TACC, Col, LoadX, Epi>, dim3(grid), dim3(BLK), 0, s, e0, e1, 0, a.n, \
-                            a.rp, col, v, lx, epi);                                                        \
-    else                                                                                                   \
-      k_csr<L, TV, TACC, Col, LoadX, Epi><<<grid, BLK, 0, s>>>(a.n, a.rp, col, v, lx, epi);                \
-    break;
-  switch (lpr) {
-    HBGS_CASE(1)
-    HBGS_CASE(2)
-    HBGS_CASE(4)
-    HBGS_CASE(8)
-    HBGS_CASE(16)
-    HBGS_CASE(32)
-    HBGS_CASE(64)
-  }
-#undef HBGS_CASE
-  HBGS_HIP(hipGetLastError());
+  sh.kind = Shape::LANES;
+  sh.vec = 0;
+  const float avg = a.avg_row();
+  sh.par = avg <= 1.5f ? 1 : avg <= 3.f ? 2 : avg <= 6.f ? 4 : avg <= 16.f ? 8 : avg <= 64.f ? 16 : avg <= 128.f ? 32 : 64;
+  return sh;
 }
 
-template <class TV>
-static const TV* slice_vals(const DCsr& a);
-template <>
-const double* slice_vals<double>(const DCsr& a) {
-  return a.dv;
-}
-template <>
-const float* slice_vals<float>(const DCsr& a) {
-  return a.dvf;
-}
-
-template <int NACC, class TM, class TV, class TACC, class TX, class Epi>
-static void launch_slices(const DCsr& a, const TM* mask, const TX* x, Epi epi, hipStream_t s, hipEvent_t e0,
-                          hipEvent_t e1) {
-  const unsigned grid = (unsigned)(((int64_t)a.n + BLK - 1) / BLK);
-  const TV* v = slice_vals<TV>(a);
+// e0/e1 (optional): events that the dispatch itself stamps with the
+// kernel's start and end (no extra packets in the stream), for timing one
+// class of launches inside a timed run
+template <class K, class B>
+static void launch_batch(K kern, unsigned grid, unsigned lds, const B& b, hipStream_t s, hipEvent_t e0,
+                         hipEvent_t e1) {
+  static_assert(BLK == SBLK, "one block size");
   if (e0)
-    hipExtLaunchKernelGGL(k_slices<NACC, TM, TV, TACC, TX, Epi>, dim3(grid), dim3(BLK), 0, s, e0, e1, 0, a.n, a.dia_w,
-                          a.dia_tab, mask, v, x, epi);
+    hipExtLaunchKernelGGL(kern, dim3(grid), dim3(BLK), lds, s, e0, e1, 0, b);
   else
-    k_slices<NACC, TM, TV, TACC, TX, Epi><<<grid, BLK, 0, s>>>(a.n, a.dia_w, a.dia_tab, mask, v, x, epi);
+    kern<<<grid, BLK, lds, s>>>(b);
   HBGS_HIP(hipGetLastError());
 }
+// fills a batch's block ranges from `blocks(q)`; returns the grid
+template <class B, class F>
+static unsigned batch_blocks(B& b, int nj, F blocks) {
+  unsigned grid = 0;
+  for (int q = 0; q < MAXB; ++q) {
+    b.first[q] = q < nj ? grid : UINT32_MAX;
+    if (q < nj) grid += (unsigned)blocks(q);
+  }
+  return grid;
+}
+static unsigned cdiv(int64_t a, int64_t b) { return (unsigned)((a + b - 1) / b); }
 
-template <class TV, class TACC, class LoadX, class Epi>
-static void launch_csr(const DCsr& a, const TV* v, LoadX lx, Epi epi, hipStream_t s, hipEvent_t e0 = nullptr,
-                       hipEvent_t e1 = nullptr) {
-  if (a.n == 0) return;
-  using TX = typename load_arr_elem<LoadX>::type;
-  if constexpr (!std::is_void<TX>::value) {
-    if (a.dia_w && g_tiles_on && slice_vals<TV>(a)) {
-      const int rb = rows_per_block(a, ROWS_LDS_BYTES / (int)sizeof(TACC), true);
-#define HBGS_SLICES(RB)                                                                            \
-  if (rb == RB) {                                                                                  \
-    if (a.dia_m16)                                                                                 \
-      launch_slices<SBLK / RB, uint16_t, TV, TACC>(a, a.dia_m16, lx.x, epi, s, e0, e1);            \
-    else                                                                                           \
-      launch_slices<SBLK / RB, uint32_t, TV, TACC>(a, a.dia_m32, lx.x, epi, s, e0, e1);            \
-    return;                                                                                        \
+template <class TM, class TV, class TACC, class TX, class Epi>
+static void launch_slices(const Pass<TX, Epi>* const* p, int nj, int rb, hipStream_t s, hipEvent_t e0,
+                          hipEvent_t e1) {
+  Batch<SliceJob<TM, TV, TX, Epi>> b;
+  for (int q = 0; q < MAXB; ++q) {
+    const DCsr& a = *p[q < nj ? q : 0]->a;
+    const TM* mask = sizeof(TM) == 2 ? (const TM*)a.dia_m16 : (const TM*)a.dia_m32;
+    const Pass<TX, Epi>& j = *p[q < nj ? q : 0];
+    b.d[q] = {a.n, a.dia_tab, mask, slice_vals<TV>(a), j.x, j.epi};
   }
-      HBGS_SLICES(256)
-      HBGS_SLICES(128)
-      HBGS_SLICES(64)
-      HBGS_SLICES(32)
-#undef HBGS_SLICES
-    }
+  const unsigned grid = batch_blocks(b, nj, [&](int q) { return cdiv(p[q]->a->n, BLK); });
+  switch (rb) {
+    case 256: launch_batch(k_slices<1, TM, TV, TACC, TX, Epi>, grid, 0, b, s, e0, e1); break;
+    case 128: launch_batch(k_slices<2, TM, TV, TACC, TX, Epi>, grid, 0, b, s, e0, e1); break;
+    case 64: launch_batch(k_slices<4, TM, TV, TACC, TX, Epi>, grid, 0, b, s, e0, e1); break;
+    default: launch_batch(k_slices<8, TM, TV, TACC, TX, Epi>, grid, 0, b, s, e0, e1); break;
   }
-  if (a.nnz == 0) {  // rows without entries: epilogue of an empty sum
-    if (e0) HBGS_HIP(hipEventRecord(e0, s));
-    k_empty<TACC, Epi><<<grid_for(a.n, 256), 256, 0, s>>>(a.n, epi);
-    HBGS_HIP(hipGetLastError());
-    if (e1) HBGS_HIP(hipEventRecord(e1, s));
+}
+template <class TV, class TACC, class TX, class Epi>
+static void launch_tiled(const Pass<TX, Epi>* const* p, int nj, int rb, hipStream_t s, hipEvent_t e0,
+                         hipEvent_t e1) {
+  Batch<TiledJob<TV, TX, Epi>> b;
+  unsigned lds = 0;
+  for (int q = 0; q < MAXB; ++q) {
+    const Pass<TX, Epi>& j = *p[q < nj ? q : 0];
+    const DCsr& a = *j.a;
+    const int pb = tile_prod_bytes(a, rb, (int)sizeof(TACC));
+    lds = std::max(lds, (unsigned)(pb + a.tile_cnt * TILE_W * (int)sizeof(TX)));
+    b.d[q] = {a.n, a.m, a.tile_cnt, pb, a.rp, a.lc, a.tiles, csr_vals<TV>(a), j.x, j.epi};
+  }
+  const unsigned grid = batch_blocks(b, nj, [&](int q) { return cdiv(p[q]->a->n, rb); });
+  switch (rb) {
+    case 256: launch_batch(k_csr_rows_tiled<256, TV, TACC, TX, Epi>, grid, lds, b, s, e0, e1); break;
+    case 128: launch_batch(k_csr_rows_tiled<128, TV, TACC, TX, Epi>, grid, lds, b, s, e0, e1); break;
+    default: launch_batch(k_csr_rows_tiled<64, TV, TACC, TX, Epi>, grid, lds, b, s, e0, e1); break;
+  }
+}
+static inline ColPlain col_of(const DCsr& a, ColPlain) { return {a.ci}; }
+static inline ColPacked col_of(const DCsr& a, ColPacked) { return {a.cd, a.cb}; }
+template <class Col, class TV, class TACC, class TX, class Epi>
+static void launch_cols(const Pass<TX, Epi>* const* p, int nj, const Shape& sh, hipStream_t s, hipEvent_t e0,
+                        hipEvent_t e1) {
+  Batch<CsrJob<Col, TV, TX, Epi>> b;
+  for (int q = 0; q < MAXB; ++q) {
+    const Pass<TX, Epi>& j = *p[q < nj ? q : 0];
+    b.d[q] = {j.a->n, sh.vec, j.a->rp, col_of(*j.a, Col{}), csr_vals<TV>(*j.a), j.x, j.epi};
+  }
+  const bool rows = sh.kind == Shape::ROWS;
+  const unsigned grid = batch_blocks(b, nj, [&](int q) {
+    return rows ? cdiv(p[q]->a->n, sh.par) : cdiv((int64_t)p[q]->a->n * sh.par, BLK);
+  });
+#define HBGS_KERN(K, N)                                               \
+  case N:                                                             \
+    launch_batch(K<N, TV, TACC, Col, TX, Epi>, grid, 0, b, s, e0, e1); \
     return;
-  }
-  if (a.cd)
-    launch_csr_cols<TV, TACC>(a, ColPacked{a.cd, a.cb}, v, lx, epi, s, e0, e1);
-  else
-    launch_csr_cols<TV, TACC>(a, ColPlain{a.ci}, v, lx, epi, s, e0, e1);
+  if (rows) switch (sh.par) {
+      HBGS_KERN(k_csr_rows, 512)
+      HBGS_KERN(k_csr_rows, 256)
+      HBGS_KERN(k_csr_rows, 128)
+      HBGS_KERN(k_csr_rows, 64)
+      HBGS_KERN(k_csr_rows, 32)
+      HBGS_KERN(k_csr_rows, 16)
+      HBGS_KERN(k_csr_rows, 8)
+      HBGS_KERN(k_csr_rows, 4)
+    }
+  else switch (sh.par) {
+      HBGS_KERN(k_csr, 1)
+      HBGS_KERN(k_csr, 2)
+      HBGS_KERN(k_csr, 4)
+      HBGS_KERN(k_csr, 8)
+      HBGS_KERN(k_csr, 16)
+      HBGS_KERN(k_csr, 32)
+      HBGS_KERN(k_csr, 64)
+    }
+#undef HBGS_KERN
 }
 
-// operand loaders
-template <class T>
-struct LoadArr {
-  const T* __restrict__ x;
-  __device__ T operator()(int k) const { return x[k]; }
-};
+// the passes of all jobs, as few launches as their shapes allow
+template <class TV, class TACC, class TX, class Epi>
+static void launch_csr(const Pass<TX, Epi>* jobs, int nj, hipStream_t s, hipEvent_t e0 = nullptr,
+                       hipEvent_t e1 = nullptr) {
+  Shape sh[HBGS_MAX_FIELDS];
+  bool done[HBGS_MAX_FIELDS] = {};
+  for (int q = 0; q < nj; ++q) {
+    done[q] = jobs[q].a->n == 0;
+    if (!done[q]) sh[q] = shape_of<TV, TACC, TX>(*jobs[q].a);
+  }
+  for (int q = 0; q < nj; ++q) {
+    if (done[q]) continue;
+    if (sh[q].kind == Shape::EMPTY) {
+      if (e0) HBGS_HIP(hipEventRecord(e0, s));
+      k_empty<TACC, Epi><<<grid_for(jobs[q].a->n, 256), 256, 0, s>>>(jobs[q].a->n, jobs[q].epi);
+      HBGS_HIP(hipGetLastError());
+      if (e1) HBGS_HIP(hipEventRecord(e1, s));
+      continue;
+    }
+    const Pass<TX, Epi>* p[MAXB];
+    int np = 0;
+    for (int k = q; k < nj && np < MAXB; ++k)
+      if (!done[k] && sh[k] == sh[q]) {
+        p[np++] = &jobs[k];
+        done[k] = true;
+      }
+    switch (sh[q].kind) {
+      case Shape::SLICES:
+        if (sh[q].flag)
+          launch_slices<uint16_t, TV, TACC>(p, np, sh[q].par, s, e0, e1);
+        else
+          launch_slices<uint32_t, TV, TACC>(p, np, sh[q].par, s, e0, e1);
+        break;
+      case Shape::TILED: launch_tiled<TV, TACC>(p, np, sh[q].par, s, e0, e1); break;
+      default:
+        if (sh[q].flag)
+          launch_cols<ColPacked, TV, TACC>(p, np, sh[q], s, e0, e1);
+        else
+          launch_cols<ColPlain, TV, TACC>(p, np, sh[q], s, e0, e1);
+    }
+  }
+}
+template <class TV, class TACC, class TX, class Epi>
+static void launch_csr(const DCsr& a, const TX* x, const Epi& epi, hipStream_t s, hipEvent_t e0 = nullptr,
+                       hipEvent_t e1 = nullptr) {
+  const Pass<TX, Epi> j{&a, x, epi};
+  launch_csr<TV, TACC>(&j, 1, s, e0, e1);
+}
 
 // Epilogues: load(i) issues the row's vector loads (before the row sum, so
 // they overlap it); store(i, acc, pre) finishes the row.
@@ -716,149 +861,179 @@ struct EpiSubFrom {
 
 // ---------------------------------------------------------- outer SpMV
 void spmv_outer_f64(const DCsr& a, const double* x, double* y, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-  launch_csr<double, double>(a, a.v, LoadArr<double>{x}, EpiStore<double, double>{y}, s, e0, e1);
+  launch_csr<double, double>(a, x, EpiStore<double, double>{y}, s, e0, e1);
 }
 void spmv_outer_mixed(const DCsr& a, const float* x, double* y, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-  launch_csr<double, double>(a, a.v, LoadArr<float>{x}, EpiStore<double, double>{y}, s, e0, e1);
+  launch_csr<double, double>(a, x, EpiStore<double, double>{y}, s, e0, e1);
 }
 template <class TZ>
 void couple_f64(const DCsr& a, const double* v, const TZ* z, double* t, const double* vs, hipStream_t s) {
-  launch_csr<double, double>(a, a.v, LoadArr<TZ>{z}, EpiSubFrom{v, t, vs}, s);
+  launch_csr<double, double>(a, z, EpiSubFrom{v, t, vs}, s);
 }
 template void couple_f64<float>(const DCsr&, const double*, const float*, double*, const double*, hipStream_t);
 template void couple_f64<double>(const DCsr&, const double*, const double*, double*, const double*, hipStream_t);
 void spmv_resid_f64(const DCsr& a, const double* x, const double* b, double* r, hipStream_t s) {
-  launch_csr<double, double>(a, a.v, LoadArr<double>{x}, EpiResid<double>{b, r}, s);
+  launch_csr<double, double>(a, x, EpiResid<double>{b, r}, s);
 }
 
 // ------------------------------------------------------- V-cycle pieces
+// Element-wise passes over several jobs' vectors: block blk of a job takes
+// its elements [BLK blk, BLK (blk + 1)).
 template <class T>
-static const T* vals_of(const DCsr& a);
-template <>
-const double* vals_of<double>(const DCsr& a) {
-  return a.v;
-}
-template <>
-const float* vals_of<float>(const DCsr& a) {
-  return a.vf;
-}
-
+struct InitJob {
+  int n;
+  const T *dinv, *b;
+  T c0;
+  T *r, *d, *x;
+};
 template <class T>
-__global__ void k_cheb_init0(int n, const T* __restrict__ dinv, const T* __restrict__ b, T c0, T* __restrict__ r,
-                             T* __restrict__ d, T* __restrict__ x) {
-  for (int64_t i = (int64_t)blockIdx.x * BLK + threadIdx.x; i < n; i += (int64_t)gridDim.x * BLK) {
-    T di = dinv[i] * b[i] * c0;
-    r[i] = b[i];
-    d[i] = di;
-    x[i] = di;
-  }
+__global__ __launch_bounds__(BLK) void k_cheb_init0(const Batch<InitJob<T>> batch) {
+  int blk;
+  const auto& j = batch_job(batch, &blk);
+  const int64_t i = (int64_t)blk * BLK + threadIdx.x;
+  if (i >= j.n) return;
+  const T bi = j.b[i];
+  const T di = j.dinv[i] * bi * j.c0;
+  j.r[i] = bi;
+  j.d[i] = di;
+  j.x[i] = di;
 }
-
-template <class T>
-void VcOps<T>::pre2(const DCsr& a, const T* dinv, const ChebCoef& c, const T* b, const T* d0, T* x, hipStream_t s) {
-  launch_csr<T, T>(a, vals_of<T>(a), LoadArr<T>{d0}, EpiChebPre2<T>{dinv, b, d0, x, (T)c.c1[1], (T)c.c2[1]}, s);
-}
-
-template <class T>
-__global__ void k_make_d0(int n, const T* __restrict__ b, const T* __restrict__ dinv, T c0, T* __restrict__ d0) {
-  for (int64_t i = (int64_t)blockIdx.x * BLK + threadIdx.x; i < n; i += (int64_t)gridDim.x * BLK) d0[i] = dinv[i] * b[i] * c0;
-}
-template <class T>
-void VcOps<T>::make_d0(int n, const T* b, const T* dinv, double c0, T* d0, hipStream_t s) {
-  k_make_d0<T><<<grid_for(n, BLK), BLK, 0, s>>>(n, b, dinv, (T)c0, d0);
-  HBGS_HIP(hipGetLastError());
-}
-
-template <class T>
-void VcOps<T>::init0(int n, const T* dinv, const ChebCoef& c, const T* b, T* r, T* d, T* x, hipStream_t s) {
-  k_cheb_init0<T><<<grid_for(n, BLK), BLK, 0, s>>>(n, dinv, b, (T)c.c0, r, d, x);
-  HBGS_HIP(hipGetLastError());
-}
-
-template <class T>
-void VcOps<T>::post_start(const DCsr& a, const T* dinv, const ChebCoef& c, const T* b, const T* x, T* r, T* d,
-                          hipStream_t s) {
-  launch_csr<T, T>(a, vals_of<T>(a), LoadArr<T>{x}, EpiChebPostA<T>{dinv, b, r, d, (T)c.c0}, s);
-}
-
 template <class T>
 __global__ void k_add(int n, const T* __restrict__ d, T* __restrict__ x) {
   for (int64_t i = (int64_t)blockIdx.x * BLK + threadIdx.x; i < n; i += (int64_t)gridDim.x * BLK) x[i] = x[i] + d[i];
 }
 
-template <class T>
-void VcOps<T>::step(const DCsr& a, const T* dinv, const ChebCoef& c, int k, bool add_d, bool keep, T* r,
-                    const T* d, T* dn, T* x, hipStream_t s) {
-  const T* av = vals_of<T>(a);
-  const T c1 = (T)c.c1[k], c2 = (T)c.c2[k];
-  if (add_d && keep)
-    launch_csr<T, T>(a, av, LoadArr<T>{d}, EpiChebStep<T, true, true>{dinv, d, r, dn, x, c1, c2}, s);
-  else if (add_d)
-    launch_csr<T, T>(a, av, LoadArr<T>{d}, EpiChebStep<T, true, false>{dinv, d, r, dn, x, c1, c2}, s);
-  else if (keep)
-    launch_csr<T, T>(a, av, LoadArr<T>{d}, EpiChebStep<T, false, true>{dinv, d, r, dn, x, c1, c2}, s);
-  else
-    launch_csr<T, T>(a, av, LoadArr<T>{d}, EpiChebStep<T, false, false>{dinv, d, r, dn, x, c1, c2}, s);
+// jobs -> passes through `make(job)`, then the launches
+template <class T, class F>
+static void level_pass(const LevelJob<T>* j, int nj, hipStream_t s, F make) {
+  using P = decltype(make(j[0]));
+  P p[HBGS_MAX_FIELDS];
+  for (int q = 0; q < nj; ++q) p[q] = make(j[q]);
+  launch_csr<T, T>(p, nj, s);
 }
-
+template <class T>
+void VcOps<T>::pre2(const LevelJob<T>* j, int nj, hipStream_t s) {
+  level_pass<T>(j, nj, s, [](const LevelJob<T>& J) {
+    return Pass<T, EpiChebPre2<T>>{J.A, J.d, {J.dinv, J.b, J.d, J.x, (T)J.cc->c1[1], (T)J.cc->c2[1]}};
+  });
+}
+template <class T>
+void VcOps<T>::init0(const LevelJob<T>* j, int nj, hipStream_t s) {
+  for (int q0 = 0; q0 < nj; q0 += MAXB) {
+    const int m = std::min(MAXB, nj - q0);
+    Batch<InitJob<T>> b;
+    for (int q = 0; q < MAXB; ++q) {
+      const LevelJob<T>& J = j[q0 + (q < m ? q : 0)];
+      b.d[q] = {J.A->n, J.dinv, J.b, (T)J.cc->c0, J.r, J.d, J.x};
+    }
+    const unsigned grid = batch_blocks(b, m, [&](int q) { return cdiv(j[q0 + q].A->n, BLK); });
+    launch_batch(k_cheb_init0<T>, grid, 0, b, s, nullptr, nullptr);
+  }
+}
+template <class T>
+void VcOps<T>::post_start(const LevelJob<T>* j, int nj, hipStream_t s) {
+  level_pass<T>(j, nj, s, [](const LevelJob<T>& J) {
+    return Pass<T, EpiChebPostA<T>>{J.A, J.x, {J.dinv, J.b, J.r, J.d, (T)J.cc->c0}};
+  });
+}
+template <class T, bool ADD_D, bool KEEP>
+static void cheb_step(const LevelJob<T>* j, int nj, int k, hipStream_t s) {
+  level_pass<T>(j, nj, s, [k](const LevelJob<T>& J) {
+    return Pass<T, EpiChebStep<T, ADD_D, KEEP>>{
+        J.A, J.d, {J.dinv, J.d, J.r, J.dn, J.x, (T)J.cc->c1[k], (T)J.cc->c2[k]}};
+  });
+}
+template <class T>
+void VcOps<T>::step(const LevelJob<T>* j, int nj, int k, bool add_d, bool keep, hipStream_t s) {
+  if (add_d && keep)
+    cheb_step<T, true, true>(j, nj, k, s);
+  else if (add_d)
+    cheb_step<T, true, false>(j, nj, k, s);
+  else if (keep)
+    cheb_step<T, false, true>(j, nj, k, s);
+  else
+    cheb_step<T, false, false>(j, nj, k, s);
+}
 template <class T>
 void VcOps<T>::add(int n, const T* d, T* x, hipStream_t s) {
   k_add<T><<<grid_for(n, BLK), BLK, 0, s>>>(n, d, x);
   HBGS_HIP(hipGetLastError());
 }
+template <class T>
+void VcOps<T>::resid(const LevelJob<T>* j, int nj, hipStream_t s) {
+  level_pass<T>(j, nj, s, [](const LevelJob<T>& J) { return Pass<T, EpiResid<T>>{J.A, J.x, {J.b, J.r}}; });
+}
+template <class T>
+void VcOps<T>::restrict_(const LevelJob<T>* j, int nj, hipStream_t s) {
+  level_pass<T>(j, nj, s, [](const LevelJob<T>& J) {
+    return Pass<T, EpiRhs<T>>{J.R, J.r, {J.bc, J.dinv_c, J.d0_c, (T)J.c0_c}};
+  });
+}
+template <class T>
+void VcOps<T>::prolong(const LevelJob<T>* j, int nj, hipStream_t s) {
+  level_pass<T>(j, nj, s, [](const LevelJob<T>& J) { return Pass<T, EpiAdd<T, T>>{J.P, J.xc, {J.x}}; });
+}
+template <class T>
+void VcOps<T>::post_q(const LevelJob<T>* j, int nj, hipStream_t s) {
+  level_pass<T>(j, nj, s, [](const LevelJob<T>& J) {
+    return Pass<T, EpiPostQ<T>>{J.Q, J.xc, {J.dinv, J.r, J.x, J.d, (T)J.cc->c0}};
+  });
+}
+template <class T>
+void VcOps<T>::couple(const RhsJob<T>* j, int nj, const T* z, const double* vs, hipStream_t s) {
+  Pass<T, EpiCouple<T>> p[HBGS_MAX_FIELDS];
+  for (int q = 0; q < nj; ++q) p[q] = {j[q].cpl, z, {j[q].v, j[q].t, j[q].dinv, j[q].d0, (T)j[q].c0, vs}};
+  launch_csr<T, T>(p, nj, s);
+}
 
 template <class T>
-void VcOps<T>::resid(const DCsr& a, const T* b, const T* x, T* r, hipStream_t s) {
-  launch_csr<T, T>(a, vals_of<T>(a), LoadArr<T>{x}, EpiResid<T>{b, r}, s);
+struct CastJob {
+  int n;
+  const double* v;
+  T* t;  // null: not wanted
+  const T* dinv;
+  T c0;
+  T* d0;  // null: not wanted
+};
+template <class T>
+__global__ __launch_bounds__(BLK) void k_cast_in(const Batch<CastJob<T>> batch, const double* __restrict__ vs) {
+  int blk;
+  const auto& j = batch_job(batch, &blk);
+  const int64_t i = (int64_t)blk * BLK + threadIdx.x;
+  if (i >= j.n) return;
+  const double v = j.v[i];
+  const T ti = (T)(vs ? v / *vs : v);
+  if (j.t) j.t[i] = ti;
+  if (j.d0) j.d0[i] = j.dinv[i] * ti * j.c0;
 }
 template <class T>
-void VcOps<T>::restrict_(const DCsr& rmat, const T* r, T* bc, const T* dinv_c, double c0_c, T* d0_c,
-                         hipStream_t s) {
-  launch_csr<T, T>(rmat, vals_of<T>(rmat), LoadArr<T>{r}, EpiRhs<T>{bc, dinv_c, d0_c, (T)c0_c}, s);
-}
-template <class T>
-void VcOps<T>::prolong(const DCsr& p, const T* xc, T* x, hipStream_t s) {
-  launch_csr<T, T>(p, vals_of<T>(p), LoadArr<T>{xc}, EpiAdd<T, T>{x}, s);
-}
-template <class T>
-void VcOps<T>::post_q(const DCsr& q, const T* dinv, const ChebCoef& c, const T* xc, T* r, T* x, T* d,
-                      hipStream_t s) {
-  launch_csr<T, T>(q, vals_of<T>(q), LoadArr<T>{xc}, EpiPostQ<T>{dinv, r, x, d, (T)c.c0}, s);
-}
-template <class T>
-void VcOps<T>::couple(const DCsr& c, const double* v, const T* z, T* t, const T* dinv, double c0, T* d0,
-                      const double* vs, hipStream_t s) {
-  launch_csr<T, T>(c, vals_of<T>(c), LoadArr<T>{z}, EpiCouple<T>{v, t, dinv, d0, (T)c0, vs}, s);
-}
-
-template <class T>
-__global__ void k_cast_in(int n, const double* __restrict__ v, T* __restrict__ t, const T* __restrict__ dinv, T c0,
-                          T* __restrict__ d0, const double* __restrict__ vs) {
-  const double h = vs ? *vs : 1.0;
-  for (int64_t i = (int64_t)blockIdx.x * BLK + threadIdx.x; i < n; i += (int64_t)gridDim.x * BLK) {
-    T ti = (T)(vs ? v[i] / h : v[i]);
-    t[i] = ti;
-    if (d0) d0[i] = dinv[i] * ti * c0;
+void VcOps<T>::cast_in(const RhsJob<T>* j, int nj, const double* vs, hipStream_t s) {
+  for (int q0 = 0; q0 < nj; q0 += MAXB) {
+    const int m = std::min(MAXB, nj - q0);
+    Batch<CastJob<T>> b;
+    for (int q = 0; q < MAXB; ++q) {
+      const RhsJob<T>& J = j[q0 + (q < m ? q : 0)];
+      b.d[q] = {J.n, J.v, J.t, J.dinv, (T)J.c0, J.d0};
+    }
+    const unsigned grid = batch_blocks(b, m, [&](int q) { return cdiv(j[q0 + q].n, BLK); });
+    k_cast_in<T><<<grid, BLK, 0, s>>>(b, vs);
+    HBGS_HIP(hipGetLastError());
   }
-}
-template <class T>
-void VcOps<T>::cast_in(int n, const double* v, T* t, const T* dinv, double c0, T* d0, const double* vs,
-                       hipStream_t s) {
-  k_cast_in<T><<<grid_for(n, BLK), BLK, 0, s>>>(n, v, t, dinv, (T)c0, d0, vs);
-  HBGS_HIP(hipGetLastError());
 }
 
 // coarsest level: x = A^-1 b with the dense FP64 inverse (row-major; the
 // transposed solve passes the stored transpose).  One block per row: the
 // row's 8 n bytes are streamed by 256 threads and reduced in fixed order.
 template <class T>
-__global__ __launch_bounds__(BLK) void k_gemv_block(int n, const double* __restrict__ inv, const T* __restrict__ b,
-                                                    T* __restrict__ x) {
+__global__ __launch_bounds__(BLK) void k_gemv_block(const Batch<DenseJob<T>> batch) {
   __shared__ double sh[BLK / 64];
-  const int row = blockIdx.x;
-  const double* m = inv + (int64_t)row * n;
+  int row;
+  const auto& j = batch_job(batch, &row);
+  const int n = j.n;
+  const double* __restrict__ m = j.inv + (int64_t)row * n;
+  const T* __restrict__ b = j.b;
   double acc = 0.0;
-  for (int j = threadIdx.x; j < n; j += BLK) acc += m[j] * (double)b[j];
+  for (int k = threadIdx.x; k < n; k += BLK) acc += m[k] * (double)b[k];
   acc = lanes_sum<double>(acc, 64);
   if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = acc;
   __syncthreads();
@@ -866,25 +1041,38 @@ __global__ __launch_bounds__(BLK) void k_gemv_block(int n, const double* __restr
     double t = 0.0;
 #pragma unroll
     for (int q = 0; q < BLK / 64; ++q) t += sh[q];
-    x[row] = (T)t;
+    j.x[row] = (T)t;
   }
 }
 template <class T>
-void VcOps<T>::coarse(int n, const double* inv, int transpose, const T* b, T* x, hipStream_t s) {
-  (void)transpose;  // the caller passes the stored transpose of the inverse
-  if (n <= 0) return;
-  k_gemv_block<T><<<n, BLK, 0, s>>>(n, inv, b, x);
-  HBGS_HIP(hipGetLastError());
+void VcOps<T>::coarse(const DenseJob<T>* j, int nj, hipStream_t s) {
+  for (int q0 = 0; q0 < nj; q0 += MAXB) {
+    const int m = std::min(MAXB, nj - q0);
+    Batch<DenseJob<T>> b;
+    for (int q = 0; q < MAXB; ++q) b.d[q] = j[q0 + (q < m ? q : 0)];
+    const unsigned grid = batch_blocks(b, m, [&](int q) { return j[q0 + q].n; });
+    launch_batch(k_gemv_block<T>, grid, 0, b, s, nullptr, nullptr);
+  }
 }
 
 // DD(0)-ILU(0) sweeps: one block per subdomain, level by level, one thread
 // per row (each sum in ascending column)
+template <class T>
+struct SweepJob {
+  const int *ord, *lev, *sub, *rp, *ci;
+  const T* v;
+  const int* dpos;
+  const T* t;
+  T* y;
+};
 template <class T, bool DIAG>
-__global__ __launch_bounds__(BLK) void k_ilu_lower(const int* __restrict__ ord, const int* __restrict__ lev,
-                                                   const int* __restrict__ sub, const int* __restrict__ rp,
-                                                   const int* __restrict__ ci, const T* __restrict__ v,
-                                                   const int* __restrict__ dpos, const T* __restrict__ t, T* y) {
-  const int b = blockIdx.x;
+__global__ __launch_bounds__(BLK) void k_ilu_lower(const Batch<SweepJob<T>> batch) {
+  int b;
+  const SweepJob<T>& j = batch_job(batch, &b);
+  const int *__restrict__ ord = j.ord, *__restrict__ lev = j.lev, *__restrict__ sub = j.sub, *__restrict__ rp = j.rp,
+            *__restrict__ ci = j.ci, *__restrict__ dpos = j.dpos;
+  const T *__restrict__ v = j.v, *__restrict__ t = j.t;
+  T* y = j.y;
   for (int l = sub[b]; l + 1 < sub[b + 1]; ++l) {
     for (int q = lev[l] + threadIdx.x; q < lev[l + 1]; q += BLK) {
       const int i = ord[q];
@@ -896,17 +1084,19 @@ __global__ __launch_bounds__(BLK) void k_ilu_lower(const int* __restrict__ ord, 
   }
 }
 template <class T, bool DIAG>
-__global__ __launch_bounds__(BLK) void k_ilu_upper(const int* __restrict__ ord, const int* __restrict__ lev,
-                                                   const int* __restrict__ sub, const int* __restrict__ rp,
-                                                   const int* __restrict__ ci, const T* __restrict__ v,
-                                                   const int* __restrict__ dpos, const T* __restrict__ y, T* z) {
-  const int b = blockIdx.x;
+__global__ __launch_bounds__(BLK) void k_ilu_upper(const Batch<SweepJob<T>> batch) {
+  int b;
+  const SweepJob<T>& j = batch_job(batch, &b);
+  const int *__restrict__ ord = j.ord, *__restrict__ lev = j.lev, *__restrict__ sub = j.sub, *__restrict__ rp = j.rp,
+            *__restrict__ ci = j.ci, *__restrict__ dpos = j.dpos;
+  const T *__restrict__ v = j.v, *__restrict__ t = j.t;
+  T* y = j.y;
   for (int l = sub[b]; l + 1 < sub[b + 1]; ++l) {
     for (int q = lev[l] + threadIdx.x; q < lev[l + 1]; q += BLK) {
       const int i = ord[q];
-      T s = y[i];
-      for (int k = dpos[i] + 1; k < rp[i + 1]; ++k) s -= v[k] * z[ci[k]];
-      z[i] = DIAG ? s / v[dpos[i]] : s;
+      T s = t[i];
+      for (int k = dpos[i] + 1; k < rp[i + 1]; ++k) s -= v[k] * y[ci[k]];
+      y[i] = DIAG ? s / v[dpos[i]] : s;
     }
     __syncthreads();
   }
@@ -924,18 +1114,28 @@ const float* ilu_vals<float>(const IluLeaf& f, int transpose) {
 // z = U^-1 L^-1 t, or z = L^-T U^-T t (lower sweep on the transposed
 // factors dividing by the diagonal, then the unit upper sweep)
 template <class T>
-void VcOps<T>::ilu(const IluLeaf& f, int transpose, const T* t, T* z, hipStream_t s) {
-  const T* v = ilu_vals<T>(f, transpose);
-  T* y = sizeof(T) == sizeof(double) ? reinterpret_cast<T*>(f.yd) : reinterpret_cast<T*>(f.yf);
-  const DCsr& F = f.F;
-  if (!transpose) {
-    k_ilu_lower<T, false><<<f.nsub, BLK, 0, s>>>(f.ford, f.flev, f.fsub, F.rp, F.ci, v, f.dpos, t, y);
-    k_ilu_upper<T, true><<<f.nsub, BLK, 0, s>>>(f.bord, f.blev, f.bsub, F.rp, F.ci, v, f.dpos, y, z);
-  } else {
-    k_ilu_lower<T, true><<<f.nsub, BLK, 0, s>>>(f.ford, f.flev, f.fsub, F.rp, F.ci, v, f.dpos, t, y);
-    k_ilu_upper<T, false><<<f.nsub, BLK, 0, s>>>(f.bord, f.blev, f.bsub, F.rp, F.ci, v, f.dpos, y, z);
+void VcOps<T>::ilu(const IluJob<T>* j, int nj, int transpose, hipStream_t s) {
+  for (int q0 = 0; q0 < nj; q0 += MAXB) {
+    const int m = std::min(MAXB, nj - q0);
+    Batch<SweepJob<T>> lo, up;
+    for (int q = 0; q < MAXB; ++q) {
+      const IluJob<T>& J = j[q0 + (q < m ? q : 0)];
+      const IluLeaf& f = *J.f;
+      const T* v = ilu_vals<T>(f, transpose);
+      T* y = sizeof(T) == sizeof(double) ? reinterpret_cast<T*>(f.yd) : reinterpret_cast<T*>(f.yf);
+      lo.d[q] = {f.ford, f.flev, f.fsub, f.F.rp, f.F.ci, v, f.dpos, J.t, y};
+      up.d[q] = {f.bord, f.blev, f.bsub, f.F.rp, f.F.ci, v, f.dpos, y, J.z};
+    }
+    const unsigned grid = batch_blocks(lo, m, [&](int q) { return j[q0 + q].f->nsub; });
+    batch_blocks(up, m, [&](int q) { return j[q0 + q].f->nsub; });
+    if (!transpose) {
+      launch_batch(k_ilu_lower<T, false>, grid, 0, lo, s, nullptr, nullptr);
+      launch_batch(k_ilu_upper<T, true>, grid, 0, up, s, nullptr, nullptr);
+    } else {
+      launch_batch(k_ilu_lower<T, true>, grid, 0, lo, s, nullptr, nullptr);
+      launch_batch(k_ilu_upper<T, false>, grid, 0, up, s, nullptr, nullptr);
+    }
   }
-  HBGS_HIP(hipGetLastError());
 }
 
 template struct VcOps<float>;
