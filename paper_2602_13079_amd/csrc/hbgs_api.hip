@@ -94,6 +94,31 @@ void* Pool::raw(size_t bytes, Allocator& a) {
   return p;
 }
 
+Mail::~Mail() {
+  if (host_) (void)hipHostFree(host_);
+}
+MailArg Mail::next() {
+  if (!host_) {
+    HBGS_HIP(hipHostMalloc((void**)&host_, 64 + kBytes, hipHostMallocCoherent));
+    HBGS_HIP(hipHostGetDevicePointer((void**)&dev_, host_, 0));
+    host_[0] = 0;
+  }
+  return {dev_, ++seq_};
+}
+const void* Mail::wait(hipStream_t s) {
+  const volatile uint64_t* flag = host_;
+  for (unsigned spins = 1; *flag != seq_; ++spins) {
+    if ((spins & 1023u) == 0) {
+      const hipError_t e = hipStreamQuery(s);
+      if (e == hipSuccess && *flag != seq_) HBGS_FAIL(HBGS_EHIP, "a setup kernel ended without its result");
+      if (e != hipSuccess && e != hipErrorNotReady) HBGS_HIP(e);
+    }
+    __builtin_ia32_pause();
+  }
+  std::atomic_thread_fence(std::memory_order_acquire);
+  return host_ + 8;
+}
+
 Scratch::~Scratch() {
   for (auto& c : chunks_) free_block(c.base, c.a);
 }
@@ -606,10 +631,7 @@ static bool structurally_symmetric_dev(const DCsr& a, hipStream_t s) {
   HBGS_HIP(hipMemsetAsync(diff.p, 0, sizeof(int), s));
   solve::compare_int(a.n + 1, a.rp, t.rp, diff.p, s);
   solve::compare_int(a.nnz, a.ci, t.ci, diff.p, s);
-  int d = 0;
-  HBGS_HIP(hipMemcpyAsync(&d, diff.p, sizeof(int), hipMemcpyDeviceToHost, s));
-  HBGS_HIP(hipStreamSynchronize(s));
-  return d == 0;
+  return setup::read_one(diff.p, s) == 0;
 }
 
 // host wall time per setup stage: to(q) closes the running stage and starts q
@@ -649,10 +671,7 @@ static void build_hierarchy(hbgs_ctx* c, Field& F, hipStream_t s) {
     Tmp<double> d(n);
     HBGS_HIP(hipMemsetAsync(flag1.p, 0, sizeof(int), s));
     setup::diagonal(F.lv[l].A, d.p, flag1.p, s);
-    int missing = 0;
-    HBGS_HIP(hipMemcpyAsync(&missing, flag1.p, sizeof(int), hipMemcpyDeviceToHost, s));
-    HBGS_HIP(hipStreamSynchronize(s));
-    if (missing) HBGS_FAIL(HBGS_EINVAL, "zero or missing diagonal entry in a field block");
+    if (setup::read_one(flag1.p, s)) HBGS_FAIL(HBGS_EINVAL, "zero or missing diagonal entry in a field block");
     if (F.leaf != 0) {  // one-level leaf: diagonal inverse, or the incomplete factors
       Level& L = F.lv[0];
       if (!structurally_symmetric_dev(L.A, s))
@@ -680,10 +699,7 @@ static void build_hierarchy(hbgs_ctx* c, Field& F, hipStream_t s) {
       setup::mis2_init(n, excluded.p, state.p, s);
       for (int round = 0;; ++round) {
         setup::mis2_round(A, strong.p, salt, state.p, m1.p, r1.p, flag1.p, s);
-        int und = 0;
-        HBGS_HIP(hipMemcpyAsync(&und, flag1.p, sizeof(int), hipMemcpyDeviceToHost, s));
-        HBGS_HIP(hipStreamSynchronize(s));
-        if (und == 0) break;
+        if (setup::read_one(flag1.p, s) == 0) break;
         if (round > n + 2) HBGS_FAIL(HBGS_ESETUP, "aggregation did not terminate");
       }
       Tmp<int> rflag(n), sflag(n);
@@ -990,8 +1006,7 @@ static void field_deps(hbgs_ctx* c, int tr, hipStream_t s) {
     solve::column_fields(tr ? c->F[f].upperT : c->F[f].lower, c->nf, lo.data(), hi.data(), masks.p + f, s);
   }
   std::vector<int> hm(c->nf);
-  HBGS_HIP(hipMemcpyAsync(hm.data(), masks.p, sizeof(int) * c->nf, hipMemcpyDeviceToHost, s));
-  HBGS_HIP(hipStreamSynchronize(s));
+  setup::read_back(hm.data(), masks.p, sizeof(int) * c->nf, s);
   for (int f = 0; f < c->nf; ++f) c->F[f].deps[tr] = (uint32_t)hm[f];
 }
 

@@ -97,6 +97,30 @@ struct StreamScope {
   ~StreamScope() { tmp_stream() = prev; }
 };
 
+// Small results that a setup thread needs on the host (sizes, flags, sums):
+// a kernel writes them into coherent pinned memory, then, after a
+// system-scope fence, the flag that the host polls.  A copy to pageable
+// memory instead is a copy kernel, a completion signal and a staging pass.
+// One message at a time: post, then wait.
+struct MailArg {  // for the posting kernel
+  uint64_t* slot;  // slot[0]: flag; data from slot[8] (64 bytes) on
+  uint64_t seq;
+};
+class Mail {
+ public:
+  static constexpr size_t kBytes = 4096;  // data of one message at most
+  Mail() = default;
+  ~Mail();
+  Mail(const Mail&) = delete;
+  Mail& operator=(const Mail&) = delete;
+  MailArg next();                              // the next message's address
+  const void* wait(hipStream_t s);             // until it has arrived; its data
+ private:
+  uint64_t* host_ = nullptr;
+  uint64_t* dev_ = nullptr;
+  uint64_t seq_ = 0;
+};
+
 // Scratch memory for the setup temporaries of one host thread: a stack of
 // device chunks that is kept across rebuilds, so a rebuild of the same size
 // makes no allocation call (allocation calls from several setup threads
@@ -112,6 +136,7 @@ class Scratch {
   Scratch& operator=(const Scratch&) = delete;
   void* get(size_t bytes);
   void put(void* p);
+  Mail mail;
 
  private:
   struct Chunk {
@@ -274,6 +299,15 @@ inline unsigned grid_for(int64_t work, int block, int64_t cap = 1 << 20) {
 // (setup_kernels.hip, compiled without floating-point contraction so that
 // every value matches a sequential, rounded-product-then-add evaluation)
 namespace setup {
+// bytes (a multiple of 4) of device memory to the host, after the work
+// enqueued on s so far: through the thread's mail when it has a scratch
+void read_back(void* dst, const void* src, size_t bytes, hipStream_t s);
+template <class T>
+T read_one(const T* src, hipStream_t s) {
+  T t;
+  read_back(&t, src, sizeof(T), s);
+  return t;
+}
 // exclusive prefix sums; out has n+1 entries (out[n] = total); returns total
 int64_t scan_i32_to_i64(const int* in, int64_t* out, int64_t n, hipStream_t s);
 int64_t scan_i64(const int64_t* in, int64_t* out, int64_t n, hipStream_t s);

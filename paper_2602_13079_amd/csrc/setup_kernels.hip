@@ -115,28 +115,97 @@ static int row_lanes(int64_t n, int64_t nnz) {
     HBGS_HIP(hipGetLastError());                                       \
   } while (0)
 
+// ------------------------------------------------------- results on the host
+// one block: the message's words, then (every thread's stores fenced) its flag
+__device__ __forceinline__ void mail_flag(MailArg m) {
+  __threadfence_system();
+  __syncthreads();
+  if (threadIdx.x == 0) __hip_atomic_store(m.slot, m.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+__global__ __launch_bounds__(BLK) void k_mail(const uint32_t* __restrict__ src, int words, MailArg m) {
+  uint32_t* dst = reinterpret_cast<uint32_t*>(m.slot + 8);
+  for (int t = threadIdx.x; t < words; t += BLK) dst[t] = src[t];
+  mail_flag(m);
+}
+void read_back(void* dst, const void* src, size_t bytes, hipStream_t s) {
+  Scratch* sc = tmp_scratch();
+  if (!sc || bytes > Mail::kBytes || bytes % 4) {
+    HBGS_HIP(hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s));
+    HBGS_HIP(hipStreamSynchronize(s));
+    return;
+  }
+  const MailArg m = sc->mail.next();
+  k_mail<<<1, BLK, 0, s>>>(static_cast<const uint32_t*>(src), (int)(bytes / 4), m);
+  HBGS_HIP(hipGetLastError());
+  std::memcpy(dst, sc->mail.wait(s), bytes);
+}
+
 // ------------------------------------------------------------------ scans
-// Exclusive scan in tiles of 1024: tile sums, scan of the tile sums
-// (recursive), then a block-local scan with the tile offset.  Integers only.
+// Exclusive scan in tiles of 1024: tile sums, one block scans the tile sums
+// (and posts the total to the host, which goes on while the last kernel
+// runs), then a block-local scan with the tile offset.  Integers only.
+// Three launches and one wait; scanning the tile sums by recursion with the
+// totals copied back took eight launches and three waits.
 template <class TI>
 __global__ void k_tile_sums(const TI* in, int64_t n, int64_t* tsum) {
-  __shared__ int64_t sh[BLK];
+  __shared__ int64_t sh[BLK / 64];
   int64_t base = (int64_t)blockIdx.x * SCAN_TILE + (int64_t)threadIdx.x * SCAN_PER_THREAD;
   int64_t acc = 0;
   for (int q = 0; q < SCAN_PER_THREAD; ++q)
     if (base + q < n) acc += (int64_t)in[base + q];
-  sh[threadIdx.x] = acc;
+  for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = acc;
   __syncthreads();
-  for (int s = BLK / 2; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
-    __syncthreads();
+  if (threadIdx.x == 0) tsum[blockIdx.x] = sh[0] + sh[1] + sh[2] + sh[3];
+}
+static_assert(BLK == 256, "four waves per tile");
+
+// exclusive scan of one value per thread of the block; *total: their sum
+template <int NT>
+__device__ __forceinline__ int64_t block_scan(int64_t v, int64_t* sh, int64_t* total) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  int64_t inc = v;
+  for (int off = 1; off < 64; off <<= 1) {
+    const int64_t o = __shfl_up(inc, off, 64);
+    if (lane >= off) inc += o;
   }
-  if (threadIdx.x == 0) tsum[blockIdx.x] = sh[0];
+  __syncthreads();
+  if (lane == 63) sh[w] = inc;
+  __syncthreads();
+  int64_t before = 0, all = 0;
+#pragma unroll
+  for (int k = 0; k < NT / 64; ++k) {
+    before += k < w ? sh[k] : 0;
+    all += sh[k];
+  }
+  *total = all;
+  return before + inc - v;
+}
+// toff[t] = sum of tsum[0 .. t-1], toff[nt] = total (mailed when m.slot is set)
+constexpr int SCAN_TOP = 1024;
+__global__ __launch_bounds__(SCAN_TOP) void k_scan_tiles(const int64_t* __restrict__ tsum, int64_t nt,
+                                                         int64_t* __restrict__ toff, MailArg m) {
+  __shared__ int64_t sh[SCAN_TOP / 64];
+  int64_t run = 0;
+  for (int64_t b = 0; b < nt; b += SCAN_TOP) {
+    const int64_t i = b + threadIdx.x;
+    int64_t all;
+    const int64_t x = block_scan<SCAN_TOP>(i < nt ? tsum[i] : 0, sh, &all);
+    if (i < nt) toff[i] = run + x;
+    run += all;
+  }
+  if (threadIdx.x == 0) {
+    toff[nt] = run;
+    if (m.slot) m.slot[8] = (uint64_t)run;
+  }
+  if (m.slot) mail_flag(m);
 }
 
+// toff null: one tile, whose total goes to *total and (m.slot set) the host
 template <class TI, class TO>
-__global__ void k_tile_scan(const TI* in, int64_t n, const int64_t* toff, TO* out) {
-  __shared__ int64_t sh[BLK];
+__global__ __launch_bounds__(BLK) void k_tile_scan(const TI* in, int64_t n, const int64_t* toff, TO* out,
+                                                   int64_t* total, MailArg m) {
+  __shared__ int64_t sh[BLK / 64];
   int64_t base = (int64_t)blockIdx.x * SCAN_TILE + (int64_t)threadIdx.x * SCAN_PER_THREAD;
   int64_t v[SCAN_PER_THREAD];
   int64_t acc = 0;
@@ -144,55 +213,44 @@ __global__ void k_tile_scan(const TI* in, int64_t n, const int64_t* toff, TO* ou
     v[q] = base + q < n ? (int64_t)in[base + q] : 0;
     acc += v[q];
   }
-  sh[threadIdx.x] = acc;
-  __syncthreads();
-  // inclusive Hillis-Steele scan of the per-thread sums
-  for (int s = 1; s < BLK; s <<= 1) {
-    int64_t t = (int)threadIdx.x >= s ? sh[threadIdx.x - s] : 0;
-    __syncthreads();
-    sh[threadIdx.x] += t;
-    __syncthreads();
-  }
-  int64_t run = toff[blockIdx.x] + sh[threadIdx.x] - acc;
+  int64_t all;
+  int64_t run = block_scan<BLK>(acc, sh, &all);
+  if (toff) run += toff[blockIdx.x];
   for (int q = 0; q < SCAN_PER_THREAD; ++q) {
     if (base + q < n) out[base + q] = (TO)run;
     run += v[q];
   }
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    const int64_t t = toff ? toff[gridDim.x] : all;
+    out[n] = (TO)t;
+    if (!toff) {
+      *total = t;
+      if (m.slot) m.slot[8] = (uint64_t)t;
+    }
+  }
+  if (!toff && m.slot) mail_flag(m);
 }
 
-template <class TO>
-__global__ void k_scan_total(const int64_t* toff, int64_t ntiles, int64_t n, TO* out) {
-  out[n] = (TO)toff[ntiles];
-}
-
-// out[0..n] exclusive prefix of in[0..n-1] (out[n] = total); toff scratch
+// out[0..n] exclusive prefix of in[0..n-1] (out[n] = total)
 template <class TI, class TO>
 static int64_t scan_impl(const TI* in, TO* out, int64_t n, hipStream_t s) {
-  if (n == 0) {
-    TO z = 0;
-    HBGS_HIP(hipMemcpyAsync(out, &z, sizeof(TO), hipMemcpyHostToDevice, s));
-    HBGS_HIP(hipStreamSynchronize(s));
-    return 0;
-  }
-  int64_t nt = (n + SCAN_TILE - 1) / SCAN_TILE;
+  const int64_t nt = std::max<int64_t>(1, (n + SCAN_TILE - 1) / SCAN_TILE);
   Tmp<int64_t> tsum(nt), toff(nt + 1);
-  k_tile_sums<TI><<<(unsigned)nt, BLK, 0, s>>>(in, n, tsum.p);
-  HBGS_HIP(hipGetLastError());
+  Scratch* sc = tmp_scratch();
+  const MailArg m = sc ? sc->mail.next() : MailArg{nullptr, 0};
   if (nt == 1) {
-    int64_t h[2] = {0, 0};
-    HBGS_HIP(hipMemcpyAsync(&h[1], tsum.p, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    HBGS_HIP(hipStreamSynchronize(s));
-    HBGS_HIP(hipMemcpyAsync(toff.p, h, 2 * sizeof(int64_t), hipMemcpyHostToDevice, s));
+    k_tile_scan<TI, TO><<<1, BLK, 0, s>>>(in, n, nullptr, out, toff.p + nt, m);
   } else {
-    scan_impl<int64_t, int64_t>(tsum.p, toff.p, nt, s);
+    k_tile_sums<TI><<<(unsigned)nt, BLK, 0, s>>>(in, n, tsum.p);
+    k_scan_tiles<<<1, SCAN_TOP, 0, s>>>(tsum.p, nt, toff.p, m);
+    k_tile_scan<TI, TO><<<(unsigned)nt, BLK, 0, s>>>(in, n, toff.p, out, nullptr, MailArg{nullptr, 0});
   }
-  k_tile_scan<TI, TO><<<(unsigned)nt, BLK, 0, s>>>(in, n, toff.p, out);
-  HBGS_HIP(hipGetLastError());
-  k_scan_total<TO><<<1, 1, 0, s>>>(toff.p, nt, n, out);
   HBGS_HIP(hipGetLastError());
   int64_t total = 0;
-  HBGS_HIP(hipMemcpyAsync(&total, toff.p + nt, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-  HBGS_HIP(hipStreamSynchronize(s));
+  if (sc)
+    std::memcpy(&total, sc->mail.wait(s), sizeof(total));
+  else
+    read_back(&total, toff.p + nt, sizeof(total), s);
   return total;
 }
 
@@ -387,30 +445,37 @@ __global__ __launch_bounds__(SORT_BLK) void k_sort_rows_lds(int n, const int* rp
   }
 }
 
-// one block per listed row of up to LONG_LDS entries: every entry's
-// destination is its rank (the number of smaller columns in the row)
-__global__ __launch_bounds__(BLK) void k_sort_long_rows(const int* rows, const int* rp, int* ci, double* v) {
+// the *count listed rows of up to LONG_LDS entries, one block per row:
+// every entry's destination is its rank (the number of smaller columns in
+// the row)
+__global__ __launch_bounds__(BLK) void k_sort_long_rows(const int* count, const int* rows, const int* rp, int* ci,
+                                                        double* v) {
   __shared__ int sc[LONG_LDS];
   __shared__ double sv[LONG_LDS];
-  const int row = rows[blockIdx.x];
-  const int s = rp[row], len = rp[row + 1] - s;
-  if (len > LONG_LDS) return;
-  for (int k = threadIdx.x; k < len; k += BLK) {
-    sc[k] = ci[s + k];
-    sv[k] = v ? v[s + k] : 0.0;
-  }
-  __syncthreads();
-  for (int k = threadIdx.x; k < len; k += BLK) {
-    const int c = sc[k];
-    int rank = 0;
-    for (int q = 0; q < len; ++q) rank += sc[q] < c;
-    ci[s + rank] = c;
-    if (v) v[s + rank] = sv[k];
+  const int cnt = *count;
+  for (int b = blockIdx.x; b < cnt; b += gridDim.x) {
+    const int row = rows[b];
+    const int s = rp[row], len = rp[row + 1] - s;
+    if (len > LONG_LDS) continue;
+    __syncthreads();  // the previous row's entries are no longer read
+    for (int k = threadIdx.x; k < len; k += BLK) {
+      sc[k] = ci[s + k];
+      sv[k] = v ? v[s + k] : 0.0;
+    }
+    __syncthreads();
+    for (int k = threadIdx.x; k < len; k += BLK) {
+      const int c = sc[k];
+      int rank = 0;
+      for (int q = 0; q < len; ++q) rank += sc[q] < c;
+      ci[s + rank] = c;
+      if (v) v[s + rank] = sv[k];
+    }
   }
 }
 
 // rows longer than LONG_LDS: insertion sort by one thread per listed row
-__global__ void k_sort_huge_rows(int cnt, const int* rows, const int* rp, int* ci, double* v) {
+__global__ void k_sort_huge_rows(const int* count, const int* rows, const int* rp, int* ci, double* v) {
+  const int cnt = *count;
   GRID_STRIDE(t, cnt) {
     const int i = rows[t];
     int s = rp[i], e = rp[i + 1];
@@ -436,13 +501,10 @@ void sort_rows(const DCsr& a, hipStream_t s) {
   HBGS_HIP(hipMemsetAsync(n_long.p, 0, sizeof(int), s));
   k_sort_rows_lds<<<grid_for(a.n, SORT_BLK), SORT_BLK, 0, s>>>(a.n, a.rp, a.ci, a.v, n_long.p, long_rows.p);
   HBGS_HIP(hipGetLastError());
-  int nl = 0;
-  HBGS_HIP(hipMemcpyAsync(&nl, n_long.p, sizeof(int), hipMemcpyDeviceToHost, s));
-  HBGS_HIP(hipStreamSynchronize(s));
-  if (nl > 0) {
-    k_sort_long_rows<<<nl, BLK, 0, s>>>(long_rows.p, a.rp, a.ci, a.v);
-    HBGS_HIP(hipGetLastError());
-    k_sort_huge_rows<<<grid_for(nl, BLK), BLK, 0, s>>>(nl, long_rows.p, a.rp, a.ci, a.v);
+  k_sort_long_rows<<<grid_for(a.n, 1, 2048), BLK, 0, s>>>(n_long.p, long_rows.p, a.rp, a.ci, a.v);
+  HBGS_HIP(hipGetLastError());
+  if (a.m > LONG_LDS) {  // a row can be that long
+    k_sort_huge_rows<<<grid_for(a.n, BLK, 256), BLK, 0, s>>>(n_long.p, long_rows.p, a.rp, a.ci, a.v);
     HBGS_HIP(hipGetLastError());
   }
 }
@@ -460,7 +522,6 @@ void transpose(const DCsr& a, DCsr& t, hipStream_t s) {
   const int L = row_lanes(a.n, a.nnz);
   LAUNCH_ROW_GROUPS(k_transpose_scatter, L, a.n, s, a.n, a.rp, a.ci, a.v, cnt.p, t.ci, t.v);
   sort_rows(t, s);
-  HBGS_HIP(hipStreamSynchronize(s));
 }
 
 // ----------------------------------------------------------- block extract
@@ -727,7 +788,6 @@ void agg_phase12(const DCsr& a, const char* strong, uint64_t salt, const char* s
   const int L = row_lanes(a.n, a.nnz);
   LAUNCH_ROW_GROUPS(k_agg_phase1, L, a.n, s, a.n, a.rp, a.ci, strong, state, root_rank, p1.p);
   LAUNCH_ROW_GROUPS(k_agg_phase2, L, a.n, s, a.n, a.rp, a.ci, strong, salt, state, p1.p, agg, single_flag);
-  HBGS_HIP(hipStreamSynchronize(s));
 }
 void agg_phase3(int n, const int* single_flag, const int64_t* single_rank, int nroot, int* agg, hipStream_t s) {
   k_agg_phase3<<<grid_for(n, BLK), BLK, 0, s>>>(n, single_flag, single_rank, nroot, agg);
@@ -898,10 +958,11 @@ static void pw_apply(const DCsr& b, const double* d, const double* win, const un
 #undef HBGS_PW
   HBGS_HIP(hipGetLastError());
 }
-// w = y * 2^-e with max|y| = f * 2^e, f in [0.5, 1)
-__global__ void k_pw_scale(int n, const double* y, const unsigned long long* amax, double* w) {
+// w = y * 2^-e with max|y| = f * 2^e, f in [0.5, 1); *mx_out = max|y|
+__global__ void k_pw_scale(int n, const double* y, const unsigned long long* amax, double* w, double* mx_out) {
   double mx = __longlong_as_double((long long)*amax);
   int e = 0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) *mx_out = mx;
   if (mx > 0.0) frexp(mx, &e);
   GRID_STRIDE(i, n) w[i] = mx > 0.0 ? ldexp(y[i], -e) : 0.0;
 }
@@ -947,23 +1008,22 @@ __global__ void __launch_bounds__(256) k_chunk_total(int64_t m, const double* pa
   if (threadIdx.x == 0) *out = s;
 }
 
-static double chunked_dot(int64_t n, const double* x, const double* y, double* part, double* out,
-                          hipStream_t s) {
-  if (n == 0) return 0.0;
+// out[0] = x . y, out[1] = x . x
+static void chunked_dots(int64_t n, const double* x, const double* y, double* part, double* out, hipStream_t s) {
   const int64_t m = (n + 255) / 256;
-  k_chunk_dot<<<grid_for(m, DOT_RUNS, 2048), 256, 0, s>>>(n, x, y, part);
+  const double* other[2] = {y, x};
+  for (int q = 0; q < 2; ++q) {
+    k_chunk_dot<<<grid_for(m, DOT_RUNS, 2048), 256, 0, s>>>(n, x, other[q], part);
+    k_chunk_total<<<1, 256, 0, s>>>(m, part, out + q);
+  }
   HBGS_HIP(hipGetLastError());
-  k_chunk_total<<<1, 256, 0, s>>>(m, part, out);
-  HBGS_HIP(hipGetLastError());
-  double r = 0.0;
-  HBGS_HIP(hipMemcpyAsync(&r, out, sizeof(double), hipMemcpyDeviceToHost, s));
-  HBGS_HIP(hipStreamSynchronize(s));
-  return r;
 }
 
 double power_estimate(const DCsr& b, const double* d, int iters, uint64_t salt, hipStream_t s) {
   const int n = b.n;
-  Tmp<double> w(n), y(n), pa((n + 255) / 256 + 1), pb(1);
+  if (n == 0) return 0.0;
+  Tmp<double> w(n), y(n), pa((n + 255) / 256 + 1);
+  Tmp<double> res(3);  // the two dots and the last iterate's largest entry
   Tmp<unsigned long long> amax(iters > 0 ? iters : 1);
   const unsigned g = grid_for(n, BLK);
   k_pw_init<<<g, BLK, 0, s>>>(n, salt, w.p);
@@ -974,28 +1034,22 @@ double power_estimate(const DCsr& b, const double* d, int iters, uint64_t salt, 
   for (int it = 0; it < iters; ++it) {
     pw_apply(b, d, buf[(it + 1) & 1], it ? amax.p + it - 1 : nullptr, buf[it & 1], amax.p + it, s);
   }
-  const double* wl = w.p;  // the normalised last iterate
+  double h[3] = {0.0, 0.0, 0.0};
   if (iters > 0) {
-    unsigned long long mx = 0;
-    HBGS_HIP(hipMemcpyAsync(&mx, amax.p + iters - 1, sizeof(mx), hipMemcpyDeviceToHost, s));
-    HBGS_HIP(hipStreamSynchronize(s));
-    double m = 0.0;
-    std::memcpy(&m, &mx, sizeof(m));
-    if (m == 0.0) return 0.0;
+    // the normalised last iterate and its image (all zero when it vanished)
     double* last = buf[(iters - 1) & 1];
     double* other = buf[iters & 1];
-    k_pw_scale<<<g, BLK, 0, s>>>(n, last, amax.p + iters - 1, other);
+    k_pw_scale<<<g, BLK, 0, s>>>(n, last, amax.p + iters - 1, other, res.p + 2);
     HBGS_HIP(hipGetLastError());
-    wl = other;
     pw_apply(b, d, other, nullptr, last, nullptr, s);
-    double wy = chunked_dot(n, wl, last, pa.p, pb.p, s);
-    double ww = chunked_dot(n, wl, wl, pa.p, pb.p, s);
-    return wy / ww;
+    chunked_dots(n, other, last, pa.p, res.p, s);
+    read_back(h, res.p, sizeof(h), s);
+    return h[2] == 0.0 ? 0.0 : h[0] / h[1];
   }
   pw_apply(b, d, w.p, nullptr, y.p, nullptr, s);
-  double wy = chunked_dot(n, w.p, y.p, pa.p, pb.p, s);
-  double ww = chunked_dot(n, w.p, w.p, pa.p, pb.p, s);
-  return wy / ww;
+  chunked_dots(n, w.p, y.p, pa.p, res.p, s);
+  read_back(h, res.p, 2 * sizeof(double), s);
+  return h[0] / h[1];
 }
 
 // ------------------------------------------------------ smoothed prolongator
@@ -1527,68 +1581,82 @@ __global__ void k_spgemm_numeric(int r0, int r1, const int* arp, const int* aci,
 __global__ void k_spgemm_mark_all(int n, const int64_t* ub, int* cnt) {
   GRID_STRIDE(i, n) cnt[i] = ub[i] > 0 ? -1 : 0;
 }
-// global table sizes of the rows the group kernels marked (cnt < 0)
-__global__ void k_spgemm_tsize_sym(int n, int bm, const int64_t* ub, const int* cnt, int64_t* ts) {
-  GRID_STRIDE(i, n) ts[i] = cnt[i] < 0 ? table_size(sym_need(ub[i], bm)) : 0;
+// global table sizes of the rows the group kernels marked (cnt < 0); *any:
+// some row has one
+__global__ void k_spgemm_tsize_sym(int n, int bm, const int64_t* ub, const int* cnt, int64_t* ts, int* any) {
+  int some = 0;
+  GRID_STRIDE(i, n) {
+    const int64_t t = cnt[i] < 0 ? table_size(sym_need(ub[i], bm)) : 0;
+    ts[i] = t;
+    some |= t > 0;
+  }
+  if (some) atomicOr(any, 1);
 }
 // rows beyond the wave kernels (more than wave_max entries) are listed for
 // the one-block-per-row kernel; rows beyond it (block_max) get a global table
+// (*any: some row does)
 __global__ void k_spgemm_tsize_num(int n, const int* crp, int64_t wave_max, int64_t block_max, int64_t* ts,
-                                   int* nmid, int* mid) {
+                                   int* nmid, int* mid, int* any) {
   GRID_STRIDE(i, n) {
     const int64_t cnt = crp[i + 1] - crp[i];
     ts[i] = 0;
     if (cnt <= wave_max) continue;
     if (cnt <= block_max)
       mid[atomicAdd(nmid, 1)] = (int)i;
-    else
+    else {
       ts[i] = table_size(cnt);
+      atomicOr(any, 1);
+    }
   }
 }
 
-// numeric product of one listed row per block (rows of up to
+// numeric product of the *count listed rows, one per block (rows of up to
 // SPG_BLK_SLOTS / 2 entries): the threads take the entries of one B row at a
 // time and the block synchronises between rows of B, so every slot sums its
 // products in ascending k
-__global__ __launch_bounds__(BLK) void k_spgemm_num_block(const int* rows, const int* arp, const int* aci,
-                                                          const double* av, const int* brp, const int* bci,
+__global__ __launch_bounds__(BLK) void k_spgemm_num_block(const int* count, const int* rows, const int* arp,
+                                                          const int* aci, const double* av, const int* brp, const int* bci,
                                                           const double* bv, const int* crp, int* cci, double* cv,
                                                           int* overflow) {
   __shared__ int keys[SPG_BLK_SLOTS];
   __shared__ double vals[SPG_BLK_SLOTS];
-  const int i = rows[blockIdx.x];
-  const int o = crp[i], cnt = crp[i + 1] - o;
-  int T = 64;
-  while (T < 2 * cnt) T <<= 1;
-  for (int q = threadIdx.x; q < T; q += BLK) {
-    keys[q] = -1;
-    vals[q] = 0.0;
-  }
-  __syncthreads();
-  const uint32_t mask = (uint32_t)(T - 1);
-  for (int k = arp[i]; k < arp[i + 1]; ++k) {
-    const int kk = aci[k];
-    const double a = av[k];
-    for (int q = brp[kk] + threadIdx.x; q < brp[kk + 1]; q += BLK) {
-      bool fresh;
-      const int h = lds_claim(keys, mask, bci[q], &fresh);
-      if (h >= 0)
-        vals[h] += a * bv[q];
-      else
-        atomicOr(overflow, 1);
+  const int nrows = *count;
+  for (int r = blockIdx.x; r < nrows; r += gridDim.x) {
+    const int i = rows[r];
+    const int o = crp[i], cnt = crp[i + 1] - o;
+    int T = 64;
+    while (T < 2 * cnt) T <<= 1;
+    for (int q = threadIdx.x; q < T; q += BLK) {
+      keys[q] = -1;
+      vals[q] = 0.0;
     }
     __syncthreads();
-  }
-  for (int q = threadIdx.x; q < T; q += BLK) {
-    const int c = keys[q];
-    if (c < 0) continue;
-    int rank = 0;
-    for (int p = 0; p < T; ++p) {
-      const int d = keys[p];
-      rank += (d >= 0) & (d < c);
+    const uint32_t mask = (uint32_t)(T - 1);
+    for (int k = arp[i]; k < arp[i + 1]; ++k) {
+      const int kk = aci[k];
+      const double a = av[k];
+      for (int q = brp[kk] + threadIdx.x; q < brp[kk + 1]; q += BLK) {
+        bool fresh;
+        const int h = lds_claim(keys, mask, bci[q], &fresh);
+        if (h >= 0)
+          vals[h] += a * bv[q];
+        else
+          atomicOr(overflow, 1);
+      }
+      __syncthreads();
     }
-    cci[o + rank] = c;
-    cv[o + rank] = vals[q];
+    for (int q = threadIdx.x; q < T; q += BLK) {
+      const int c = keys[q];
+      if (c < 0) continue;
+      int rank = 0;
+      for (int p = 0; p < T; ++p) {
+        const int d = keys[p];
+        rank += (d >= 0) & (d < c);
+      }
+      cci[o + rank] = c;
+      cv[o + rank] = vals[q];
+    }
+    __syncthreads();  // the tables are cleared for the next row
   }
 }
 
@@ -1620,8 +1688,12 @@ void spgemm(const DCsr& a, const DCsr& b, DCsr& c, Pool& pool, hipStream_t s) {
   c.n = n;
   c.m = b.m;
   Tmp<int64_t> ub(n), ts(n), toff(n + 1);
-  Tmp<int> cnt(n), overflow(1);
-  HBGS_HIP(hipMemsetAsync(overflow.p, 0, sizeof(int), s));
+  // counters: accumulator overflow, rows with global tables (symbolic,
+  // numeric), wide rows (symbolic, numeric), one-block rows
+  enum { OVF, ANY_SYM, ANY_NUM, WIDE_SYM, WIDE_NUM, MID, NFLAGS };
+  Tmp<int> cnt(n), flags(NFLAGS);
+  int* overflow = flags.p + OVF;
+  HBGS_HIP(hipMemsetAsync(flags.p, 0, NFLAGS * sizeof(int), s));
   k_spgemm_ub<<<grid_for(n, BLK), BLK, 0, s>>>(n, a.rp, a.ci, b.rp, ub.p);
   HBGS_HIP(hipGetLastError());
   // lanes per row from the mean length of B's rows; rows too long for the
@@ -1634,15 +1706,14 @@ void spgemm(const DCsr& a, const DCsr& b, DCsr& c, Pool& pool, hipStream_t s) {
   const int64_t num_b = route == 3 ? 0 : SPG_BLK_SLOTS / 2;              // block kernel's rows
   auto groups = [&](int l) { return (unsigned)(((int64_t)n + (int64_t)SPG_WAVES * (64 / l) - 1) / (SPG_WAVES * (64 / l))); };
   // the wide kernels stride over the listed rows (every row when lpr = 64)
-  Tmp<int> wide(lpr < 64 ? n : 1), nwide(1);
+  Tmp<int> wide(lpr < 64 ? n : 1);
   int* wl = lpr < 64 ? wide.p : nullptr;
-  int* wn = lpr < 64 ? nwide.p : nullptr;
+  int* wn = lpr < 64 ? flags.p + WIDE_SYM : nullptr;
   const unsigned wgrid = lpr < 64 ? grid_for(n, SPG_WAVES, 8192) : grid_for(n, SPG_WAVES);
   // symbolic: distinct columns per row
-  HBGS_HIP(hipMemsetAsync(nwide.p, 0, sizeof(int), s));
 #define HBGS_SYM(L)                                                                                            \
   k_spgemm_sym_grp<L><<<groups(L), 64 * SPG_WAVES, 0, s>>>(n, b.m, a.rp, a.ci, b.rp, b.ci, ub.p, sym_g, cnt.p, \
-                                                           overflow.p)
+                                                           overflow)
   if (route == 3) {
     k_spgemm_mark_all<<<grid_for(n, BLK), BLK, 0, s>>>(n, ub.p, cnt.p);
   } else {
@@ -1654,16 +1725,17 @@ void spgemm(const DCsr& a, const DCsr& b, DCsr& c, Pool& pool, hipStream_t s) {
     }
     if (lpr < 64)
       k_spgemm_list<<<grid_for(n, BLK, 8192), BLK, 0, s>>>(n, ub.p, b.m, nullptr, sym_g, INT64_MAX, wide.p,
-                                                           nwide.p);
+                                                           flags.p + WIDE_SYM);
     k_spgemm_sym_wave<<<wgrid, 64 * SPG_WAVES, 0, s>>>(n, b.m, a.rp, a.ci, b.rp, b.ci, ub.p, wl, wn, cnt.p);
   }
 #undef HBGS_SYM
   HBGS_HIP(hipGetLastError());
-  k_spgemm_tsize_sym<<<grid_for(n, BLK), BLK, 0, s>>>(n, b.m, ub.p, cnt.p, ts.p);
+  k_spgemm_tsize_sym<<<grid_for(n, BLK, 4096), BLK, 0, s>>>(n, b.m, ub.p, cnt.p, ts.p, flags.p + ANY_SYM);
   HBGS_HIP(hipGetLastError());
   std::vector<int64_t> h_off;  // row offsets of the global tables, only when some row needs one
   std::vector<int> cuts;
-  if (scan_i64(ts.p, toff.p, n, s) > 0) {
+  if (read_one(flags.p + ANY_SYM, s)) {
+    scan_i64(ts.p, toff.p, n, s);
     h_off.resize(n + 1);
     HBGS_HIP(hipMemcpyAsync(h_off.data(), toff.p, sizeof(int64_t) * (n + 1), hipMemcpyDeviceToHost, s));
     HBGS_HIP(hipStreamSynchronize(s));
@@ -1681,10 +1753,9 @@ void spgemm(const DCsr& a, const DCsr& b, DCsr& c, Pool& pool, hipStream_t s) {
   c.ci = pool.make<int>(c.nnz);
   c.v = pool.make<double>(c.nnz);
   // numeric
-  HBGS_HIP(hipMemsetAsync(nwide.p, 0, sizeof(int), s));
 #define HBGS_NUM(L)                                                                                            \
   k_spgemm_num_grp<L><<<groups(L), 64 * SPG_WAVES, 0, s>>>(n, a.rp, a.ci, a.v, b.rp, b.ci, b.v, c.rp, num_g,     \
-                                                           nullptr, nullptr, c.ci, c.v, overflow.p)
+                                                           nullptr, nullptr, c.ci, c.v, overflow)
   switch (lpr) {
     case 8: HBGS_NUM(8); break;
     case 16: HBGS_NUM(16); break;
@@ -1693,22 +1764,25 @@ void spgemm(const DCsr& a, const DCsr& b, DCsr& c, Pool& pool, hipStream_t s) {
   }
 #undef HBGS_NUM
   if (lpr < 64)
-    k_spgemm_list<<<grid_for(n, BLK, 8192), BLK, 0, s>>>(n, nullptr, 0, c.rp, num_g, num_w, wide.p, nwide.p);
+    k_spgemm_list<<<grid_for(n, BLK, 8192), BLK, 0, s>>>(n, nullptr, 0, c.rp, num_g, num_w, wide.p,
+                                                         flags.p + WIDE_NUM);
+  wn = lpr < 64 ? flags.p + WIDE_NUM : nullptr;
   k_spgemm_num_grp<64><<<wgrid, 64 * SPG_WAVES, 0, s>>>(n, a.rp, a.ci, a.v, b.rp, b.ci, b.v, c.rp, num_w, wl, wn,
-                                                         c.ci, c.v, overflow.p);
+                                                         c.ci, c.v, overflow);
   HBGS_HIP(hipGetLastError());
-  Tmp<int> nmid(1), mid(n);
-  HBGS_HIP(hipMemsetAsync(nmid.p, 0, sizeof(int), s));
-  k_spgemm_tsize_num<<<grid_for(n, BLK), BLK, 0, s>>>(n, c.rp, num_w, num_b, ts.p, nmid.p, mid.p);
+  Tmp<int> mid(n);
+  k_spgemm_tsize_num<<<grid_for(n, BLK), BLK, 0, s>>>(n, c.rp, num_w, num_b, ts.p, flags.p + MID, mid.p,
+                                                      flags.p + ANY_NUM);
   HBGS_HIP(hipGetLastError());
-  int h_nmid = 0;
-  HBGS_HIP(hipMemcpyAsync(&h_nmid, nmid.p, sizeof(int), hipMemcpyDeviceToHost, s));
-  HBGS_HIP(hipStreamSynchronize(s));
-  if (h_nmid > 0) {
-    k_spgemm_num_block<<<h_nmid, BLK, 0, s>>>(mid.p, a.rp, a.ci, a.v, b.rp, b.ci, b.v, c.rp, c.ci, c.v, overflow.p);
+  if (b.m > num_w) {  // a row can have more entries than the wave kernel takes
+    k_spgemm_num_block<<<grid_for(n, 1, 1024), BLK, 0, s>>>(flags.p + MID, mid.p, a.rp, a.ci, a.v, b.rp, b.ci, b.v,
+                                                            c.rp, c.ci, c.v, overflow);
     HBGS_HIP(hipGetLastError());
   }
-  if (scan_i64(ts.p, toff.p, n, s) > 0) {
+  int h_flags[NFLAGS];
+  read_back(h_flags, flags.p, sizeof(h_flags), s);
+  if (h_flags[ANY_NUM]) {
+    scan_i64(ts.p, toff.p, n, s);
     h_off.resize(n + 1);
     HBGS_HIP(hipMemcpyAsync(h_off.data(), toff.p, sizeof(int64_t) * (n + 1), hipMemcpyDeviceToHost, s));
     HBGS_HIP(hipStreamSynchronize(s));
@@ -1723,10 +1797,7 @@ void spgemm(const DCsr& a, const DCsr& b, DCsr& c, Pool& pool, hipStream_t s) {
       HBGS_HIP(hipGetLastError());
     }
   }
-  int ovf = 0;
-  HBGS_HIP(hipMemcpyAsync(&ovf, overflow.p, sizeof(int), hipMemcpyDeviceToHost, s));
-  HBGS_HIP(hipStreamSynchronize(s));
-  if (ovf) HBGS_FAIL(HBGS_ESETUP, "sparse product: accumulator table overflow");
+  if (h_flags[OVF]) HBGS_FAIL(HBGS_ESETUP, "sparse product: accumulator table overflow");
 }
 
 // ------------------------------------------------------- dense coarsest LU
@@ -2288,9 +2359,9 @@ void transpose_symmetric(const DCsr& a, double* vt, hipStream_t s) {
 // entries of the fullest block of row_block(q) consecutive rows, over the
 // units block b visits.  Unit u covers rows [4u, 4u + 4); the unit that
 // starts a row block of each size also reads that block's end.  Wave maxima
-// through shuffles, block maxima through LDS; the host takes the maximum
-// over the blocks (no atomics: same-address atomics from every wave cost
-// more than the kernel's loads).
+// through shuffles, block maxima through LDS, then one atomic per block and
+// figure (at most 256 blocks: same-address atomics from every wave cost more
+// than the kernel's loads).
 __global__ __launch_bounds__(BLK) void k_row_stats(int n, const int* __restrict__ rp, int* __restrict__ part) {
   __shared__ int red[BLK / 64][1 + kRowBlocks];
   int m[1 + kRowBlocks] = {};
@@ -2321,7 +2392,7 @@ __global__ __launch_bounds__(BLK) void k_row_stats(int n, const int* __restrict_
   if (threadIdx.x <= kRowBlocks) {
     int x = 0;
     for (int k = 0; k < BLK / 64; ++k) x = max(x, red[k][threadIdx.x]);
-    part[(size_t)blockIdx.x * (1 + kRowBlocks) + threadIdx.x] = x;
+    if (x) atomicMax(&part[threadIdx.x], x);
   }
 }
 void row_stats(DCsr& a, hipStream_t s) {
@@ -2329,17 +2400,14 @@ void row_stats(DCsr& a, hipStream_t s) {
   for (int q = 0; q < kRowBlocks; ++q) a.blkmax[q] = 0;
   if (a.n <= 0) return;
   constexpr int S = 1 + kRowBlocks;
-  const unsigned nb = grid_for(((int64_t)a.n + 3) / 4, BLK, 1024);
-  Tmp<int> part((size_t)nb * S);
-  std::vector<int> h((size_t)nb * S);
-  k_row_stats<<<nb, BLK, 0, s>>>(a.n, a.rp, part.p);
+  Tmp<int> part(S);
+  int h[S];
+  HBGS_HIP(hipMemsetAsync(part.p, 0, sizeof(h), s));
+  k_row_stats<<<grid_for(((int64_t)a.n + 3) / 4, BLK, 256), BLK, 0, s>>>(a.n, a.rp, part.p);
   HBGS_HIP(hipGetLastError());
-  HBGS_HIP(hipMemcpyAsync(h.data(), part.p, sizeof(int) * h.size(), hipMemcpyDeviceToHost, s));
-  HBGS_HIP(hipStreamSynchronize(s));
-  for (unsigned b = 0; b < nb; ++b) {
-    a.maxlen = std::max(a.maxlen, h[(size_t)b * S]);
-    for (int q = 0; q < kRowBlocks; ++q) a.blkmax[q] = std::max(a.blkmax[q], h[(size_t)b * S + 1 + q]);
-  }
+  read_back(h, part.p, sizeof(h), s);
+  a.maxlen = h[0];
+  for (int q = 0; q < kRowBlocks; ++q) a.blkmax[q] = h[1 + q];
 }
 
 // Operand tiles of one row block per workgroup: the tile ids (col /
@@ -2428,8 +2496,7 @@ void build_tiles(Pool& pool, DCsr& a, int rb, hipStream_t s) {
   k_tiles<<<(unsigned)nblk, 256, 0, s>>>(a.n, rb, a.rp, a.ci, tiles, lc, flags.p, flags.p + 1);
   HBGS_HIP(hipGetLastError());
   int h[2] = {0, 0};
-  HBGS_HIP(hipMemcpyAsync(h, flags.p, sizeof(h), hipMemcpyDeviceToHost, s));
-  HBGS_HIP(hipStreamSynchronize(s));
+  read_back(h, flags.p, sizeof(h), s);
   if (h[0] || h[1] <= 0) {
     pool.release(lc);
     pool.release(tiles);
@@ -2508,8 +2575,7 @@ void build_slices(Pool& pool, DCsr& a, hipStream_t s) {
   k_slice_diags<<<grid_for((nsl + 3) / 4, 1, 2048), 256, 0, s>>>(a.n, a.rp, a.ci, tab, count.p, m16, m32, stat.p);
   HBGS_HIP(hipGetLastError());
   int h[2] = {0, 0};
-  HBGS_HIP(hipMemcpyAsync(h, stat.p, sizeof(h), hipMemcpyDeviceToHost, s));
-  HBGS_HIP(hipStreamSynchronize(s));
+  read_back(h, stat.p, sizeof(h), s);
   bool use = !h[1] && h[0] > 0;
   if (use) {
     a.dia_places = counts_to_rowptr(count.p, base.p, nsl, s) * DIA_ROWS;
@@ -2663,8 +2729,7 @@ int ilu_setup(Pool& pool, const DCsr& a, int sub, IluLeaf& out, hipStream_t s) {
     k_sub_fill<<<grid_for(n, BLK), BLK, 0, s>>>(n, a.rp, a.ci, a.v, sub, F.rp, F.ci, F.v, out.dpos, missing.p);
     HBGS_HIP(hipGetLastError());
     int h_missing = 0;
-    HBGS_HIP(hipMemcpyAsync(&h_missing, missing.p, sizeof(int), hipMemcpyDeviceToHost, s));
-    HBGS_HIP(hipStreamSynchronize(s));
+    read_back(&h_missing, missing.p, sizeof(int), s);
     if (h_missing) return -4;
   }
   // schedules (host)
@@ -2700,8 +2765,7 @@ int ilu_setup(Pool& pool, const DCsr& a, int sub, IluLeaf& out, hipStream_t s) {
   k_ilu_factor<<<out.nsub, BLK, 0, s>>>(out.ford, out.flev, out.fsub, F.rp, F.ci, F.v, out.dpos, zp.p);
   HBGS_HIP(hipGetLastError());
   int h_zero = 0;
-  HBGS_HIP(hipMemcpyAsync(&h_zero, zp.p, sizeof(int), hipMemcpyDeviceToHost, s));
-  HBGS_HIP(hipStreamSynchronize(s));
+  read_back(&h_zero, zp.p, sizeof(int), s);
   if (h_zero) return -4;
   F.vf = pool.make<float>(F.nnz);
   cast_f32(F.nnz, F.v, F.vf, s);
@@ -2780,10 +2844,7 @@ void pack_columns(Pool& pool, DCsr& a, hipStream_t s) {
   HBGS_HIP(hipMemsetAsync(bad.p, 0, sizeof(int), s));
   k_col_base<<<grid_for((nch + 3) / 4, 1, 8192), 256, 0, s>>>(a.nnz, a.ci, cb, bad.p);
   HBGS_HIP(hipGetLastError());
-  int h_bad = 0;
-  HBGS_HIP(hipMemcpyAsync(&h_bad, bad.p, sizeof(int), hipMemcpyDeviceToHost, s));
-  HBGS_HIP(hipStreamSynchronize(s));
-  if (h_bad) {
+  if (read_one(bad.p, s)) {
     pool.release(cb);
     return;
   }
