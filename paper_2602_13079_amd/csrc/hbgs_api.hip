@@ -128,9 +128,11 @@ void* Scratch::get(size_t bytes) {
   size_t c = stack_.empty() ? 0 : (size_t)stack_.back().chunk;
   for (; c < chunks_.size(); ++c)
     if (chunks_[c].size - chunks_[c].used >= need) break;
-  if (c == chunks_.size()) {  // grow: a new chunk at least twice the last
+  if (c == chunks_.size()) {  // grow by half
     Chunk k{};
-    k.size = std::max<size_t>(need, chunks_.empty() ? size_t(64) << 20 : 2 * chunks_.back().size);
+    size_t have = 0;
+    for (auto& q : chunks_) have += q.size;
+    k.size = std::max<size_t>({need, size_t(64) << 20, have / 2});
     k.a = current_allocator();
     if (k.a.alloc) {
       k.base = static_cast<char*>(k.a.alloc(k.size, k.a.user));
@@ -344,13 +346,23 @@ struct Field {
   DCsr upperT;            // rows of A^T in this field, columns of later leaves (global)
   double* td = nullptr;   // fine-level right-hand side
   float* tf = nullptr;
-  uint32_t deps[2] = {0, 0};  // fields read by the coupling rows: [0] forward, [1] adjoint sweep
   double setup_seconds = 0.0;  // wall time of this field's part of the last setup
   double stage_seconds[8] = {};  // per setup stage (see hbgs_stats_t)
   int leaf = 0;                  // 0 SA-AMG V-cycle, 1 Jacobi sweep, 2 DD(0)-ILU(0)
   double bytes[2] = {};          // algorithmic bytes of its sweep step: [0] FP64, [1] mixed
   IluLeaf ilu;
   int n() const { return hi - lo; }
+};
+
+// What a field's finest level and couplings keep of the pattern, which value
+// updates do not change: rows, columns and solve-phase layouts (no values),
+// and for each entry the position of its value in A_p's values (srcAT: of
+// its mirror image, A's pattern being symmetric).  Built with the first
+// hierarchy (tr: the adjoint's part, with the first adjoint operators).
+struct FieldPattern {
+  bool fwd = false, tr = false;
+  DCsr A, lower, upperT;
+  int *srcA = nullptr, *srcAT = nullptr, *srcL = nullptr, *srcU = nullptr;
 };
 
 // The sweep's stages: a field's step (coupling + V-cycle) only reads the z of
@@ -427,6 +439,10 @@ struct Group {
   std::vector<int> fields;    // leaves in visiting order
   DCsr A, AT;                 // its diagonal block and transpose (columns relative to lo)
   DCsr lower, upperT;         // couplings to earlier / later groups (global columns)
+  // their patterns, kept across value updates, and each entry's position in
+  // A_p's values
+  bool fwd = false, tr = false;
+  int *srcA = nullptr, *srcAT = nullptr, *srcL = nullptr, *srcU = nullptr;
   SweepPlan plan[2];          // the group's own sweep (forward, adjoint)
   std::unique_ptr<Krylov> K;  // inner solver workspace
   int n() const { return hi - lo; }
@@ -447,13 +463,18 @@ struct hbgs_ctx {
   hbgs::Scratch scratch[HBGS_MAX_FIELDS + 1];
   int *rp0 = nullptr, *ci0 = nullptr;  // caller's pattern
   int *perm = nullptr, *iperm = nullptr, *src = nullptr;
-  int* posT = nullptr;  // position in A_p of each A_p^T entry
+  int* posT = nullptr;  // position in A_p's values of each A_p^T entry
+  const int* posA = nullptr;  // of each A_p entry, while setup extracts patterns (null: its index)
   // transposed operators: A_p^T's values follow A_p's (apt_fresh); the
   // hierarchy's transposed parts exist for the current hierarchy (hier_t)
   bool apt_fresh = false, hier_t = false;
   hbgs::DCsr Ap, ApT;
   std::vector<int> leaf_order, f_lo, f_hi;
   std::vector<hbgs::Field> F;
+  hbgs::Pool patterns{true};  // the fields' patterns (arena, filled once)
+  std::vector<hbgs::FieldPattern> pat;
+  uint32_t deps[2][HBGS_MAX_FIELDS] = {};  // fields read by each field's coupling rows
+  bool planned[2] = {false, false};        // deps and the sweep plans exist
   // outer GMRES workspace (permuted ordering)
   int m = 0;
   hbgs::Krylov K;
@@ -550,9 +571,10 @@ static void parse_tree(hbgs_ctx* c, const int32_t* tree, int len) {
     if (!seen[f]) HBGS_FAIL(HBGS_EINVAL, "group tree: a field is missing");
 }
 
-// extract rows [r0,r1) x columns [c0,c1) (shifted by -coff) of a into a new CSR
-static DCsr extract(Pool& pool, const DCsr& a, int r0, int r1, int c0, int c1, int coff, int ncols,
-                    hipStream_t s) {
+// the pattern of rows [r0,r1) x columns [c0,c1) (shifted by -coff) of a;
+// *src: for each entry pos[k] (null: k) of its entry k of a
+static DCsr extract_pattern(Pool& pool, const DCsr& a, const int* pos, int r0, int r1, int c0, int c1, int coff,
+                            int ncols, int** src, hipStream_t s) {
   DCsr b;
   b.n = r1 - r0;
   b.m = ncols;
@@ -561,8 +583,8 @@ static DCsr extract(Pool& pool, const DCsr& a, int r0, int r1, int c0, int c1, i
   setup::block_count(a, r0, r1, c0, c1, cnt.p, s);
   b.nnz = setup::counts_to_rowptr(cnt.p, b.rp, b.n, s);
   b.ci = pool.make<int>(b.nnz);
-  b.v = pool.make<double>(b.nnz);
-  setup::block_fill(a, r0, r1, c0, c1, coff, b.rp, b.ci, b.v, s);
+  *src = pool.make<int>(b.nnz);
+  setup::block_pattern(a, pos, r0, r1, c0, c1, coff, b.rp, b.ci, *src, s);
   return b;
 }
 
@@ -588,18 +610,24 @@ static void add_f32(Pool& pool, DCsr& a, hipStream_t s) {
 // thread would leave most of the chip idle there).  try_slices is false for
 // matrices that have no diagonals by construction (transfer operators,
 // Galerkin products), which saves looking.
-static void solve_layout(Pool& pool, DCsr& a, int cap, bool try_slices, bool f32, hipStream_t s) {
+static void solve_layout(Pool& pool, DCsr& a, int cap, bool try_slices, hipStream_t s) {
   const int rb = solve::rows_per_block(a, cap, true);
   if (try_slices && rb >= 32 && solve::rows_per_block(a, solve::ROWS_CAP_F64, true) >= 32) {
     setup::build_slices(pool, a, s);
-    if (a.dia_w) {
-      setup::alloc_slice_values(pool, a, f32);
-      return;
-    }
+    if (a.dia_w) return;
   }
   setup::pack_columns(pool, a, s);
   setup::build_tiles(pool, a, rb, s);
 }
+// arrays for the values of a pattern with its layout: row order, or the
+// slices' (and both when the setup reads the values in row order too)
+static void make_values(Pool& pool, DCsr& a, bool f32, bool in_rows = false) {
+  a.v = in_rows || !a.dia_w ? pool.make<double>(a.nnz) : nullptr;
+  a.vf = f32 && !a.dia_w ? pool.make<float>(a.nnz) : nullptr;
+  setup::alloc_slice_values(pool, a, f32);
+}
+// where A_p holds its values, which the fields' and groups' are read from
+static const double* ap_values(const hbgs_ctx* c) { return c->Ap.dia_w ? c->Ap.dv : c->Ap.v; }
 
 static solve::ChebCoef cheb_coef(const hbgs_options& o, double lam) {
   solve::ChebCoef c{};
@@ -615,23 +643,6 @@ static solve::ChebCoef cheb_coef(const hbgs_options& o, double lam) {
     rho = rn;
   }
   return c;
-}
-
-// pattern of a equals the pattern of its transpose
-static bool structurally_symmetric_dev(const DCsr& a, hipStream_t s) {
-  DCsr t;
-  Pool tmp{Pool::FromScratch{}};
-  t.rp = tmp.make<int>(a.m + 1);
-  t.ci = tmp.make<int>(a.nnz);
-  t.v = nullptr;
-  DCsr pat = a;
-  pat.v = nullptr;
-  setup::transpose(pat, t, s);
-  Tmp<int> diff(1);
-  HBGS_HIP(hipMemsetAsync(diff.p, 0, sizeof(int), s));
-  solve::compare_int(a.n + 1, a.rp, t.rp, diff.p, s);
-  solve::compare_int(a.nnz, a.ci, t.ci, diff.p, s);
-  return setup::read_one(diff.p, s) == 0;
 }
 
 // host wall time per setup stage: to(q) closes the running stage and starts q
@@ -674,9 +685,6 @@ static void build_hierarchy(hbgs_ctx* c, Field& F, hipStream_t s) {
     if (setup::read_one(flag1.p, s)) HBGS_FAIL(HBGS_EINVAL, "zero or missing diagonal entry in a field block");
     if (F.leaf != 0) {  // one-level leaf: diagonal inverse, or the incomplete factors
       Level& L = F.lv[0];
-      if (!structurally_symmetric_dev(L.A, s))
-        HBGS_FAIL(HBGS_EINVAL, "a diagonal field block is not structurally symmetric");
-      clk.to(6);
       L.dinv = pool.make<double>(n);
       L.dinvf = pool.make<float>(n);
       setup::reciprocal(n, d.p, L.dinv, L.dinvf, s);
@@ -779,25 +787,24 @@ static void build_hierarchy(hbgs_ctx* c, Field& F, hipStream_t s) {
   }
   // solve-phase data: transposes, FP32 copies, work vectors
   clk.to(7);
-  if (!structurally_symmetric_dev(F.lv[0].A, s))
-    HBGS_FAIL(HBGS_EINVAL, "a diagonal field block is not structurally symmetric");
   for (size_t l = 0; l < F.lv.size(); ++l) {
     Level& L = F.lv[l];
-    add_f32(pool, L.A, s);
-    setup::row_stats(L.A, s);
-    solve_layout(pool, L.A, solve::ROWS_CAP_F32, l == 0, true, s);
-    setup::fill_slices(L.A, s);
+    if (l > 0) {  // the finest level came with its pattern's layout
+      add_f32(pool, L.A, s);
+      setup::row_stats(L.A, s);
+      solve_layout(pool, L.A, solve::ROWS_CAP_F32, false, s);
+    }
     if (l + 1 < F.lv.size()) {
       add_f32(pool, L.P, s);
       add_f32(pool, L.R, s);
       setup::row_stats(L.P, s);
       setup::row_stats(L.R, s);
-      solve_layout(pool, L.P, solve::ROWS_CAP_F32, false, true, s);
+      solve_layout(pool, L.P, solve::ROWS_CAP_F32, false, s);
       setup::pack_columns(pool, L.R, s);
       if (L.Q.n) {
         add_f32(pool, L.Q, s);
         setup::row_stats(L.Q, s);
-        solve_layout(pool, L.Q, solve::ROWS_CAP_F32, false, true, s);
+        solve_layout(pool, L.Q, solve::ROWS_CAP_F32, false, s);
       }
     }
     const int n = L.A.n;
@@ -882,7 +889,7 @@ static void plan_sweep(hbgs_ctx* c, const std::vector<int>& leaves, int tr, Swee
     const int f = leaves[tr ? nl - 1 - q : q];
     int k = 0;
     for (int g = 0; g < c->nf; ++g)
-      if ((c->F[f].deps[tr] >> g & 1u) && at[g] >= 0) k = std::max(k, at[g] + 1);
+      if ((c->deps[tr][f] >> g & 1u) && at[g] >= 0) k = std::max(k, at[g] + 1);
     at[f] = k;
     if ((int)p.stage.size() <= k) p.stage.resize(k + 1);
     p.stage[k].push_back(f);
@@ -903,32 +910,46 @@ static void plan_sweep(hbgs_ctx* c, const std::vector<int>& leaves, int tr, Swee
 // R A P with R = P^T keep the property -- so A_l^T shares A_l's pattern and
 // packed columns); the coarsest inverse transposed; the transposed ILU
 // factors.  Counted in the solve-data stage.
+static void field_range(const hbgs_ctx* c, const Field& F, int* glo, int* ghi) {
+  *glo = 0;
+  *ghi = c->n;
+  if (c->o.nested) {
+    const std::vector<int>& gf = c->group_fields[c->group_of[F.id]];
+    *glo = c->f_lo[gf.front()];
+    *ghi = c->f_hi[gf.back()];
+  }
+}
 static void build_field_T(hbgs_ctx* c, Field& F, hipStream_t s) {
   StageClock clk(F.stage_seconds);
   clk.to(7);
   Pool& pool = c->hier;
-  int glo = 0, ghi = c->n;
-  if (c->o.nested) {
-    const std::vector<int>& gf = c->group_fields[c->group_of[F.id]];
-    glo = c->f_lo[gf.front()];
-    ghi = c->f_hi[gf.back()];
+  FieldPattern& fp = c->pat[F.id];
+  if (!fp.tr) {
+    int glo, ghi;
+    field_range(c, F, &glo, &ghi);
+    const bool bj = c->o.block_jacobi != 0;
+    fp.upperT = extract_pattern(c->patterns, c->ApT, c->posT, F.lo, F.hi, bj ? ghi : F.hi, ghi, glo, ghi - glo,
+                                &fp.srcU, s);
+    setup::row_stats(fp.upperT, s);
+    solve_layout(c->patterns, fp.upperT, solve::ROWS_CAP_F32, true, s);
+    fp.tr = true;
   }
-  const bool bj = c->o.block_jacobi != 0;
-  F.upperT = extract(pool, c->ApT, F.lo, F.hi, bj ? ghi : F.hi, ghi, glo, ghi - glo, s);
-  add_f32(pool, F.upperT, s);
-  setup::row_stats(F.upperT, s);
-  solve_layout(pool, F.upperT, solve::ROWS_CAP_F32, true, true, s);
-  setup::fill_slices(F.upperT, s);
+  F.upperT = fp.upperT;
+  make_values(pool, F.upperT, true);
+  setup::load_values(F.upperT, ap_values(c), fp.srcU, s);
   if (F.leaf == 2) setup::ilu_transpose(pool, F.ilu, s);
   if (F.leaf == 0) {
     for (size_t l = 0; l < F.lv.size(); ++l) {
       Level& L = F.lv[l];
-      L.AT = L.A;  // pattern, row statistics and packed columns
-      L.AT.v = pool.make<double>(L.A.nnz);
-      setup::transpose_symmetric(L.A, L.AT.v, s);
-      add_f32(pool, L.AT, s);
-      setup::alloc_slice_values(pool, L.AT, true);  // the pattern's slices, values of its own
-      setup::fill_slices(L.AT, s);
+      L.AT = L.A;  // pattern, row statistics and layout
+      if (l == 0) {
+        make_values(pool, L.AT, true, L.Q.n > 0);
+        setup::load_values(L.AT, ap_values(c), fp.srcAT, s);
+      } else {
+        L.AT.v = pool.make<double>(L.A.nnz);
+        setup::transpose_symmetric(L.A, L.AT.v, s);
+        add_f32(pool, L.AT, s);
+      }
       if (L.Q.n) {  // A_l^T P_l for the adjoint's fused prolongation (same pattern as A_l P_l)
         DCsr ATP;
         Pool tmp_pool{Pool::FromScratch{}};
@@ -957,22 +978,34 @@ static void build_field(hbgs_ctx* c, Field& F, hipStream_t s) {
   F.lv.clear();
   F.lv.emplace_back();
   F.inv = F.invT = nullptr;  // set again if the new hierarchy ends in a dense-solved level
-  F.lv[0].A = extract(c->hier, c->Ap, F.lo, F.hi, F.lo, F.hi, F.lo, F.n(), s);
-  // couplings read by this field's sweep step: every earlier (later, for the
-  // adjoint) field; in the nested form only those of its own group, with
-  // columns relative to the group; none in block Jacobi
-  int glo = 0, ghi = c->n;
-  if (c->o.nested) {
-    const std::vector<int>& gf = c->group_fields[c->group_of[F.id]];
-    glo = c->f_lo[gf.front()];
-    ghi = c->f_hi[gf.back()];
+  FieldPattern& fp = c->pat[F.id];
+  if (!fp.fwd) {
+    // the diagonal block (A_p's rows and columns of the field) and the
+    // couplings read by this field's sweep step: every earlier (later, for
+    // the adjoint) field; in the nested form only those of its own group,
+    // with columns relative to the group; none in block Jacobi
+    int glo, ghi;
+    field_range(c, F, &glo, &ghi);
+    const bool bj = c->o.block_jacobi != 0;
+    fp.A = extract_pattern(c->patterns, c->Ap, c->posA, F.lo, F.hi, F.lo, F.hi, F.lo, F.n(), &fp.srcA, s);
+    fp.srcAT = c->patterns.make<int>(fp.A.nnz);
+    if (!setup::mirror_positions(fp.A, fp.srcA, fp.srcAT, s))
+      HBGS_FAIL(HBGS_EINVAL, "a diagonal field block is not structurally symmetric");
+    fp.lower = extract_pattern(c->patterns, c->Ap, c->posA, F.lo, F.hi, glo, bj ? glo : F.lo, glo, ghi - glo,
+                               &fp.srcL, s);
+    for (DCsr* a : {&fp.A, &fp.lower}) {
+      if (a == &fp.A && F.leaf != 0) continue;  // no V-cycle reads the block
+      setup::row_stats(*a, s);
+      solve_layout(c->patterns, *a, solve::ROWS_CAP_F32, true, s);
+    }
+    fp.fwd = true;
   }
-  const bool bj = c->o.block_jacobi != 0;
-  F.lower = extract(c->hier, c->Ap, F.lo, F.hi, glo, bj ? glo : F.lo, glo, ghi - glo, s);
-  add_f32(c->hier, F.lower, s);
-  setup::row_stats(F.lower, s);
-  solve_layout(c->hier, F.lower, solve::ROWS_CAP_F32, true, true, s);
-  setup::fill_slices(F.lower, s);
+  F.lv[0].A = fp.A;
+  F.lower = fp.lower;
+  make_values(c->hier, F.lv[0].A, F.leaf == 0, true);
+  make_values(c->hier, F.lower, true);
+  setup::load_values(F.lv[0].A, ap_values(c), fp.srcA, s);
+  setup::load_values(F.lower, ap_values(c), fp.srcL, s);
   F.td = c->hier.make<double>(F.n());
   F.tf = c->hier.make<float>(F.n());
   HBGS_HIP(hipStreamSynchronize(s));
@@ -1003,29 +1036,47 @@ static void field_deps(hbgs_ctx* c, int tr, hipStream_t s) {
       lo[g] = c->f_lo[g] - origin;
       hi[g] = c->f_hi[g] - origin;
     }
-    solve::column_fields(tr ? c->F[f].upperT : c->F[f].lower, c->nf, lo.data(), hi.data(), masks.p + f, s);
+    solve::column_fields(tr ? c->pat[f].upperT : c->pat[f].lower, c->nf, lo.data(), hi.data(), masks.p + f, s);
   }
   std::vector<int> hm(c->nf);
   setup::read_back(hm.data(), masks.p, sizeof(int) * c->nf, s);
-  for (int f = 0; f < c->nf; ++f) c->F[f].deps[tr] = (uint32_t)hm[f];
+  for (int f = 0; f < c->nf; ++f) c->deps[tr][f] = (uint32_t)hm[f];
+}
+
+// the coupling dependencies and the sweep plans of a direction (pattern only)
+static void plan_direction(hbgs_ctx* c, int tr, hipStream_t s) {
+  if (c->planned[tr]) return;
+  field_deps(c, tr, s);
+  plan_sweep(c, c->leaf_order, tr, c->plan[tr]);
+  for (Group& g : c->G) plan_sweep(c, g.fields, tr, g.plan[tr]);
+  c->planned[tr] = true;
+}
+static void group_layout(hbgs_ctx* c, DCsr& a, DCsr& b, hipStream_t s) {
+  for (DCsr* m : {&a, &b}) {
+    setup::row_stats(*m, s);
+    solve_layout(c->patterns, *m, solve::ROWS_CAP_F64, true, s);
+  }
+}
+static void group_values(hbgs_ctx* c, DCsr& a, const int* src, hipStream_t s) {
+  make_values(c->hier, a, false);
+  setup::load_values(a, ap_values(c), src, s);
 }
 
 // the adjoint's parts above the fields (after every build_field_T): the
 // groups' transposed blocks, the adjoint dependencies and sweep plans
 static void build_rest_T(hbgs_ctx* c, hipStream_t s) {
+  const bool bj = c->o.block_jacobi != 0;
   for (Group& g : c->G) {
-    const bool bj = c->o.block_jacobi != 0;
-    g.AT = extract(c->hier, c->ApT, g.lo, g.hi, g.lo, g.hi, g.lo, g.n(), s);
-    g.upperT = extract(c->hier, c->ApT, g.lo, g.hi, bj ? c->n : g.hi, c->n, 0, c->n, s);
-    for (DCsr* a : {&g.AT, &g.upperT}) {
-      setup::row_stats(*a, s);
-      solve_layout(c->hier, *a, solve::ROWS_CAP_F64, true, false, s);
-      setup::fill_slices(*a, s);
+    if (!g.tr) {
+      g.AT = extract_pattern(c->patterns, c->ApT, c->posT, g.lo, g.hi, g.lo, g.hi, g.lo, g.n(), &g.srcAT, s);
+      g.upperT = extract_pattern(c->patterns, c->ApT, c->posT, g.lo, g.hi, bj ? c->n : g.hi, c->n, 0, c->n, &g.srcU, s);
+      group_layout(c, g.AT, g.upperT, s);
+      g.tr = true;
     }
+    group_values(c, g.AT, g.srcAT, s);
+    group_values(c, g.upperT, g.srcU, s);
   }
-  field_deps(c, 1, s);
-  plan_sweep(c, c->leaf_order, 1, c->plan[1]);
-  for (Group& g : c->G) plan_sweep(c, g.fields, 1, g.plan[1]);
+  plan_direction(c, 1, s);
   c->hier_t = true;
 }
 
@@ -1042,6 +1093,7 @@ static void build_values(hbgs_ctx* c, hipStream_t s) {
   for (size_t q = 0; q < c->group_fields.size(); ++q)
     for (int f : c->group_fields[q]) c->group_of[f] = (int)q;
   c->F.assign(c->nf, Field{});
+  if (c->pat.empty()) c->pat.resize(c->nf);
   for (int f = 0; f < c->nf; ++f) {
     Field& F = c->F[f];
     F.id = f;
@@ -1114,18 +1166,17 @@ static void build_values(hbgs_ctx* c, hipStream_t s) {
     g.fields = c->group_fields[q];
     g.lo = c->f_lo[g.fields.front()];
     g.hi = c->f_hi[g.fields.back()];
-    g.A = extract(c->hier, c->Ap, g.lo, g.hi, g.lo, g.hi, g.lo, g.n(), s);
-    const bool bj = c->o.block_jacobi != 0;
-    g.lower = extract(c->hier, c->Ap, g.lo, g.hi, 0, bj ? 0 : g.lo, 0, c->n, s);
-    for (DCsr* a : {&g.A, &g.lower}) {
-      setup::row_stats(*a, s);
-      solve_layout(c->hier, *a, solve::ROWS_CAP_F64, true, false, s);
-      setup::fill_slices(*a, s);
+    if (!g.fwd) {
+      const bool bj = c->o.block_jacobi != 0;
+      g.A = extract_pattern(c->patterns, c->Ap, c->posA, g.lo, g.hi, g.lo, g.hi, g.lo, g.n(), &g.srcA, s);
+      g.lower = extract_pattern(c->patterns, c->Ap, c->posA, g.lo, g.hi, 0, bj ? 0 : g.lo, 0, c->n, &g.srcL, s);
+      group_layout(c, g.A, g.lower, s);
+      g.fwd = true;
     }
+    group_values(c, g.A, g.srcA, s);
+    group_values(c, g.lower, g.srcL, s);
   }
-  field_deps(c, 0, s);
-  plan_sweep(c, c->leaf_order, 0, c->plan[0]);
-  for (Group& g : c->G) plan_sweep(c, g.fields, 0, g.plan[0]);
+  plan_direction(c, 0, s);
   if (c->o.build_transpose) build_rest_T(c, s);
   HBGS_HIP(hipStreamSynchronize(s));
   compute_stats(c);
@@ -1415,6 +1466,28 @@ static void sweep(hbgs_ctx* c, const SweepPlan& plan, int tr, const double* v, T
   }
 }
 
+// Test knob off (set_tiles): the row-block kernels read values in row order,
+// which matrices with slices do not keep; they are written out once.
+static void rows_for_tests(hbgs_ctx* c, hipStream_t s) {
+  if (solve::tiles_on()) return;
+  auto rows = [&](Pool& pool, DCsr& a) {
+    if (!a.dia_w || !a.dv) return;
+    const bool v = !a.v, vf = a.dvf && !a.vf;
+    if (v) a.v = pool.make<double>(a.nnz);
+    if (vf) a.vf = pool.make<float>(a.nnz);
+    if (v || vf) setup::unslice(a, nullptr, v ? a.v : nullptr, vf ? a.vf : nullptr, s);
+  };
+  rows(c->pool, c->Ap);
+  if (c->apt_fresh) rows(c->pool, c->ApT);
+  for (Field& F : c->F) {
+    if (F.leaf == 0)
+      for (DCsr* a : {&F.lv[0].A, &F.lv[0].AT}) rows(c->hier, *a);
+    for (DCsr* a : {&F.lower, &F.upperT}) rows(c->hier, *a);
+  }
+  for (Group& g : c->G)
+    for (DCsr* a : {&g.A, &g.AT, &g.lower, &g.upperT}) rows(c->hier, *a);
+}
+
 // ------------------------------------------------------------------ GMRES
 static void ensure_workspace(hbgs_ctx* c) {
   c->K.ensure(c->pool, c->n, c->m, c->precision);
@@ -1695,9 +1768,6 @@ static hbgs_status gmres(hbgs_ctx* c, int tr, int use_x0, int32_t* iters, double
 
 #define HBGS_FOR_ALL(k, n) \
   for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < (n); k += (int64_t)gridDim.x * blockDim.x)
-__global__ void k_gather_vals(int64_t nnz, const double* v, const int* src, double* vp) {
-  HBGS_FOR_ALL(k, nnz) vp[k] = v[src[k]];
-}
 __global__ void k_iota_f64(int64_t nnz, double* p) {
   HBGS_FOR_ALL(k, nnz) p[k] = (double)k;
 }
@@ -1707,9 +1777,7 @@ __global__ void k_pos_int(int64_t nnz, const double* pos, int* posT) {
 
 // A_p^T's values from A_p's
 static void gather_apt(hbgs_ctx* c, hipStream_t s) {
-  k_gather_vals<<<grid_for(c->nnz, 256), 256, 0, s>>>(c->nnz, c->Ap.v, c->posT, c->ApT.v);
-  HBGS_HIP(hipGetLastError());
-  setup::fill_slices(c->ApT, s);
+  setup::load_values(c->ApT, ap_values(c), c->posT, s);
   c->apt_fresh = true;
 }
 
@@ -1882,11 +1950,25 @@ hbgs_status hbgs_setup(hbgs_ctx** out, int32_t n, int64_t nnz, const int32_t* ro
   }
   for (DCsr* a : {&c->Ap, &c->ApT}) {
     setup::row_stats(*a, s);
-    solve_layout(c->pool, *a, solve::ROWS_CAP_F64, true, false, s);
+    solve_layout(c->pool, *a, solve::ROWS_CAP_F64, true, s);
+    if (a->dia_w) {  // the slices' values replace those in row order
+      HBGS_HIP(hipStreamSynchronize(s));
+      c->pool.release(a->v);
+      a->v = nullptr;
+      setup::alloc_slice_values(c->pool, *a, false);
+    }
   }
-  setup::fill_slices(c->Ap, s);
+  setup::load_values(c->Ap, val, c->src, s);
+  Tmp<int> place;
+  if (c->Ap.dia_w) {  // positions are places of the slices
+    place.alloc(nnz);
+    setup::unslice(c->Ap, place.p, nullptr, nullptr, s);
+    setup::remap(nnz, place.p, c->posT, s);
+    c->posA = place.p;
+  }
   if (c->o.build_transpose) gather_apt(c, s);  // else on first use
   build_values(c, s);
+  c->posA = nullptr;
   c->stats.setup_seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
   *out = c;
   return HBGS_OK;
@@ -1914,9 +1996,7 @@ hbgs_status hbgs_set_values(hbgs_ctx* c, const double* val, int32_t rebuild_hier
   // a kept hierarchy keeps its adjoint consistent with it: its transposed
   // parts are built from the old values before they change
   if (!rebuild_hierarchy && !c->hier_t) ensure_transpose(c, s);
-  k_gather_vals<<<grid_for(c->nnz, 256), 256, 0, s>>>(c->nnz, val, c->src, c->Ap.v);
-  HBGS_HIP(hipGetLastError());
-  setup::fill_slices(c->Ap, s);
+  setup::load_values(c->Ap, val, c->src, s);
   c->apt_fresh = false;
   if (c->o.build_transpose) gather_apt(c, s);
   if (rebuild_hierarchy) {
@@ -1957,6 +2037,7 @@ hbgs_status hbgs_apply(hbgs_ctx* c, const double* r, double* z, int32_t transpos
   hipStream_t s = (hipStream_t)stream;
   ensure_workspace(c);
   if (transpose) ensure_transpose(c, s);
+  rows_for_tests(c, s);
   Krylov& K = c->K;
   solve::permute_in(c->n, c->perm, r, K.bp, s);
   apply_perm(c, transpose ? 1 : 0, K.bp, 0, nullptr, s);
@@ -1986,6 +2067,7 @@ hbgs_status hbgs_apply_noalloc(hbgs_ctx* c, const double* r, double* z, int32_t 
   if (!c->noalloc_scratch) HBGS_FAIL(HBGS_EHIP, "hbgs_apply_noalloc: no fixed scratch buffer");
   // [0, 8n): the permuted input; then the output column, 256-byte aligned;
   // both are written in full before they are read
+  rows_for_tests(c, s);
   char* base = static_cast<char*>(c->noalloc_scratch);
   double* vp = reinterpret_cast<double*>(base);
   void* zp = base + ((size_t)c->n * sizeof(double) + 255) / 256 * 256;
@@ -2017,6 +2099,7 @@ hbgs_status hbgs_solve(hbgs_ctx* c, const double* b, double* x, int32_t use_x0, 
   HBGS_HIP(hipEventRecord(c->join_in, us));
   HBGS_HIP(hipStreamWaitEvent(s, c->join_in, 0));
   if (transpose) ensure_transpose(c, s);
+  rows_for_tests(c, s);
   solve::permute_in(c->n, c->perm, b, c->K.bp, s);
   if (use_x0) solve::permute_in(c->n, c->perm, x, c->K.xp, s);
   hbgs_status st = gmres(c, transpose ? 1 : 0, use_x0, &it, hist, hist_cap, &hl, s);
@@ -2064,13 +2147,20 @@ hbgs_status hbgs_get_level(hbgs_ctx* c, int32_t field, int32_t level, int32_t wh
   bool coarsest = level + 1 == (int)c->F[field].lv.size();
   if ((which == 1 || which == 2) && coarsest) HBGS_FAIL(HBGS_EINVAL, "the coarsest level has no transfer operators");
   const DCsr& a = which == 0 ? L.A : which == 1 ? L.P : which == 2 ? L.R : L.AT;
-  if (!a.rp || !a.v) HBGS_FAIL(HBGS_EINVAL, "this operator is not built for the field's leaf solver");
+  if (!a.rp || !(a.v || a.dv)) HBGS_FAIL(HBGS_EINVAL, "this operator is not built for the field's leaf solver");
   if (n_rows) *n_rows = a.n;
   if (n_cols) *n_cols = a.m;
   if (nnz) *nnz = a.nnz;
   if (rowptr) HBGS_HIP(hipMemcpy(rowptr, a.rp, sizeof(int) * (a.n + 1), hipMemcpyDeviceToHost));
   if (col) HBGS_HIP(hipMemcpy(col, a.ci, sizeof(int) * a.nnz, hipMemcpyDeviceToHost));
-  if (val) HBGS_HIP(hipMemcpy(val, a.v, sizeof(double) * a.nnz, hipMemcpyDeviceToHost));
+  if (val) {
+    Tmp<double> rows;
+    if (!a.v) {  // held in slices only
+      rows.alloc(a.nnz);
+      setup::unslice(a, nullptr, rows.p, nullptr, nullptr);
+    }
+    HBGS_HIP(hipMemcpy(val, a.v ? a.v : rows.p, sizeof(double) * a.nnz, hipMemcpyDeviceToHost));
+  }
   return HBGS_OK;
   HBGS_API_END
 }

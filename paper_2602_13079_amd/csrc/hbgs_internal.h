@@ -328,8 +328,12 @@ void scatter_values(int64_t nnz, const double* v, const int* pos, double* v_p, h
 void transpose(const DCsr& a, DCsr& t, hipStream_t s);
 // sub-block: rows [r0,r1), columns [c0,c1) shifted by -coff; two passes
 void block_count(const DCsr& a, int r0, int r1, int c0, int c1, int* cnt, hipStream_t s);
-void block_fill(const DCsr& a, int r0, int r1, int c0, int c1, int coff, const int* rp_out, int* ci_out,
-                double* v_out, hipStream_t s);
+// (the pattern; src gets pos[k] (null: k) for entry k of a)
+void block_pattern(const DCsr& a, const int* pos, int r0, int r1, int c0, int c1, int coff, const int* rp_out,
+                   int* ci_out, int* src, hipStream_t s);
+// dst[k] = src[position of entry k's mirror image]; false when the pattern
+// is not symmetric
+bool mirror_positions(const DCsr& a, const int* src, int* dst, hipStream_t s);
 
 void diagonal(const DCsr& a, double* d, int* missing, hipStream_t s);
 void strength(const DCsr& a, const double* d, double theta, char* strong, char* excluded, hipStream_t s);
@@ -379,7 +383,13 @@ void build_tiles(Pool& pool, DCsr& a, int rb, hipStream_t s);
 void build_slices(Pool& pool, DCsr& a, hipStream_t s);
 // the slices' values (new arrays) from a.v: FP64 always, FP32 when asked
 void alloc_slice_values(Pool& pool, DCsr& a, bool f32);
-void fill_slices(const DCsr& a, hipStream_t s);
+// a's values, wherever it holds them (v, vf, dv, dvf), from from[src[k]]
+void load_values(const DCsr& a, const double* from, const int* src, hipStream_t s);
+// each entry's place in a's slices (where), or its value in row order (v,
+// vf) from them; null arrays are skipped
+void unslice(const DCsr& a, int* where, double* v, float* vf, hipStream_t s);
+// idx[i] = from[idx[i]]
+void remap(int64_t n, const int* from, int* idx, hipStream_t s);
 // DD(0)-ILU(0) of the n x n block a with subdomains of `sub` rows (factors,
 // transposed factors, schedules, FP32 copies); returns -4 on a zero pivot
 int ilu_setup(Pool& pool, const DCsr& a, int sub, IluLeaf& out, hipStream_t s);
@@ -399,8 +409,10 @@ namespace solve {
 // cap products per block (0: no row-block shape fits)
 int rows_per_block(const DCsr& a, int cap, bool vec);
 constexpr int ROWS_CAP_F32 = 4096, ROWS_CAP_F64 = 2048;
-// use the operand tiles where a matrix has them (default) or never (tests)
+// use the slices and operand tiles where a matrix has them (default) or
+// never (tests)
 void set_tiles(bool on);
+bool tiles_on();
 // kernel classes tracked by the optional profiler
 enum Kind {
   K_SPMV_OUTER = 0,
@@ -572,8 +584,6 @@ void norm2_partial(int n, const double* x, double* part, hipStream_t s);
 void scale_copy(int n, const double* r, const double* part_sum, double* v, hipStream_t s);  // v = r / sqrt(sum)
 void grad_values(int n, const int* rp, const int* ci, const double* lam, const double* x, double* g,
                  hipStream_t s);
-// *diff |= (a[i] != b[i]) for some i
-void compare_int(int64_t n, const int* a, const int* b, int* diff, hipStream_t s);
 // *mask |= 1 << f for every field f (column ranges [lo[f], hi[f])) that a column of c falls in
 void column_fields(const DCsr& c, int nf, const int* lo, const int* hi, int* mask, hipStream_t s);
 }  // namespace solve

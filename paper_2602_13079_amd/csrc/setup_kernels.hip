@@ -536,9 +536,10 @@ __global__ void k_block_count(int r0, int r1, const int* rp, const int* ci, int 
     if (gl == 0) cnt[t] = c;
   }
 }
+// the block's pattern, and for each entry pos[k] (null: k) of its entry k of a
 template <int L>
-__global__ void k_block_fill(int r0, int r1, const int* rp, const int* ci, const double* v, int c0, int c1,
-                             int coff, const int* rpo, int* cio, double* vo) {
+__global__ void k_block_fill(int r0, int r1, const int* rp, const int* ci, const int* pos, int c0, int c1, int coff,
+                             const int* rpo, int* cio, int* src) {
   const int64_t m = r1 - r0;
   ROW_GROUPS(L, t, gl, m) {
     const int i = r0 + (int)t, e = rp[i + 1];
@@ -551,7 +552,7 @@ __global__ void k_block_fill(int r0, int r1, const int* rp, const int* ci, const
       const int r = grp_rank<L>(keep, &tot);
       if (keep) {
         cio[q + r] = c - coff;
-        vo[q + r] = v[k];
+        src[q + r] = pos ? pos[k] : k;
       }
       q += tot;
     }
@@ -561,10 +562,10 @@ void block_count(const DCsr& a, int r0, int r1, int c0, int c1, int* cnt, hipStr
   const int L = row_lanes(a.n, a.nnz);
   LAUNCH_ROW_GROUPS(k_block_count, L, r1 - r0, s, r0, r1, a.rp, a.ci, c0, c1, cnt);
 }
-void block_fill(const DCsr& a, int r0, int r1, int c0, int c1, int coff, const int* rp_out, int* ci_out,
-                double* v_out, hipStream_t s) {
+void block_pattern(const DCsr& a, const int* pos, int r0, int r1, int c0, int c1, int coff, const int* rp_out,
+                   int* ci_out, int* src, hipStream_t s) {
   const int L = row_lanes(a.n, a.nnz);
-  LAUNCH_ROW_GROUPS(k_block_fill, L, r1 - r0, s, r0, r1, a.rp, a.ci, a.v, c0, c1, coff, rp_out, ci_out, v_out);
+  LAUNCH_ROW_GROUPS(k_block_fill, L, r1 - r0, s, r0, r1, a.rp, a.ci, pos, c0, c1, coff, rp_out, ci_out, src);
 }
 
 // ---------------------------------------------------------------- strength
@@ -2313,6 +2314,43 @@ __global__ void k_transpose_sym(int n, const int* __restrict__ rp, const int* __
     }
   }
 }
+// dst[q] = src[position of (j, i)] for entry q = (i, j); *missing: some entry
+// has no mirror image (the pattern is not symmetric)
+template <int L>
+__global__ void k_mirror(int n, const int* __restrict__ rp, const int* __restrict__ ci, const int* __restrict__ src,
+                         int* __restrict__ dst, int* missing) {
+  int bad = 0;
+  ROW_GROUPS(L, j, gl, n) {
+    for (int q = rp[j] + gl; q < rp[j + 1]; q += L) {
+      const int i = ci[q];
+      int lo = rp[i], hi = rp[i + 1] - 1, at = -1;
+      while (lo <= hi) {
+        const int mid = (lo + hi) >> 1;
+        const int c = ci[mid];
+        if (c == (int)j) {
+          at = mid;
+          break;
+        }
+        if (c < (int)j)
+          lo = mid + 1;
+        else
+          hi = mid - 1;
+      }
+      bad |= at < 0;
+      dst[q] = at < 0 ? 0 : src[at];
+    }
+  }
+  if (bad) atomicOr(missing, 1);
+}
+bool mirror_positions(const DCsr& a, const int* src, int* dst, hipStream_t s) {
+  if (a.n == 0) return true;
+  Tmp<int> missing(1);
+  HBGS_HIP(hipMemsetAsync(missing.p, 0, sizeof(int), s));
+  const int L = row_lanes(a.n, a.nnz);
+  LAUNCH_ROW_GROUPS(k_mirror, L, a.n, s, a.n, a.rp, a.ci, src, dst, missing.p);
+  return read_one(missing.p, s) == 0;
+}
+
 // Q with rows 2i = row i of a and 2i+1 = row i of b (same column count):
 // one row-block pass over Q then forms both products with one operand
 template <int L>
@@ -2567,34 +2605,30 @@ void build_slices(Pool& pool, DCsr& a, hipStream_t s) {
   a.dvf = nullptr;
   if (a.n <= 0 || a.nnz <= 0) return;
   const int nsl = (a.n + DIA_ROWS - 1) / DIA_ROWS;
-  int* tab = pool.make<int>((size_t)nsl * DIA_TS);
-  uint16_t* m16 = pool.make<uint16_t>(a.n);
-  uint32_t* m32 = pool.make<uint32_t>(a.n);
-  Tmp<int> stat(2), count(nsl), base(nsl + 1);
+  Tmp<int> tab((size_t)nsl * DIA_TS), stat(2), count(nsl), base(nsl + 1);
+  Tmp<uint16_t> m16(a.n);
+  Tmp<uint32_t> m32(a.n);
   HBGS_HIP(hipMemsetAsync(stat.p, 0, 2 * sizeof(int), s));
-  k_slice_diags<<<grid_for((nsl + 3) / 4, 1, 2048), 256, 0, s>>>(a.n, a.rp, a.ci, tab, count.p, m16, m32, stat.p);
+  k_slice_diags<<<grid_for((nsl + 3) / 4, 1, 2048), 256, 0, s>>>(a.n, a.rp, a.ci, tab.p, count.p, m16.p, m32.p,
+                                                                 stat.p);
   HBGS_HIP(hipGetLastError());
   int h[2] = {0, 0};
   read_back(h, stat.p, sizeof(h), s);
-  bool use = !h[1] && h[0] > 0;
-  if (use) {
-    a.dia_places = counts_to_rowptr(count.p, base.p, nsl, s) * DIA_ROWS;
-    use = (double)a.dia_places <= 1.25 * (double)a.nnz;
-  }
-  if (!use || h[0] <= 16) pool.release(m32);
-  if (!use || h[0] > 16) pool.release(m16);
-  if (!use) {
-    pool.release(tab);
-    return;
-  }
-  k_slice_base<<<grid_for(nsl, 256), 256, 0, s>>>(nsl, base.p, tab);
+  if (h[1] || h[0] <= 0) return;
+  a.dia_places = counts_to_rowptr(count.p, base.p, nsl, s) * DIA_ROWS;
+  if ((double)a.dia_places > 1.25 * (double)a.nnz || a.dia_places > INT_MAX) return;
+  k_slice_base<<<grid_for(nsl, 256), 256, 0, s>>>(nsl, base.p, tab.p);
   HBGS_HIP(hipGetLastError());
+  auto keep = [&](void* dst, const void* from, size_t bytes) {
+    HBGS_HIP(hipMemcpyAsync(dst, from, bytes, hipMemcpyDeviceToDevice, s));
+  };
   a.dia_w = h[0];
-  a.dia_tab = tab;
+  a.dia_tab = pool.make<int>(tab.count);
+  keep(a.dia_tab, tab.p, tab.count * sizeof(int));
   if (h[0] <= 16)
-    a.dia_m16 = m16;
+    keep(a.dia_m16 = pool.make<uint16_t>(a.n), m16.p, sizeof(uint16_t) * a.n);
   else
-    a.dia_m32 = m32;
+    keep(a.dia_m32 = pool.make<uint32_t>(a.n), m32.p, sizeof(uint32_t) * a.n);
 }
 
 void alloc_slice_values(Pool& pool, DCsr& a, bool f32) {
@@ -2602,31 +2636,94 @@ void alloc_slice_values(Pool& pool, DCsr& a, bool f32) {
   a.dv = pool.make<double>(a.dia_places);
   a.dvf = f32 ? pool.make<float>(a.dia_places) : nullptr;
 }
+// A matrix's values from an array they are read from by position: in row
+// order (v, FP32 copy vf) and in the slices' places (dv, dvf), each where
+// the matrix has the array.  A block takes the
+// entries of 256 rows with consecutive threads and leaves them in LDS, from
+// which each thread then takes its row's; blocks with more than LOAD_LDS
+// entries (the fullest blocks of a few long rows) read the source again.
+constexpr int LOAD_LDS = 4096;
 template <class TM>
-__global__ __launch_bounds__(256) void k_slice_fill(int n, const int* __restrict__ rp,
-                                                    const double* __restrict__ v, const int* __restrict__ tab,
-                                                    const TM* __restrict__ mask, double* __restrict__ dv,
-                                                    float* __restrict__ dvf) {
-  const int row = (int)((int64_t)blockIdx.x * 256 + threadIdx.x);
+__global__ __launch_bounds__(256) void k_load_values(int n, const int* __restrict__ rp, const double* __restrict__ from,
+                                                     const int* __restrict__ src, double* __restrict__ v,
+                                                     float* __restrict__ vf, const int* __restrict__ tab,
+                                                     const TM* __restrict__ mask, double* __restrict__ dv,
+                                                     float* __restrict__ dvf) {
+  __shared__ double sh[LOAD_LDS];
+  const int r0 = (int)((int64_t)blockIdx.x * 256), r1 = min(n, r0 + 256);
+  const int row = r0 + (int)threadIdx.x;
+  const int e0 = rp[r0], e1 = rp[r1];
+  const bool staged = e1 - e0 <= LOAD_LDS;
+  for (int k = e0 + (int)threadIdx.x; k < e1; k += 256) {
+    const double x = from[src[k]];
+    if (v) v[k] = x;
+    if (vf) vf[k] = (float)x;
+    if (staged) sh[k - e0] = x;
+  }
   const int q = row / DIA_ROWS;
+  if (!dv) return;
+  __syncthreads();
   if (q * DIA_ROWS >= n) return;  // the last slice's absent rows get zeros
-  const int cnt = tab[(size_t)q * DIA_TS];
+  const int* t = tab + (size_t)q * DIA_TS;
+  const int cnt = t[0];
   const uint32_t m = row < n ? (uint32_t)mask[row] : 0u;
   int k = row < n ? rp[row] : 0;
-  const size_t base = (size_t)tab[(size_t)q * DIA_TS + DIA_BASE] * DIA_ROWS + row % DIA_ROWS;
+  const size_t base = (size_t)t[DIA_BASE] * DIA_ROWS + row % DIA_ROWS;
   for (int j = 0; j < cnt; ++j) {
-    const double x = m >> j & 1u ? v[k++] : 0.0;
+    double x = 0.0;
+    if (m >> j & 1u) {
+      x = staged ? sh[k - e0] : from[src[k]];
+      ++k;
+    }
     dv[base + (size_t)j * DIA_ROWS] = x;
     if (dvf) dvf[base + (size_t)j * DIA_ROWS] = (float)x;
   }
 }
-void fill_slices(const DCsr& a, hipStream_t s) {
-  if (!a.dia_w) return;
+void load_values(const DCsr& a, const double* from, const int* src, hipStream_t s) {
+  if (a.n == 0) return;
   const unsigned g = (unsigned)(((int64_t)a.n + 255) / 256);
-  if (a.dia_m16)
-    k_slice_fill<uint16_t><<<g, 256, 0, s>>>(a.n, a.rp, a.v, a.dia_tab, a.dia_m16, a.dv, a.dvf);
+  if (a.dia_m32)
+    k_load_values<uint32_t><<<g, 256, 0, s>>>(a.n, a.rp, from, src, a.v, a.vf, a.dia_tab, a.dia_m32, a.dv, a.dvf);
   else
-    k_slice_fill<uint32_t><<<g, 256, 0, s>>>(a.n, a.rp, a.v, a.dia_tab, a.dia_m32, a.dv, a.dvf);
+    k_load_values<uint16_t><<<g, 256, 0, s>>>(a.n, a.rp, from, src, a.v, a.vf, a.dia_tab, a.dia_m16, a.dv, a.dvf);
+  HBGS_HIP(hipGetLastError());
+}
+// each entry's place in the slices' values (where), or the values in row
+// order (v, vf) from the slices'; null arrays are skipped
+template <class TM>
+__global__ __launch_bounds__(256) void k_unslice(int n, const int* __restrict__ rp, const int* __restrict__ tab,
+                                                 const TM* __restrict__ mask, const double* __restrict__ dv,
+                                                 const float* __restrict__ dvf, int* __restrict__ where,
+                                                 double* __restrict__ v, float* __restrict__ vf) {
+  const int row = (int)((int64_t)blockIdx.x * 256 + threadIdx.x);
+  if (row >= n) return;
+  const int* t = tab + (size_t)(row / DIA_ROWS) * DIA_TS;
+  const int64_t base = (int64_t)t[DIA_BASE] * DIA_ROWS + row % DIA_ROWS;
+  const uint32_t m = mask[row];
+  int k = rp[row];
+  for (int j = 0; j < t[0]; ++j)
+    if (m >> j & 1u) {
+      const int64_t p = base + (int64_t)j * DIA_ROWS;
+      if (where) where[k] = (int)p;
+      if (v) v[k] = dv[p];
+      if (vf) vf[k] = dvf[p];
+      ++k;
+    }
+}
+void unslice(const DCsr& a, int* where, double* v, float* vf, hipStream_t s) {
+  const unsigned g = (unsigned)(((int64_t)a.n + 255) / 256);
+  if (a.dia_m32)
+    k_unslice<uint32_t><<<g, 256, 0, s>>>(a.n, a.rp, a.dia_tab, a.dia_m32, a.dv, a.dvf, where, v, vf);
+  else
+    k_unslice<uint16_t><<<g, 256, 0, s>>>(a.n, a.rp, a.dia_tab, a.dia_m16, a.dv, a.dvf, where, v, vf);
+  HBGS_HIP(hipGetLastError());
+}
+__global__ void k_gather_i32(int64_t n, const int* __restrict__ from, int* __restrict__ idx) {
+  GRID_STRIDE(i, n) idx[i] = from[idx[i]];
+}
+void remap(int64_t n, const int* from, int* idx, hipStream_t s) {
+  if (n == 0) return;
+  k_gather_i32<<<grid_for(n, BLK, 65536), BLK, 0, s>>>(n, from, idx);
   HBGS_HIP(hipGetLastError());
 }
 

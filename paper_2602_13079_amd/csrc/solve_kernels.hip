@@ -447,6 +447,7 @@ __global__ __launch_bounds__(BLK) void k_slices(const Batch<SliceJob<TM, TV, TX,
 
 static bool g_tiles_on = true;  // slices, and the LDS-staged operand, where a matrix has them
 void set_tiles(bool on) { g_tiles_on = on; }
+bool tiles_on() { return g_tiles_on; }
 
 int rows_per_block(const DCsr& a, int cap, bool vec) {
   // the largest RB whose every block's entries fit the LDS staging
@@ -1481,17 +1482,6 @@ __global__ void k_grad(int n, const int* __restrict__ rp, const int* __restrict_
 void grad_values(int n, const int* rp, const int* ci, const double* lam, const double* x, double* g,
                  hipStream_t s) {
   k_grad<<<grid_for(n, BLK), BLK, 0, s>>>(n, rp, ci, lam, x, g);
-  HBGS_HIP(hipGetLastError());
-}
-
-__global__ void k_compare_int(int64_t n, const int* __restrict__ a, const int* __restrict__ b, int* diff) {
-  int d = 0;
-  for (int64_t i = (int64_t)blockIdx.x * BLK + threadIdx.x; i < n; i += (int64_t)gridDim.x * BLK) d |= a[i] != b[i];
-  if (d) atomicOr(diff, 1);
-}
-void compare_int(int64_t n, const int* a, const int* b, int* diff, hipStream_t s) {
-  if (n == 0) return;
-  k_compare_int<<<grid_for(n, BLK, 65536), BLK, 0, s>>>(n, a, b, diff);
   HBGS_HIP(hipGetLastError());
 }
 
