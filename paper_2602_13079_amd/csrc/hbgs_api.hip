@@ -1497,15 +1497,43 @@ static void ensure_workspace(hbgs_ctx* c) {
   }
 }
 
+// The Givens kernel stores ||w||, h_{j+1,j} and then, after a system-scope
+// fence, the residual estimate into coherent pinned memory.  The host waits
+// for the estimate slot to leave its sentinel instead of synchronising the
+// stream, so it decides on the next step as soon as the store lands, while
+// the Givens kernel's last wave and the stream's completion are still
+// pending (enqueuing several steps ahead instead runs slower: the runtime
+// handles a queue many steps deep worse than one a step deep).  Should the
+// store not arrive, the stream's
+// completion ends the wait (and an idle stream with the sentinel still in
+// place is an error).
+constexpr double kEstPending = -1.0;  // estimates are norms (>= 0, or NaN)
+static void wait_estimate(const double* host, hipStream_t s) {
+  const volatile double* slot = host;
+  for (unsigned spins = 1;; ++spins) {
+    if (*slot != kEstPending) return;
+    if ((spins & 4095u) == 0) {
+      const hipError_t e = hipStreamQuery(s);
+      if (e == hipSuccess) {
+        if (*slot != kEstPending) return;
+        HBGS_FAIL(HBGS_EHIP, "a GMRES step or norm ended without its result");
+      }
+      if (e != hipErrorNotReady) HBGS_HIP(e);
+    }
+    __builtin_ia32_pause();
+  }
+}
+
+// ||x||^2 (also left in K.hn2); the reduction's kernel writes it to the host
 static double norm2(hbgs_ctx* c, Krylov& K, const double* x, hipStream_t s) {
   int nb = solve::dot_blocks(K.n);
+  K.host[0] = kEstPending;
   {
     Prof p(c->prof, s, solve::K_REDUCE, 8.0 * K.n);
     solve::norm2_partial(K.n, x, K.part, s);
-    solve::mdot_reduce(1, nb, K.part, K.hn2, s);
+    solve::sum_to_host(nb, K.part, K.hn2, K.host_dev, s);
   }
-  HBGS_HIP(hipMemcpyAsync(K.host, K.hn2, sizeof(double), hipMemcpyDeviceToHost, s));
-  HBGS_HIP(hipStreamSynchronize(s));
+  wait_estimate(K.host, s);
   return K.host[0];
 }
 
@@ -1607,33 +1635,6 @@ static void run_iteration(hbgs_ctx* c, Krylov& K, const DCsr& A, Prec& prec, int
   HBGS_HIP(hipGraphLaunch(it->second.exec, s));
 }
 
-// The Givens kernel stores ||w||, h_{j+1,j} and then, after a system-scope
-// fence, the residual estimate into coherent pinned memory.  The host waits
-// for the estimate slot to leave its sentinel instead of synchronising the
-// stream, so it decides on the next step as soon as the store lands, while
-// the Givens kernel's last wave and the stream's completion are still
-// pending (enqueuing several steps ahead instead runs slower: the runtime
-// handles a queue many steps deep worse than one a step deep).  Should the
-// store not arrive, the stream's
-// completion ends the wait (and an idle stream with the sentinel still in
-// place is an error).
-constexpr double kEstPending = -1.0;  // estimates are norms (>= 0, or NaN)
-static void wait_estimate(const double* host, hipStream_t s) {
-  const volatile double* slot = host;
-  for (unsigned spins = 1;; ++spins) {
-    if (*slot != kEstPending) return;
-    if ((spins & 4095u) == 0) {
-      const hipError_t e = hipStreamQuery(s);
-      if (e == hipSuccess) {
-        if (*slot != kEstPending) return;
-        HBGS_FAIL(HBGS_EHIP, "GMRES step ended without a residual estimate");
-      }
-      if (e != hipErrorNotReady) HBGS_HIP(e);
-    }
-    __builtin_ia32_pause();
-  }
-}
-
 // Flexible GMRES(K.m) for A x = b with b in K.bp and x in K.xp (zero start
 // unless use_x0); the relative residual target is rtol, at most max_iters
 // Arnoldi steps.  hist (optional) receives the residual estimates, the true
@@ -1656,7 +1657,6 @@ static hbgs_status fgmres(hbgs_ctx* c, Krylov& K, const DCsr& A, Prec& prec, dou
     push(0.0);
     return HBGS_OK;
   }
-  if (!use_x0) HBGS_HIP(hipMemsetAsync(K.xp, 0, sizeof(double) * n, s));
   auto true_resid = [&]() {
     {
       Prof p(c->prof, s, solve::K_SPMV_RESID, spmv_bytes(A, 8, 8, 8, 1));
@@ -1664,18 +1664,21 @@ static hbgs_status fgmres(hbgs_ctx* c, Krylov& K, const DCsr& A, Prec& prec, dou
     }
     return std::sqrt(norm2(c, K, K.r, s));
   };
-  double beta = true_resid();
+  // from a zero start the residual is b itself, whose norm is in hn2, and x
+  // is written, not updated, at the end of the first cycle
+  bool zero = !use_x0;
+  const double* r = zero ? K.bp : K.r;
+  double beta = zero ? bnorm : true_resid();
   push(beta / bnorm);
   for (;;) {
-    if (beta / bnorm <= rtol) return HBGS_OK;
-    if (*iters >= max_iters) return HBGS_NOT_CONVERGED;
+    if (beta / bnorm <= rtol || *iters >= max_iters) {
+      if (zero) HBGS_HIP(hipMemsetAsync(K.xp, 0, sizeof(double) * n, s));
+      return beta / bnorm <= rtol ? HBGS_OK : HBGS_NOT_CONVERGED;
+    }
     {
       Prof p(c->prof, s, solve::K_SCALE, 16.0 * n);
-      solve::scale_copy(n, K.r, K.hn2, K.V, s);  // hn2 holds ||r||^2 from true_resid
+      solve::start_cycle(n, r, K.hn2, K.V, m, K.g, s);  // hn2 holds ||r||^2
     }
-    std::vector<double> g0(m + 1, 0.0);
-    g0[0] = beta;
-    HBGS_HIP(hipMemcpyAsync(K.g, g0.data(), sizeof(double) * (m + 1), hipMemcpyHostToDevice, s));
     int jend = 0;
     for (int j = 0; j < m; ++j) {
       K.host[0] = kEstPending;
@@ -1692,10 +1695,12 @@ static hbgs_status fgmres(hbgs_ctx* c, Krylov& K, const DCsr& A, Prec& prec, dou
     {
       Prof p(c->prof, s, solve::K_XUPDATE, (double)n * (16 + jend * (c->precision ? 4 : 8)));
       if (c->precision == 1)
-        solve::xupdate<float>(n, jend, K.Zf, ld, K.y, K.xp, s);
+        solve::xupdate<float>(n, jend, K.Zf, ld, K.y, zero, K.xp, s);
       else
-        solve::xupdate<double>(n, jend, K.Zd, ld, K.y, K.xp, s);
+        solve::xupdate<double>(n, jend, K.Zd, ld, K.y, zero, K.xp, s);
     }
+    zero = false;
+    r = K.r;
     beta = true_resid();
     if (hist && *hlen - 1 < cap) hist[*hlen - 1] = beta / bnorm;
   }

@@ -579,9 +579,13 @@ void reduce_givens(int n, int j, const double* part, double* h2, const GivensArg
 void mdot_reduce(int nvec, int nblocks, const double* part, double* out, hipStream_t s);
 void backsolve(int jend, int m, const double* H, const double* g, double* y, hipStream_t s);
 template <class TZ>
-void xupdate(int n, int jend, const TZ* Z, size_t ldz, const double* y, double* x, hipStream_t s);
+void xupdate(int n, int jend, const TZ* Z, size_t ldz, const double* y, bool zero, double* x,
+             hipStream_t s);  // x = (zero ? 0 : x) + Z y
 void norm2_partial(int n, const double* x, double* part, hipStream_t s);
-void scale_copy(int n, const double* r, const double* part_sum, double* v, hipStream_t s);  // v = r / sqrt(sum)
+// the sum of part's nblocks entries to out and to pinned host memory
+void sum_to_host(int nblocks, const double* part, double* out, double* host, hipStream_t s);
+// v = r / sqrt(sum), g = (sqrt(sum), 0, ..., 0) of m + 1 entries
+void start_cycle(int n, const double* r, const double* sum, double* v, int m, double* g, hipStream_t s);
 void grad_values(int n, const int* rp, const int* ci, const double* lam, const double* x, double* g,
                  hipStream_t s);
 // *mask |= 1 << f for every field f (column ranges [lo[f], hi[f])) that a column of c falls in

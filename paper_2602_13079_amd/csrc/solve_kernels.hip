@@ -1434,20 +1434,20 @@ void backsolve(int jend, int m, const double* H, const double* g, double* y, hip
 
 template <class TZ>
 __global__ void k_xupdate(int n, int jend, const TZ* __restrict__ Z, size_t ldz, const double* __restrict__ y,
-                          double* __restrict__ x) {
+                          bool zero, double* __restrict__ x) {
   for (int64_t i = (int64_t)blockIdx.x * BLK + threadIdx.x; i < n; i += (int64_t)gridDim.x * BLK) {
-    double xi = x[i];
+    double xi = zero ? 0.0 : x[i];
     for (int k = 0; k < jend; ++k) xi += y[k] * (double)Z[(size_t)k * ldz + i];
     x[i] = xi;
   }
 }
 template <class TZ>
-void xupdate(int n, int jend, const TZ* Z, size_t ldz, const double* y, double* x, hipStream_t s) {
-  k_xupdate<TZ><<<grid_for(n, BLK), BLK, 0, s>>>(n, jend, Z, ldz, y, x);
+void xupdate(int n, int jend, const TZ* Z, size_t ldz, const double* y, bool zero, double* x, hipStream_t s) {
+  k_xupdate<TZ><<<grid_for(n, BLK), BLK, 0, s>>>(n, jend, Z, ldz, y, zero, x);
   HBGS_HIP(hipGetLastError());
 }
-template void xupdate<float>(int, int, const float*, size_t, const double*, double*, hipStream_t);
-template void xupdate<double>(int, int, const double*, size_t, const double*, double*, hipStream_t);
+template void xupdate<float>(int, int, const float*, size_t, const double*, bool, double*, hipStream_t);
+template void xupdate<double>(int, int, const double*, size_t, const double*, bool, double*, hipStream_t);
 
 __global__ __launch_bounds__(BLK) void k_norm2_part(int n, const double* __restrict__ x, double* __restrict__ part) {
   __shared__ double sh[BLK / 64];
@@ -1462,13 +1462,33 @@ void norm2_partial(int n, const double* x, double* part, hipStream_t s) {
   HBGS_HIP(hipGetLastError());
 }
 
-__global__ void k_scale_copy(int n, const double* __restrict__ r, const double* __restrict__ ss,
-                             double* __restrict__ v) {
+// the sums k_reduce forms, of one vector, to the device and (last, the host
+// polls it) to pinned host memory
+__global__ __launch_bounds__(BLK) void k_sum_to_host(int nb, const double* __restrict__ part, double* __restrict__ out,
+                                                     double* __restrict__ host) {
+  __shared__ double sh[BLK / 64];
+  double acc = 0.0;
+  for (int b = threadIdx.x; b < nb; b += BLK) acc += part[b];
+  const double t = block_sum(acc, sh);
+  if (threadIdx.x == 0) {
+    *out = t;
+    *host = t;
+  }
+}
+void sum_to_host(int nblocks, const double* part, double* out, double* host, hipStream_t s) {
+  k_sum_to_host<<<1, BLK, 0, s>>>(nblocks, part, out, host);
+  HBGS_HIP(hipGetLastError());
+}
+
+__global__ void k_start_cycle(int n, const double* __restrict__ r, const double* __restrict__ ss,
+                              double* __restrict__ v, int m, double* __restrict__ g) {
   const double nr = sqrt(*ss);
+  if (blockIdx.x == 0)
+    for (int i = threadIdx.x; i <= m; i += BLK) g[i] = i == 0 ? nr : 0.0;
   for (int64_t i = (int64_t)blockIdx.x * BLK + threadIdx.x; i < n; i += (int64_t)gridDim.x * BLK) v[i] = r[i] / nr;
 }
-void scale_copy(int n, const double* r, const double* part_sum, double* v, hipStream_t s) {
-  k_scale_copy<<<grid_for(n, BLK), BLK, 0, s>>>(n, r, part_sum, v);
+void start_cycle(int n, const double* r, const double* sum, double* v, int m, double* g, hipStream_t s) {
+  k_start_cycle<<<grid_for(n, BLK), BLK, 0, s>>>(n, r, sum, v, m, g);
   HBGS_HIP(hipGetLastError());
 }
 
