@@ -406,7 +406,11 @@ struct Krylov {
     }
     n = n_;
     m = m_;
-    ld = ((size_t)n + 63) / 64 * 64;
+    // columns start on 512-byte bounds and 2,560 bytes apart modulo the
+    // powers of two that n often is a multiple of, so that the same rows of
+    // the basis vectors do not all fall on one memory channel (1M rows: the
+    // passes over the basis 29-32 -> 27-28 us at 9-16 vectors)
+    ld = ((size_t)n + 63) / 64 * 64 + 320;
     V = pool.make<double>((size_t)(m + 1) * ld);
     if (precision == 1)
       Zf = pool.make<float>((size_t)m * ld);
@@ -1229,6 +1233,13 @@ struct VcField {
   T* x;
 };
 
+// Matrix bytes of a stage's finest level above which its passes alternate
+// their direction: each then starts on what the previous one left in the
+// caches (4.2M rows mixed 11.93 -> 11.71 ms, 5.3M FP64 adjoint apply 883 ->
+// 864 us, 25M mixed 72.6 -> 72.0 ms).  Below it the level stays in the eight
+// XCDs' L2 (32 MB together) in either order (1M rows: no gain, 1% lost).
+constexpr double kTurnBytes = 24e6;
+
 // Kernel-class bytes of a step over several jobs
 template <class T, class F>
 static double sum_bytes(const solve::LevelJob<T>* j, int nj, F f) {
@@ -1243,7 +1254,7 @@ static double sum_bytes(const solve::LevelJob<T>* j, int nj, F f) {
 // `dense` and launched with those of the deepest level.
 template <class T>
 static void vcycle(hbgs_ctx* c, const VcField<T>* v, int nv, int l, int tr, solve::DenseJob<T>* dense, int* nd,
-                   hipStream_t s) {
+                   bool& rev, hipStream_t s) {
   using B = Buf<T>;
   using J = solve::LevelJob<T>;
   using Ops = VcOps<T>;
@@ -1295,6 +1306,11 @@ static void vcycle(hbgs_ctx* c, const VcField<T>* v, int nv, int l, int tr, solv
   };
   int most = 0;
   for (int q = 0; q < nj; ++q) most = std::max(most, j[q].cc->degree);
+  // the finest level's passes alternate their direction
+  double pass_bytes = 0;
+  for (int q = 0; q < nj; ++q) pass_bytes += (double)TS * j[q].A->nnz;
+  const bool turning = l == 0 && pass_bytes > kTurnBytes;
+  auto turn = [&]() { return turning && (rev = !rev); };
   // Chebyshev steps of the first m jobs: before (every degree but 2, whose
   // one step pre2 includes) or after the coarse correction
   auto steps = [&](int m, bool post) {
@@ -1307,7 +1323,7 @@ static void vcycle(hbgs_ctx* c, const VcField<T>* v, int nv, int l, int tr, solv
                         sum_bytes(w, n, [&](const J& x) {
                           return spmv_bytes(*x.A, TS, TS, post ? TS : 3 * TS, post ? 3 : 2);
                         }));
-                 Ops::step(w, n, k, post && k == 1, keep != 0, s);
+                 Ops::step(w, n, k, post && k == 1, keep != 0, turn(), s);
                });
       for (int t = 0; t < m; ++t)
         if (has(j[t])) std::swap(j[t].d, j[t].dn);
@@ -1318,25 +1334,25 @@ static void vcycle(hbgs_ctx* c, const VcField<T>* v, int nv, int l, int tr, solv
   select(nj, [](const J& k) { return k.cc->degree == 2; }, [&](const J* w, int n) {
     Prof p(c->prof, s, lk(solve::K_CHEB_PRE, l),
            sum_bytes(w, n, [&](const J& x) { return spmv_bytes(*x.A, TS, TS, TS, 2); }));
-    Ops::pre2(w, n, s);
+    Ops::pre2(w, n, turn(), s);
   });
   select(nj, [](const J& k) { return k.cc->degree != 2; }, [&](const J* w, int n) {
     Prof p(c->prof, s, lk(solve::K_CHEB_OTHER, l), 4.0 * TS * sum_bytes(w, n, [](const J& x) { return (double)x.A->n; }));
-    Ops::init0(w, n, s);
+    Ops::init0(w, n, turn(), s);
   });
   steps(nj, false);
   if (nn > 0) {  // a smoothed coarsest level: the polynomial from zero only
     {
       Prof p(c->prof, s, lk(solve::K_RESID, l),
              sum_bytes(j, nn, [&](const J& x) { return spmv_bytes(*x.A, TS, TS, TS, 1); }));
-      Ops::resid(j, nn, s);
+      Ops::resid(j, nn, turn(), s);
     }
     {
       Prof p(c->prof, s, lk(solve::K_RESTRICT, l),
              sum_bytes(j, nn, [&](const J& x) { return spmv_bytes(*x.R, TS, TS, TS, x.d0_c ? 2 : 0); }));
-      Ops::restrict_(j, nn, s);
+      Ops::restrict_(j, nn, turn(), s);
     }
-    vcycle<T>(c, next, nn, l + 1, tr, dense, nd, s);
+    vcycle<T>(c, next, nn, l + 1, tr, dense, nd, rev, s);
   } else if (*nd > 0) {  // no field goes deeper: the coarsest solves met so far
     double b = 0;
     for (int q = 0; q < *nd; ++q) b += 8.0 * dense[q].n * dense[q].n + 2.0 * dense[q].n * TS;
@@ -1356,17 +1372,17 @@ static void vcycle(hbgs_ctx* c, const VcField<T>* v, int nv, int l, int tr, solv
   select(nn, [](const J& k) { return k.Q != nullptr; }, [&](const J* w, int n) {
     Prof p(c->prof, s, lk(solve::K_CHEB_POST_A, l),
            sum_bytes(w, n, [&](const J& x) { return spmv_bytes(*x.Q, TS, TS, TS, 2); }));
-    Ops::post_q(w, n, s);
+    Ops::post_q(w, n, turn(), s);
   });
   select(nn, [](const J& k) { return k.Q == nullptr; }, [&](const J* w, int n) {
     {
       Prof p(c->prof, s, lk(solve::K_PROLONG, l),
              sum_bytes(w, n, [&](const J& x) { return spmv_bytes(*x.P, TS, TS, TS, 1); }));
-      Ops::prolong(w, n, s);
+      Ops::prolong(w, n, turn(), s);
     }
     Prof p(c->prof, s, lk(solve::K_CHEB_POST_A, l),
            sum_bytes(w, n, [&](const J& x) { return spmv_bytes(*x.A, TS, TS, 2 * TS, 2); }));
-    Ops::post_start(w, n, s);
+    Ops::post_start(w, n, turn(), s);
   });
   for (int t = 0; t < nn; ++t)
     if (j[t].cc->degree == 1) {
@@ -1387,6 +1403,7 @@ static void sweep(hbgs_ctx* c, const SweepPlan& plan, int tr, const double* v, T
   for (auto& st : plan.stage)
     for (int f : st) plan_bytes += c->F[f].bytes[TS == 4 ? 1 : 0];
   Prof whole(c->prof, s, solve::K_SWEEP, plan_bytes);
+  bool rev = true;
   for (auto& st : plan.stage) {
     // right-hand sides; the finest level's first Chebyshev direction is
     // formed with its rhs, a Jacobi leaf's z = D^-1 t likewise
@@ -1436,11 +1453,11 @@ static void sweep(hbgs_ctx* c, const SweepPlan& plan, int tr, const double* v, T
     }
     if (nc) {
       Prof p(c->prof, s, solve::K_COUPLE, cpl_bytes);
-      VcOps<T>::couple(cpl, nc, z, vs, s);
+      VcOps<T>::couple(cpl, nc, z, vs, rev = !rev, s);
     }
     if (nk) {
       Prof p(c->prof, s, solve::K_COUPLE, cast_bytes);
-      VcOps<T>::cast_in(cast, nk, vs, s);
+      VcOps<T>::cast_in(cast, nk, vs, rev = !rev, s);
     }
     // ILU sweeps take one workgroup per subdomain: they leave room for the
     // stage's V-cycles beside them
@@ -1460,7 +1477,7 @@ static void sweep(hbgs_ctx* c, const SweepPlan& plan, int tr, const double* v, T
     if (na) {
       solve::DenseJob<T> dense[HBGS_MAX_FIELDS];
       int nd = 0;
-      vcycle<T>(c, amg, na, 0, tr, dense, &nd, s);
+      vcycle<T>(c, amg, na, 0, tr, dense, &nd, rev, s);
     }
     if (beside) HBGS_HIP(hipStreamWaitEvent(s, c->side_done, 0));
   }
@@ -1741,7 +1758,7 @@ static void nested_apply(hbgs_ctx* c, int tr, const double* v, int j, const doub
         solve::couple_f64<double>(cpl, v + g.lo, K.Zd + (size_t)j * K.ld, KG.bp, vs, s);
     } else if (vs) {
       const solve::RhsJob<double> in{g.n(), nullptr, v + g.lo, KG.bp, nullptr, 0.0, nullptr};
-      VcOps<double>::cast_in(&in, 1, vs, s);
+      VcOps<double>::cast_in(&in, 1, vs, false, s);
     } else {
       HBGS_HIP(hipMemcpyAsync(KG.bp, v + g.lo, sizeof(double) * g.n(), hipMemcpyDeviceToDevice, s));
     }
@@ -1756,7 +1773,7 @@ static void nested_apply(hbgs_ctx* c, int tr, const double* v, int j, const doub
                  s);
     if (c->precision == 1) {
       const solve::RhsJob<float> out{g.n(), nullptr, KG.xp, K.Zf + (size_t)j * K.ld + g.lo, nullptr, 0.0, nullptr};
-      VcOps<float>::cast_in(&out, 1, nullptr, s);
+      VcOps<float>::cast_in(&out, 1, nullptr, false, s);
     } else
       HBGS_HIP(hipMemcpyAsync(K.Zd + (size_t)j * K.ld + g.lo, KG.xp, sizeof(double) * g.n(),
                               hipMemcpyDeviceToDevice, s));

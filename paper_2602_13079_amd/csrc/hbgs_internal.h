@@ -469,6 +469,9 @@ void spmv_resid_f64(const DCsr& a, const double* x, const double* b, double* r, 
 // What the passes of one field's level read and write.  The operations below
 // take several jobs (at most HBGS_MAX_FIELDS): the same step of independent
 // fields, put into as few launches as the matrices' kernel shapes allow.
+// rev: the pass walks its rows from the last to the first (the results do not
+// depend on it); passes that follow each other over the same data alternate,
+// so that each meets what the previous one left in the last-level cache.
 template <class T>
 struct LevelJob {
   const DCsr *A, *P, *R, *Q;  // P, R, Q: null on the coarsest level; Q null where it was not built
@@ -515,30 +518,30 @@ struct VcOps {
   // degree-2 pre-smoothing from a zero guess, one fused kernel, with the
   // first direction d0 = D^-1 b / theta precomputed (in d) by the rhs
   // producer: x = d0 + c1 d0 + c2 D^-1 (b - A d0)
-  static void pre2(const LevelJob<T>* j, int nj, hipStream_t s);
+  static void pre2(const LevelJob<T>* j, int nj, bool rev, hipStream_t s);
   // general degree, zero guess: r = b, d = D^-1 b / theta, x = d
-  static void init0(const LevelJob<T>* j, int nj, hipStream_t s);
+  static void init0(const LevelJob<T>* j, int nj, bool rev, hipStream_t s);
   // post-smoothing start from x: r = b - A x, d = D^-1 r / theta (x not yet updated)
-  static void post_start(const LevelJob<T>* j, int nj, hipStream_t s);
+  static void post_start(const LevelJob<T>* j, int nj, bool rev, hipStream_t s);
   // Chebyshev step k >= 1: r -= A d; dn = c1 d + c2 D^-1 r; x (+ d when add_d) += dn;
   // r and dn are stored only when keep
-  static void step(const LevelJob<T>* j, int nj, int k, bool add_d, bool keep, hipStream_t s);
+  static void step(const LevelJob<T>* j, int nj, int k, bool add_d, bool keep, bool rev, hipStream_t s);
   static void add(int n, const T* d, T* x, hipStream_t s);
-  static void resid(const LevelJob<T>* j, int nj, hipStream_t s);
+  static void resid(const LevelJob<T>* j, int nj, bool rev, hipStream_t s);
   // bc = R r; when d0_c is given also d0_c = (Dc^-1 bc) * c0_c for the coarse level
-  static void restrict_(const LevelJob<T>* j, int nj, hipStream_t s);
-  static void prolong(const LevelJob<T>* j, int nj, hipStream_t s);
+  static void restrict_(const LevelJob<T>* j, int nj, bool rev, hipStream_t s);
+  static void prolong(const LevelJob<T>* j, int nj, bool rev, hipStream_t s);
   // prolongation fused with the post-smoother's start: with Q the rows of
   // A P (even) and P (odd) interleaved and r the residual b - A x from
   // before the coarse correction, one pass forms r = r - (A P) xc,
   // d = D^-1 r / theta and x = x + P xc, i.e. the residual and first
   // direction of the corrected x without re-reading A
-  static void post_q(const LevelJob<T>* j, int nj, hipStream_t s);
+  static void post_q(const LevelJob<T>* j, int nj, bool rev, hipStream_t s);
   static void coarse(const DenseJob<T>* j, int nj, hipStream_t s);
   static void ilu(const IluJob<T>* j, int nj, int transpose, hipStream_t s);
   // right-hand sides with couplings to z, and without
-  static void couple(const RhsJob<T>* j, int nj, const T* z, const double* vs, hipStream_t s);
-  static void cast_in(const RhsJob<T>* j, int nj, const double* vs, hipStream_t s);
+  static void couple(const RhsJob<T>* j, int nj, const T* z, const double* vs, bool rev, hipStream_t s);
+  static void cast_in(const RhsJob<T>* j, int nj, const double* vs, bool rev, hipStream_t s);
 };
 
 // GMRES pieces (FP64)

@@ -94,17 +94,22 @@ __device__ __forceinline__ void load4(const double* p, double* w) {
 constexpr int MAXB = 4;
 template <class D>
 struct Batch {
+  unsigned rev;  // whole groups of eight blocks to walk backwards (0: forwards)
   unsigned first[MAXB];
   D d[MAXB];
 };
 // the job of this block (uniform) and the block's index within it
 template <class D>
 __device__ __forceinline__ const D& batch_job(const Batch<D>& b, int* blk) {
+  // backwards by groups of eight: the hardware deals consecutive workgroups
+  // to the eight XCDs in turn, so a block keeps its XCD (and what the
+  // previous pass left in that L2) in either direction
+  const unsigned bi = blockIdx.x < 8 * b.rev ? 8 * (b.rev - 1 - blockIdx.x / 8) + blockIdx.x % 8 : blockIdx.x;
   int q = 0;
 #pragma unroll
   for (int k = 1; k < MAXB; ++k)
-    if (blockIdx.x >= b.first[k]) q = k;
-  *blk = (int)(blockIdx.x - b.first[q]);
+    if (bi >= b.first[k]) q = k;
+  *blk = (int)(bi - b.first[q]);
   return b.d[q];
 }
 
@@ -555,18 +560,19 @@ static void launch_batch(K kern, unsigned grid, unsigned lds, const B& b, hipStr
 }
 // fills a batch's block ranges from `blocks(q)`; returns the grid
 template <class B, class F>
-static unsigned batch_blocks(B& b, int nj, F blocks) {
+static unsigned batch_blocks(B& b, int nj, bool rev, F blocks) {
   unsigned grid = 0;
   for (int q = 0; q < MAXB; ++q) {
     b.first[q] = q < nj ? grid : UINT32_MAX;
     if (q < nj) grid += (unsigned)blocks(q);
   }
+  b.rev = rev ? grid / 8 : 0;
   return grid;
 }
 static unsigned cdiv(int64_t a, int64_t b) { return (unsigned)((a + b - 1) / b); }
 
 template <class TM, class TV, class TACC, class TX, class Epi>
-static void launch_slices(const Pass<TX, Epi>* const* p, int nj, int rb, hipStream_t s, hipEvent_t e0,
+static void launch_slices(const Pass<TX, Epi>* const* p, int nj, bool rev, int rb, hipStream_t s, hipEvent_t e0,
                           hipEvent_t e1) {
   Batch<SliceJob<TM, TV, TX, Epi>> b;
   for (int q = 0; q < MAXB; ++q) {
@@ -575,7 +581,7 @@ static void launch_slices(const Pass<TX, Epi>* const* p, int nj, int rb, hipStre
     const Pass<TX, Epi>& j = *p[q < nj ? q : 0];
     b.d[q] = {a.n, a.dia_tab, mask, slice_vals<TV>(a), j.x, j.epi};
   }
-  const unsigned grid = batch_blocks(b, nj, [&](int q) { return cdiv(p[q]->a->n, BLK); });
+  const unsigned grid = batch_blocks(b, nj, rev, [&](int q) { return cdiv(p[q]->a->n, BLK); });
   switch (rb) {
     case 256: launch_batch(k_slices<1, TM, TV, TACC, TX, Epi>, grid, 0, b, s, e0, e1); break;
     case 128: launch_batch(k_slices<2, TM, TV, TACC, TX, Epi>, grid, 0, b, s, e0, e1); break;
@@ -584,7 +590,7 @@ static void launch_slices(const Pass<TX, Epi>* const* p, int nj, int rb, hipStre
   }
 }
 template <class TV, class TACC, class TX, class Epi>
-static void launch_tiled(const Pass<TX, Epi>* const* p, int nj, int rb, hipStream_t s, hipEvent_t e0,
+static void launch_tiled(const Pass<TX, Epi>* const* p, int nj, bool rev, int rb, hipStream_t s, hipEvent_t e0,
                          hipEvent_t e1) {
   Batch<TiledJob<TV, TX, Epi>> b;
   unsigned lds = 0;
@@ -595,7 +601,7 @@ static void launch_tiled(const Pass<TX, Epi>* const* p, int nj, int rb, hipStrea
     lds = std::max(lds, (unsigned)(pb + a.tile_cnt * TILE_W * (int)sizeof(TX)));
     b.d[q] = {a.n, a.m, a.tile_cnt, pb, a.rp, a.lc, a.tiles, csr_vals<TV>(a), j.x, j.epi};
   }
-  const unsigned grid = batch_blocks(b, nj, [&](int q) { return cdiv(p[q]->a->n, rb); });
+  const unsigned grid = batch_blocks(b, nj, rev, [&](int q) { return cdiv(p[q]->a->n, rb); });
   switch (rb) {
     case 256: launch_batch(k_csr_rows_tiled<256, TV, TACC, TX, Epi>, grid, lds, b, s, e0, e1); break;
     case 128: launch_batch(k_csr_rows_tiled<128, TV, TACC, TX, Epi>, grid, lds, b, s, e0, e1); break;
@@ -605,7 +611,7 @@ static void launch_tiled(const Pass<TX, Epi>* const* p, int nj, int rb, hipStrea
 static inline ColPlain col_of(const DCsr& a, ColPlain) { return {a.ci}; }
 static inline ColPacked col_of(const DCsr& a, ColPacked) { return {a.cd, a.cb}; }
 template <class Col, class TV, class TACC, class TX, class Epi>
-static void launch_cols(const Pass<TX, Epi>* const* p, int nj, const Shape& sh, hipStream_t s, hipEvent_t e0,
+static void launch_cols(const Pass<TX, Epi>* const* p, int nj, bool rev, const Shape& sh, hipStream_t s, hipEvent_t e0,
                         hipEvent_t e1) {
   Batch<CsrJob<Col, TV, TX, Epi>> b;
   for (int q = 0; q < MAXB; ++q) {
@@ -613,7 +619,7 @@ static void launch_cols(const Pass<TX, Epi>* const* p, int nj, const Shape& sh, 
     b.d[q] = {j.a->n, sh.vec, j.a->rp, col_of(*j.a, Col{}), csr_vals<TV>(*j.a), j.x, j.epi};
   }
   const bool rows = sh.kind == Shape::ROWS;
-  const unsigned grid = batch_blocks(b, nj, [&](int q) {
+  const unsigned grid = batch_blocks(b, nj, rev, [&](int q) {
     return rows ? cdiv(p[q]->a->n, sh.par) : cdiv((int64_t)p[q]->a->n * sh.par, BLK);
   });
 #define HBGS_KERN(K, N)                                               \
@@ -644,7 +650,7 @@ static void launch_cols(const Pass<TX, Epi>* const* p, int nj, const Shape& sh, 
 
 // the passes of all jobs, as few launches as their shapes allow
 template <class TV, class TACC, class TX, class Epi>
-static void launch_csr(const Pass<TX, Epi>* jobs, int nj, hipStream_t s, hipEvent_t e0 = nullptr,
+static void launch_csr(const Pass<TX, Epi>* jobs, int nj, bool rev, hipStream_t s, hipEvent_t e0 = nullptr,
                        hipEvent_t e1 = nullptr) {
   Shape sh[HBGS_MAX_FIELDS];
   bool done[HBGS_MAX_FIELDS] = {};
@@ -671,24 +677,24 @@ static void launch_csr(const Pass<TX, Epi>* jobs, int nj, hipStream_t s, hipEven
     switch (sh[q].kind) {
       case Shape::SLICES:
         if (sh[q].flag)
-          launch_slices<uint16_t, TV, TACC>(p, np, sh[q].par, s, e0, e1);
+          launch_slices<uint16_t, TV, TACC>(p, np, rev, sh[q].par, s, e0, e1);
         else
-          launch_slices<uint32_t, TV, TACC>(p, np, sh[q].par, s, e0, e1);
+          launch_slices<uint32_t, TV, TACC>(p, np, rev, sh[q].par, s, e0, e1);
         break;
-      case Shape::TILED: launch_tiled<TV, TACC>(p, np, sh[q].par, s, e0, e1); break;
+      case Shape::TILED: launch_tiled<TV, TACC>(p, np, rev, sh[q].par, s, e0, e1); break;
       default:
         if (sh[q].flag)
-          launch_cols<ColPacked, TV, TACC>(p, np, sh[q], s, e0, e1);
+          launch_cols<ColPacked, TV, TACC>(p, np, rev, sh[q], s, e0, e1);
         else
-          launch_cols<ColPlain, TV, TACC>(p, np, sh[q], s, e0, e1);
+          launch_cols<ColPlain, TV, TACC>(p, np, rev, sh[q], s, e0, e1);
     }
   }
 }
 template <class TV, class TACC, class TX, class Epi>
-static void launch_csr(const DCsr& a, const TX* x, const Epi& epi, hipStream_t s, hipEvent_t e0 = nullptr,
+static void launch_csr(const DCsr& a, const TX* x, const Epi& epi, bool rev, hipStream_t s, hipEvent_t e0 = nullptr,
                        hipEvent_t e1 = nullptr) {
   const Pass<TX, Epi> j{&a, x, epi};
-  launch_csr<TV, TACC>(&j, 1, s, e0, e1);
+  launch_csr<TV, TACC>(&j, 1, rev, s, e0, e1);
 }
 
 // Epilogues: load(i) issues the row's vector loads (before the row sum, so
@@ -862,19 +868,19 @@ struct EpiSubFrom {
 
 // ---------------------------------------------------------- outer SpMV
 void spmv_outer_f64(const DCsr& a, const double* x, double* y, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-  launch_csr<double, double>(a, x, EpiStore<double, double>{y}, s, e0, e1);
+  launch_csr<double, double>(a, x, EpiStore<double, double>{y}, true, s, e0, e1);
 }
 void spmv_outer_mixed(const DCsr& a, const float* x, double* y, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-  launch_csr<double, double>(a, x, EpiStore<double, double>{y}, s, e0, e1);
+  launch_csr<double, double>(a, x, EpiStore<double, double>{y}, true, s, e0, e1);
 }
 template <class TZ>
 void couple_f64(const DCsr& a, const double* v, const TZ* z, double* t, const double* vs, hipStream_t s) {
-  launch_csr<double, double>(a, z, EpiSubFrom{v, t, vs}, s);
+  launch_csr<double, double>(a, z, EpiSubFrom{v, t, vs}, false, s);
 }
 template void couple_f64<float>(const DCsr&, const double*, const float*, double*, const double*, hipStream_t);
 template void couple_f64<double>(const DCsr&, const double*, const double*, double*, const double*, hipStream_t);
 void spmv_resid_f64(const DCsr& a, const double* x, const double* b, double* r, hipStream_t s) {
-  launch_csr<double, double>(a, x, EpiResid<double>{b, r}, s);
+  launch_csr<double, double>(a, x, EpiResid<double>{b, r}, false, s);
 }
 
 // ------------------------------------------------------- V-cycle pieces
@@ -906,20 +912,20 @@ __global__ void k_add(int n, const T* __restrict__ d, T* __restrict__ x) {
 
 // jobs -> passes through `make(job)`, then the launches
 template <class T, class F>
-static void level_pass(const LevelJob<T>* j, int nj, hipStream_t s, F make) {
+static void level_pass(const LevelJob<T>* j, int nj, bool rev, hipStream_t s, F make) {
   using P = decltype(make(j[0]));
   P p[HBGS_MAX_FIELDS];
   for (int q = 0; q < nj; ++q) p[q] = make(j[q]);
-  launch_csr<T, T>(p, nj, s);
+  launch_csr<T, T>(p, nj, rev, s);
 }
 template <class T>
-void VcOps<T>::pre2(const LevelJob<T>* j, int nj, hipStream_t s) {
-  level_pass<T>(j, nj, s, [](const LevelJob<T>& J) {
+void VcOps<T>::pre2(const LevelJob<T>* j, int nj, bool rev, hipStream_t s) {
+  level_pass<T>(j, nj, rev, s, [](const LevelJob<T>& J) {
     return Pass<T, EpiChebPre2<T>>{J.A, J.d, {J.dinv, J.b, J.d, J.x, (T)J.cc->c1[1], (T)J.cc->c2[1]}};
   });
 }
 template <class T>
-void VcOps<T>::init0(const LevelJob<T>* j, int nj, hipStream_t s) {
+void VcOps<T>::init0(const LevelJob<T>* j, int nj, bool rev, hipStream_t s) {
   for (int q0 = 0; q0 < nj; q0 += MAXB) {
     const int m = std::min(MAXB, nj - q0);
     Batch<InitJob<T>> b;
@@ -927,33 +933,33 @@ void VcOps<T>::init0(const LevelJob<T>* j, int nj, hipStream_t s) {
       const LevelJob<T>& J = j[q0 + (q < m ? q : 0)];
       b.d[q] = {J.A->n, J.dinv, J.b, (T)J.cc->c0, J.r, J.d, J.x};
     }
-    const unsigned grid = batch_blocks(b, m, [&](int q) { return cdiv(j[q0 + q].A->n, BLK); });
+    const unsigned grid = batch_blocks(b, m, rev, [&](int q) { return cdiv(j[q0 + q].A->n, BLK); });
     launch_batch(k_cheb_init0<T>, grid, 0, b, s, nullptr, nullptr);
   }
 }
 template <class T>
-void VcOps<T>::post_start(const LevelJob<T>* j, int nj, hipStream_t s) {
-  level_pass<T>(j, nj, s, [](const LevelJob<T>& J) {
+void VcOps<T>::post_start(const LevelJob<T>* j, int nj, bool rev, hipStream_t s) {
+  level_pass<T>(j, nj, rev, s, [](const LevelJob<T>& J) {
     return Pass<T, EpiChebPostA<T>>{J.A, J.x, {J.dinv, J.b, J.r, J.d, (T)J.cc->c0}};
   });
 }
 template <class T, bool ADD_D, bool KEEP>
-static void cheb_step(const LevelJob<T>* j, int nj, int k, hipStream_t s) {
-  level_pass<T>(j, nj, s, [k](const LevelJob<T>& J) {
+static void cheb_step(const LevelJob<T>* j, int nj, int k, bool rev, hipStream_t s) {
+  level_pass<T>(j, nj, rev, s, [k](const LevelJob<T>& J) {
     return Pass<T, EpiChebStep<T, ADD_D, KEEP>>{
         J.A, J.d, {J.dinv, J.d, J.r, J.dn, J.x, (T)J.cc->c1[k], (T)J.cc->c2[k]}};
   });
 }
 template <class T>
-void VcOps<T>::step(const LevelJob<T>* j, int nj, int k, bool add_d, bool keep, hipStream_t s) {
+void VcOps<T>::step(const LevelJob<T>* j, int nj, int k, bool add_d, bool keep, bool rev, hipStream_t s) {
   if (add_d && keep)
-    cheb_step<T, true, true>(j, nj, k, s);
+    cheb_step<T, true, true>(j, nj, k, rev, s);
   else if (add_d)
-    cheb_step<T, true, false>(j, nj, k, s);
+    cheb_step<T, true, false>(j, nj, k, rev, s);
   else if (keep)
-    cheb_step<T, false, true>(j, nj, k, s);
+    cheb_step<T, false, true>(j, nj, k, rev, s);
   else
-    cheb_step<T, false, false>(j, nj, k, s);
+    cheb_step<T, false, false>(j, nj, k, rev, s);
 }
 template <class T>
 void VcOps<T>::add(int n, const T* d, T* x, hipStream_t s) {
@@ -961,30 +967,30 @@ void VcOps<T>::add(int n, const T* d, T* x, hipStream_t s) {
   HBGS_HIP(hipGetLastError());
 }
 template <class T>
-void VcOps<T>::resid(const LevelJob<T>* j, int nj, hipStream_t s) {
-  level_pass<T>(j, nj, s, [](const LevelJob<T>& J) { return Pass<T, EpiResid<T>>{J.A, J.x, {J.b, J.r}}; });
+void VcOps<T>::resid(const LevelJob<T>* j, int nj, bool rev, hipStream_t s) {
+  level_pass<T>(j, nj, rev, s, [](const LevelJob<T>& J) { return Pass<T, EpiResid<T>>{J.A, J.x, {J.b, J.r}}; });
 }
 template <class T>
-void VcOps<T>::restrict_(const LevelJob<T>* j, int nj, hipStream_t s) {
-  level_pass<T>(j, nj, s, [](const LevelJob<T>& J) {
+void VcOps<T>::restrict_(const LevelJob<T>* j, int nj, bool rev, hipStream_t s) {
+  level_pass<T>(j, nj, rev, s, [](const LevelJob<T>& J) {
     return Pass<T, EpiRhs<T>>{J.R, J.r, {J.bc, J.dinv_c, J.d0_c, (T)J.c0_c}};
   });
 }
 template <class T>
-void VcOps<T>::prolong(const LevelJob<T>* j, int nj, hipStream_t s) {
-  level_pass<T>(j, nj, s, [](const LevelJob<T>& J) { return Pass<T, EpiAdd<T, T>>{J.P, J.xc, {J.x}}; });
+void VcOps<T>::prolong(const LevelJob<T>* j, int nj, bool rev, hipStream_t s) {
+  level_pass<T>(j, nj, rev, s, [](const LevelJob<T>& J) { return Pass<T, EpiAdd<T, T>>{J.P, J.xc, {J.x}}; });
 }
 template <class T>
-void VcOps<T>::post_q(const LevelJob<T>* j, int nj, hipStream_t s) {
-  level_pass<T>(j, nj, s, [](const LevelJob<T>& J) {
+void VcOps<T>::post_q(const LevelJob<T>* j, int nj, bool rev, hipStream_t s) {
+  level_pass<T>(j, nj, rev, s, [](const LevelJob<T>& J) {
     return Pass<T, EpiPostQ<T>>{J.Q, J.xc, {J.dinv, J.r, J.x, J.d, (T)J.cc->c0}};
   });
 }
 template <class T>
-void VcOps<T>::couple(const RhsJob<T>* j, int nj, const T* z, const double* vs, hipStream_t s) {
+void VcOps<T>::couple(const RhsJob<T>* j, int nj, const T* z, const double* vs, bool rev, hipStream_t s) {
   Pass<T, EpiCouple<T>> p[HBGS_MAX_FIELDS];
   for (int q = 0; q < nj; ++q) p[q] = {j[q].cpl, z, {j[q].v, j[q].t, j[q].dinv, j[q].d0, (T)j[q].c0, vs}};
-  launch_csr<T, T>(p, nj, s);
+  launch_csr<T, T>(p, nj, rev, s);
 }
 
 template <class T>
@@ -1008,7 +1014,7 @@ __global__ __launch_bounds__(BLK) void k_cast_in(const Batch<CastJob<T>> batch, 
   if (j.d0) j.d0[i] = j.dinv[i] * ti * j.c0;
 }
 template <class T>
-void VcOps<T>::cast_in(const RhsJob<T>* j, int nj, const double* vs, hipStream_t s) {
+void VcOps<T>::cast_in(const RhsJob<T>* j, int nj, const double* vs, bool rev, hipStream_t s) {
   for (int q0 = 0; q0 < nj; q0 += MAXB) {
     const int m = std::min(MAXB, nj - q0);
     Batch<CastJob<T>> b;
@@ -1016,7 +1022,7 @@ void VcOps<T>::cast_in(const RhsJob<T>* j, int nj, const double* vs, hipStream_t
       const RhsJob<T>& J = j[q0 + (q < m ? q : 0)];
       b.d[q] = {J.n, J.v, J.t, J.dinv, (T)J.c0, J.d0};
     }
-    const unsigned grid = batch_blocks(b, m, [&](int q) { return cdiv(j[q0 + q].n, BLK); });
+    const unsigned grid = batch_blocks(b, m, rev, [&](int q) { return cdiv(j[q0 + q].n, BLK); });
     k_cast_in<T><<<grid, BLK, 0, s>>>(b, vs);
     HBGS_HIP(hipGetLastError());
   }
@@ -1051,7 +1057,7 @@ void VcOps<T>::coarse(const DenseJob<T>* j, int nj, hipStream_t s) {
     const int m = std::min(MAXB, nj - q0);
     Batch<DenseJob<T>> b;
     for (int q = 0; q < MAXB; ++q) b.d[q] = j[q0 + (q < m ? q : 0)];
-    const unsigned grid = batch_blocks(b, m, [&](int q) { return j[q0 + q].n; });
+    const unsigned grid = batch_blocks(b, m, false, [&](int q) { return j[q0 + q].n; });
     launch_batch(k_gemv_block<T>, grid, 0, b, s, nullptr, nullptr);
   }
 }
@@ -1127,8 +1133,8 @@ void VcOps<T>::ilu(const IluJob<T>* j, int nj, int transpose, hipStream_t s) {
       lo.d[q] = {f.ford, f.flev, f.fsub, f.F.rp, f.F.ci, v, f.dpos, J.t, y};
       up.d[q] = {f.bord, f.blev, f.bsub, f.F.rp, f.F.ci, v, f.dpos, y, J.z};
     }
-    const unsigned grid = batch_blocks(lo, m, [&](int q) { return j[q0 + q].f->nsub; });
-    batch_blocks(up, m, [&](int q) { return j[q0 + q].f->nsub; });
+    const unsigned grid = batch_blocks(lo, m, false, [&](int q) { return j[q0 + q].f->nsub; });
+    batch_blocks(up, m, false, [&](int q) { return j[q0 + q].f->nsub; });
     if (!transpose) {
       launch_batch(k_ilu_lower<T, false>, grid, 0, lo, s, nullptr, nullptr);
       launch_batch(k_ilu_upper<T, true>, grid, 0, up, s, nullptr, nullptr);
@@ -1234,6 +1240,9 @@ __device__ void givens_update(const GivensArgs& ga, const double* h2, double* co
   }
 }
 
+// Last-level (Infinity) cache of the MI355X, 256 MB.
+constexpr double kLastLevelCache = 256e6;
+
 // Classical Gram-Schmidt pass over rows: w holds column j+1 of V.
 //   UPD:  w -= sum_k h_k V_k           (k <= j)
 //   DOTS: part_k = sum V_k . w          (k <= j), after the update
@@ -1248,7 +1257,7 @@ template <int MAXV, bool UPD, bool DOTS, bool FIN>
 __global__ __launch_bounds__(BLK) void k_cgs(int n, int nv, double* __restrict__ V, size_t ldv,
                                              double* __restrict__ w, const double* __restrict__ h,
                                              double* __restrict__ part, const double* __restrict__ hp,
-                                             const double* __restrict__ scal) {
+                                             const double* __restrict__ scal, bool rev) {
   static_assert(!(FIN && UPD) && (!FIN || DOTS), "FIN finishes a basis vector ahead of a dots-only pass");
   __shared__ double sh[BLK / 64];
   double acc[DOTS ? MAXV : 1];
@@ -1271,7 +1280,9 @@ __global__ __launch_bounds__(BLK) void k_cgs(int n, int nv, double* __restrict__
   // use; the rows are accumulated in the order of a one-row loop
   constexpr int U = MAXV <= 16 ? 2 : 1;
   const int64_t stride = (int64_t)gridDim.x * BLK;
-  for (int64_t i0 = (int64_t)blockIdx.x * BLK + threadIdx.x; i0 < n; i0 += U * stride) {
+  const int64_t steps = ((int64_t)n + U * stride - 1) / (U * stride);
+  for (int64_t st = 0; st < steps; ++st) {
+    const int64_t i0 = (int64_t)blockIdx.x * BLK + threadIdx.x + (rev ? steps - 1 - st : st) * U * stride;
     double vk[U][MAXV], uu[U], wv[U];
 #pragma unroll
     for (int r = 0; r < U; ++r) {
@@ -1324,18 +1335,18 @@ __global__ __launch_bounds__(BLK) void k_cgs(int n, int nv, double* __restrict__
 
 template <bool UPD, bool DOTS, bool FIN = false>
 static void launch_cgs(int n, int nv, double* V, size_t ldv, double* w, const double* h, double* part,
-                       const double* hp, const double* scal, hipStream_t s) {
+                       const double* hp, const double* scal, bool rev, hipStream_t s) {
   int nb = dot_blocks(n);
   if (nv <= 8)
-    k_cgs<8, UPD, DOTS, FIN><<<nb, BLK, 0, s>>>(n, nv, V, ldv, w, h, part, hp, scal);
+    k_cgs<8, UPD, DOTS, FIN><<<nb, BLK, 0, s>>>(n, nv, V, ldv, w, h, part, hp, scal, rev);
   else if (nv <= 16)
-    k_cgs<16, UPD, DOTS, FIN><<<nb, BLK, 0, s>>>(n, nv, V, ldv, w, h, part, hp, scal);
+    k_cgs<16, UPD, DOTS, FIN><<<nb, BLK, 0, s>>>(n, nv, V, ldv, w, h, part, hp, scal, rev);
   else if (nv <= 32)
-    k_cgs<32, UPD, DOTS, FIN><<<nb, BLK, 0, s>>>(n, nv, V, ldv, w, h, part, hp, scal);
+    k_cgs<32, UPD, DOTS, FIN><<<nb, BLK, 0, s>>>(n, nv, V, ldv, w, h, part, hp, scal, rev);
   else if (nv <= 48)  // 16-25% faster than the 64-vector form (one wave per SIMD) at 33-48 vectors
-    k_cgs<48, UPD, DOTS, FIN><<<nb, BLK, 0, s>>>(n, nv, V, ldv, w, h, part, hp, scal);
+    k_cgs<48, UPD, DOTS, FIN><<<nb, BLK, 0, s>>>(n, nv, V, ldv, w, h, part, hp, scal, rev);
   else
-    k_cgs<64, UPD, DOTS, FIN><<<nb, BLK, 0, s>>>(n, nv, V, ldv, w, h, part, hp, scal);
+    k_cgs<64, UPD, DOTS, FIN><<<nb, BLK, 0, s>>>(n, nv, V, ldv, w, h, part, hp, scal, rev);
   HBGS_HIP(hipGetLastError());
 }
 
@@ -1388,15 +1399,18 @@ __global__ __launch_bounds__(RG_BLK) void k_reduce_givens(int nvec, int nb, cons
 
 void cgs_dots(int n, int j, const double* V, size_t ldv, const double* w, double* part, hipStream_t s) {
   launch_cgs<false, true>(n, j + 1, const_cast<double*>(V), ldv, const_cast<double*>(w), nullptr, part, nullptr,
-                          nullptr, s);
+                          nullptr, false, s);
 }
 void cgs_finish_dots(int n, int j, double* V, size_t ldv, const double* w, const double* hp, const double* scal,
                      double* part, hipStream_t s) {
-  launch_cgs<false, true, true>(n, j + 1, V, ldv, const_cast<double*>(w), nullptr, part, hp, scal, s);
+  launch_cgs<false, true, true>(n, j + 1, V, ldv, const_cast<double*>(w), nullptr, part, hp, scal, false, s);
 }
 void cgs_update_dots(int n, int j, const double* V, size_t ldv, double* w, const double* h1, double* part,
                      hipStream_t s) {
-  launch_cgs<true, true>(n, j + 1, const_cast<double*>(V), ldv, w, h1, part, nullptr, nullptr, s);
+  // where the basis exceeds the last-level cache this pass walks the rows
+  // backwards: it meets the rows that the first pass read last
+  const bool rev = (double)n * (j + 2) * sizeof(double) > kLastLevelCache;
+  launch_cgs<true, true>(n, j + 1, const_cast<double*>(V), ldv, w, h1, part, nullptr, nullptr, rev, s);
 }
 void reduce_givens(int n, int j, const double* part, double* h2, const GivensArgs& ga, hipStream_t s) {
   if (j + 2 > RG_MAXV) HBGS_FAIL(HBGS_EINVAL, "Gram-Schmidt basis too large");
