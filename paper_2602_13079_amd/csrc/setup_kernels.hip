@@ -1858,218 +1858,219 @@ __global__ void k_lu_update(int n, int k, double* m) {
     m[(int64_t)i * n + j] -= m[(int64_t)i * n + k] * m[(int64_t)k * n + j];
   }
 }
-// Blocked form of the same factorisation (partial pivoting, the first row
-// of maximal |a_ik| as pivot, interchanges recorded as in the unblocked
-// steps) for n <= LU_MAXN: panels of LU_NB columns are factored by one
-// block holding the panel rows in registers; then the panel's interchanges
-// are applied to the other columns together with U12 = L11^-1 A12, and the
-// trailing matrix is updated by A22 -= L21 U12.
-__global__ void k_iota_i32(int n, int* p) {
-  GRID_STRIDE(i, n) p[i] = (int)i;
-}
-constexpr int LU_NB = 16;
-constexpr int LU_PT = 1024;
-constexpr int LU_R = 2;
-constexpr int LU_MAXN = LU_PT * LU_R;
+// Inverse of up to GJ_MAXN rows: in-place Gauss-Jordan elimination with
+// partial pivoting (the first row of maximal |a_ik| as pivot) by panels of
+// NB columns, one launch per panel.  With K a panel's rows and columns,
+// after its row interchanges, and B the K rows (the identity in the K
+// columns), a step is
+//   A <- A' + M B,   A' = A with the K rows and columns zeroed,
+//   M_K = A_KK^-1,   M_r = -A_rK A_KK^-1 elsewhere,
+// and M is what eliminating the panel's own columns in place leaves in them.
+// Launch k applies step k to the matrix (tiles, from one buffer to another,
+// so the interchanged rows are read where they lie) while its block 0 forms
+// the next panel: it applies step k to those NB columns only, all rows in
+// registers, and eliminates them.  After the last step A holds the inverse
+// of the interchanged matrix.
+// Bound by the serial chain of n pivot searches in one block (a launch of
+// 1,444 rows 50 us, its tiles alone 16).  Against a factorisation followed by
+// two substitutions (three launches per 16 columns, then four per 32 rows):
+// 1,444 rows 7.6 -> 4.7 ms, 512 rows 2.7 -> 1.0, and a 4.2M-row rebuild, with
+// four such inverses side by side, 34.6 -> 31.0 ms.
+constexpr int GJ_T = 512;             // threads; two waves per SIMD leave a thread 256 registers
+constexpr int GJ_R = 4;               // panel rows per thread at most
+constexpr int GJ_MAXN = GJ_T * GJ_R;
+// columns of a panel: 8 for the matrices with four rows per thread, whose 16
+// columns would not stay in registers (2,000 rows: 15 ms, with 8 columns 7.5)
+constexpr int gj_nb(int rows_per_thread) { return rows_per_thread < 4 ? 16 : 8; }
+constexpr int GJ_TR = 64, GJ_TC = 128;  // rows and columns of a tile
+constexpr int GJ_MOVED = 32;          // rows that one panel's interchanges move at most
+// interchanges of a panel: count, then the rows that change, then where each
+// takes its values from; the panel's own rows come first
+constexpr int GJ_LIST = 1 + 2 * GJ_MOVED;
 
-constexpr int LU_CH = 256;  // panel rows per staging pass through LDS
-
-// Register-only (DPP) reductions within rows of 16 lanes; all 64 lanes must
-// be active.  Every lane of a 16-lane row ends with the row's result: pairs
+// Register-only (DPP) maximum within rows of 16 lanes; all 64 lanes must be
+// active.  Every lane of a 16-lane row ends with the row's result: pairs
 // within quads (quad_perm [1,0,3,2] and [2,3,0,1]), then quads (rotate right
-// by 4 and by 8 lanes).  A lane whose source is unavailable keeps its own
-// value (old = own).
-template <int CTRL>
-__device__ __forceinline__ double dpp_f64(double v) {
-  const long long bits = __double_as_longlong(v);
-  const int lo = (int)bits, hi = (int)(bits >> 32);
-  const int olo = __builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xF, 0xF, false);
-  const int ohi = __builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xF, 0xF, false);
-  return __longlong_as_double(((long long)ohi << 32) | (unsigned int)olo);
+// by 4 and by 8 lanes).
+__device__ __forceinline__ unsigned max_row16(unsigned v) {
+  v = max(v, (unsigned)__builtin_amdgcn_update_dpp((int)v, (int)v, 0xB1, 0xF, 0xF, false));
+  v = max(v, (unsigned)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x4E, 0xF, 0xF, false));
+  v = max(v, (unsigned)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x124, 0xF, 0xF, false));
+  return max(v, (unsigned)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x128, 0xF, 0xF, false));
 }
-__device__ __forceinline__ double max_row16(double v) {
-  v = fmax(v, dpp_f64<0xB1>(v));
-  v = fmax(v, dpp_f64<0x4E>(v));
-  v = fmax(v, dpp_f64<0x124>(v));
-  return fmax(v, dpp_f64<0x128>(v));
+__device__ __forceinline__ unsigned readlane_u32(unsigned v, int lane) {
+  return (unsigned)__builtin_amdgcn_readlane((int)v, lane);
 }
-__device__ __forceinline__ int min_row16(int r) {
-  r = min(r, __builtin_amdgcn_update_dpp(r, r, 0xB1, 0xF, 0xF, false));
-  r = min(r, __builtin_amdgcn_update_dpp(r, r, 0x4E, 0xF, 0xF, false));
-  r = min(r, __builtin_amdgcn_update_dpp(r, r, 0x124, 0xF, 0xF, false));
-  return min(r, __builtin_amdgcn_update_dpp(r, r, 0x128, 0xF, 0xF, false));
-}
-__device__ __forceinline__ double readlane_f64(double v, int lane) {
-  const long long bits = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_readlane((int)bits, lane), hi = __builtin_amdgcn_readlane((int)(bits >> 32), lane);
-  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-// the wavefront's maximum (uniform); fmax passes over NaN
-__device__ __forceinline__ double wave_max(double v) {
+// the wavefront's maximum (uniform)
+__device__ __forceinline__ unsigned wave_max(unsigned v) {
   v = max_row16(v);
-  return fmax(fmax(readlane_f64(v, 0), readlane_f64(v, 16)), fmax(readlane_f64(v, 32), readlane_f64(v, 48)));
-}
-__device__ __forceinline__ int wave_min(int r) {
-  r = min_row16(r);
-  return min(min(__builtin_amdgcn_readlane(r, 0), __builtin_amdgcn_readlane(r, 16)),
-             min(__builtin_amdgcn_readlane(r, 32), __builtin_amdgcn_readlane(r, 48)));
+  return max(max(readlane_u32(v, 0), readlane_u32(v, 16)), max(readlane_u32(v, 32), readlane_u32(v, 48)));
 }
 
-// The panel's rows move between memory and registers through LDS in passes
-// of LU_CH rows, so that consecutive lanes touch consecutive columns of a row
-// (a row's LU_NB values are one contiguous run) rather than one row each.
-// Each column's pivot search runs in registers (DPP within 16-lane rows,
-// lane reads across rows) and needs one barrier to combine the wavefronts.
-__global__ __launch_bounds__(LU_PT) void k_lu_panel(int n, int k0, double* m, int* piv, int* singular) {
-  static_assert(LU_PT / 64 <= 16, "the wavefronts' candidates are combined within one 16-lane row");
-  const int PT = blockDim.x, NW = PT / 64;  // a multiple of 64, at least half the rows
-  __shared__ double stage[LU_CH][LU_NB + 1];
-  // per column: each wavefront's pivot candidate (|value|, row, the row's
-  // values) and row j before the interchange; two sets, used by alternate
-  // columns, so one barrier per column suffices
-  __shared__ double cv[2][LU_PT / 64];
-  __shared__ int cr[2][LU_PT / 64];
-  __shared__ double crow[2][LU_PT / 64][LU_NB];
-  __shared__ double xrow[2][LU_NB];
-  const int rows = n - k0, nb = min(LU_NB, n - k0);
+struct GjStep {
+  int n, ld;   // rows; ld: rows rounded up to GJ_T (R GJ_T)
+  int k0, nb;  // the step's panel (nb = 0: no step, the first launch)
+  int p0, pb;  // the panel that block 0 forms (pb = 0: none, and no such block)
+  int q0, qb;  // the panel after it: its columns are written to Tn as well
+  const double* src;
+  double* dst;
+  const double* M;  // the step's M by columns: M[t * ld + r]
+  double* Mn;       // the next step's
+  const int* list;  // the interchanges (GJ_LIST)
+  int* listn;
+  const double* T;  // columns of panel p0 before the step: T[t * ld + r]
+  double* Tn;
+  int* orig;  // orig[r]: the original index of the row now at r
+  int* singular;
+};
+template <int R, int NB>
+__device__ void gj_panel(const GjStep& g) {
+  constexpr int NW = GJ_T / 64;
+  static_assert(NW <= 16, "the wavefronts' candidates are combined within one 16-lane row");
+  // per column: each wavefront's pivot candidate (key, row, its values) and
+  // row j before the interchange; two sets, used by alternate columns, so one
+  // barrier per column suffices
+  __shared__ uint2 ckey[2][NW];
+  __shared__ __align__(16) double crow[2][NW][NB];
+  __shared__ __align__(16) double xrow[2][NB];
+  __shared__ __align__(16) double Bp[NB][NB];
+  __shared__ uint16_t at[GJ_T * R];
+  __shared__ int spiv[NB];
+  constexpr unsigned LD = GJ_T * R;
+  const int n = g.n, p0 = g.p0, pb = g.pb;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  double a[LU_R][LU_NB];
+  if (tid < NB) spiv[tid] = p0 + tid;  // no interchange unless a pivot is found
+  double a[R][NB];
+  if (g.nb > 0) {
 #pragma unroll
-  for (int q = 0; q < LU_R; ++q)
-#pragma unroll
-    for (int t = 0; t < LU_NB; ++t) a[q][t] = 0.0;
-  for (int c0 = 0; c0 < rows; c0 += LU_CH) {
-    const int ce = min(LU_CH, rows - c0) * LU_NB;
-    for (int e = tid; e < ce; e += PT) {
-      const int i = e / LU_NB, t = e % LU_NB;
-      stage[i][t] = t < nb ? m[(int64_t)(k0 + c0 + i) * n + k0 + t] : 0.0;
+    for (int q = 0; q < R; ++q) at[tid + q * GJ_T] = (uint16_t)(tid + q * GJ_T);
+    if (tid < NB * NB) {
+      const int u = tid / NB, t = tid % NB;
+      Bp[u][t] = u < g.nb && t < pb ? g.T[t * LD + g.list[1 + GJ_MOVED + u]] : 0.0;
     }
     __syncthreads();
-#pragma unroll
-    for (int q = 0; q < LU_R; ++q) {
-      const int r = tid + q * PT;
-      if (r >= c0 && r < c0 + LU_CH && r < rows)
-#pragma unroll
-        for (int t = 0; t < LU_NB; ++t) a[q][t] = stage[r - c0][t];
-    }
+    if (tid < g.list[0]) at[g.list[1 + tid]] = (uint16_t)g.list[1 + GJ_MOVED + tid];
     __syncthreads();
-  }
 #pragma unroll
-  for (int j = 0; j < LU_NB; ++j) {
-    const int b = j & 1;
-    if (j >= nb) break;  // uniform across the block
-    // this wavefront's candidate: the largest |a_rj| over its rows r >= j,
-    // then the first of its rows holding that value (two branch-free
-    // reductions; NaN is never chosen)
-    double best = -1.0;
+    for (int q = 0; q < R; ++q) {
+      const int r = tid + q * GJ_T;
+      const unsigned from = at[r];
+      const bool old = r < n && !(r >= g.k0 && r < g.k0 + g.nb);
 #pragma unroll
-    for (int q = 0; q < LU_R; ++q) {
-      const int r = tid + q * PT;
-      if (r >= j && r < rows) best = fmax(best, fabs(a[q][j]));
-    }
-    best = wave_max(best);
-    int bi = INT32_MAX;
-#pragma unroll
-    for (int q = 0; q < LU_R; ++q) {
-      const int r = tid + q * PT;
-      if (r >= j && r < rows && fabs(a[q][j]) == best) bi = min(bi, r);
-    }
-    bi = wave_min(bi);
-    if (lane == 0) {
-      cv[b][wave] = best;
-      cr[b][wave] = bi;
-    }
-#pragma unroll
-    for (int q = 0; q < LU_R; ++q) {
-      const int r = tid + q * PT;
-      if (r == bi)
-#pragma unroll
-        for (int t = 0; t < LU_NB; ++t) crow[b][wave][t] = a[q][t];
-    }
-    if (tid == j)  // row j lives in a[0] of thread j (j < LU_NB <= PT)
-#pragma unroll
-      for (int t = 0; t < LU_NB; ++t) xrow[b][t] = a[0][t];
-    __syncthreads();
-    // lanes 0..NW-1 of every wavefront hold the wavefronts' candidates
-    {
-      const double cvl = lane < NW ? cv[b][lane] : -1.0;
-      const int crl = lane < NW ? cr[b][lane] : INT32_MAX;
-      best = readlane_f64(max_row16(cvl), 0);
-      bi = __builtin_amdgcn_readlane(min_row16(cvl == best ? crl : INT32_MAX), 0);
-    }
-    if (!(best > 0.0)) {  // uniform: the factorisation has failed
-      if (tid == 0) *singular = 1;
-      return;
-    }
-    const int p = bi;
-    if (tid == 0) piv[k0 + j] = k0 + p;
-    const double* prow = crow[b][(p % PT) / 64];  // the pivot row (LDS)
-    // interchange rows j and p
-#pragma unroll
-    for (int q = 0; q < LU_R; ++q) {
-      const int r = tid + q * PT;
-      if (r == j)
-#pragma unroll
-        for (int t = 0; t < LU_NB; ++t) a[q][t] = prow[t];
-      else if (r == p)
-#pragma unroll
-        for (int t = 0; t < LU_NB; ++t) a[q][t] = xrow[b][t];
-    }
-    // multipliers and the update of the panel's remaining columns
-    const double d = prow[j];
-#pragma unroll
-    for (int q = 0; q < LU_R; ++q) {
-      const int r = tid + q * PT;
-      if (r > j && r < rows) {
-        const double l = a[q][j] / d;
-        a[q][j] = l;
-#pragma unroll
-        for (int t = 0; t < LU_NB; ++t)
-          if (t > j) a[q][t] -= l * prow[t];
+      for (int t = 0; t < NB; ++t) {
+        const double x = g.T[t * LD + from];
+        a[q][t] = old && t < pb ? x : 0.0;
       }
     }
+#pragma unroll 4
+    for (int u = 0; u < NB; ++u) {
+      double m[R];
+#pragma unroll
+      for (int q = 0; q < R; ++q) m[q] = g.M[u * LD + q * GJ_T + (unsigned)tid];
+#pragma unroll
+      for (int t = 0; t < NB; ++t) {
+        const double b = Bp[u][t];
+#pragma unroll
+        for (int q = 0; q < R; ++q) a[q][t] = fma(m[q], b, a[q][t]);
+      }
+    }
+  } else {
+#pragma unroll
+    for (int q = 0; q < R; ++q)
+#pragma unroll
+      for (int t = 0; t < NB; ++t) {
+        const double x = g.T[t * LD + q * GJ_T + (unsigned)tid];
+        a[q][t] = tid + q * GJ_T < n && t < pb ? x : 0.0;
+      }
   }
-  for (int c0 = 0; c0 < rows; c0 += LU_CH) {
+  // The columns rotate through the registers: the current one is always the
+  // first and leaves as the last, so the loop stays rolled.
+#pragma unroll 1
+  for (int j = 0; j < pb; ++j) {
+    const int b = j & 1, jr = p0 + j;
+    // this wavefront's candidate among its rows r >= jr: the first of the
+    // largest key, a value's key being the high half of its magnitude, which
+    // orders magnitudes to 2^-20 (0: none, and never NaN)
+    unsigned key[R], most = 0;
 #pragma unroll
-    for (int q = 0; q < LU_R; ++q) {
-      const int r = tid + q * PT;
-      if (r >= c0 && r < c0 + LU_CH && r < rows)
+    for (int q = 0; q < R; ++q) {
+      const unsigned hi = (unsigned)(__double_as_longlong(a[q][0]) >> 32) & 0x7fffffffu;
+      key[q] = tid + q * GJ_T >= jr && hi < 0x7ff00000u ? hi : 0;
+      most = max(most, key[q]);
+    }
+    most = wave_max(most);
+    int bq = 0;
+    uint64_t at_most = 0;
 #pragma unroll
-        for (int t = 0; t < LU_NB; ++t) stage[r - c0][t] = a[q][t];
+    for (int q = R; q-- > 0;) {
+      const uint64_t m = __ballot(key[q] == most);
+      if (m) {
+        at_most = m;
+        bq = q;
+      }
+    }
+    const int bl = __builtin_ctzll(at_most);  // some lane holds the largest key
+    const int bi = bq * GJ_T + wave * 64 + bl;
+    if (lane == 0) ckey[b][wave] = make_uint2(most, (unsigned)bi);
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+      if (q == bq && lane == bl)
+#pragma unroll
+        for (int t = 0; t < NB; ++t) crow[b][wave][t] = a[q][t];
+      if (tid + q * GJ_T == jr)
+#pragma unroll
+        for (int t = 0; t < NB; ++t) xrow[b][t] = a[q][t];
     }
     __syncthreads();
-    const int ce = min(LU_CH, rows - c0) * LU_NB;
-    for (int e = tid; e < ce; e += PT) {
-      const int i = e / LU_NB, t = e % LU_NB;
-      if (t < nb) m[(int64_t)(k0 + c0 + i) * n + k0 + t] = stage[i][t];
+    // lanes 0..NW-1 of every wavefront hold the wavefronts' candidates
+    const uint2 cand = lane < NW ? ckey[b][lane] : make_uint2(0, 0);
+    most = readlane_u32(max_row16(cand.x), 0);
+    if (most == 0) {  // uniform: the matrix is singular
+      if (tid == 0) *g.singular = 1;
+      break;
     }
-    __syncthreads();
+    const int pw = __builtin_ctzll(__ballot(cand.x == most));
+    const int p = (int)readlane_u32(cand.y, pw);
+    const double* prow = crow[b][pw];  // the pivot row (LDS)
+    if (tid == 0) spiv[j] = p;
+    const double inv = 1.0 / prow[0];
+    double sc[NB];  // the pivot row scaled; the inverse's entry takes the column
+#pragma unroll
+    for (int t = 1; t < NB; ++t) sc[t - 1] = prow[t] * inv;
+    sc[NB - 1] = inv;
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+      const int r = tid + q * GJ_T;
+      if (r == p)  // the interchange
+#pragma unroll
+        for (int t = 0; t < NB; ++t) a[q][t] = xrow[b][t];
+      const double f = -a[q][0];
+#pragma unroll
+      for (int t = 0; t < NB; ++t) a[q][t] = fma(f, sc[t], t + 1 < NB ? a[q][t + 1 < NB ? t + 1 : 0] : 0.0);
+      if (r == jr)
+#pragma unroll
+        for (int t = 0; t < NB; ++t) a[q][t] = sc[t];
+    }
   }
-}
-
-// every column outside the panel: the panel's interchanges; trailing
-// columns also get U12 = L11^-1 A12 (L11 unit lower).  The interchanges,
-// applied in order, move values among at most 2 LU_NB rows: one wavefront
-// works out where each of those rows takes its value from, then every
-// column gathers them at once (no chain of dependent swaps) and solves in
-// registers with L11 from LDS.
-__global__ __launch_bounds__(BLK) void k_lu_swap_trsm(int n, int k0, int nb, double* m, const int* piv) {
-  __shared__ int dst[2 * LU_NB], src[2 * LU_NB];
-  __shared__ int nrow;
-  __shared__ double sl[LU_NB][LU_NB + 1];
-  // The walk over the interchanges runs in the registers of wavefront 0
-  // (all 64 lanes active): lane e holds slot e's (dst, src), the panel rows
-  // first, then each other row as it is met; a row's slot is found by a
-  // ballot and two slots' sources are swapped through lane reads.
-  static_assert(2 * LU_NB <= 64, "one slot per lane");
-  if (threadIdx.x < 64) {
-    const int e = threadIdx.x;
-    const int mp = e < nb ? piv[k0 + e] : 0;
-    int d = e < nb ? k0 + e : -1, sr = d;
-    int cnt = nb;
-    for (int t = 0; t < nb; ++t) {
+#pragma unroll
+  for (int q = 0; q < R; ++q)  // rows beyond n as well: zero, and no pivots
+#pragma unroll
+    for (int t = 0; t < NB; ++t) g.Mn[(t + pb) % NB * LD + q * GJ_T + (unsigned)tid] = a[q][t];
+  __syncthreads();
+  // The interchanges, applied in order, move values among at most GJ_MOVED
+  // rows: wavefront 0 works out where each of them takes its value from, in
+  // registers (all 64 lanes active): lane e holds slot e's (row, source),
+  // the panel rows first, then each other row as it is met; a row's slot is
+  // found by a ballot and two slots' sources are swapped through lane reads.
+  static_assert(2 * NB <= GJ_MOVED && GJ_MOVED <= 64, "one slot per lane");
+  if (tid < 64) {
+    const int e = tid;
+    const int mp = e < pb ? spiv[e < NB ? e : 0] : 0;
+    int d = e < pb ? p0 + e : -1, sr = d;
+    int cnt = pb;
+    for (int t = 0; t < pb; ++t) {
       const int p = __builtin_amdgcn_readlane(mp, t);
-      if (p > k0 + t && p < n) {
+      if (p > p0 + t && p < n) {
         const unsigned long long hit = __ballot(d == p);  // at most one slot holds row p
         int q;
         if (hit) {
@@ -2083,67 +2084,163 @@ __global__ __launch_bounds__(BLK) void k_lu_swap_trsm(int n, int k0, int nb, dou
         if (e == q) sr = st;
       }
     }
-    if (e < 2 * LU_NB) {
-      dst[e] = d;
-      src[e] = sr;
+    if (e < GJ_MOVED) {
+      g.listn[1 + e] = d;
+      g.listn[1 + GJ_MOVED + e] = e < cnt ? sr : 0;
     }
-    if (e == 0) nrow = cnt;
-  }
-  for (int e = threadIdx.x; e < LU_NB * LU_NB; e += BLK) {
-    const int r = e / LU_NB, u = e % LU_NB;
-    sl[r][u] = (r < nb && u < nb) ? m[(int64_t)(k0 + r) * n + k0 + u] : 0.0;
-  }
-  __syncthreads();
-  const int cnt = nrow;
-  const int64_t c = (int64_t)blockIdx.x * BLK + threadIdx.x;  // one column per thread
-  if (c < n - nb) {
-    const int j = c < k0 ? (int)c : (int)c + nb;
-    double v[2 * LU_NB];
-#pragma unroll
-    for (int q = 0; q < 2 * LU_NB; ++q) v[q] = q < cnt ? m[(int64_t)src[q] * n + j] : 0.0;
-    if (j >= k0 + nb) {
-#pragma unroll
-      for (int t = 1; t < LU_NB; ++t) {
-        if (t < nb) {
-          double s = v[t];
-#pragma unroll
-          for (int u = 0; u < t; ++u) s = fma(-sl[t][u], v[u], s);
-          v[t] = s;
-        }
-        __builtin_amdgcn_sched_barrier(0);  // keep the LDS reads row by row (registers)
-      }
-    }
-#pragma unroll
-    for (int q = 0; q < 2 * LU_NB; ++q)
-      if (q < cnt) m[(int64_t)dst[q] * n + j] = v[q];
+    if (e == 0) g.listn[0] = cnt;
+    const int o = e < cnt ? g.orig[sr] : 0;  // all read before any is written
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    if (e < cnt) g.orig[d] = o;
   }
 }
-
-// A22 -= L21 U12 in tiles of 32 rows x 64 columns (fused multiply-adds)
-__global__ __launch_bounds__(BLK) void k_lu_gemm(int n, int k0, int nb, double* m) {
-  __shared__ double sL[32][LU_NB];
-  __shared__ double sU[LU_NB][64];
-  const int r0 = k0 + nb + blockIdx.y * 32, c0 = k0 + nb + blockIdx.x * 64;
-  for (int e = threadIdx.x; e < 32 * LU_NB; e += BLK) {
-    const int i = e / LU_NB, t = e % LU_NB;
-    sL[i][t] = (r0 + i < n && t < nb) ? m[(int64_t)(r0 + i) * n + k0 + t] : 0.0;
+// Memory-bound: a tile reads and writes its entries once; eight rows and two
+// columns per thread keep the LDS reads of M (broadcast) and B below the
+// multiply-adds.
+template <int NB>
+__device__ void gj_tile(const GjStep& g, int tile) {
+  __shared__ __align__(16) double sM[NB][GJ_TR];
+  __shared__ double sB[NB][GJ_TC];
+  __shared__ int srow[GJ_TR];
+  constexpr int RT = GJ_TR / (GJ_T / 64), CT = GJ_TC / 64;  // rows and columns per thread
+  const int n = g.n, k0 = g.k0, nb = g.nb;
+  const int tcols = (n + GJ_TC - 1) / GJ_TC;
+  const int r0 = tile / tcols * GJ_TR, c0 = tile % tcols * GJ_TC;
+  const int tid = threadIdx.x, ib = tid / 64 * RT;
+  if (tid < GJ_TR) {
+    const int r = r0 + tid, cnt = g.list[0];
+    int from = r;
+    for (int e = 0; e < cnt; ++e)
+      if (g.list[1 + e] == r) from = g.list[1 + GJ_MOVED + e];
+    srow[tid] = from;
   }
-  for (int e = threadIdx.x; e < LU_NB * 64; e += BLK) {
-    const int t = e / 64, jj = e % 64;
-    sU[t][jj] = (c0 + jj < n && t < nb) ? m[(int64_t)(k0 + t) * n + c0 + jj] : 0.0;
+#pragma unroll
+  for (int e = tid; e < NB * GJ_TR; e += GJ_T) {
+    const int u = e / GJ_TR, i = e % GJ_TR;
+    sM[u][i] = r0 + i < n ? g.M[(size_t)u * g.ld + r0 + i] : 0.0;
+  }
+#pragma unroll
+  for (int e = tid; e < NB * GJ_TC; e += GJ_T) {
+    const int u = e / GJ_TC, c = c0 + e % GJ_TC;
+    const bool own = c >= k0 && c < k0 + nb;  // a column of the panel
+    sB[u][e % GJ_TC] = own ? (c - k0 == u ? 1.0 : 0.0)
+                           : u < nb && c < n ? g.src[(size_t)g.list[1 + GJ_MOVED + u] * n + c] : 0.0;
   }
   __syncthreads();
-  const int jj = threadIdx.x & 63, ib = (threadIdx.x >> 6) * 8;
-  if (c0 + jj >= n) return;
+  double x[RT][CT], y[RT][CT];
 #pragma unroll
-  for (int u = 0; u < 8; ++u) {
-    const int i = r0 + ib + u;
-    if (i >= n) break;
-    double acc = 0.0;
+  for (int w = 0; w < CT; ++w) {
+    const int c = c0 + 64 * w + (tid & 63);
+    const bool col = c < n && !(c >= k0 && c < k0 + nb);
 #pragma unroll
-    for (int t = 0; t < LU_NB; ++t) acc = fma(sL[ib + u][t], sU[t][jj], acc);
-    m[(int64_t)i * n + c0 + jj] -= acc;
+    for (int i = 0; i < RT; ++i) {
+      const int r = r0 + ib + i;
+      const bool old = col && r < n && !(r >= k0 && r < k0 + nb);
+      x[i][w] = old ? g.src[(size_t)srow[ib + i] * n + c] : 0.0;
+      y[i][w] = 0.0;
+    }
   }
+#pragma unroll 2
+  for (int u = 0; u < NB; ++u) {
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+      for (int w = 0; w < CT; ++w) y[i][w] = fma(sM[u][ib + i], sB[u][64 * w + (tid & 63)], y[i][w]);
+  }
+#pragma unroll
+  for (int w = 0; w < CT; ++w) {
+    const int c = c0 + 64 * w + (tid & 63);
+    if (c >= n) continue;
+    const bool ahead = c >= g.q0 && c < g.q0 + g.qb;
+#pragma unroll
+    for (int i = 0; i < RT; ++i) {
+      const int r = r0 + ib + i;
+      if (r >= n) break;
+      const double z = x[i][w] + y[i][w];
+      g.dst[(size_t)r * n + c] = z;
+      if (ahead) g.Tn[(size_t)(c - g.q0) * g.ld + r] = z;
+    }
+  }
+}
+template <int R, int NB>
+__global__ __launch_bounds__(GJ_T) void k_gj_step(const GjStep g) {
+  const int panel = g.pb > 0;
+  if (panel && blockIdx.x == 0)
+    gj_panel<R, NB>(g);
+  else
+    gj_tile<NB>(g, (int)blockIdx.x - panel);
+}
+// the dense matrix, one block per row; the first two panels by columns
+__global__ __launch_bounds__(BLK) void k_gj_fill(int n, int ld, int nb, const int* __restrict__ rp, const int* __restrict__ ci,
+                                                 const double* __restrict__ v, double* __restrict__ m,
+                                                 double* __restrict__ t0, double* __restrict__ t1,
+                                                 int* __restrict__ orig) {
+  __shared__ double row[GJ_MAXN];
+  const int i = blockIdx.x;
+  for (int j = threadIdx.x; j < n; j += BLK) row[j] = 0.0;
+  __syncthreads();
+  for (int k = rp[i] + (int)threadIdx.x; k < rp[i + 1]; k += BLK) row[ci[k]] = v[k];
+  __syncthreads();
+  for (int j = threadIdx.x; j < n; j += BLK) {
+    m[(size_t)i * n + j] = row[j];
+    if (j < nb)
+      t0[(size_t)j * ld + i] = row[j];
+    else if (j < 2 * nb)
+      t1[(size_t)(j - nb) * ld + i] = row[j];
+  }
+  if (threadIdx.x == 0) orig[i] = i;
+}
+// x is the inverse of the interchanged matrix: its columns go back in order
+__global__ __launch_bounds__(BLK) void k_gj_finish(int n, const double* __restrict__ x, const int* __restrict__ orig,
+                                                   double* __restrict__ inv) {
+  const int64_t i = blockIdx.x;
+  for (int c = threadIdx.x; c < n; c += BLK) inv[i * n + orig[c]] = x[i * n + c];
+}
+static int gauss_jordan(const DCsr& a, double* inv, hipStream_t s) {
+  const int n = a.n, per = (n + GJ_T - 1) / GJ_T, ld = per * GJ_T, NB = gj_nb(per), panels = (n + NB - 1) / NB;
+  Tmp<double> work((size_t)n * n), m((size_t)2 * NB * ld), t((size_t)2 * NB * ld);
+  Tmp<int> list(2 * GJ_LIST), orig(n), sing(1);
+  // the last step writes work, from which the columns go to inv
+  double* x[2] = {panels & 1 ? inv : work.p, panels & 1 ? work.p : inv};
+  auto at = [&](Tmp<double>& w, int q) { return w.p + (size_t)(q & 1) * NB * ld; };
+  HBGS_HIP(hipMemsetAsync(sing.p, 0, sizeof(int), s));
+  k_gj_fill<<<n, BLK, 0, s>>>(n, ld, NB, a.rp, a.ci, a.v, x[0], at(t, 0), at(t, 1), orig.p);
+  const int tiles = ((n + GJ_TR - 1) / GJ_TR) * ((n + GJ_TC - 1) / GJ_TC);
+  for (int k = -1; k < panels; ++k) {
+    auto width = [&](int q) { return q < panels ? std::min(NB, n - q * NB) : 0; };
+    GjStep g{};
+    g.n = n;
+    g.ld = ld;
+    g.k0 = k * NB;
+    g.nb = k < 0 ? 0 : width(k);
+    g.p0 = (k + 1) * NB;
+    g.pb = width(k + 1);
+    g.q0 = (k + 2) * NB;
+    g.qb = width(k + 2);
+    g.src = x[k & 1];
+    g.dst = x[(k + 1) & 1];
+    g.M = at(m, k);
+    g.Mn = at(m, k + 1);
+    g.list = list.p + (k & 1) * GJ_LIST;
+    g.listn = list.p + ((k + 1) & 1) * GJ_LIST;
+    g.T = at(t, k + 1);
+    g.Tn = at(t, k);
+    g.orig = orig.p;
+    g.singular = sing.p;
+    const unsigned grid = (unsigned)((k < 0 ? 0 : tiles) + (g.pb > 0));
+    switch (per) {
+      case 1: k_gj_step<1, gj_nb(1)><<<grid, GJ_T, 0, s>>>(g); break;
+      case 2: k_gj_step<2, gj_nb(2)><<<grid, GJ_T, 0, s>>>(g); break;
+      case 3: k_gj_step<3, gj_nb(3)><<<grid, GJ_T, 0, s>>>(g); break;
+      default: k_gj_step<4, gj_nb(4)><<<grid, GJ_T, 0, s>>>(g); break;
+    }
+    HBGS_HIP(hipGetLastError());
+  }
+  if (read_one(sing.p, s)) return -4;
+  k_gj_finish<<<n, BLK, 0, s>>>(n, x[panels & 1], orig.p, inv);
+  HBGS_HIP(hipGetLastError());
+  return 0;
 }
 
 // Explicit inverse from the factors, X = U^-1 (L^-1 P), by blocks of
@@ -2230,30 +2327,16 @@ __global__ __launch_bounds__(BLK) void k_inv_update(int n, int kb, int nb, int r
 
 int dense_inverse(const DCsr& a, double* inv, hipStream_t s) {
   const int n = a.n;
+  if (n <= GJ_MAXN) return gauss_jordan(a, inv, s);
   Tmp<double> m((size_t)n * n);
   Tmp<int> piv(n), sing(1), pinv(n);
   HBGS_HIP(hipMemsetAsync(sing.p, 0, sizeof(int), s));
   k_dense_fill<<<grid_for(n, 64), 64, 0, s>>>(n, a.rp, a.ci, a.v, m.p);
   HBGS_HIP(hipGetLastError());
-  if (n <= LU_MAXN) {
-    k_iota_i32<<<grid_for(n, BLK), BLK, 0, s>>>(n, piv.p);  // no interchange unless a pivot is found
-    HBGS_HIP(hipGetLastError());
-    for (int k0 = 0; k0 < n; k0 += LU_NB) {
-      const int nb = std::min(LU_NB, n - k0);
-      // as many wavefronts as the panel's rows need (LU_R rows per thread):
-      // every wavefront runs each column's pivot search, so fewer is faster
-      const int pt = std::min(LU_PT, std::max(64, ((n - k0 + LU_R - 1) / LU_R + 63) / 64 * 64));
-      k_lu_panel<<<1, pt, 0, s>>>(n, k0, m.p, piv.p, sing.p);
-      if (n - nb > 0) k_lu_swap_trsm<<<(n - nb + BLK - 1) / BLK, BLK, 0, s>>>(n, k0, nb, m.p, piv.p);
-      const int rest = n - k0 - nb;
-      if (rest > 0) k_lu_gemm<<<dim3((rest + 63) / 64, (rest + 31) / 32), BLK, 0, s>>>(n, k0, nb, m.p);
-    }
-  } else {
-    for (int k = 0; k < n; ++k) {
-      k_lu_pivot<<<1, BLK, 0, s>>>(n, k, m.p, piv.p, sing.p);
-      if (k + 1 < n)
-        k_lu_update<<<grid_for((int64_t)(n - k - 1) * (n - k - 1), BLK, 8192), BLK, 0, s>>>(n, k, m.p);
-    }
+  for (int k = 0; k < n; ++k) {
+    k_lu_pivot<<<1, BLK, 0, s>>>(n, k, m.p, piv.p, sing.p);
+    if (k + 1 < n)
+      k_lu_update<<<grid_for((int64_t)(n - k - 1) * (n - k - 1), BLK, 8192), BLK, 0, s>>>(n, k, m.p);
   }
   HBGS_HIP(hipGetLastError());
   int singular = 0;
