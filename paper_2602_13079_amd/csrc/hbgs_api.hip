@@ -108,7 +108,9 @@ MailArg Mail::next() {
 const void* Mail::wait(hipStream_t s) {
   const volatile uint64_t* flag = host_;
   for (unsigned spins = 1; *flag != seq_; ++spins) {
-    if ((spins & 1023u) == 0) {
+    // (rarely: the query takes the runtime's locks, on which the other fields'
+    // threads launch)
+    if ((spins & 65535u) == 0) {
       const hipError_t e = hipStreamQuery(s);
       if (e == hipSuccess && *flag != seq_) HBGS_FAIL(HBGS_EHIP, "a setup kernel ended without its result");
       if (e != hipSuccess && e != hipErrorNotReady) HBGS_HIP(e);
@@ -710,7 +712,7 @@ static void build_hierarchy(hbgs_ctx* c, Field& F, hipStream_t s) {
       const uint64_t salt = salt_base + (uint64_t)l;
       setup::mis2_init(n, excluded.p, state.p, s);
       for (int round = 0;; ++round) {
-        setup::mis2_round(A, strong.p, salt, state.p, m1.p, r1.p, flag1.p, s);
+        setup::mis2_round(A, strong.p, salt, state.p, m1.p, r1.p, round == 0, flag1.p, s);
         if (setup::read_one(flag1.p, s) == 0) break;
         if (round > n + 2) HBGS_FAIL(HBGS_ESETUP, "aggregation did not terminate");
       }

@@ -339,8 +339,9 @@ void diagonal(const DCsr& a, double* d, int* missing, hipStream_t s);
 void strength(const DCsr& a, const double* d, double theta, char* strong, char* excluded, hipStream_t s);
 // MIS-2 rounds: state 0 undecided, 1 root, 2 out, 3 excluded
 void mis2_init(int n, const char* excluded, char* state, hipStream_t s);
+// (first: of a set; the rounds after it pass over rows that have settled)
 void mis2_round(const DCsr& a, const char* strong, uint64_t salt, char* state, uint64_t* m1, char* r1,
-                int* undecided, hipStream_t s);
+                bool first, int* undecided, hipStream_t s);
 void agg_roots(int n, const char* state, int* flag, hipStream_t s);
 void agg_phase12(const DCsr& a, const char* strong, uint64_t salt, const char* state, const int64_t* root_rank,
                  int* agg, int* single_flag, hipStream_t s);

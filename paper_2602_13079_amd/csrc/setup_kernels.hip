@@ -182,7 +182,9 @@ __device__ __forceinline__ int64_t block_scan(int64_t v, int64_t* sh, int64_t* t
   return before + inc - v;
 }
 // toff[t] = sum of tsum[0 .. t-1], toff[nt] = total (mailed when m.slot is set)
-constexpr int SCAN_TOP = 1024;
+// (a block of 1,024 threads waited up to 330 us for a compute unit with room
+// for it beside the other fields' work)
+constexpr int SCAN_TOP = 256;
 __global__ __launch_bounds__(SCAN_TOP) void k_scan_tiles(const int64_t* __restrict__ tsum, int64_t nt,
                                                          int64_t* __restrict__ toff, MailArg m) {
   __shared__ int64_t sh[SCAN_TOP / 64];
@@ -408,41 +410,54 @@ __global__ void k_transpose_scatter(int n, const int* rp, const int* ci, const d
     }
   }
 }
-// sort each row by column (entries are distinct, so the result is unique);
-// rows of up to SORT_LDS entries are sorted in a per-thread LDS segment,
-// longer rows are listed and sorted one block per row
-constexpr int SORT_LDS = 32;
-constexpr int SORT_BLK = 64;
+// Sort each row by column (entries are distinct, so the result is unique):
+// an entry's place is its rank, the number of smaller columns in the row.
+// One wavefront per row of up to SORT_WAVE entries, whose columns it reads
+// from LDS four at a time (broadcast); longer rows are listed and sorted one
+// block per row.  The transposed prolongators have 30 to 400 entries per row:
+// one thread per row up to 32 entries and a block for each longer one took
+// 730 us for the 95,000 rows of a 1M-row field's (four fields side by side),
+// this 140.
+constexpr int SORT_WAVE = 256;
 constexpr int LONG_LDS = 2048;
-__global__ __launch_bounds__(SORT_BLK) void k_sort_rows_lds(int n, const int* rp, int* ci, double* v,
-                                                            int* n_long, int* long_rows) {
-  __shared__ int sc[SORT_BLK][SORT_LDS + 1];
-  __shared__ double sv[SORT_BLK][SORT_LDS + 1];
-  int i = blockIdx.x * SORT_BLK + threadIdx.x;
+__global__ __launch_bounds__(BLK) void k_sort_rows_wave(int n, const int* rp, int* ci, double* v, int* n_long,
+                                                        int* long_rows) {
+  constexpr int E = SORT_WAVE / 64;  // entries per lane
+  __shared__ __align__(16) int sc[BLK / 64][SORT_WAVE];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int64_t i = (int64_t)blockIdx.x * (BLK / 64) + wave;
   if (i >= n) return;
-  int s = rp[i], e = rp[i + 1], len = e - s;
-  if (len > SORT_LDS) {
-    long_rows[atomicAdd(n_long, 1)] = i;
+  const int s = rp[i], len = rp[i + 1] - s;
+  if (len < 2) return;
+  if (len > SORT_WAVE) {
+    if (lane == 0) long_rows[atomicAdd(n_long, 1)] = (int)i;
     return;
   }
-  int* c = sc[threadIdx.x];
-  double* x = sv[threadIdx.x];
-  for (int k = 0; k < len; ++k) {
-    int cc = ci[s + k];
-    double xx = v ? v[s + k] : 0.0;
-    int q = k - 1;
-    while (q >= 0 && c[q] > cc) {
-      c[q + 1] = c[q];
-      x[q + 1] = x[q];
-      --q;
+  int c[E];
+  double x[E];
+#pragma unroll
+  for (int q = 0; q < E; ++q) {
+    const int k = lane + 64 * q;
+    c[q] = k < len ? ci[s + k] : INT32_MAX;
+    x[q] = v && k < len ? v[s + k] : 0.0;
+    if (64 * q < len) sc[wave][k] = c[q];
+  }
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  int rank[E] = {};
+  for (int p = 0; p < len; p += 4) {  // beyond len: INT32_MAX, below no column
+    const int4 d = *reinterpret_cast<const int4*>(&sc[wave][p]);
+#pragma unroll
+    for (int q = 0; q < E; ++q)
+      if (64 * q < len) rank[q] += (d.x < c[q]) + (d.y < c[q]) + (d.z < c[q]) + (d.w < c[q]);
+  }
+#pragma unroll
+  for (int q = 0; q < E; ++q)
+    if (lane + 64 * q < len) {
+      ci[s + rank[q]] = c[q];
+      if (v) v[s + rank[q]] = x[q];
     }
-    c[q + 1] = cc;
-    x[q + 1] = xx;
-  }
-  for (int k = 0; k < len; ++k) {
-    ci[s + k] = c[k];
-    if (v) v[s + k] = x[k];
-  }
 }
 
 // the *count listed rows of up to LONG_LDS entries, one block per row:
@@ -499,7 +514,8 @@ void sort_rows(const DCsr& a, hipStream_t s) {
   if (a.n == 0) return;
   Tmp<int> n_long(1), long_rows(a.n);
   HBGS_HIP(hipMemsetAsync(n_long.p, 0, sizeof(int), s));
-  k_sort_rows_lds<<<grid_for(a.n, SORT_BLK), SORT_BLK, 0, s>>>(a.n, a.rp, a.ci, a.v, n_long.p, long_rows.p);
+  k_sort_rows_wave<<<(unsigned)(((int64_t)a.n + 3) / 4), BLK, 0, s>>>(a.n, a.rp, a.ci, a.v, n_long.p, long_rows.p);
+  static_assert(BLK == 256, "four rows per block");
   HBGS_HIP(hipGetLastError());
   k_sort_long_rows<<<grid_for(a.n, 1, 2048), BLK, 0, s>>>(n_long.p, long_rows.p, a.rp, a.ci, a.v);
   HBGS_HIP(hipGetLastError());
@@ -635,13 +651,20 @@ void strength(const DCsr& a, const double* d, double theta, char* strong, char* 
 // propagate through all rows, decided or not); rows within distance 2 of a
 // root leave.  This yields the greedy maximal distance-2 independent set
 // taken in decreasing key order.
+// A row without undecided rows among itself and its neighbours (m1 = 0) never
+// has one again, and what a round leaves in its r1 only decided rows would
+// read, so every round after the first passes over such rows: a round's four
+// passes then read 8-12 bytes per row instead of its entries (four fields of
+// 1M rows side by side: rounds 5 to 7 of 7 took 200-300 us each, now 90-180).
 __global__ void k_mis2_init(int n, const char* excluded, char* state) {
   GRID_STRIDE(i, n) state[i] = excluded[i] ? 3 : 0;
 }
 template <int L>
 __global__ void k_mis2_max1(int n, const int* rp, const int* ci, const char* strong, uint64_t salt,
-                            const char* state, uint64_t* m1) {
+                            const char* state, uint64_t* m1, bool first, int* undecided) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) *undecided = 0;  // counted by the round's last pass
   ROW_GROUPS(L, i, gl, n) {
+    if (!first && m1[i] == 0) continue;
     uint64_t m = (gl == 0 && state[i] == 0) ? agg_key((int)i, salt) : 0;
     for (int k = rp[i] + gl; k < rp[i + 1]; k += L) {
       if (!strong[k]) continue;
@@ -669,8 +692,9 @@ __global__ void k_mis2_max2(int n, const int* rp, const int* ci, const char* str
 }
 template <int L>
 __global__ void k_mis2_near1(int n, const int* rp, const int* ci, const char* strong, const char* state,
-                             char* r1) {
+                             const uint64_t* m1, char* r1, bool first) {
   ROW_GROUPS(L, i, gl, n) {
+    if (!first && (m1[i] == 0 || r1[i])) continue;  // once next to a root, always
     int r = state[i] == 1;
     for (int k = rp[i] + gl; k < rp[i + 1]; k += L)
       if (strong[k] && state[ci[k]] == 1) r = 1;
@@ -712,12 +736,11 @@ void mis2_init(int n, const char* excluded, char* state, hipStream_t s) {
 }
 
 void mis2_round(const DCsr& a, const char* strong, uint64_t salt, char* state, uint64_t* m1, char* r1,
-                int* undecided, hipStream_t s) {
+                bool first, int* undecided, hipStream_t s) {
   const int L = row_lanes(a.n, a.nnz);
-  LAUNCH_ROW_GROUPS(k_mis2_max1, L, a.n, s, a.n, a.rp, a.ci, strong, salt, state, m1);
+  LAUNCH_ROW_GROUPS(k_mis2_max1, L, a.n, s, a.n, a.rp, a.ci, strong, salt, state, m1, first, undecided);
   LAUNCH_ROW_GROUPS(k_mis2_max2, L, a.n, s, a.n, a.rp, a.ci, strong, salt, m1, state);
-  LAUNCH_ROW_GROUPS(k_mis2_near1, L, a.n, s, a.n, a.rp, a.ci, strong, state, r1);
-  HBGS_HIP(hipMemsetAsync(undecided, 0, sizeof(int), s));
+  LAUNCH_ROW_GROUPS(k_mis2_near1, L, a.n, s, a.n, a.rp, a.ci, strong, state, m1, r1, first);
   LAUNCH_ROW_GROUPS_CAP(k_mis2_near2, L, a.n, 2048, s, a.n, a.rp, a.ci, strong, r1, state, undecided);
 }
 
@@ -973,10 +996,15 @@ __global__ void k_pw_scale(int n, const double* y, const unsigned long long* ama
 // add one run each, in index order.  Terms beyond n are staged as +0.0,
 // which leaves a sum that starts at +0.0 unchanged.
 constexpr int DOT_RUNS = 16;
+// blockIdx.y = 0: x . y, 1: x . x (part: m run sums each)
 __global__ __launch_bounds__(256) void k_chunk_dot(int64_t n, const double* x, const double* y, double* part) {
   __shared__ double tile[DOT_RUNS][257];
   const int64_t m = (n + 255) / 256;
   const int t = (int)threadIdx.x;
+  if (blockIdx.y) {
+    y = x;
+    part += m;
+  }
   for (int64_t c0 = (int64_t)blockIdx.x * DOT_RUNS; c0 < m; c0 += (int64_t)gridDim.x * DOT_RUNS) {
 #pragma unroll
     for (int r = 0; r < DOT_RUNS; ++r) {
@@ -992,38 +1020,38 @@ __global__ __launch_bounds__(256) void k_chunk_dot(int64_t n, const double* x, c
     __syncthreads();
   }
 }
-// ... then the m run sums added in order: the block stages 1024 of them in
+// ... then the m run sums added in order: block q stages 4096 of sum q's in
 // LDS at a time, one thread adds them
-constexpr int RUN_STAGE = 1024;
+constexpr int RUN_STAGE = 4096;
 __global__ void __launch_bounds__(256) k_chunk_total(int64_t m, const double* part, double* out) {
   __shared__ double sh[RUN_STAGE];
+  part += (int64_t)blockIdx.x * m;
   double s = 0.0;
   for (int64_t c0 = 0; c0 < m; c0 += RUN_STAGE) {
     const int e = (int)(m - c0 < RUN_STAGE ? m - c0 : RUN_STAGE);
     for (int t = threadIdx.x; t < e; t += blockDim.x) sh[t] = part[c0 + t];
     __syncthreads();
-    if (threadIdx.x == 0)
+    if (threadIdx.x == 0) {
+#pragma unroll 16
       for (int t = 0; t < e; ++t) s += sh[t];
+    }
     __syncthreads();
   }
-  if (threadIdx.x == 0) *out = s;
+  if (threadIdx.x == 0) out[blockIdx.x] = s;
 }
 
 // out[0] = x . y, out[1] = x . x
 static void chunked_dots(int64_t n, const double* x, const double* y, double* part, double* out, hipStream_t s) {
   const int64_t m = (n + 255) / 256;
-  const double* other[2] = {y, x};
-  for (int q = 0; q < 2; ++q) {
-    k_chunk_dot<<<grid_for(m, DOT_RUNS, 2048), 256, 0, s>>>(n, x, other[q], part);
-    k_chunk_total<<<1, 256, 0, s>>>(m, part, out + q);
-  }
+  k_chunk_dot<<<dim3(grid_for(m, DOT_RUNS, 2048), 2), 256, 0, s>>>(n, x, y, part);
+  k_chunk_total<<<2, 256, 0, s>>>(m, part, out);
   HBGS_HIP(hipGetLastError());
 }
 
 double power_estimate(const DCsr& b, const double* d, int iters, uint64_t salt, hipStream_t s) {
   const int n = b.n;
   if (n == 0) return 0.0;
-  Tmp<double> w(n), y(n), pa((n + 255) / 256 + 1);
+  Tmp<double> w(n), y(n), pa(2 * (((int64_t)n + 255) / 256));
   Tmp<double> res(3);  // the two dots and the last iterate's largest entry
   Tmp<unsigned long long> amax(iters > 0 ? iters : 1);
   const unsigned g = grid_for(n, BLK);
@@ -1057,16 +1085,19 @@ double power_estimate(const DCsr& b, const double* d, int iters, uint64_t salt, 
 // Row i of P = P_tent - omega D_abs^-1 A_F P_tent: its columns are the
 // aggregates met along row i of A_F (ascending); entry c is
 // [agg(i)==c] - (omega / D_abs_i) * sum_{k: agg(k)==c} a_F(i,k).
+// A group's first L entries stay in registers over the passes below, one per
+// aggregate met; only longer rows read the rest again.
 template <int L>
 __global__ void k_psmooth_count(int n, const int* rp, const int* ci, const int* agg, int* cnt) {
   ROW_GROUPS(L, i, gl, n) {
     int c = 0;
     if (agg[i] >= 0) {
       const int s = rp[i], e = rp[i + 1];
+      const int a0 = s + gl < e ? agg[ci[s + gl]] : -1;
       int prev = -1;
       for (;;) {
-        int next = INT32_MAX;
-        for (int k = s + gl; k < e; k += L) {
+        int next = a0 > prev ? a0 : INT32_MAX;
+        for (int k = s + gl + L; k < e; k += L) {
           const int a = agg[ci[k]];
           if (a > prev && a < next) next = a;
         }
@@ -1087,9 +1118,12 @@ __global__ void k_psmooth_fill(int n, const int* rp, const int* ci, const double
     if (ai < 0) continue;
     const double q = dabs[i] != 0.0 ? omega / dabs[i] : 0.0;  // a zero row of A_F: no smoothing term
     const int s = rp[i], e = rp[i + 1];
+    const bool in0 = s + gl < e;
+    const int a0 = in0 ? agg[ci[s + gl]] : -1;
+    const double v0 = in0 ? v[s + gl] : 0.0;
     int o = rpp[i];
-    int cur = INT32_MAX;
-    for (int k = s + gl; k < e; k += L) {
+    int cur = a0 >= 0 ? a0 : INT32_MAX;
+    for (int k = s + gl + L; k < e; k += L) {
       const int a = agg[ci[k]];
       if (a >= 0 && a < cur) cur = a;
     }
@@ -1097,9 +1131,10 @@ __global__ void k_psmooth_fill(int n, const int* rp, const int* ci, const double
     // one pass per aggregate met: its entries summed in column order, and
     // the next larger aggregate
     while (cur != INT32_MAX) {
-      double sum = 0.0;
-      int next = INT32_MAX;
-      for (int b = s; b < e; b += L) {
+      const bool hit0 = a0 == cur;
+      double sum = grp_ordered_add<L>(0.0, hit0 ? v0 : 0.0, hit0);
+      int next = a0 > cur ? a0 : INT32_MAX;
+      for (int b = s + L; b < e; b += L) {
         const int k = b + gl;
         const int a = k < e ? agg[ci[k]] : -1;
         const bool hit = a == cur;
@@ -1140,11 +1175,17 @@ void psmooth_fill(const DCsr& af, const int* agg, const double* dabs, double ome
 // update the same slot in one step, and a wave's LDS operations complete in
 // program order, so each slot still sums its products in ascending k.  The
 // remaining rows use one thread each and a table in global scratch memory.
+// (one thread per row took 240-310 us on the long rows of R)
+template <int L>
 __global__ void k_spgemm_ub(int n, const int* arp, const int* aci, const int* brp, int64_t* ub) {
-  GRID_STRIDE(i, n) {
+  ROW_GROUPS(L, i, gl, n) {
     int64_t u = 0;
-    for (int k = arp[i]; k < arp[i + 1]; ++k) u += brp[aci[k] + 1] - brp[aci[k]];
-    ub[i] = u;
+    for (int k = arp[i] + gl; k < arp[i + 1]; k += L) {
+      const int c = aci[k];
+      u += brp[c + 1] - brp[c];
+    }
+    for (int off = L >> 1; off > 0; off >>= 1) u += __shfl_xor(u, off, L);
+    if (gl == 0) ub[i] = u;
   }
 }
 __host__ __device__ __forceinline__ int64_t table_size(int64_t ub) {
@@ -1695,8 +1736,7 @@ void spgemm(const DCsr& a, const DCsr& b, DCsr& c, Pool& pool, hipStream_t s) {
   Tmp<int> cnt(n), flags(NFLAGS);
   int* overflow = flags.p + OVF;
   HBGS_HIP(hipMemsetAsync(flags.p, 0, NFLAGS * sizeof(int), s));
-  k_spgemm_ub<<<grid_for(n, BLK), BLK, 0, s>>>(n, a.rp, a.ci, b.rp, ub.p);
-  HBGS_HIP(hipGetLastError());
+  LAUNCH_ROW_GROUPS(k_spgemm_ub, row_lanes(n, a.nnz), n, s, n, a.rp, a.ci, b.rp, ub.p);
   // lanes per row from the mean length of B's rows; rows too long for the
   // group tables go to the one-row-per-wavefront kernels
   const double bavg = b.n ? (double)b.nnz / b.n : 0.0;
