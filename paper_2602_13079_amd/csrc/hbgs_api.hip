@@ -613,17 +613,18 @@ static void add_f32(Pool& pool, DCsr& a, hipStream_t s) {
 // of its row blocks of rb rows.  Slices replace row blocks of 32 rows up
 // only: their order of summation follows the row-block form, and below
 // 32768 rows that form has fewer rows than that in a block (one row per
-// thread would leave most of the chip idle there).  try_slices is false for
-// matrices that have no diagonals by construction (transfer operators,
-// Galerkin products), which saves looking.
-static void solve_layout(Pool& pool, DCsr& a, int cap, bool try_slices, hipStream_t s) {
+// thread would leave most of the chip idle there).  Transfer operators and
+// Galerkin products have no diagonals by construction: build_hierarchy gives
+// them columns and tiles without looking.
+static void solve_layout(Pool& pool, DCsr& a, int cap, hipStream_t s) {
   const int rb = solve::rows_per_block(a, cap, true);
-  if (try_slices && rb >= 32 && solve::rows_per_block(a, solve::ROWS_CAP_F64, true) >= 32) {
+  if (rb >= 32 && solve::rows_per_block(a, solve::ROWS_CAP_F64, true) >= 32) {
     setup::build_slices(pool, a, s);
     if (a.dia_w) return;
   }
   setup::pack_columns(pool, a, s);
-  setup::build_tiles(pool, a, rb, s);
+  DCsr* m = &a;
+  setup::build_tiles(pool, &m, &rb, 1, s);
 }
 // arrays for the values of a pattern with its layout: row order, or the
 // slices' (and both when the setup reads the values in row order too)
@@ -681,14 +682,19 @@ static void build_hierarchy(hbgs_ctx* c, Field& F, hipStream_t s) {
   StageClock clk(F.stage_seconds);
   Pool& pool = c->hier;
   const uint64_t salt_base = splitmix64_host(o.seed + 0x1000ull * (uint64_t)(F.id + 1));
-  Tmp<int> flag1(1);
+  Tmp<int> flag1(2);  // undecided rows, missing diagonal entries
   for (int l = 0;; ++l) {
     const int n = F.lv[l].A.n;
     clk.to(6);
     Tmp<double> d(n);
-    HBGS_HIP(hipMemsetAsync(flag1.p, 0, sizeof(int), s));
-    setup::diagonal(F.lv[l].A, d.p, flag1.p, s);
-    if (setup::read_one(flag1.p, s)) HBGS_FAIL(HBGS_EINVAL, "zero or missing diagonal entry in a field block");
+    bool last = n <= o.coarse_max || l + 1 >= o.max_levels;
+    HBGS_HIP(hipMemsetAsync(flag1.p, 0, 2 * sizeof(int), s));
+    setup::diagonal(F.lv[l].A, d.p, flag1.p + 1, s);
+    auto check_diagonal = [](int missing) {
+      if (missing) HBGS_FAIL(HBGS_EINVAL, "zero or missing diagonal entry in a field block");
+    };
+    // (a level that is coarsened learns it with the first aggregation round)
+    if (F.leaf != 0 || last) check_diagonal(setup::read_one(flag1.p + 1, s));
     if (F.leaf != 0) {  // one-level leaf: diagonal inverse, or the incomplete factors
       Level& L = F.lv[0];
       L.dinv = pool.make<double>(n);
@@ -702,7 +708,6 @@ static void build_hierarchy(hbgs_ctx* c, Field& F, hipStream_t s) {
       HBGS_HIP(hipStreamSynchronize(s));
       return;
     }
-    bool last = n <= o.coarse_max || l + 1 >= o.max_levels;
     if (!last) {
       DCsr& A = F.lv[l].A;
       clk.to(1);
@@ -713,7 +718,10 @@ static void build_hierarchy(hbgs_ctx* c, Field& F, hipStream_t s) {
       setup::mis2_init(n, excluded.p, state.p, s);
       for (int round = 0;; ++round) {
         setup::mis2_round(A, strong.p, salt, state.p, m1.p, r1.p, round == 0, flag1.p, s);
-        if (setup::read_one(flag1.p, s) == 0) break;
+        int h[2];
+        setup::read_back(h, flag1.p, sizeof(h), s);
+        check_diagonal(h[1]);
+        if (h[0] == 0) break;
         if (round > n + 2) HBGS_FAIL(HBGS_ESETUP, "aggregation did not terminate");
       }
       Tmp<int> rflag(n), sflag(n);
@@ -793,24 +801,21 @@ static void build_hierarchy(hbgs_ctx* c, Field& F, hipStream_t s) {
   }
   // solve-phase data: transposes, FP32 copies, work vectors
   clk.to(7);
+  std::vector<DCsr*> mats;
   for (size_t l = 0; l < F.lv.size(); ++l) {
     Level& L = F.lv[l];
     if (l > 0) {  // the finest level came with its pattern's layout
       add_f32(pool, L.A, s);
-      setup::row_stats(L.A, s);
-      solve_layout(pool, L.A, solve::ROWS_CAP_F32, false, s);
+      mats.push_back(&L.A);
     }
     if (l + 1 < F.lv.size()) {
       add_f32(pool, L.P, s);
       add_f32(pool, L.R, s);
-      setup::row_stats(L.P, s);
-      setup::row_stats(L.R, s);
-      solve_layout(pool, L.P, solve::ROWS_CAP_F32, false, s);
-      setup::pack_columns(pool, L.R, s);
+      mats.push_back(&L.P);
+      mats.push_back(&L.R);
       if (L.Q.n) {
         add_f32(pool, L.Q, s);
-        setup::row_stats(L.Q, s);
-        solve_layout(pool, L.Q, solve::ROWS_CAP_F32, false, s);
+        mats.push_back(&L.Q);
       }
     }
     const int n = L.A.n;
@@ -825,6 +830,15 @@ static void build_hierarchy(hbgs_ctx* c, Field& F, hipStream_t s) {
     L.df = pool.make<float>(n);
     L.dnf = pool.make<float>(n);
   }
+  // neither transfer operators nor Galerkin products have diagonals to keep to
+  setup::stats_and_columns(pool, mats.data(), (int)mats.size(), s);
+  std::vector<int> rb;
+  for (DCsr* m : mats) {
+    bool restriction = false;
+    for (Level& L : F.lv) restriction |= m == &L.R;
+    rb.push_back(restriction ? 0 : solve::rows_per_block(*m, solve::ROWS_CAP_F32, true));
+  }
+  setup::build_tiles(pool, mats.data(), rb.data(), (int)mats.size(), s);
 }
 
 static double spmv_bytes(const DCsr& a, int tv, int tx, int ty, int extra_vec) {
@@ -937,7 +951,7 @@ static void build_field_T(hbgs_ctx* c, Field& F, hipStream_t s) {
     fp.upperT = extract_pattern(c->patterns, c->ApT, c->posT, F.lo, F.hi, bj ? ghi : F.hi, ghi, glo, ghi - glo,
                                 &fp.srcU, s);
     setup::row_stats(fp.upperT, s);
-    solve_layout(c->patterns, fp.upperT, solve::ROWS_CAP_F32, true, s);
+    solve_layout(c->patterns, fp.upperT, solve::ROWS_CAP_F32, s);
     fp.tr = true;
   }
   F.upperT = fp.upperT;
@@ -945,6 +959,7 @@ static void build_field_T(hbgs_ctx* c, Field& F, hipStream_t s) {
   setup::load_values(F.upperT, ap_values(c), fp.srcU, s);
   if (F.leaf == 2) setup::ilu_transpose(pool, F.ilu, s);
   if (F.leaf == 0) {
+    std::vector<DCsr*> mats;
     for (size_t l = 0; l < F.lv.size(); ++l) {
       Level& L = F.lv[l];
       L.AT = L.A;  // pattern, row statistics and layout
@@ -962,10 +977,10 @@ static void build_field_T(hbgs_ctx* c, Field& F, hipStream_t s) {
         setup::spgemm(L.AT, L.P, ATP, tmp_pool, s);
         setup::interleave_rows(pool, ATP, L.P, L.QT, s);
         add_f32(pool, L.QT, s);
-        setup::row_stats(L.QT, s);
-        setup::pack_columns(pool, L.QT, s);
+        mats.push_back(&L.QT);
       }
     }
+    setup::stats_and_columns(pool, mats.data(), (int)mats.size(), s);
     if (F.inv) {
       const int nc = F.lv.back().A.n;
       F.invT = pool.make<double>((size_t)nc * nc);
@@ -1002,7 +1017,7 @@ static void build_field(hbgs_ctx* c, Field& F, hipStream_t s) {
     for (DCsr* a : {&fp.A, &fp.lower}) {
       if (a == &fp.A && F.leaf != 0) continue;  // no V-cycle reads the block
       setup::row_stats(*a, s);
-      solve_layout(c->patterns, *a, solve::ROWS_CAP_F32, true, s);
+      solve_layout(c->patterns, *a, solve::ROWS_CAP_F32, s);
     }
     fp.fwd = true;
   }
@@ -1060,7 +1075,7 @@ static void plan_direction(hbgs_ctx* c, int tr, hipStream_t s) {
 static void group_layout(hbgs_ctx* c, DCsr& a, DCsr& b, hipStream_t s) {
   for (DCsr* m : {&a, &b}) {
     setup::row_stats(*m, s);
-    solve_layout(c->patterns, *m, solve::ROWS_CAP_F64, true, s);
+    solve_layout(c->patterns, *m, solve::ROWS_CAP_F64, s);
   }
 }
 static void group_values(hbgs_ctx* c, DCsr& a, const int* src, hipStream_t s) {
@@ -1974,7 +1989,7 @@ hbgs_status hbgs_setup(hbgs_ctx** out, int32_t n, int64_t nnz, const int32_t* ro
   }
   for (DCsr* a : {&c->Ap, &c->ApT}) {
     setup::row_stats(*a, s);
-    solve_layout(c->pool, *a, solve::ROWS_CAP_F64, true, s);
+    solve_layout(c->pool, *a, solve::ROWS_CAP_F64, s);
     if (a->dia_w) {  // the slices' values replace those in row order
       HBGS_HIP(hipStreamSynchronize(s));
       c->pool.release(a->v);

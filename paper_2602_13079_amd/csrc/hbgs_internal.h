@@ -374,10 +374,11 @@ void transpose_symmetric(const DCsr& a, double* vt, hipStream_t s);
 void interleave_rows(Pool& pool, const DCsr& a, const DCsr& b, DCsr& q, hipStream_t s);
 // longest row of a and its fullest row blocks (a.maxlen, a.blkmax)
 void row_stats(DCsr& a, hipStream_t s);
-// the operand tiles of a's blocks of rb rows (a.tiles, a.lc, a.tile_cnt;
-// a.tile_rb = rb), or none (a.tile_rb = 0) where a block has more than
-// TILE_MAX tiles or more entries than one block's LDS staging holds
-void build_tiles(Pool& pool, DCsr& a, int rb, hipStream_t s);
+// the operand tiles of each matrix's blocks of rb[k] rows (a.tiles, a.lc,
+// a.tile_cnt; a.tile_rb = rb), or none (a.tile_rb = 0) where a block has more
+// than TILE_MAX tiles or more entries than one block's LDS staging holds, or
+// where rb[k] is 0; one wait for all of them
+void build_tiles(Pool& pool, DCsr* const* a, const int* rb, int count, hipStream_t s);
 // the diagonal slices of a's pattern (a.dia_w, table and masks), or none
 // (a.dia_w = 0) where a slice has more than DIA_MAX diagonals or the slices
 // would hold more than 1.25 places per entry
@@ -398,6 +399,9 @@ void ilu_transpose(Pool& pool, IluLeaf& leaf, hipStream_t s);
 // builds a.cd / a.cb when every chunk of COL_CHUNK entries fits a 16-bit
 // offset from its smallest column (leaves them null otherwise)
 void pack_columns(Pool& pool, DCsr& a, hipStream_t s);
+// row_stats and pack_columns of several matrices with one wait (a wait, and
+// the launch after it on an idle queue, cost 40-100 us beside other fields)
+void stats_and_columns(Pool& pool, DCsr* const* a, int count, hipStream_t s);
 // dense transpose of an n x n row-major matrix
 void dense_transpose(int n, const double* in, double* out, hipStream_t s);
 void reciprocal(int n, const double* d, double* dinv, float* dinvf, hipStream_t s);

@@ -77,6 +77,7 @@ __device__ __forceinline__ int grp_sum(int x) {
 // order): the sequential sum over a row's entries, L entries at a time
 template <int L>
 __device__ __forceinline__ double grp_ordered_add(double s, double x, bool take) {
+  if constexpr (L == 1) return take ? s + x : s;
   const uint64_t b = __ballot(take);
   const int lane = (int)(threadIdx.x & 63), base = lane & ~(L - 1);
   uint64_t g = L == 64 ? b : (b >> base) & ((1ull << (L & 63)) - 1);
@@ -90,6 +91,10 @@ __device__ __forceinline__ double grp_ordered_add(double s, double x, bool take)
 // number of lanes below this one in the group with pred set; *total: in the group
 template <int L>
 __device__ __forceinline__ int grp_rank(bool pred, int* total) {
+  if constexpr (L == 1) {
+    *total = pred;
+    return 0;
+  }
   const uint64_t b = __ballot(pred);
   const int lane = (int)(threadIdx.x & 63), base = lane & ~(L - 1);
   const uint64_t g = L == 64 ? b : (b >> base) & ((1ull << (L & 63)) - 1);
@@ -102,12 +107,26 @@ static int row_lanes(int64_t n, int64_t nnz) {
   const double avg = n ? (double)nnz / (double)n : 0.0;
   return avg <= 7.5 ? 8 : avg <= 15.0 ? 16 : 32;
 }
+// For passes that look at a row's entries once or twice: one thread per row
+// where rows are short.  It requests the row's first entries (row_regs)
+// together, and no cross-lane steps are left; eight lanes per row are eight
+// times the waves, each with the same chain of dependent loads (an aggregation
+// pass over 1M rows of 7 entries, four fields side by side: 130-190 us, one
+// thread per row 36-63; the strengths 172 -> 50, the filtered matrix 459 ->
+// 141, the prolongator 712 -> 162).
+static int scan_lanes(int64_t n, int64_t nnz) {
+  const int L = row_lanes(n, nnz);
+  return L == 8 ? 1 : L;
+}
+// entries per lane requested together
+constexpr int row_regs(int L) { return L == 1 ? 8 : 1; }
 #define LAUNCH_ROW_GROUPS(kern, L, nrows, s, ...) LAUNCH_ROW_GROUPS_CAP(kern, L, nrows, 1 << 20, s, __VA_ARGS__)
 // cap: most blocks (kernels that end in one atomic per block use a small cap)
 #define LAUNCH_ROW_GROUPS_CAP(kern, L, nrows, cap, s, ...)            \
   do {                                                                 \
     const unsigned g_ = grid_for((int64_t)(nrows) * (L), BLK, cap);    \
     switch (L) {                                                       \
+      case 1: kern<1><<<g_, BLK, 0, s>>>(__VA_ARGS__); break;          \
       case 8: kern<8><<<g_, BLK, 0, s>>>(__VA_ARGS__); break;          \
       case 16: kern<16><<<g_, BLK, 0, s>>>(__VA_ARGS__); break;        \
       default: kern<32><<<g_, BLK, 0, s>>>(__VA_ARGS__); break;        \
@@ -609,39 +628,56 @@ void diagonal(const DCsr& a, double* d, int* missing, hipStream_t s) {
 template <int L>
 __global__ void k_strength(int n, const int* rp, const int* ci, const double* v, const double* d, double th2,
                            char* strong, char* excluded) {
+  constexpr int U = row_regs(L);
   ROW_GROUPS(L, i, gl, n) {
     int offd = 0;
-    for (int k = rp[i] + gl; k < rp[i + 1]; k += L) {
-      const int j = ci[k];
-      if (j == (int)i) {
-        strong[k] = 0;
-        continue;
+    const int e = rp[i + 1];
+    const double di = fabs(d[i]);
+    for (int b = rp[i] + gl; b < e; b += L * U) {
+      int c[U];
+      double x[U], dj[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int k = b + u * L;
+        c[u] = k < e ? ci[k] : (int)i;
+        x[u] = k < e ? v[k] : 0.0;
       }
-      offd = 1;
-      bool st = v[k] * v[k] >= (th2 * fabs(d[i])) * fabs(d[j]);
-      if (!st) {
-        int lo = rp[j], hi = rp[j + 1] - 1;
-        while (lo <= hi) {
-          const int mid = (lo + hi) >> 1;
-          const int cm = ci[mid];
-          if (cm == (int)i) {
-            st = v[mid] * v[mid] >= (th2 * fabs(d[j])) * fabs(d[i]);
-            break;
-          }
-          if (cm < (int)i)
-            lo = mid + 1;
-          else
-            hi = mid - 1;
+#pragma unroll
+      for (int u = 0; u < U; ++u) dj[u] = fabs(d[c[u]]);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int k = b + u * L, j = c[u];
+        if (k >= e) continue;
+        if (j == (int)i) {
+          strong[k] = 0;
+          continue;
         }
+        offd = 1;
+        bool st = x[u] * x[u] >= (th2 * di) * dj[u];
+        if (!st) {
+          int lo = rp[j], hi = rp[j + 1] - 1;
+          while (lo <= hi) {
+            const int mid = (lo + hi) >> 1;
+            const int cm = ci[mid];
+            if (cm == (int)i) {
+              st = v[mid] * v[mid] >= (th2 * dj[u]) * di;
+              break;
+            }
+            if (cm < (int)i)
+              lo = mid + 1;
+            else
+              hi = mid - 1;
+          }
+        }
+        strong[k] = st ? 1 : 0;
       }
-      strong[k] = st ? 1 : 0;
     }
     offd = grp_max<L>(offd);
     if (gl == 0) excluded[i] = offd ? 0 : 1;
   }
 }
 void strength(const DCsr& a, const double* d, double theta, char* strong, char* excluded, hipStream_t s) {
-  const int L = row_lanes(a.n, a.nnz);
+  const int L = scan_lanes(a.n, a.nnz);
   LAUNCH_ROW_GROUPS(k_strength, L, a.n, s, a.n, a.rp, a.ci, a.v, d, theta * theta, strong, excluded);
 }
 
@@ -659,6 +695,24 @@ void strength(const DCsr& a, const double* d, double theta, char* strong, char* 
 __global__ void k_mis2_init(int n, const char* excluded, char* state) {
   GRID_STRIDE(i, n) state[i] = excluded[i] ? 3 : 0;
 }
+// f(j) for every strong neighbour j that lane gl of row i's group holds
+template <int L, class F>
+__device__ __forceinline__ void strong_neighbours(int s, int e, int gl, const int* ci, const char* strong, F f) {
+  constexpr int U = row_regs(L);
+  for (int b = s + gl; b < e; b += L * U) {
+    int c[U];
+    bool on[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = b + u * L;
+      on[u] = k < e && strong[k];
+      c[u] = k < e ? ci[k] : 0;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (on[u]) f(c[u]);
+  }
+}
 template <int L>
 __global__ void k_mis2_max1(int n, const int* rp, const int* ci, const char* strong, uint64_t salt,
                             const char* state, uint64_t* m1, bool first, int* undecided) {
@@ -666,14 +720,10 @@ __global__ void k_mis2_max1(int n, const int* rp, const int* ci, const char* str
   ROW_GROUPS(L, i, gl, n) {
     if (!first && m1[i] == 0) continue;
     uint64_t m = (gl == 0 && state[i] == 0) ? agg_key((int)i, salt) : 0;
-    for (int k = rp[i] + gl; k < rp[i + 1]; k += L) {
-      if (!strong[k]) continue;
-      const int j = ci[k];
-      if (state[j] == 0) {
-        const uint64_t kj = agg_key(j, salt);
-        m = kj > m ? kj : m;
-      }
-    }
+    strong_neighbours<L>(rp[i], rp[i + 1], gl, ci, strong, [&](int j) {
+      const uint64_t kj = state[j] == 0 ? agg_key(j, salt) : 0;
+      m = kj > m ? kj : m;
+    });
     m = grp_max<L>(m);
     if (gl == 0) m1[i] = m;
   }
@@ -684,8 +734,10 @@ __global__ void k_mis2_max2(int n, const int* rp, const int* ci, const char* str
   ROW_GROUPS(L, i, gl, n) {
     if (state[i] != 0) continue;
     uint64_t m = m1[i];
-    for (int k = rp[i] + gl; k < rp[i + 1]; k += L)
-      if (strong[k]) m = m1[ci[k]] > m ? m1[ci[k]] : m;
+    strong_neighbours<L>(rp[i], rp[i + 1], gl, ci, strong, [&](int j) {
+      const uint64_t mj = m1[j];
+      m = mj > m ? mj : m;
+    });
     m = grp_max<L>(m);
     if (gl == 0 && m == agg_key((int)i, salt)) state[i] = 1;
   }
@@ -696,8 +748,7 @@ __global__ void k_mis2_near1(int n, const int* rp, const int* ci, const char* st
   ROW_GROUPS(L, i, gl, n) {
     if (!first && (m1[i] == 0 || r1[i])) continue;  // once next to a root, always
     int r = state[i] == 1;
-    for (int k = rp[i] + gl; k < rp[i + 1]; k += L)
-      if (strong[k] && state[ci[k]] == 1) r = 1;
+    strong_neighbours<L>(rp[i], rp[i + 1], gl, ci, strong, [&](int j) { r |= state[j] == 1; });
     r = grp_max<L>(r);
     if (gl == 0) r1[i] = (char)r;
   }
@@ -709,8 +760,7 @@ __global__ void k_mis2_near2(int n, const int* rp, const int* ci, const char* st
   ROW_GROUPS(L, i, gl, n) {
     if (state[i] != 0) continue;
     int out = r1[i];
-    for (int k = rp[i] + gl; k < rp[i + 1] && !out; k += L)
-      if (strong[k] && r1[ci[k]]) out = 1;
+    if (!out) strong_neighbours<L>(rp[i], rp[i + 1], gl, ci, strong, [&](int j) { out |= r1[j]; });
     out = grp_max<L>(out);
     if (gl == 0) {
       if (out)
@@ -737,7 +787,7 @@ void mis2_init(int n, const char* excluded, char* state, hipStream_t s) {
 
 void mis2_round(const DCsr& a, const char* strong, uint64_t salt, char* state, uint64_t* m1, char* r1,
                 bool first, int* undecided, hipStream_t s) {
-  const int L = row_lanes(a.n, a.nnz);
+  const int L = scan_lanes(a.n, a.nnz);
   LAUNCH_ROW_GROUPS(k_mis2_max1, L, a.n, s, a.n, a.rp, a.ci, strong, salt, state, m1, first, undecided);
   LAUNCH_ROW_GROUPS(k_mis2_max2, L, a.n, s, a.n, a.rp, a.ci, strong, salt, m1, state);
   LAUNCH_ROW_GROUPS(k_mis2_near1, L, a.n, s, a.n, a.rp, a.ci, strong, state, m1, r1, first);
@@ -763,8 +813,9 @@ __global__ void k_agg_phase1(int n, const int* rp, const int* ci, const char* st
     if (state[i] == 1) {
       a = (int)root_rank[i];
     } else if (state[i] != 3) {
-      for (int k = rp[i] + gl; k < rp[i + 1]; k += L)
-        if (strong[k] && state[ci[k]] == 1) a = (int)root_rank[ci[k]];
+      int root = -1;
+      strong_neighbours<L>(rp[i], rp[i + 1], gl, ci, strong, [&](int j) { root = state[j] == 1 ? j : root; });
+      a = root >= 0 ? (int)root_rank[root] : -1;
       a = grp_max<L>(a);
     }
     if (gl == 0) p1[i] = a;
@@ -781,9 +832,7 @@ __global__ void k_agg_phase2(int n, const int* rp, const int* ci, const char* st
     if (state[i] != 3 && a < 0) {
       uint64_t best = 0;
       int bestu = -1;
-      for (int k = rp[i] + gl; k < rp[i + 1]; k += L) {
-        if (!strong[k]) continue;
-        const int u = ci[k];
+      strong_neighbours<L>(rp[i], rp[i + 1], gl, ci, strong, [&](int u) {
         if (p1[u] >= 0 && state[u] != 1) {
           const uint64_t ku = agg_key(u, salt);
           if (bestu < 0 || ku > best) {
@@ -791,7 +840,7 @@ __global__ void k_agg_phase2(int n, const int* rp, const int* ci, const char* st
             bestu = u;
           }
         }
-      }
+      });
       const uint64_t top = grp_max<L>(bestu < 0 ? 0ull : best + 1);  // 0: no candidate
       a = top ? p1[(int)(uint32_t)((top - 1) & 0xffffffffull)] : -1;
       single = top ? 0 : 1;
@@ -809,7 +858,7 @@ __global__ void k_agg_phase3(int n, const int* single_flag, const int64_t* singl
 void agg_phase12(const DCsr& a, const char* strong, uint64_t salt, const char* state, const int64_t* root_rank,
                  int* agg, int* single_flag, hipStream_t s) {
   Tmp<int> p1(a.n);
-  const int L = row_lanes(a.n, a.nnz);
+  const int L = scan_lanes(a.n, a.nnz);
   LAUNCH_ROW_GROUPS(k_agg_phase1, L, a.n, s, a.n, a.rp, a.ci, strong, state, root_rank, p1.p);
   LAUNCH_ROW_GROUPS(k_agg_phase2, L, a.n, s, a.n, a.rp, a.ci, strong, salt, state, p1.p, agg, single_flag);
 }
@@ -823,56 +872,91 @@ void agg_phase3(int n, const int* single_flag, const int64_t* single_rank, int n
 // diagonal in ascending column order; D_abs = sum |A_F| along the row
 template <int L>
 __global__ void k_filter_count(int n, const int* rp, const int* ci, const char* strong, int* cnt) {
+  constexpr int U = row_regs(L);
   ROW_GROUPS(L, i, gl, n) {
     int c = 0;
-    for (int k = rp[i] + gl; k < rp[i + 1]; k += L) c += (ci[k] == (int)i || strong[k]) ? 1 : 0;
+    const int e = rp[i + 1];
+    for (int b = rp[i] + gl; b < e; b += L * U) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int k = b + u * L;
+        const int j = k < e ? ci[k] : -1;
+        const bool st = k < e && strong[k];
+        c += j == (int)i || st;
+      }
+    }
     c = grp_sum<L>(c);
     if (gl == 0) cnt[i] = c;
   }
 }
+// the group's first L * row_regs(L) entries stay in registers; only longer
+// rows read the rest again
 template <int L>
 __global__ void k_filter_fill(int n, const int* rp, const int* ci, const double* v, const char* strong,
                               const int* rpf, int* cif, double* vf, double* dabs) {
+  constexpr int U = row_regs(L);
   ROW_GROUPS(L, i, gl, n) {
-    const int s = rp[i], e = rp[i + 1];
+    const int s = rp[i], e = rp[i + 1], more = s + L * U;
+    int c[U];
+    double x[U];
+    bool st[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = s + u * L + gl;
+      c[u] = k < e ? ci[k] : -1;
+      x[u] = k < e ? v[k] : 0.0;
+      st[u] = k < e && strong[k];
+    }
     int pos = -1;
-    for (int k = s + gl; k < e; k += L)
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (c[u] == (int)i) pos = s + u * L + gl;
+    for (int k = more + gl; k < e; k += L)
       if (ci[k] == (int)i) pos = k;
     pos = grp_max<L>(pos);
     // diagonal of A_F: a_ii, then the dropped entries in column order
     double d = pos >= 0 ? v[pos] : 0.0;
-    for (int b = s; b < e; b += L) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const bool drop = c[u] >= 0 && c[u] != (int)i && !st[u];
+      d = grp_ordered_add<L>(d, drop ? x[u] : 0.0, drop);
+    }
+    for (int b = more; b < e; b += L) {
       const int k = b + gl;
       const bool drop = k < e && ci[k] != (int)i && !strong[k];
       d = grp_ordered_add<L>(d, drop ? v[k] : 0.0, drop);
     }
     int q = rpf[i];
     double sa = 0.0;
-    for (int b = s; b < e; b += L) {
-      const int k = b + gl;
-      const int c = k < e ? ci[k] : -1;
-      const bool diag = c == (int)i;
-      const bool keep = k < e && (diag || strong[k]);
-      const double x = keep ? (diag ? d : v[k]) : 0.0;
+    auto put = [&](int col, double val, bool on) {
+      const bool diag = col == (int)i;
+      const bool keep = diag || on;
+      const double w = keep ? (diag ? d : val) : 0.0;
       int tot;
       const int r = grp_rank<L>(keep, &tot);
       if (keep) {
-        cif[q + r] = c;
-        vf[q + r] = x;
+        cif[q + r] = col;
+        vf[q + r] = w;
       }
       q += tot;
-      sa = grp_ordered_add<L>(sa, fabs(x), keep);
+      sa = grp_ordered_add<L>(sa, fabs(w), keep);
+    };
+#pragma unroll
+    for (int u = 0; u < U; ++u) put(c[u], x[u], st[u]);
+    for (int b = more; b < e; b += L) {
+      const int k = b + gl;
+      put(k < e ? ci[k] : -1, k < e ? v[k] : 0.0, k < e && strong[k]);
     }
     if (gl == 0) dabs[i] = sa;
   }
 }
 void filter_count(const DCsr& a, const char* strong, int* cnt, hipStream_t s) {
-  const int L = row_lanes(a.n, a.nnz);
+  const int L = scan_lanes(a.n, a.nnz);
   LAUNCH_ROW_GROUPS(k_filter_count, L, a.n, s, a.n, a.rp, a.ci, strong, cnt);
 }
 void filter_fill(const DCsr& a, const char* strong, const int* rp_f, int* ci_f, double* v_f, double* dabs,
                  hipStream_t s) {
-  const int L = row_lanes(a.n, a.nnz);
+  const int L = scan_lanes(a.n, a.nnz);
   LAUNCH_ROW_GROUPS(k_filter_fill, L, a.n, s, a.n, a.rp, a.ci, a.v, strong, rp_f, ci_f, v_f, dabs);
 }
 
@@ -1085,21 +1169,28 @@ double power_estimate(const DCsr& b, const double* d, int iters, uint64_t salt, 
 // Row i of P = P_tent - omega D_abs^-1 A_F P_tent: its columns are the
 // aggregates met along row i of A_F (ascending); entry c is
 // [agg(i)==c] - (omega / D_abs_i) * sum_{k: agg(k)==c} a_F(i,k).
-// A group's first L entries stay in registers over the passes below, one per
-// aggregate met; only longer rows read the rest again.
+// A group's first L * row_regs(L) entries stay in registers over the passes
+// below, one per aggregate met; only longer rows read the rest again.
 template <int L>
 __global__ void k_psmooth_count(int n, const int* rp, const int* ci, const int* agg, int* cnt) {
+  constexpr int U = row_regs(L);
   ROW_GROUPS(L, i, gl, n) {
     int c = 0;
     if (agg[i] >= 0) {
       const int s = rp[i], e = rp[i + 1];
-      const int a0 = s + gl < e ? agg[ci[s + gl]] : -1;
+      int a[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) a[u] = s + u * L + gl < e ? ci[s + u * L + gl] : -1;
+#pragma unroll
+      for (int u = 0; u < U; ++u) a[u] = a[u] >= 0 ? agg[a[u]] : -1;
       int prev = -1;
       for (;;) {
-        int next = a0 > prev ? a0 : INT32_MAX;
-        for (int k = s + gl + L; k < e; k += L) {
-          const int a = agg[ci[k]];
-          if (a > prev && a < next) next = a;
+        int next = INT32_MAX;
+#pragma unroll
+        for (int u = 0; u < U; ++u) next = a[u] > prev && a[u] < next ? a[u] : next;
+        for (int k = s + L * U + gl; k < e; k += L) {
+          const int b = agg[ci[k]];
+          if (b > prev && b < next) next = b;
         }
         next = grp_min<L>(next);
         if (next == INT32_MAX) break;
@@ -1113,52 +1204,63 @@ __global__ void k_psmooth_count(int n, const int* rp, const int* ci, const int* 
 template <int L>
 __global__ void k_psmooth_fill(int n, const int* rp, const int* ci, const double* v, const int* agg,
                                const double* dabs, double omega, const int* rpp, int* cip, double* vp) {
+  constexpr int U = row_regs(L);
   ROW_GROUPS(L, i, gl, n) {
     const int ai = agg[i];
     if (ai < 0) continue;
     const double q = dabs[i] != 0.0 ? omega / dabs[i] : 0.0;  // a zero row of A_F: no smoothing term
     const int s = rp[i], e = rp[i + 1];
-    const bool in0 = s + gl < e;
-    const int a0 = in0 ? agg[ci[s + gl]] : -1;
-    const double v0 = in0 ? v[s + gl] : 0.0;
-    int o = rpp[i];
-    int cur = a0 >= 0 ? a0 : INT32_MAX;
-    for (int k = s + gl + L; k < e; k += L) {
-      const int a = agg[ci[k]];
-      if (a >= 0 && a < cur) cur = a;
+    int a[U];
+    double x[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = s + u * L + gl;
+      a[u] = k < e ? ci[k] : -1;
+      x[u] = k < e ? v[k] : 0.0;
     }
-    cur = grp_min<L>(cur);
+#pragma unroll
+    for (int u = 0; u < U; ++u) a[u] = a[u] >= 0 ? agg[a[u]] : -1;
+    int o = rpp[i];
+    int cur = -1;
     // one pass per aggregate met: its entries summed in column order, and
-    // the next larger aggregate
-    while (cur != INT32_MAX) {
-      const bool hit0 = a0 == cur;
-      double sum = grp_ordered_add<L>(0.0, hit0 ? v0 : 0.0, hit0);
-      int next = a0 > cur ? a0 : INT32_MAX;
-      for (int b = s + L; b < e; b += L) {
+    // the next larger aggregate (the first pass looks for the smallest only)
+    for (;;) {
+      double sum = 0.0;
+      int next = INT32_MAX;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const bool hit = cur >= 0 && a[u] == cur;
+        sum = grp_ordered_add<L>(sum, hit ? x[u] : 0.0, hit);
+        next = a[u] > cur && a[u] < next ? a[u] : next;
+      }
+      for (int b = s + L * U; b < e; b += L) {
         const int k = b + gl;
-        const int a = k < e ? agg[ci[k]] : -1;
-        const bool hit = a == cur;
+        const int ak = k < e ? agg[ci[k]] : -1;
+        const bool hit = cur >= 0 && ak == cur;
         sum = grp_ordered_add<L>(sum, hit ? v[k] : 0.0, hit);
-        if (a > cur && a < next) next = a;
+        if (ak > cur && ak < next) next = ak;
       }
       next = grp_min<L>(next);
-      if (gl == 0) {
-        const double tent = ai == cur ? 1.0 : 0.0;
-        cip[o] = cur;
-        vp[o] = tent - q * sum;
+      if (cur >= 0) {
+        if (gl == 0) {
+          const double tent = ai == cur ? 1.0 : 0.0;
+          cip[o] = cur;
+          vp[o] = tent - q * sum;
+        }
+        ++o;
       }
-      ++o;
+      if (next == INT32_MAX) break;
       cur = next;
     }
   }
 }
 void psmooth_count(const DCsr& af, const int* agg, int* cnt, hipStream_t s) {
-  const int L = row_lanes(af.n, af.nnz);
+  const int L = scan_lanes(af.n, af.nnz);
   LAUNCH_ROW_GROUPS(k_psmooth_count, L, af.n, s, af.n, af.rp, af.ci, agg, cnt);
 }
 void psmooth_fill(const DCsr& af, const int* agg, const double* dabs, double omega, const int* rp_p, int* ci_p,
                   double* v_p, hipStream_t s) {
-  const int L = row_lanes(af.n, af.nnz);
+  const int L = scan_lanes(af.n, af.nnz);
   LAUNCH_ROW_GROUPS(k_psmooth_fill, L, af.n, s, af.n, af.rp, af.ci, af.v, agg, dabs, omega, rp_p, ci_p, v_p);
 }
 
@@ -2556,19 +2658,25 @@ __global__ __launch_bounds__(BLK) void k_row_stats(int n, const int* __restrict_
     if (x) atomicMax(&part[threadIdx.x], x);
   }
 }
-void row_stats(DCsr& a, hipStream_t s) {
-  a.maxlen = 0;
-  for (int q = 0; q < kRowBlocks; ++q) a.blkmax[q] = 0;
-  if (a.n <= 0) return;
-  constexpr int S = 1 + kRowBlocks;
-  Tmp<int> part(S);
-  int h[S];
-  HBGS_HIP(hipMemsetAsync(part.p, 0, sizeof(h), s));
-  k_row_stats<<<grid_for(((int64_t)a.n + 3) / 4, BLK, 256), BLK, 0, s>>>(a.n, a.rp, part.p);
-  HBGS_HIP(hipGetLastError());
-  read_back(h, part.p, sizeof(h), s);
+constexpr int STATS = 1 + kRowBlocks;  // k_row_stats' results
+static void set_stats(DCsr& a, const int* h) {
   a.maxlen = h[0];
   for (int q = 0; q < kRowBlocks; ++q) a.blkmax[q] = h[1 + q];
+}
+static void launch_row_stats(const DCsr& a, int* part, hipStream_t s) {
+  if (a.n <= 0) return;
+  k_row_stats<<<grid_for(((int64_t)a.n + 3) / 4, BLK, 256), BLK, 0, s>>>(a.n, a.rp, part);
+  HBGS_HIP(hipGetLastError());
+}
+void row_stats(DCsr& a, hipStream_t s) {
+  int h[STATS] = {};
+  if (a.n > 0) {
+    Tmp<int> part(STATS);
+    HBGS_HIP(hipMemsetAsync(part.p, 0, sizeof(h), s));
+    launch_row_stats(a, part.p, s);
+    read_back(h, part.p, sizeof(h), s);
+  }
+  set_stats(a, h);
 }
 
 // Operand tiles of one row block per workgroup: the tile ids (col /
@@ -2640,33 +2748,44 @@ __global__ __launch_bounds__(256) void k_tiles(int n, int rb, const int* __restr
     lc[k] = (uint16_t)(lo * TILE_W + col % TILE_W);
   }
 }
-void build_tiles(Pool& pool, DCsr& a, int rb, hipStream_t s) {
-  a.tile_rb = 0;
-  a.tile_cnt = 0;
-  a.tiles = nullptr;
-  a.lc = nullptr;
-  if (a.n <= 0 || a.nnz <= 0 || rb <= 0) return;
-  int q = 0;
-  while (q < kRowBlocks && row_block(q) != rb) ++q;
-  if (q == kRowBlocks || a.blkmax[q] > TILE_ENTRIES) return;
-  const int64_t nblk = ((int64_t)a.n + rb - 1) / rb;
-  int* tiles = pool.make<int>((size_t)nblk * TILE_MAX);
-  uint16_t* lc = pool.make<uint16_t>(a.nnz);
-  Tmp<int> flags(2);
-  HBGS_HIP(hipMemsetAsync(flags.p, 0, 2 * sizeof(int), s));
-  k_tiles<<<(unsigned)nblk, 256, 0, s>>>(a.n, rb, a.rp, a.ci, tiles, lc, flags.p, flags.p + 1);
-  HBGS_HIP(hipGetLastError());
-  int h[2] = {0, 0};
-  read_back(h, flags.p, sizeof(h), s);
-  if (h[0] || h[1] <= 0) {
-    pool.release(lc);
-    pool.release(tiles);
-    return;
+void build_tiles(Pool& pool, DCsr* const* a, const int* rb, int count, hipStream_t s) {
+  Tmp<int> flags(2 * (size_t)count);
+  bool any = false;
+  for (int k = 0; k < count; ++k) {
+    DCsr& m = *a[k];
+    m.tile_rb = 0;
+    m.tile_cnt = 0;
+    m.tiles = nullptr;
+    m.lc = nullptr;
+    if (m.n <= 0 || m.nnz <= 0 || rb[k] <= 0) continue;
+    int q = 0;
+    while (q < kRowBlocks && row_block(q) != rb[k]) ++q;
+    if (q == kRowBlocks || m.blkmax[q] > TILE_ENTRIES) continue;
+    if (!any) HBGS_HIP(hipMemsetAsync(flags.p, 0, 2 * (size_t)count * sizeof(int), s));
+    any = true;
+    const int64_t nblk = ((int64_t)m.n + rb[k] - 1) / rb[k];
+    m.tiles = pool.make<int>((size_t)nblk * TILE_MAX);
+    m.lc = pool.make<uint16_t>(m.nnz);
+    k_tiles<<<(unsigned)nblk, 256, 0, s>>>(m.n, rb[k], m.rp, m.ci, m.tiles, m.lc, flags.p + 2 * k,
+                                           flags.p + 2 * k + 1);
+    HBGS_HIP(hipGetLastError());
   }
-  a.tile_rb = rb;
-  a.tile_cnt = h[1];
-  a.tiles = tiles;
-  a.lc = lc;
+  if (!any) return;
+  std::vector<int> h(2 * (size_t)count);
+  read_back(h.data(), flags.p, h.size() * sizeof(int), s);
+  for (int k = 0; k < count; ++k) {
+    DCsr& m = *a[k];
+    if (!m.tiles) continue;
+    if (h[2 * k] || h[2 * k + 1] <= 0) {
+      pool.release(m.lc);
+      pool.release(m.tiles);
+      m.lc = nullptr;
+      m.tiles = nullptr;
+      continue;
+    }
+    m.tile_rb = rb[k];
+    m.tile_cnt = h[2 * k + 1];
+  }
 }
 
 // --------------------------------------------------------- diagonal slices
@@ -3053,26 +3172,46 @@ __global__ __launch_bounds__(256) void k_col_pack(int64_t nnz, const int* __rest
     }
   }
 }
-void pack_columns(Pool& pool, DCsr& a, hipStream_t s) {
+// a's packed columns, whose validity *bad tells (zeroed by the caller)
+static void launch_pack(Pool& pool, DCsr& a, int* bad, hipStream_t s) {
   a.cd = nullptr;
   a.cb = nullptr;
   if (a.nnz == 0) return;
   const int64_t nch = (a.nnz + COL_CHUNK - 1) / COL_CHUNK;
-  const unsigned g = grid_for((nch + 3) / 4, 1);
-  int* cb = pool.make<int>(nch);
+  a.cb = pool.make<int>(nch);
+  a.cd = pool.make<uint16_t>(a.nnz);
+  k_col_base<<<grid_for((nch + 3) / 4, 1, 8192), 256, 0, s>>>(a.nnz, a.ci, a.cb, bad);
+  HBGS_HIP(hipGetLastError());
+  k_col_pack<<<grid_for((nch + 3) / 4, 1), 256, 0, s>>>(a.nnz, a.ci, a.cb, a.cd);
+  HBGS_HIP(hipGetLastError());
+}
+static void drop_packed(Pool& pool, DCsr& a) {
+  pool.release(a.cd);
+  pool.release(a.cb);
+  a.cd = nullptr;
+  a.cb = nullptr;
+}
+void pack_columns(Pool& pool, DCsr& a, hipStream_t s) {
   Tmp<int> bad(1);
   HBGS_HIP(hipMemsetAsync(bad.p, 0, sizeof(int), s));
-  k_col_base<<<grid_for((nch + 3) / 4, 1, 8192), 256, 0, s>>>(a.nnz, a.ci, cb, bad.p);
-  HBGS_HIP(hipGetLastError());
-  if (read_one(bad.p, s)) {
-    pool.release(cb);
-    return;
+  launch_pack(pool, a, bad.p, s);
+  if (a.cd && read_one(bad.p, s)) drop_packed(pool, a);
+}
+void stats_and_columns(Pool& pool, DCsr* const* a, int count, hipStream_t s) {
+  if (count <= 0) return;
+  constexpr int W = STATS + 1;
+  Tmp<int> part(W * (size_t)count);
+  HBGS_HIP(hipMemsetAsync(part.p, 0, W * (size_t)count * sizeof(int), s));
+  for (int k = 0; k < count; ++k) {
+    launch_row_stats(*a[k], part.p + W * k, s);
+    launch_pack(pool, *a[k], part.p + W * k + STATS, s);
   }
-  uint16_t* cd = pool.make<uint16_t>(a.nnz);
-  k_col_pack<<<g, 256, 0, s>>>(a.nnz, a.ci, cb, cd);
-  HBGS_HIP(hipGetLastError());
-  a.cd = cd;
-  a.cb = cb;
+  std::vector<int> h(W * (size_t)count);
+  read_back(h.data(), part.p, h.size() * sizeof(int), s);
+  for (int k = 0; k < count; ++k) {
+    set_stats(*a[k], &h[W * k]);
+    if (h[W * k + STATS] && a[k]->cd) drop_packed(pool, *a[k]);
+  }
 }
 
 __global__ void k_dense_transpose(int n, const double* __restrict__ in, double* __restrict__ out) {
