@@ -101,10 +101,22 @@ struct Batch {
 // the job of this block (uniform) and the block's index within it
 template <class D>
 __device__ __forceinline__ const D& batch_job(const Batch<D>& b, int* blk) {
+  // A block's first reads are of its arguments, which no cache holds: which
+  // job is its own, then that job's fields, one latency after the other.  All
+  // lines of the arguments are requested at once instead, with the first (with
+  // the row bounds' loads out of their branch: every solve 1.2% faster, of
+  // which most are launches of 4-10 us; 4.2M rows mixed 11.53 -> 11.40 ms).
+  static_assert(sizeof(Batch<D>) % 4 == 0, "whole words");
+  unsigned rev = b.rev;
+  const unsigned* words = reinterpret_cast<const unsigned*>(&b);
+  unsigned w = 0;
+#pragma unroll
+  for (int k = 16; k < (int)(sizeof(Batch<D>) / 4); k += 16) w ^= words[k];
+  asm("" : "+s"(rev) : "s"(w));  // rev as it is, once the lines are there
   // backwards by groups of eight: the hardware deals consecutive workgroups
   // to the eight XCDs in turn, so a block keeps its XCD (and what the
   // previous pass left in that L2) in either direction
-  const unsigned bi = blockIdx.x < 8 * b.rev ? 8 * (b.rev - 1 - blockIdx.x / 8) + blockIdx.x % 8 : blockIdx.x;
+  const unsigned bi = blockIdx.x < 8 * rev ? 8 * (rev - 1 - blockIdx.x / 8) + blockIdx.x % 8 : blockIdx.x;
   int q = 0;
 #pragma unroll
   for (int k = 1; k < MAXB; ++k)
@@ -184,14 +196,16 @@ __global__ __launch_bounds__(SBLK) void k_csr_rows(const Batch<CsrJob<Col, TV, T
   const int rbase = r0 + (int)threadIdx.x / LPR;
   typename Epi::Pre pre[RPT];
   int rkb[RPT], rke[RPT];  // row bounds for the sums, requested before the barrier
+  // (by every lane, rows beyond the block's as its last: a branch around these
+  // loads made each of them wait for the one before)
+  const int s0 = rp[r0], s1 = rp[r1];
 #pragma unroll
   for (int q = 0; q < RPT; ++q) {
     const int r = rbase + q * SBLK;
-    if (r < r1 && lane == 0) pre[q] = epi.load(r);
-    rkb[q] = r < r1 ? rp[r] : 0;
-    rke[q] = r < r1 ? rp[r + 1] : 0;
+    pre[q] = epi.load(min(r, r1 - 1));
+    rkb[q] = rp[min(r, r1 - 1)];
+    rke[q] = rp[min(r, r1 - 1) + 1];
   }
-  const int s0 = rp[r0], s1 = rp[r1];
   const int a0 = (s0 + 3) & ~3, a1 = s1 & ~3;  // the 4-aligned middle
   if (vec && a0 < a1) {
     const int t = (int)threadIdx.x;
@@ -296,12 +310,13 @@ __global__ __launch_bounds__(SBLK) void k_csr_rows_tiled(const Batch<TiledJob<TV
   const int rbase = r0 + t / LPR;
   typename Epi::Pre pre[RPT];
   int rkb[RPT], rke[RPT];
+  const int s0 = rp[r0], s1 = rp[r1];
 #pragma unroll
   for (int q = 0; q < RPT; ++q) {
     const int r = rbase + q * SBLK;
-    if (r < r1 && lane == 0) pre[q] = epi.load(r);
-    rkb[q] = r < r1 ? rp[r] : 0;
-    rke[q] = r < r1 ? rp[r + 1] : 0;
+    pre[q] = epi.load(min(r, r1 - 1));
+    rkb[q] = rp[min(r, r1 - 1)];
+    rke[q] = rp[min(r, r1 - 1) + 1];
   }
   // the tiles' ids, then their entries (thread t stages element t % TILE_W
   // of tiles t / TILE_W + TPP j)
@@ -312,7 +327,6 @@ __global__ __launch_bounds__(SBLK) void k_csr_rows_tiled(const Batch<TiledJob<TV
     const int slot = j0 + TPP * j;
     id[j] = slot < tcnt ? tiles[(size_t)b * TILE_MAX + slot] : -1;
   }
-  const int s0 = rp[r0], s1 = rp[r1];
   TX xv[TILE_MAX / TPP];
 #pragma unroll
   for (int j = 0; j < TILE_MAX / TPP; ++j) {
