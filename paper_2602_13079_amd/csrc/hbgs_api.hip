@@ -400,6 +400,16 @@ struct Krylov {
   ~Krylov() {
     if (host) (void)hipHostFree(host);
   }
+  // what one preconditioner application needs: its input and its result (the
+  // first column of Z once a solve has made that).  The basis of a solve is
+  // 50 to 100 times as much, and allocating it was most of a first application
+  float* af = nullptr;
+  double* ad = nullptr;
+  void ensure_apply(Pool& pool, int n_, int precision) {
+    if (!bp) bp = pool.make<double>(n_);
+    if (precision == 1 && !Zf && !af) af = pool.make<float>(n_);
+    if (precision == 0 && !Zd && !ad) ad = pool.make<double>(n_);
+  }
   void ensure(Pool& pool, int n_, int m_, int precision) {
     if (V) {
       if (precision == 1 && !Zf) Zf = pool.make<float>((size_t)m * ld);
@@ -418,7 +428,7 @@ struct Krylov {
       Zf = pool.make<float>((size_t)m * ld);
     else
       Zd = pool.make<double>((size_t)m * ld);
-    bp = pool.make<double>(n);
+    if (!bp) bp = pool.make<double>(n);
     xp = pool.make<double>(n);
     r = pool.make<double>(n);
     part = pool.make<double>((size_t)(m + 2) * solve::dot_blocks(n));
@@ -2074,16 +2084,27 @@ hbgs_status hbgs_apply(hbgs_ctx* c, const double* r, double* z, int32_t transpos
   }
   HBGS_API_BEGIN
   hipStream_t s = (hipStream_t)stream;
-  ensure_workspace(c);
+  const int tr = transpose ? 1 : 0;
+  Krylov& K = c->K;
+  if (c->o.nested)  // inner solves
+    ensure_workspace(c);
+  else
+    K.ensure_apply(c->pool, c->n, c->precision);
   if (transpose) ensure_transpose(c, s);
   rows_for_tests(c, s);
-  Krylov& K = c->K;
   solve::permute_in(c->n, c->perm, r, K.bp, s);
-  apply_perm(c, transpose ? 1 : 0, K.bp, 0, nullptr, s);
-  if (c->precision == 1)  // the FP32 result, widened as it is permuted back
-    solve::permute_out_f32(c->n, c->perm, K.Zf, z, s);
+  float* zf = K.Zf ? K.Zf : K.af;
+  double* zd = K.Zd ? K.Zd : K.ad;
+  if (c->o.nested)
+    nested_apply(c, tr, K.bp, 0, nullptr, s);
+  else if (c->precision == 1)
+    sweep<float>(c, c->plan[tr], tr, K.bp, zf, 0, nullptr, s);
   else
-    solve::permute_out(c->n, c->perm, K.Zd, z, s);
+    sweep<double>(c, c->plan[tr], tr, K.bp, zd, 0, nullptr, s);
+  if (c->precision == 1)  // the FP32 result, widened as it is permuted back
+    solve::permute_out_f32(c->n, c->perm, zf, z, s);
+  else
+    solve::permute_out(c->n, c->perm, zd, z, s);
   HBGS_HIP(hipStreamSynchronize(s));
   return HBGS_OK;
   HBGS_API_END
