@@ -2001,8 +2001,8 @@ __global__ void k_lu_update(int n, int k, double* m) {
   }
 }
 // Inverse of up to GJ_MAXN rows: in-place Gauss-Jordan elimination with
-// partial pivoting (the first row of maximal |a_ik| as pivot) by panels of
-// NB columns, one launch per panel.  With K a panel's rows and columns,
+// partial pivoting (the first row whose |a_ik| is maximal to 2^-20) by panels
+// of NB columns, one launch per panel.  With K a panel's rows and columns,
 // after its row interchanges, and B the K rows (the identity in the K
 // columns), a step is
 //   A <- A' + M B,   A' = A with the K rows and columns zeroed,
