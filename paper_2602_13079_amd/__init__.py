@@ -125,10 +125,21 @@ def _check(code):
     return code
 
 
-def _values_key(val):
-    """Identity of a value tensor's current contents: storage address and
-    in-place version counter."""
-    return (val.data_ptr(), getattr(val, "_version", 0), val.numel())
+class _Values:
+    """The contents that a value tensor has now: its place in storage and its
+    in-place version counter.  The storage is held: freed, its address could
+    come back with other values at the same version."""
+
+    def __init__(self, val):
+        self._held = val.detach()
+        self._key = self._key_of(val)
+
+    @staticmethod
+    def _key_of(val):
+        return val.data_ptr(), getattr(val, "_version", 0), val.numel(), val.stride(), val.dtype
+
+    def are(self, val):
+        return self._key == self._key_of(val)
 
 
 def _stream(torch):
@@ -204,7 +215,7 @@ class Solver:
         import torch
         self._torch = torch
         self.lib = load()
-        values_key = _values_key(val)
+        values = _Values(val)
         rowptr = _dev(rowptr, torch.int32, torch)
         col = _dev(col, torch.int32, torch)
         val = _dev(val, torch.float64, torch)
@@ -219,7 +230,7 @@ class Solver:
                                    val.data_ptr(), n_fields, field_of_row.data_ptr(), len(tree), tr,
                                    ctypes.byref(self.opts), _stream(torch)))
         self.h = h
-        self._values_key = values_key
+        self._values = values
 
     def __del__(self):
         if getattr(self, "h", None) and self.h.value:
@@ -235,10 +246,11 @@ class Solver:
 
     def set_values(self, val, rebuild=True):
         """New values on the same pattern; rebuild=False keeps the preconditioner."""
-        key = _values_key(val)
+        values = _Values(val)
         val = _dev(val, self._torch.float64, self._torch)
+        self._values = None  # after a failure: none that are known
         _check(self.lib.hbgs_set_values(self.h, val.data_ptr(), int(rebuild), _stream(self._torch)))
-        self._values_key = key
+        self._values = values
 
     def apply(self, r, transpose=False):
         torch = self._torch
@@ -364,7 +376,7 @@ def _autograd_function():
 
         @staticmethod
         def forward(ctx, val, b, solver):
-            if _values_key(val) != solver._values_key:  # new values: rebuild the preconditioner
+            if solver._values is None or not solver._values.are(val):  # new values: rebuild the preconditioner
                 solver.set_values(val)
             x, st, it, _ = solver.solve(b)
             if st != 0:
