@@ -160,7 +160,10 @@ hbgs_status hbgs_setup(hbgs_ctx **out, int32_t n, int64_t nnz, const int32_t *ro
  * rebuild_hierarchy != 0 rebuilds the whole preconditioner from the new
  * values; 0 replaces only the operator GMRES iterates with (and its
  * transpose) and keeps the current preconditioner, which then acts as a
- * preconditioner for the new matrix (e.g. for small perturbations). */
+ * preconditioner for the new matrix (e.g. for small perturbations).
+ * After a rebuild that failed (e.g. HBGS_ESINGULAR) the context has no
+ * preconditioner: until a rebuild succeeds, applies, solves, hierarchy
+ * queries and updates without a rebuild return HBGS_ESETUP. */
 hbgs_status hbgs_set_values(hbgs_ctx *ctx, const double *val, int32_t rebuild_hierarchy, void *stream);
 
 /* Select the precision mode of later apply/solve calls (0 FP64, 1 mixed). */

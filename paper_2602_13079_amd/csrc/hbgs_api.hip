@@ -484,6 +484,9 @@ struct hbgs_ctx {
   // transposed operators: A_p^T's values follow A_p's (apt_fresh); the
   // hierarchy's transposed parts exist for the current hierarchy (hier_t)
   bool apt_fresh = false, hier_t = false;
+  // the hierarchy, layouts and plans are whole (false while they are built, and
+  // after a build that failed: what it left is not to be read)
+  bool built = false;
   hbgs::DCsr Ap, ApT;
   std::vector<int> leaf_order, f_lo, f_hi;
   std::vector<hbgs::Field> F;
@@ -1117,6 +1120,7 @@ static void build_rest_T(hbgs_ctx* c, hipStream_t s) {
 // aggregation rounds and the factorisation steps, overlap the others').
 static void build_values(hbgs_ctx* c, hipStream_t s) {
   ScratchScope main_scratch(&c->scratch[HBGS_MAX_FIELDS]);
+  c->built = false;
   c->hier_t = false;
   c->clear_graphs();
   c->hier.clear();
@@ -1211,6 +1215,10 @@ static void build_values(hbgs_ctx* c, hipStream_t s) {
   if (c->o.build_transpose) build_rest_T(c, s);
   HBGS_HIP(hipStreamSynchronize(s));
   compute_stats(c);
+  c->built = true;
+}
+static void require_built(const hbgs_ctx* c) {
+  if (!c->built) HBGS_FAIL(HBGS_ESETUP, "no preconditioner: the last value update failed");
 }
 
 // --------------------------------------------------------------- V-cycle
@@ -2042,6 +2050,7 @@ hbgs_status hbgs_set_values(hbgs_ctx* c, const double* val, int32_t rebuild_hier
   HBGS_API_BEGIN
   hipStream_t s = (hipStream_t)stream;
   auto t0 = std::chrono::steady_clock::now();
+  if (!rebuild_hierarchy) require_built(c);
   // a kept hierarchy keeps its adjoint consistent with it: its transposed
   // parts are built from the old values before they change
   if (!rebuild_hierarchy && !c->hier_t) ensure_transpose(c, s);
@@ -2083,6 +2092,7 @@ hbgs_status hbgs_apply(hbgs_ctx* c, const double* r, double* z, int32_t transpos
     return HBGS_EINVAL;
   }
   HBGS_API_BEGIN
+  require_built(c);
   hipStream_t s = (hipStream_t)stream;
   const int tr = transpose ? 1 : 0;
   Krylov& K = c->K;
@@ -2116,6 +2126,7 @@ hbgs_status hbgs_apply_noalloc(hbgs_ctx* c, const double* r, double* z, int32_t 
     return HBGS_EINVAL;
   }
   HBGS_API_BEGIN
+  require_built(c);
   hipStream_t s = (hipStream_t)stream;
   if ((int64_t)c->n > kNoAllocMaxRows)
     HBGS_FAIL(HBGS_EINVAL, "hbgs_apply_noalloc: " + std::to_string(c->n) + " rows exceed the fixed buffer's " +
@@ -2151,6 +2162,7 @@ hbgs_status hbgs_solve(hbgs_ctx* c, const double* b, double* x, int32_t use_x0, 
     return HBGS_EINVAL;
   }
   HBGS_API_BEGIN
+  require_built(c);
   hipStream_t us = (hipStream_t)stream;
   ensure_workspace(c);
   int32_t it = 0, hl = 0;
@@ -2196,12 +2208,14 @@ hbgs_status hbgs_stats(hbgs_ctx* c, hbgs_stats_t* out) {
 
 hbgs_status hbgs_get_level(hbgs_ctx* c, int32_t field, int32_t level, int32_t which, int32_t* n_rows,
                            int32_t* n_cols, int64_t* nnz, int32_t* rowptr, int32_t* col, double* val) {
-  if (!c || field < 0 || field >= c->nf || level < 0 || level >= (int)c->F[field].lv.size() || which < 0 ||
-      which > 3) {
-    set_error("invalid field/level/which");
+  if (!c) {
+    set_error("NULL context");
     return HBGS_EINVAL;
   }
   HBGS_API_BEGIN
+  require_built(c);
+  if (field < 0 || field >= c->nf || level < 0 || level >= (int)c->F[field].lv.size() || which < 0 || which > 3)
+    HBGS_FAIL(HBGS_EINVAL, "invalid field/level/which");
   if (which == 3) ensure_transpose(c, nullptr);
   const Level& L = c->F[field].lv[level];
   bool coarsest = level + 1 == (int)c->F[field].lv.size();
@@ -2226,11 +2240,14 @@ hbgs_status hbgs_get_level(hbgs_ctx* c, int32_t field, int32_t level, int32_t wh
 }
 
 hbgs_status hbgs_get_aggregates(hbgs_ctx* c, int32_t field, int32_t level, int32_t* agg, double* out3) {
-  if (!c || field < 0 || field >= c->nf || level < 0 || level >= (int)c->F[field].lv.size()) {
-    set_error("invalid field/level");
+  if (!c) {
+    set_error("NULL context");
     return HBGS_EINVAL;
   }
   HBGS_API_BEGIN
+  require_built(c);
+  if (field < 0 || field >= c->nf || level < 0 || level >= (int)c->F[field].lv.size())
+    HBGS_FAIL(HBGS_EINVAL, "invalid field/level");
   const Level& L = c->F[field].lv[level];
   if (agg) {
     if (!L.agg) HBGS_FAIL(HBGS_EINVAL, "the coarsest level has no aggregates");
