@@ -2000,35 +2000,45 @@ __global__ void k_lu_update(int n, int k, double* m) {
     m[(int64_t)i * n + j] -= m[(int64_t)i * n + k] * m[(int64_t)k * n + j];
   }
 }
-// Inverse of up to GJ_MAXN rows: in-place Gauss-Jordan elimination with
-// partial pivoting (the first row whose |a_ik| is maximal to 2^-20) by panels
-// of NB columns, one launch per panel.  With K a panel's rows and columns,
-// after its row interchanges, and B the K rows (the identity in the K
-// columns), a step is
-//   A <- A' + M B,   A' = A with the K rows and columns zeroed,
-//   M_K = A_KK^-1,   M_r = -A_rK A_KK^-1 elsewhere,
-// and M is what eliminating the panel's own columns in place leaves in them.
-// Launch k applies step k to the matrix (tiles, from one buffer to another,
-// so the interchanged rows are read where they lie) while its block 0 forms
-// the next panel: it applies step k to those NB columns only, all rows in
-// registers, and eliminates them.  After the last step A holds the inverse
-// of the interchanged matrix.
-// Bound by the serial chain of n pivot searches in one block (a launch of
-// 1,444 rows 50 us, its tiles alone 16).  Against a factorisation followed by
-// two substitutions (three launches per 16 columns, then four per 32 rows):
-// 1,444 rows 7.6 -> 4.7 ms, 512 rows 2.7 -> 1.0, and a 4.2M-row rebuild, with
-// four such inverses side by side, 34.6 -> 31.0 ms.
-constexpr int GJ_T = 512;             // threads; two waves per SIMD leave a thread 256 registers
-constexpr int GJ_R = 4;               // panel rows per thread at most
-constexpr int GJ_MAXN = GJ_T * GJ_R;
-// columns of a panel: 8 for the matrices with four rows per thread, whose 16
-// columns would not stay in registers (2,000 rows: 15 ms, with 8 columns 7.5)
-constexpr int gj_nb(int rows_per_thread) { return rows_per_thread < 4 ? 16 : 8; }
-constexpr int GJ_TR = 64, GJ_TC = 128;  // rows and columns of a tile
-constexpr int GJ_MOVED = 32;          // rows that one panel's interchanges move at most
+// Inverse of up to LU_MAXN rows: LU factorisation with partial pivoting (the
+// first row of maximal |a_ik|), then X = U^-1 (L^-1 P).  Forward, by panels of
+// NB columns, one launch per panel: with K a panel's rows and columns, after
+// its row interchanges, and B the K rows,
+//   K rows      <- L11^-1 B                (substitution),
+//   rows below  <- A - L21 (L11^-1 B)
+// in every column: right of K that is the factorisation, left of K it turns
+// what earlier panels left there into rows of L^-1 (in K itself B is the
+// identity; U11 stays in its upper triangle).  Launch k applies step k to the
+// rows from its panel on (tiles, from one buffer to another, so the
+// interchanged rows are read where they lie) while its block 0 forms the next
+// panel: it applies step k to those NB columns only, the remaining rows in
+// registers, and factors them.  Then each row lies, final, in the buffer its
+// panel's step wrote; k_lu_turn parts U from L^-1, and k_lu_back finishes
+// X block row by block row, one launch each.
+// Every column of X is a forward and a backward substitution, so A X is as
+// near I as the factorisation allows, rows of any scale.  (In-place
+// Gauss-Jordan elimination, which needs no second pass, is not: on 400-row
+// diffusion matrices with rows scaled over 1e4 its ||b - A X b|| is some 500
+// times that of LU, over 1e8 some 1e4 times.)
+// Bound by the serial chain of n pivot searches in one block: a launch takes
+// 29 us with one row per thread, 41 with two and 55 with three, its tiles
+// alone 6-16; the backward pass 14.5 us per 32 rows.  484 / 900 / 1,444 /
+// 1,936 rows 1.2 / 2.4 / 4.6 / 6.9 ms, where three launches per panel of the
+// factorisation, then four per 32 rows of two substitutions, took 2.4 / 4.2 /
+// 7.5 / 10.8 (and Gauss-Jordan 0.9 / 2.2 / 4.7 / 7.2).
+constexpr int LU_T = 512;             // threads; two waves per SIMD leave a thread 256 registers
+constexpr int LU_R = 4;               // panel rows per thread at most
+constexpr int LU_MAXN = LU_T * LU_R;
+// columns of a panel: 8 while a thread holds four rows, whose 16 columns
+// would not stay in registers
+constexpr int lu_nb(int rows_per_thread) { return rows_per_thread < 4 ? 16 : 8; }
+constexpr int LU_NB = 16;             // at most
+constexpr int LU_TR = 64, LU_TC = 128;  // rows and columns of a tile
+constexpr int LU_BACK = 32;           // rows of a block of the backward pass
+constexpr int LU_MOVED = 32;          // rows that one panel's interchanges move at most
 // interchanges of a panel: count, then the rows that change, then where each
 // takes its values from; the panel's own rows come first
-constexpr int GJ_LIST = 1 + 2 * GJ_MOVED;
+constexpr int LU_LIST = 1 + 2 * LU_MOVED;
 
 // Register-only (DPP) maximum within rows of 16 lanes; all 64 lanes must be
 // active.  Every lane of a 16-lane row ends with the row's result: pairs
@@ -2049,66 +2059,96 @@ __device__ __forceinline__ unsigned wave_max(unsigned v) {
   return max(max(readlane_u32(v, 0), readlane_u32(v, 16)), max(readlane_u32(v, 32), readlane_u32(v, 48)));
 }
 
-struct GjStep {
-  int n, ld;   // rows; ld: rows rounded up to GJ_T (R GJ_T)
+struct LuStep {
+  int n, ld;   // rows; ld: at least n + LU_T
   int k0, nb;  // the step's panel (nb = 0: no step, the first launch)
   int p0, pb;  // the panel that block 0 forms (pb = 0: none, and no such block)
   int q0, qb;  // the panel after it: its columns are written to Tn as well
   const double* src;
   double* dst;
-  const double* M;  // the step's M by columns: M[t * ld + r]
+  const double* M;  // the step's panel, factored, by columns: M[t * ld + r], rows from k0 on
   double* Mn;       // the next step's
-  const int* list;  // the interchanges (GJ_LIST)
+  const int* list;  // the interchanges (LU_LIST)
   int* listn;
   const double* T;  // columns of panel p0 before the step: T[t * ld + r]
   double* Tn;
   int* orig;  // orig[r]: the original index of the row now at r
   int* singular;
 };
-template <int R, int NB>
-__device__ void gj_panel(const GjStep& g) {
-  constexpr int NW = GJ_T / 64;
+// x / d from dinv = 1 / d (both ordinary numbers), corrected by the remainder:
+// the division's result but for a rare last bit, in 3 dependent operations
+__device__ __forceinline__ double lu_quotient(double x, double d, double dinv) {
+  const double q = x * dinv;
+  return fma(fma(-d, q, x), dinv, q);
+}
+// v <- L11^-1 v for one column; L: L11 (unit lower, the rest not read)
+template <int NB>
+__device__ __forceinline__ void lu_unit_lower(double (&v)[NB], const double (&L)[NB][NB]) {
+#pragma unroll
+  for (int w = 0; w + 1 < NB; ++w)
+#pragma unroll
+    for (int u = w + 1; u < NB; ++u) v[u] = fma(-L[u][w], v[w], v[u]);
+}
+// R rows per thread, from p0 on; NB: columns of the panel; NBS: of the step's
+template <int R, int NB, int NBS>
+__device__ void lu_panel(const LuStep& g) {
+  constexpr int NW = LU_T / 64;
   static_assert(NW <= 16, "the wavefronts' candidates are combined within one 16-lane row");
-  // per column: each wavefront's pivot candidate (key, row, its values) and
-  // row j before the interchange; two sets, used by alternate columns, so one
-  // barrier per column suffices
-  __shared__ uint2 ckey[2][NW];
+  // per column: each wavefront's pivot candidate (magnitude's high and low
+  // word, the row inverted, its values) and row j before the interchange; two
+  // sets, used by alternate columns, so one barrier per column suffices
+  __shared__ uint4 ckey[2][NW];
   __shared__ __align__(16) double crow[2][NW][NB];
   __shared__ __align__(16) double xrow[2][NB];
-  __shared__ __align__(16) double Bp[NB][NB];
-  __shared__ uint16_t at[GJ_T * R];
+  __shared__ double Lp[NBS][NBS];
+  __shared__ __align__(16) double Bp[NBS][NB];
+  __shared__ uint16_t at[LU_T * R];  // where row p0 + i takes its values from
   __shared__ int spiv[NB];
-  constexpr unsigned LD = GJ_T * R;
   const int n = g.n, p0 = g.p0, pb = g.pb;
+  const unsigned LD = (unsigned)g.ld;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   if (tid < NB) spiv[tid] = p0 + tid;  // no interchange unless a pivot is found
   double a[R][NB];
   if (g.nb > 0) {
 #pragma unroll
-    for (int q = 0; q < R; ++q) at[tid + q * GJ_T] = (uint16_t)(tid + q * GJ_T);
-    if (tid < NB * NB) {
-      const int u = tid / NB, t = tid % NB;
-      Bp[u][t] = u < g.nb && t < pb ? g.T[t * LD + g.list[1 + GJ_MOVED + u]] : 0.0;
+    for (int q = 0; q < R; ++q) at[tid + q * LU_T] = (uint16_t)min(p0 + tid + q * LU_T, n - 1);
+    for (int e = tid; e < NBS * NB; e += LU_T) {
+      const int u = e / NB, t = e % NB;
+      Bp[u][t] = u < g.nb && t < pb ? g.T[t * LD + g.list[1 + LU_MOVED + u]] : 0.0;
+    }
+    for (int e = tid; e < NBS * NBS; e += LU_T) {
+      const int u = e / NBS, w = e % NBS;
+      Lp[u][w] = u < g.nb && w < u ? g.M[w * LD + g.k0 + u] : 0.0;
     }
     __syncthreads();
-    if (tid < g.list[0]) at[g.list[1 + tid]] = (uint16_t)g.list[1 + GJ_MOVED + tid];
+    if (tid < g.list[0] && g.list[1 + tid] >= p0) at[g.list[1 + tid] - p0] = (uint16_t)g.list[1 + LU_MOVED + tid];
+    if (tid < NB) {
+      double v[NBS];
+#pragma unroll
+      for (int u = 0; u < NBS; ++u) v[u] = Bp[u][tid];
+      lu_unit_lower<NBS>(v, Lp);
+#pragma unroll
+      for (int u = 0; u < NBS; ++u) Bp[u][tid] = v[u];
+    }
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < R; ++q) {
-      const int r = tid + q * GJ_T;
-      const unsigned from = at[r];
-      const bool old = r < n && !(r >= g.k0 && r < g.k0 + g.nb);
+      const int r = p0 + tid + q * LU_T;
+      const unsigned from = at[tid + q * LU_T];
 #pragma unroll
       for (int t = 0; t < NB; ++t) {
         const double x = g.T[t * LD + from];
-        a[q][t] = old && t < pb ? x : 0.0;
+        a[q][t] = r < n && t < pb ? x : 0.0;
       }
     }
 #pragma unroll 4
-    for (int u = 0; u < NB; ++u) {
+    for (int u = 0; u < NBS; ++u) {
       double m[R];
 #pragma unroll
-      for (int q = 0; q < R; ++q) m[q] = g.M[u * LD + q * GJ_T + (unsigned)tid];
+      for (int q = 0; q < R; ++q) {
+        const int r = p0 + tid + q * LU_T;
+        m[q] = r < n ? -g.M[u * LD + (unsigned)r] : 0.0;
+      }
 #pragma unroll
       for (int t = 0; t < NB; ++t) {
         const double b = Bp[u][t];
@@ -2121,90 +2161,110 @@ __device__ void gj_panel(const GjStep& g) {
     for (int q = 0; q < R; ++q)
 #pragma unroll
       for (int t = 0; t < NB; ++t) {
-        const double x = g.T[t * LD + q * GJ_T + (unsigned)tid];
-        a[q][t] = tid + q * GJ_T < n && t < pb ? x : 0.0;
+        const int r = p0 + tid + q * LU_T;
+        const double x = g.T[t * LD + (unsigned)r];
+        a[q][t] = r < n && t < pb ? x : 0.0;
       }
   }
   // The columns rotate through the registers: the current one is always the
-  // first and leaves as the last, so the loop stays rolled.
+  // first and leaves as the last, so the loop stays rolled, but for a copy of
+  // its body per four columns: columns that left before them only move on.
+  // i = r - p0.
+#pragma unroll
+  for (int j0 = 0; j0 < NB; j0 += 4) {
 #pragma unroll 1
-  for (int j = 0; j < pb; ++j) {
-    const int b = j & 1, jr = p0 + j;
-    // this wavefront's candidate among its rows r >= jr: the first of the
-    // largest key, a value's key being the high half of its magnitude, which
-    // orders magnitudes to 2^-20 (0: none, and never NaN)
-    unsigned key[R], most = 0;
+    for (int j = j0; j < min(j0 + 4, pb); ++j) {
+      const int b = j & 1;
+      // this wavefront's candidate among its rows i >= j: the first of the
+      // largest magnitude, by the bits of |a_rj| (0: none, and never NaN).
+      // One lane mostly has the largest high word, and the rest is its own
+      uint64_t top = 0;
+      int tq = 0;
 #pragma unroll
-    for (int q = 0; q < R; ++q) {
-      const unsigned hi = (unsigned)(__double_as_longlong(a[q][0]) >> 32) & 0x7fffffffu;
-      key[q] = tid + q * GJ_T >= jr && hi < 0x7ff00000u ? hi : 0;
-      most = max(most, key[q]);
-    }
-    most = wave_max(most);
-    int bq = 0;
-    uint64_t at_most = 0;
-#pragma unroll
-    for (int q = R; q-- > 0;) {
-      const uint64_t m = __ballot(key[q] == most);
-      if (m) {
-        at_most = m;
-        bq = q;
+      for (int q = 0; q < R; ++q) {
+        uint64_t mag = (uint64_t)__double_as_longlong(a[q][0]) & 0x7fffffffffffffffull;
+        mag = tid + q * LU_T >= j && mag <= 0x7ff0000000000000ull ? mag : 0;
+        if (q > 0 && mag > top) tq = q;
+        top = mag > top ? mag : top;
       }
-    }
-    const int bl = __builtin_ctzll(at_most);  // some lane holds the largest key
-    const int bi = bq * GJ_T + wave * 64 + bl;
-    if (lane == 0) ckey[b][wave] = make_uint2(most, (unsigned)bi);
+      unsigned hi = wave_max((unsigned)(top >> 32)), lo;
+      uint64_t tie = __ballot((unsigned)(top >> 32) == hi);
+      int bq, bl = __builtin_ctzll(tie);
+      if ((tie & (tie - 1)) == 0) {
+        lo = readlane_u32((unsigned)top, bl);
+        bq = (int)readlane_u32((unsigned)tq, bl);
+      } else {
+        lo = wave_max((unsigned)(top >> 32) == hi ? (unsigned)top : 0u);
+        tie = __ballot(top == ((uint64_t)hi << 32 | lo));
+        bq = 0;
 #pragma unroll
-    for (int q = 0; q < R; ++q) {
-      if (q == bq && lane == bl)
+        for (int q = R; q-- > 0;) {
+          const uint64_t m = __ballot(tq == q) & tie;
+          if (m) {
+            bl = __builtin_ctzll(m);
+            bq = q;
+          }
+        }
+      }
+      if (lane == 0) ckey[b][wave] = make_uint4(hi, lo, ~(unsigned)(bq * LU_T + wave * 64 + bl), 0);
 #pragma unroll
-        for (int t = 0; t < NB; ++t) crow[b][wave][t] = a[q][t];
-      if (tid + q * GJ_T == jr)
+      for (int q = 0; q < R; ++q) {
+        if (q == bq && lane == bl)
 #pragma unroll
-        for (int t = 0; t < NB; ++t) xrow[b][t] = a[q][t];
-    }
-    __syncthreads();
-    // lanes 0..NW-1 of every wavefront hold the wavefronts' candidates
-    const uint2 cand = lane < NW ? ckey[b][lane] : make_uint2(0, 0);
-    most = readlane_u32(max_row16(cand.x), 0);
-    if (most == 0) {  // uniform: the matrix is singular
-      if (tid == 0) *g.singular = 1;
-      break;
-    }
-    const int pw = __builtin_ctzll(__ballot(cand.x == most));
-    const int p = (int)readlane_u32(cand.y, pw);
-    const double* prow = crow[b][pw];  // the pivot row (LDS)
-    if (tid == 0) spiv[j] = p;
-    const double inv = 1.0 / prow[0];
-    double sc[NB];  // the pivot row scaled; the inverse's entry takes the column
+          for (int t = 0; t < NB; ++t) crow[b][wave][t] = a[q][t];
+        if (tid + q * LU_T == j)
 #pragma unroll
-    for (int t = 1; t < NB; ++t) sc[t - 1] = prow[t] * inv;
-    sc[NB - 1] = inv;
+          for (int t = 0; t < NB; ++t) xrow[b][t] = a[q][t];
+      }
+      __syncthreads();
+      // lanes 0..NW-1 of every wavefront hold the wavefronts' candidates: the
+      // largest magnitude, then the first row
+      const uint4 cand = lane < NW ? ckey[b][lane] : make_uint4(0, 0, 0, 0);
+      hi = readlane_u32(max_row16(cand.x), 0);
+      uint64_t best = __ballot(lane < NW && cand.x == hi);
+      int pw = __builtin_ctzll(best);
+      if (best & (best - 1)) {
+        lo = readlane_u32(max_row16(cand.x == hi ? cand.y : 0u), 0);
+        const unsigned first = readlane_u32(max_row16(cand.x == hi && cand.y == lo ? cand.z : 0u), 0);
+        pw = __builtin_ctzll(__ballot(lane < NW && cand.x == hi && cand.z == first));
+        if ((hi | lo) == 0 && tid == 0) *g.singular = 1;  // (what follows is not used)
+      }
+      const int p = (int)~readlane_u32(cand.z, pw);
+      const double* prow = crow[b][pw];  // the pivot row (LDS)
+      if (tid == 0) spiv[j] = p0 + p;
+      // row j is final: column t of the rotated panel is column t + j of it
+      if (tid < NB) g.Mn[(unsigned)((tid + j) % NB) * LD + (unsigned)(p0 + j)] = prow[tid];
+      const double d = prow[0];
+      double pv[NB - 1];  // of the columns still to come
 #pragma unroll
-    for (int q = 0; q < R; ++q) {
-      const int r = tid + q * GJ_T;
-      if (r == p)  // the interchange
+      for (int t = 0; t + 1 < NB - j0; ++t) {
+        const double x = prow[t + 1];
+        pv[t] = t + 1 < NB - j0 - 3 || t + 1 < NB - j ? x : 0.0;
+      }
 #pragma unroll
-        for (int t = 0; t < NB; ++t) a[q][t] = xrow[b][t];
-      const double f = -a[q][0];
+      for (int q = 0; q < R; ++q) {  // (rows up to j are done with: their registers hold anything)
+        if (tid + q * LU_T == p)  // the interchange
 #pragma unroll
-      for (int t = 0; t < NB; ++t) a[q][t] = fma(f, sc[t], t + 1 < NB ? a[q][t + 1 < NB ? t + 1 : 0] : 0.0);
-      if (r == jr)
+          for (int t = 0; t < NB; ++t) a[q][t] = xrow[b][t];
+        const double l = a[q][0] / d;
 #pragma unroll
-        for (int t = 0; t < NB; ++t) a[q][t] = sc[t];
+        for (int t = 0; t + 1 < NB; ++t) a[q][t] = t + 1 < NB - j0 ? fma(-l, pv[t], a[q][t + 1]) : a[q][t + 1];
+        a[q][NB - 1] = l;
+      }
     }
   }
 #pragma unroll
-  for (int q = 0; q < R; ++q)  // rows beyond n as well: zero, and no pivots
+  for (int q = 0; q < R; ++q)
+    if (tid + q * LU_T >= pb)
 #pragma unroll
-    for (int t = 0; t < NB; ++t) g.Mn[(t + pb) % NB * LD + q * GJ_T + (unsigned)tid] = a[q][t];
+      for (int t = 0; t < NB; ++t) g.Mn[(unsigned)((t + pb) % NB) * LD + (unsigned)(p0 + tid + q * LU_T)] = a[q][t];
   __syncthreads();
-  // The interchanges, applied in order, move values among at most GJ_MOVED
+  // The interchanges, applied in order, move values among at most LU_MOVED
   // rows: wavefront 0 works out where each of them takes its value from, in
   // registers (all 64 lanes active): lane e holds slot e's (row, source),
   // the panel rows first, then each other row as it is met; a row's slot is
   // found by a ballot and two slots' sources are swapped through lane reads.
-  static_assert(2 * NB <= GJ_MOVED && GJ_MOVED <= 64, "one slot per lane");
+  static_assert(2 * NB <= LU_MOVED && LU_MOVED <= 64, "one slot per lane");
   if (tid < 64) {
     const int e = tid;
     const int mp = e < pb ? spiv[e < NB ? e : 0] : 0;
@@ -2216,7 +2276,7 @@ __device__ void gj_panel(const GjStep& g) {
         const unsigned long long hit = __ballot(d == p);  // at most one slot holds row p
         int q;
         if (hit) {
-          q = __ffsll(hit) - 1;
+          q = __builtin_ctzll(hit);
         } else {
           q = cnt++;
           if (e == q) d = sr = p;
@@ -2226,9 +2286,9 @@ __device__ void gj_panel(const GjStep& g) {
         if (e == q) sr = st;
       }
     }
-    if (e < GJ_MOVED) {
+    if (e < LU_MOVED) {
       g.listn[1 + e] = d;
-      g.listn[1 + GJ_MOVED + e] = e < cnt ? sr : 0;
+      g.listn[1 + LU_MOVED + e] = e < cnt ? sr : 0;
     }
     if (e == 0) g.listn[0] = cnt;
     const int o = e < cnt ? g.orig[sr] : 0;  // all read before any is written
@@ -2237,88 +2297,131 @@ __device__ void gj_panel(const GjStep& g) {
     if (e < cnt) g.orig[d] = o;
   }
 }
-// Memory-bound: a tile reads and writes its entries once; eight rows and two
-// columns per thread keep the LDS reads of M (broadcast) and B below the
-// multiply-adds.
+// A tile's update on the matrix cores: wavefront w takes 16 rows and 64
+// columns of it, four 16 x 16 blocks whose entries a lane holds in column
+// l % 16 and rows l / 16 + 4 v.  (On the vector units, eight rows and two
+// columns per thread, reading sM and sB from LDS, a backward launch took 18.7
+// us instead of 14.5.)  The substitution is repeated by every tile of a column
+// range (an eighth of its multiply-adds).
+typedef double lu_acc __attribute__((ext_vector_type(4)));
+constexpr int LU_PADM = LU_TR + 16, LU_PADB = LU_TC + 16;  // rows of 4 k's on different banks
+static_assert(LU_TR == 64 && LU_TC == 128 && LU_T == 512, "eight wavefronts of 16 x 64 entries");
+struct LuLane {
+  int row, col, k;  // of its first entry in the tile; l / 16
+  __device__ __forceinline__ LuLane() {
+    const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
+    k = l / 16;
+    row = w % 4 * 16 + k;
+    col = w / 4 * 64 + l % 16;
+  }
+};
+// z -= sM^T sB for the wavefront's entries
 template <int NB>
-__device__ void gj_tile(const GjStep& g, int tile) {
-  __shared__ __align__(16) double sM[NB][GJ_TR];
-  __shared__ double sB[NB][GJ_TC];
-  __shared__ int srow[GJ_TR];
-  constexpr int RT = GJ_TR / (GJ_T / 64), CT = GJ_TC / 64;  // rows and columns per thread
-  const int n = g.n, k0 = g.k0, nb = g.nb;
-  const int tcols = (n + GJ_TC - 1) / GJ_TC;
-  const int r0 = tile / tcols * GJ_TR, c0 = tile % tcols * GJ_TC;
-  const int tid = threadIdx.x, ib = tid / 64 * RT;
-  if (tid < GJ_TR) {
+__device__ __forceinline__ void lu_tile_update(lu_acc (&z)[4], const double (&sM)[NB][LU_PADM],
+                                               const double (&sB)[NB][LU_PADB], const LuLane& at) {
+  static_assert(NB % 4 == 0, "four k's per matrix instruction");
+  const int l16 = threadIdx.x & 15;
+  lu_acc y[4] = {};
+#pragma unroll
+  for (int u = 0; u < NB; u += 4) {
+    const double m = sM[u + at.k][at.row - at.k + l16];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      y[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(m, sB[u + at.k][at.col + 16 * q], y[q], 0, 0, 0);
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q) z[q] -= y[q];
+}
+template <int NB>
+__device__ void lu_tile(const LuStep& g, int tile) {
+  __shared__ double sM[NB][LU_PADM];
+  __shared__ double sB[NB][LU_PADB];
+  __shared__ double sL[NB][NB];
+  __shared__ int srow[LU_TR];
+  const int n = g.n, k0 = g.k0, nb = g.nb, p0 = k0 + nb;
+  const int tcols = (n + LU_TC - 1) / LU_TC;
+  const int r0 = k0 + tile / tcols * LU_TR, c0 = tile % tcols * LU_TC;
+  const int tid = threadIdx.x;
+  const LuLane at;
+  if (tid < LU_TR) {
     const int r = r0 + tid, cnt = g.list[0];
-    int from = r;
+    int from = min(r, n - 1);
     for (int e = 0; e < cnt; ++e)
-      if (g.list[1 + e] == r) from = g.list[1 + GJ_MOVED + e];
+      if (g.list[1 + e] == r) from = g.list[1 + LU_MOVED + e];
     srow[tid] = from;
   }
 #pragma unroll
-  for (int e = tid; e < NB * GJ_TR; e += GJ_T) {
-    const int u = e / GJ_TR, i = e % GJ_TR;
-    sM[u][i] = r0 + i < n ? g.M[(size_t)u * g.ld + r0 + i] : 0.0;
+  for (int e = tid; e < NB * LU_TR; e += LU_T) {
+    const int u = e / LU_TR, r = r0 + e % LU_TR;
+    sM[u][e % LU_TR] = u < nb && r >= p0 && r < n ? g.M[(size_t)u * g.ld + r] : 0.0;
   }
 #pragma unroll
-  for (int e = tid; e < NB * GJ_TC; e += GJ_T) {
-    const int u = e / GJ_TC, c = c0 + e % GJ_TC;
-    const bool own = c >= k0 && c < k0 + nb;  // a column of the panel
-    sB[u][e % GJ_TC] = own ? (c - k0 == u ? 1.0 : 0.0)
-                           : u < nb && c < n ? g.src[(size_t)g.list[1 + GJ_MOVED + u] * n + c] : 0.0;
+  for (int e = tid; e < NB * LU_TC; e += LU_T) {
+    const int u = e / LU_TC, c = c0 + e % LU_TC;
+    const bool own = c >= k0 && c < p0;  // a column of the panel
+    sB[u][e % LU_TC] = own ? (c - k0 == u ? 1.0 : 0.0)
+                           : u < nb && c < n ? g.src[(size_t)g.list[1 + LU_MOVED + u] * n + c] : 0.0;
+  }
+  if (tid < NB * NB) {
+    const int u = tid / NB, w = tid % NB;
+    sL[u][w] = u < nb && w < nb ? g.M[(size_t)w * g.ld + k0 + u] : 0.0;
+  }
+  static_assert(NB * NB <= LU_T && LU_TC <= LU_T, "one pass each");
+  __syncthreads();
+  lu_acc z[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int c = c0 + at.col + 16 * q;
+    const bool col = c < n && !(c >= k0 && c < p0);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int i = at.row + 4 * v, r = r0 + i;
+      const double x = g.src[(size_t)srow[i] * n + min(c, n - 1)];
+      z[q][v] = col && r >= p0 && r < n ? x : 0.0;
+    }
+  }
+  if (tid < LU_TC) {
+    double v[NB];
+#pragma unroll
+    for (int u = 0; u < NB; ++u) v[u] = sB[u][tid];
+    lu_unit_lower<NB>(v, sL);
+#pragma unroll
+    for (int u = 0; u < NB; ++u) sB[u][tid] = v[u];
   }
   __syncthreads();
-  double x[RT][CT], y[RT][CT];
+  lu_tile_update(z, sM, sB, at);
 #pragma unroll
-  for (int w = 0; w < CT; ++w) {
-    const int c = c0 + 64 * w + (tid & 63);
-    const bool col = c < n && !(c >= k0 && c < k0 + nb);
-#pragma unroll
-    for (int i = 0; i < RT; ++i) {
-      const int r = r0 + ib + i;
-      const bool old = col && r < n && !(r >= k0 && r < k0 + nb);
-      x[i][w] = old ? g.src[(size_t)srow[ib + i] * n + c] : 0.0;
-      y[i][w] = 0.0;
-    }
-  }
-#pragma unroll 2
-  for (int u = 0; u < NB; ++u) {
-#pragma unroll
-    for (int i = 0; i < RT; ++i)
-#pragma unroll
-      for (int w = 0; w < CT; ++w) y[i][w] = fma(sM[u][ib + i], sB[u][64 * w + (tid & 63)], y[i][w]);
-  }
-#pragma unroll
-  for (int w = 0; w < CT; ++w) {
-    const int c = c0 + 64 * w + (tid & 63);
+  for (int q = 0; q < 4; ++q) {
+    const int cl = at.col + 16 * q, c = c0 + cl;
     if (c >= n) continue;
-    const bool ahead = c >= g.q0 && c < g.q0 + g.qb;
+    const bool own = c >= k0 && c < p0, ahead = c >= g.q0 && c < g.q0 + g.qb;
 #pragma unroll
-    for (int i = 0; i < RT; ++i) {
-      const int r = r0 + ib + i;
+    for (int v = 0; v < 4; ++v) {
+      const int r = r0 + at.row + 4 * v;
       if (r >= n) break;
-      const double z = x[i][w] + y[i][w];
-      g.dst[(size_t)r * n + c] = z;
-      if (ahead) g.Tn[(size_t)(c - g.q0) * g.ld + r] = z;
+      double x = z[q][v];
+      if (r < p0)  // a row of the panel, final; in its own columns U11 above L11^-1
+        x = own && c >= r ? sL[r - k0][c - k0] : sB[r - k0][cl];
+      g.dst[(size_t)r * n + c] = x;
+      if (ahead) g.Tn[(size_t)(c - g.q0) * g.ld + r] = x;
     }
   }
 }
-template <int R, int NB>
-__global__ __launch_bounds__(GJ_T) void k_gj_step(const GjStep g) {
+template <int R, int NB, int NBS>
+__global__ __launch_bounds__(LU_T) void k_lu_step(const LuStep g) {
   const int panel = g.pb > 0;
   if (panel && blockIdx.x == 0)
-    gj_panel<R, NB>(g);
+    lu_panel<R, NB, NBS>(g);
   else
-    gj_tile<NB>(g, (int)blockIdx.x - panel);
+    lu_tile<NBS>(g, (int)blockIdx.x - panel);
 }
-// the dense matrix, one block per row; the first two panels by columns
-__global__ __launch_bounds__(BLK) void k_gj_fill(int n, int ld, int nb, const int* __restrict__ rp, const int* __restrict__ ci,
-                                                 const double* __restrict__ v, double* __restrict__ m,
-                                                 double* __restrict__ t0, double* __restrict__ t1,
-                                                 int* __restrict__ orig) {
-  __shared__ double row[GJ_MAXN];
+// the dense matrix, one block per row; the first two panels (nb0, nb1
+// columns) by columns
+__global__ __launch_bounds__(BLK) void k_lu_fill(int n, int ld, int nb0, int nb1, const int* __restrict__ rp,
+                                                 const int* __restrict__ ci, const double* __restrict__ v,
+                                                 double* __restrict__ m, double* __restrict__ t0,
+                                                 double* __restrict__ t1, int* __restrict__ orig) {
+  __shared__ double row[LU_MAXN];
   const int i = blockIdx.x;
   for (int j = threadIdx.x; j < n; j += BLK) row[j] = 0.0;
   __syncthreads();
@@ -2326,63 +2429,197 @@ __global__ __launch_bounds__(BLK) void k_gj_fill(int n, int ld, int nb, const in
   __syncthreads();
   for (int j = threadIdx.x; j < n; j += BLK) {
     m[(size_t)i * n + j] = row[j];
-    if (j < nb)
+    if (j < nb0)
       t0[(size_t)j * ld + i] = row[j];
-    else if (j < 2 * nb)
-      t1[(size_t)(j - nb) * ld + i] = row[j];
+    else if (j < nb0 + nb1)
+      t1[(size_t)(j - nb0) * ld + i] = row[j];
   }
   if (threadIdx.x == 0) orig[i] = i;
 }
+// Between the passes, one block per row: the row's final form (in buffer a or
+// b: panels of 8 columns up to row e8, of 16 after it, alternate) parts into
+// L^-1 (to y) and U (to u; y and u are a and b in some order), U's diagonal
+// blocks of LU_BACK rows to diag
+__global__ __launch_bounds__(BLK) void k_lu_turn(int n, int e8, const double* a, const double* b, double* y, double* u,
+                                                 double* __restrict__ diag) {
+  __shared__ double row[LU_MAXN];
+  const int r = blockIdx.x;
+  const int k = r < e8 ? r / 8 : e8 / 8 + (r - e8) / 16;
+  const double* f = (k & 1 ? a : b) + (size_t)r * n;  // step k wrote buffer (k + 1) % 2
+  for (int c = threadIdx.x; c < n; c += BLK) row[c] = f[c];
+  __syncthreads();
+  for (int c = threadIdx.x; c < n; c += BLK) {
+    y[(size_t)r * n + c] = c < r ? row[c] : c == r ? 1.0 : 0.0;
+    u[(size_t)r * n + c] = row[c];
+  }
+  const int b0 = r / LU_BACK * LU_BACK;
+  for (int w = threadIdx.x; w < LU_BACK; w += BLK) diag[(size_t)r * LU_BACK + w] = b0 + w >= r && b0 + w < n ? row[b0 + w] : 0.0;
+}
+// The backward pass at rows k0 .. k0+nb: X_K = U_KK^-1 Y_K by substitution (in
+// every tile), Y_r -= U_rK X_K for the rows above; X_K replaces U's rows K,
+// whose part right of K the launches before this have used
+// rows o .. o + LU_BACK/2 of one column of sB against the upper triangle of sD
+// (by columns) there
+__device__ __forceinline__ void lu_upper_half(double (&sB)[LU_BACK][LU_PADB], const double (&sD)[LU_BACK][LU_BACK],
+                                              const double (&sInv)[LU_BACK], int o, int c) {
+  constexpr int H = LU_BACK / 2;
+  double v[H];
+#pragma unroll
+  for (int t = 0; t < H; ++t) v[t] = sB[o + t][c];
+#pragma unroll
+  for (int w = H; w-- > 0;) {
+    v[w] = lu_quotient(v[w], sD[o + w][o + w], sInv[o + w]);
+#pragma unroll
+    for (int t = 0; t < w; ++t) v[t] = fma(-sD[o + w][o + t], v[w], v[t]);
+  }
+#pragma unroll
+  for (int t = 0; t < H; ++t) sB[o + t][c] = v[t];
+}
+__global__ __launch_bounds__(LU_T) void k_lu_back(int n, int k0, int nb, const double* __restrict__ diag, double* u,
+                                                  double* y) {
+  __shared__ double sM[LU_BACK][LU_PADM];
+  __shared__ double sB[LU_BACK][LU_PADB];
+  __shared__ __align__(16) double sD[LU_BACK][LU_BACK];  // by columns
+  __shared__ double sInv[LU_BACK];
+  constexpr int H = LU_BACK / 2;
+  const int tcols = (n + LU_TC - 1) / LU_TC;
+  const int r0 = (int)blockIdx.x / tcols * LU_TR, c0 = (int)blockIdx.x % tcols * LU_TC;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const LuLane at;
+#pragma unroll
+  for (int e = tid; e < LU_BACK * LU_TC; e += LU_T) {
+    const int t = e / LU_TC, c = c0 + e % LU_TC;
+    sB[t][e % LU_TC] = t < nb && c < n ? y[(size_t)(k0 + t) * n + c] : 0.0;
+  }
+#pragma unroll
+  for (int e = tid; e < LU_BACK * LU_BACK; e += LU_T) {
+    const int t = e / LU_BACK, w = e % LU_BACK;
+    const double d = t < nb && w < nb ? diag[(size_t)(k0 + t) * LU_BACK + w] : t == w ? 1.0 : 0.0;
+    sD[w][t] = d;
+    if (t == w) sInv[w] = 1.0 / d;
+  }
+#pragma unroll
+  for (int e = tid; e < LU_BACK * LU_TR; e += LU_T) {
+    const int r = r0 + e / LU_BACK, t = e % LU_BACK;
+    sM[t][e / LU_BACK] = t < nb && r < k0 ? u[(size_t)r * n + k0 + t] : 0.0;
+  }
+  __syncthreads();
+  lu_acc z[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+#pragma unroll
+    for (int v = 0; v < 4; ++v)  // (entries outside are not stored)
+      z[q][v] = y[(size_t)min(r0 + at.row + 4 * v, n - 1) * n + min(c0 + at.col + 16 * q, n - 1)];
+  // U_KK^-1: quotients by way of 1 / d unless a d is near the ends of the
+  // range; half of the rows at a time, in registers
+  const double dd = fabs(sD[lane % LU_BACK][lane % LU_BACK]);
+  if (__all(dd > 1e-290 && dd < 1e290)) {
+    if (tid < LU_TC) lu_upper_half(sB, sD, sInv, H, tid);
+    __syncthreads();
+    for (int e = tid; e < H * LU_TC; e += LU_T) {
+      const int t = e / LU_TC, c = e % LU_TC;
+      double x = sB[t][c];
+#pragma unroll
+      for (int w = H; w < LU_BACK; ++w) x = fma(-sD[w][t], sB[w][c], x);
+      sB[t][c] = x;
+    }
+    __syncthreads();
+    if (tid < LU_TC) lu_upper_half(sB, sD, sInv, 0, tid);
+  } else if (tid < LU_TC) {
+    for (int w = LU_BACK; w-- > 0;) {
+      const double x = sB[w][tid] = sB[w][tid] / sD[w][w];
+      for (int t = 0; t < w; ++t) sB[t][tid] = fma(-sD[w][t], x, sB[t][tid]);
+    }
+  }
+  __syncthreads();
+  if (r0 == 0)
+    for (int e = tid; e < nb * LU_TC; e += LU_T) {
+      const int c = c0 + e % LU_TC;
+      if (c < n) u[(size_t)(k0 + e / LU_TC) * n + c] = sB[e / LU_TC][e % LU_TC];
+    }
+  if (k0 == 0) return;
+  lu_tile_update(z, sM, sB, at);
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int r = r0 + at.row + 4 * v, c = c0 + at.col + 16 * q;
+      if (r < k0 && c < n) y[(size_t)r * n + c] = z[q][v];
+    }
+}
 // x is the inverse of the interchanged matrix: its columns go back in order
-__global__ __launch_bounds__(BLK) void k_gj_finish(int n, const double* __restrict__ x, const int* __restrict__ orig,
+__global__ __launch_bounds__(BLK) void k_lu_finish(int n, const double* __restrict__ x, const int* __restrict__ orig,
                                                    double* __restrict__ inv) {
   const int64_t i = blockIdx.x;
   for (int c = threadIdx.x; c < n; c += BLK) inv[i * n + orig[c]] = x[i * n + c];
 }
-static int gauss_jordan(const DCsr& a, double* inv, hipStream_t s) {
-  const int n = a.n, per = (n + GJ_T - 1) / GJ_T, ld = per * GJ_T, NB = gj_nb(per), panels = (n + NB - 1) / NB;
-  Tmp<double> work((size_t)n * n), m((size_t)2 * NB * ld), t((size_t)2 * NB * ld);
-  Tmp<int> list(2 * GJ_LIST), orig(n), sing(1);
-  // the last step writes work, from which the columns go to inv
-  double* x[2] = {panels & 1 ? inv : work.p, panels & 1 ? work.p : inv};
-  auto at = [&](Tmp<double>& w, int q) { return w.p + (size_t)(q & 1) * NB * ld; };
+static int lu_inverse(const DCsr& a, double* inv, hipStream_t s) {
+  const int n = a.n, ld = n + LU_T;
+  struct Panel {
+    int k0, nb, per;  // per: rows per thread when it is formed
+  };
+  std::vector<Panel> panels;
+  int e8 = 0;  // columns in panels of 8
+  for (int k0 = 0; k0 < n;) {
+    const int per = (n - k0 + LU_T - 1) / LU_T, nb = std::min(lu_nb(per), n - k0);
+    panels.push_back({k0, nb, per});
+    k0 += nb;
+    if (per == LU_R) e8 = k0;
+  }
+  const int np = (int)panels.size();
+  Tmp<double> work((size_t)n * n), m((size_t)2 * LU_NB * ld), t((size_t)2 * LU_NB * ld), diag((size_t)n * LU_BACK);
+  Tmp<int> list(2 * LU_LIST), orig(n), sing(1);
+  double* x[2] = {inv, work.p};
+  auto at = [&](Tmp<double>& w, int q) { return w.p + (size_t)(q & 1) * LU_NB * ld; };
   HBGS_HIP(hipMemsetAsync(sing.p, 0, sizeof(int), s));
-  k_gj_fill<<<n, BLK, 0, s>>>(n, ld, NB, a.rp, a.ci, a.v, x[0], at(t, 0), at(t, 1), orig.p);
-  const int tiles = ((n + GJ_TR - 1) / GJ_TR) * ((n + GJ_TC - 1) / GJ_TC);
-  for (int k = -1; k < panels; ++k) {
-    auto width = [&](int q) { return q < panels ? std::min(NB, n - q * NB) : 0; };
-    GjStep g{};
+  k_lu_fill<<<n, BLK, 0, s>>>(n, ld, panels[0].nb, np > 1 ? panels[1].nb : 0, a.rp, a.ci, a.v, x[0], at(t, 0), at(t, 1),
+                              orig.p);
+  const int tcols = (n + LU_TC - 1) / LU_TC;
+  for (int k = -1; k < np; ++k) {
+    const Panel none{n, 0, 1};
+    const Panel step = k < 0 ? Panel{0, 0, panels[0].per} : panels[k];
+    const Panel next = k + 1 < np ? panels[k + 1] : none, after = k + 2 < np ? panels[k + 2] : none;
+    LuStep g{};
     g.n = n;
     g.ld = ld;
-    g.k0 = k * NB;
-    g.nb = k < 0 ? 0 : width(k);
-    g.p0 = (k + 1) * NB;
-    g.pb = width(k + 1);
-    g.q0 = (k + 2) * NB;
-    g.qb = width(k + 2);
+    g.k0 = step.k0;
+    g.nb = step.nb;
+    g.p0 = next.k0;
+    g.pb = next.nb;
+    g.q0 = after.k0;
+    g.qb = after.nb;
     g.src = x[k & 1];
     g.dst = x[(k + 1) & 1];
     g.M = at(m, k);
     g.Mn = at(m, k + 1);
-    g.list = list.p + (k & 1) * GJ_LIST;
-    g.listn = list.p + ((k + 1) & 1) * GJ_LIST;
+    g.list = list.p + (k & 1) * LU_LIST;
+    g.listn = list.p + ((k + 1) & 1) * LU_LIST;
     g.T = at(t, k + 1);
     g.Tn = at(t, k);
     g.orig = orig.p;
     g.singular = sing.p;
-    const unsigned grid = (unsigned)((k < 0 ? 0 : tiles) + (g.pb > 0));
-    switch (per) {
-      case 1: k_gj_step<1, gj_nb(1)><<<grid, GJ_T, 0, s>>>(g); break;
-      case 2: k_gj_step<2, gj_nb(2)><<<grid, GJ_T, 0, s>>>(g); break;
-      case 3: k_gj_step<3, gj_nb(3)><<<grid, GJ_T, 0, s>>>(g); break;
-      default: k_gj_step<4, gj_nb(4)><<<grid, GJ_T, 0, s>>>(g); break;
+    const int tiles = k < 0 ? 0 : (n - step.k0 + LU_TR - 1) / LU_TR * tcols;
+    const unsigned grid = (unsigned)(tiles + (g.pb > 0));
+    switch (next.per) {
+      case 4: k_lu_step<4, lu_nb(4), lu_nb(4)><<<grid, LU_T, 0, s>>>(g); break;
+      case 3:
+        if (step.per == 4)
+          k_lu_step<3, lu_nb(3), lu_nb(4)><<<grid, LU_T, 0, s>>>(g);
+        else
+          k_lu_step<3, lu_nb(3), lu_nb(3)><<<grid, LU_T, 0, s>>>(g);
+        break;
+      case 2: k_lu_step<2, lu_nb(2), lu_nb(2)><<<grid, LU_T, 0, s>>>(g); break;
+      default: k_lu_step<1, lu_nb(1), lu_nb(1)><<<grid, LU_T, 0, s>>>(g); break;
     }
     HBGS_HIP(hipGetLastError());
   }
-  if (read_one(sing.p, s)) return -4;
-  k_gj_finish<<<n, BLK, 0, s>>>(n, x[panels & 1], orig.p, inv);
+  k_lu_turn<<<n, BLK, 0, s>>>(n, e8, x[0], x[1], inv, work.p, diag.p);
+  for (int k0 = (n - 1) / LU_BACK * LU_BACK; k0 >= 0; k0 -= LU_BACK)
+    k_lu_back<<<(unsigned)(std::max(1, (k0 + LU_TR - 1) / LU_TR) * tcols), LU_T, 0, s>>>(
+        n, k0, std::min(LU_BACK, n - k0), diag.p, work.p, inv);
+  k_lu_finish<<<n, BLK, 0, s>>>(n, work.p, orig.p, inv);
   HBGS_HIP(hipGetLastError());
-  return 0;
+  return read_one(sing.p, s) ? -4 : 0;
 }
 
 // Explicit inverse from the factors, X = U^-1 (L^-1 P), by blocks of
@@ -2469,7 +2706,7 @@ __global__ __launch_bounds__(BLK) void k_inv_update(int n, int kb, int nb, int r
 
 int dense_inverse(const DCsr& a, double* inv, hipStream_t s) {
   const int n = a.n;
-  if (n <= GJ_MAXN) return gauss_jordan(a, inv, s);
+  if (n <= LU_MAXN) return lu_inverse(a, inv, s);
   Tmp<double> m((size_t)n * n);
   Tmp<int> piv(n), sing(1), pinv(n);
   HBGS_HIP(hipMemsetAsync(sing.p, 0, sizeof(int), s));
