@@ -444,39 +444,41 @@ __global__ __launch_bounds__(BLK) void k_sort_rows_wave(int n, const int* rp, in
   constexpr int E = SORT_WAVE / 64;  // entries per lane
   __shared__ __align__(16) int sc[BLK / 64][SORT_WAVE];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int64_t i = (int64_t)blockIdx.x * (BLK / 64) + wave;
-  if (i >= n) return;
-  const int s = rp[i], len = rp[i + 1] - s;
-  if (len < 2) return;
-  if (len > SORT_WAVE) {
-    if (lane == 0) long_rows[atomicAdd(n_long, 1)] = (int)i;
-    return;
-  }
-  int c[E];
-  double x[E];
+  for (int64_t i = (int64_t)blockIdx.x * (BLK / 64) + wave; i < n; i += (int64_t)gridDim.x * (BLK / 64)) {
+    const int s = rp[i], len = rp[i + 1] - s;
+    if (len < 2) continue;
+    if (len > SORT_WAVE) {
+      if (lane == 0) long_rows[atomicAdd(n_long, 1)] = (int)i;
+      continue;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // the previous row's columns have been read
+    __builtin_amdgcn_wave_barrier();
+    int c[E];
+    double x[E];
 #pragma unroll
-  for (int q = 0; q < E; ++q) {
-    const int k = lane + 64 * q;
-    c[q] = k < len ? ci[s + k] : INT32_MAX;
-    x[q] = v && k < len ? v[s + k] : 0.0;
-    if (64 * q < len) sc[wave][k] = c[q];
-  }
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  int rank[E] = {};
-  for (int p = 0; p < len; p += 4) {  // beyond len: INT32_MAX, below no column
-    const int4 d = *reinterpret_cast<const int4*>(&sc[wave][p]);
+    for (int q = 0; q < E; ++q) {
+      const int k = lane + 64 * q;
+      c[q] = k < len ? ci[s + k] : INT32_MAX;
+      x[q] = v && k < len ? v[s + k] : 0.0;
+      if (64 * q < len) sc[wave][k] = c[q];
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    int rank[E] = {};
+    for (int p = 0; p < len; p += 4) {  // beyond len: INT32_MAX, below no column
+      const int4 d = *reinterpret_cast<const int4*>(&sc[wave][p]);
+#pragma unroll
+      for (int q = 0; q < E; ++q)
+        if (64 * q < len) rank[q] += (d.x < c[q]) + (d.y < c[q]) + (d.z < c[q]) + (d.w < c[q]);
+    }
 #pragma unroll
     for (int q = 0; q < E; ++q)
-      if (64 * q < len) rank[q] += (d.x < c[q]) + (d.y < c[q]) + (d.z < c[q]) + (d.w < c[q]);
+      if (lane + 64 * q < len) {
+        ci[s + rank[q]] = c[q];
+        if (v) v[s + rank[q]] = x[q];
+      }
   }
-#pragma unroll
-  for (int q = 0; q < E; ++q)
-    if (lane + 64 * q < len) {
-      ci[s + rank[q]] = c[q];
-      if (v) v[s + rank[q]] = x[q];
-    }
 }
 
 // the *count listed rows of up to LONG_LDS entries, one block per row:
@@ -533,7 +535,8 @@ void sort_rows(const DCsr& a, hipStream_t s) {
   if (a.n == 0) return;
   Tmp<int> n_long(1), long_rows(a.n);
   HBGS_HIP(hipMemsetAsync(n_long.p, 0, sizeof(int), s));
-  k_sort_rows_wave<<<(unsigned)(((int64_t)a.n + 3) / 4), BLK, 0, s>>>(a.n, a.rp, a.ci, a.v, n_long.p, long_rows.p);
+  // (a wavefront for every row would pass a launch's 2^32 threads from 2^26 rows on)
+  k_sort_rows_wave<<<grid_for(a.n, BLK / 64, 1 << 22), BLK, 0, s>>>(a.n, a.rp, a.ci, a.v, n_long.p, long_rows.p);
   static_assert(BLK == 256, "four rows per block");
   HBGS_HIP(hipGetLastError());
   k_sort_long_rows<<<grid_for(a.n, 1, 2048), BLK, 0, s>>>(n_long.p, long_rows.p, a.rp, a.ci, a.v);
