@@ -370,9 +370,17 @@ struct FieldPattern {
 // The sweep's stages: a field's step (coupling + V-cycle) only reads the z of
 // the fields its coupling rows reference, so the fields whose couplings are
 // all satisfied by earlier stages form one stage.  A stage's fields advance
-// together in the same launches on one stream.
+// together in the same launches on one stream.  ILU leaves take one workgroup
+// per subdomain and leave the chip to others: where the stage has V-cycles, or
+// the next one can do without their result, they run on a stream of their own,
+// which the first stage that reads them (else the sweep's end) waits for.
+struct SweepStage {
+  std::vector<int> fields;  // in visiting order
+  bool wait = false;        // for the ILU leaves of earlier stages
+  bool beside = false;      // its own ILU leaves run on the other stream
+};
 struct SweepPlan {
-  std::vector<std::vector<int>> stage;  // fields, in visiting order within a stage
+  std::vector<SweepStage> stage;
 };
 
 // one captured GMRES iteration (key: precision, transpose, column j)
@@ -504,7 +512,7 @@ struct hbgs_ctx {
   hbgs::Profiler prof;
   hbgs_stats_t stats{};
   hbgs::SweepPlan plan[2];
-  // ILU leaves run on a stream of their own beside a stage's V-cycles
+  // ILU leaves that run beside others
   hipStream_t side = nullptr;
   hipEvent_t fork = nullptr, side_done = nullptr;
   // concurrent setup: one stream per field
@@ -925,7 +933,26 @@ static void plan_sweep(hbgs_ctx* c, const std::vector<int>& leaves, int tr, Swee
       if ((c->deps[tr][f] >> g & 1u) && at[g] >= 0) k = std::max(k, at[g] + 1);
     at[f] = k;
     if ((int)p.stage.size() <= k) p.stage.resize(k + 1);
-    p.stage[k].push_back(f);
+    p.stage[k].fields.push_back(f);
+  }
+  auto reads = [&](const SweepStage& st) {  // the fields that its couplings read
+    uint32_t m = 0;
+    for (int f : st.fields) m |= c->deps[tr][f];
+    return m;
+  };
+  uint32_t out = 0;  // on the other stream and not waited for
+  for (size_t k = 0; k < p.stage.size(); ++k) {
+    SweepStage& st = p.stage[k];
+    st.wait = (reads(st) & out) != 0;
+    if (st.wait) out = 0;
+    uint32_t ilu = 0;
+    bool amg = false;
+    for (int f : st.fields) {
+      amg |= c->F[f].leaf == 0;
+      if (c->F[f].leaf == 2) ilu |= 1u << f;
+    }
+    st.beside = ilu && (amg || (k + 1 < p.stage.size() && !(reads(p.stage[k + 1]) & ilu)));
+    if (st.beside) out |= ilu;
   }
   if (!c->side) HBGS_HIP(hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking));
   if (!c->fork) HBGS_HIP(hipEventCreateWithFlags(&c->fork, hipEventDisableTiming));
@@ -1436,10 +1463,14 @@ static void sweep(hbgs_ctx* c, const SweepPlan& plan, int tr, const double* v, T
   const int TS = (int)sizeof(T);
   double plan_bytes = 0;
   for (auto& st : plan.stage)
-    for (int f : st) plan_bytes += c->F[f].bytes[TS == 4 ? 1 : 0];
+    for (int f : st.fields) plan_bytes += c->F[f].bytes[TS == 4 ? 1 : 0];
   Prof whole(c->prof, s, solve::K_SWEEP, plan_bytes);
-  bool rev = true;
+  bool rev = true, away = false;
   for (auto& st : plan.stage) {
+    if (st.wait) {
+      HBGS_HIP(hipStreamWaitEvent(s, c->side_done, 0));
+      away = false;
+    }
     // right-hand sides; the finest level's first Chebyshev direction is
     // formed with its rhs, a Jacobi leaf's z = D^-1 t likewise
     solve::RhsJob<T> cpl[HBGS_MAX_FIELDS], cast[HBGS_MAX_FIELDS];
@@ -1447,7 +1478,7 @@ static void sweep(hbgs_ctx* c, const SweepPlan& plan, int tr, const double* v, T
     solve::IluJob<T> ilu[HBGS_MAX_FIELDS];
     int nc = 0, nk = 0, na = 0, ni = 0;
     double cpl_bytes = 0, cast_bytes = 0, ilu_bytes = 0;
-    for (int f : st) {
+    for (int f : st.fields) {
       Field& F = c->F[f];
       const DCsr& a = tr ? F.upperT : F.lower;
       const int off = F.lo - base;
@@ -1494,12 +1525,9 @@ static void sweep(hbgs_ctx* c, const SweepPlan& plan, int tr, const double* v, T
       Prof p(c->prof, s, solve::K_COUPLE, cast_bytes);
       VcOps<T>::cast_in(cast, nk, vs, rev = !rev, s);
     }
-    // ILU sweeps take one workgroup per subdomain: they leave room for the
-    // stage's V-cycles beside them
-    const bool beside = ni > 0 && na > 0;
     if (ni) {
-      hipStream_t si = beside ? c->side : s;
-      if (beside) {
+      hipStream_t si = st.beside ? c->side : s;
+      if (st.beside) {
         HBGS_HIP(hipEventRecord(c->fork, s));
         HBGS_HIP(hipStreamWaitEvent(si, c->fork, 0));
       }
@@ -1507,15 +1535,18 @@ static void sweep(hbgs_ctx* c, const SweepPlan& plan, int tr, const double* v, T
         Prof p(c->prof, si, solve::K_COARSE, ilu_bytes);
         VcOps<T>::ilu(ilu, ni, tr, si);
       }
-      if (beside) HBGS_HIP(hipEventRecord(c->side_done, si));
+      if (st.beside) {
+        HBGS_HIP(hipEventRecord(c->side_done, si));
+        away = true;
+      }
     }
     if (na) {
       solve::DenseJob<T> dense[HBGS_MAX_FIELDS];
       int nd = 0;
       vcycle<T>(c, amg, na, 0, tr, dense, &nd, rev, s);
     }
-    if (beside) HBGS_HIP(hipStreamWaitEvent(s, c->side_done, 0));
   }
+  if (away) HBGS_HIP(hipStreamWaitEvent(s, c->side_done, 0));
 }
 
 // Test knob off (set_tiles): the row-block kernels read values in row order,
