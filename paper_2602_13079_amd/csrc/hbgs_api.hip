@@ -763,6 +763,7 @@ static void build_hierarchy(hbgs_ctx* c, Field& F, hipStream_t s) {
         clk.to(2);
         DCsr af;
         af.n = af.m = n;
+        af.maxlen = A.maxlen;
         Tmp<int> cnt(n), afrp(n + 1);
         setup::filter_count(A, strong.p, cnt.p, s);
         af.nnz = setup::counts_to_rowptr(cnt.p, afrp.p, n, s);
@@ -792,7 +793,7 @@ static void build_hierarchy(hbgs_ctx* c, Field& F, hipStream_t s) {
         DCsr AP, Ac;
         Pool tmp_pool{Pool::FromScratch{}};
         setup::spgemm(A, P, AP, tmp_pool, s);
-        setup::spgemm(R, AP, Ac, pool, s);
+        setup::spgemm(R, AP, Ac, pool, s, true);
         // the fused prolongation pays where A P has no more entries than A
         // (coarse levels: about half; the finest level: 10-20% more, where
         // the separate prolongation and residual passes are as fast)

@@ -224,7 +224,7 @@ struct DCsr {
   int* ci = nullptr;
   double* v = nullptr;
   float* vf = nullptr;  // FP32 copy of v (solve phase, mixed precision)
-  int maxlen = 0;  // longest row
+  int maxlen = 0;  // longest row, or a bound on it (setup picks lanes per row by it too)
   // entries of the fullest block of row_block(q) consecutive rows (block b:
   // rows [b RB, min(n, (b + 1) RB))); with maxlen, selects the solve-phase
   // kernel shape
@@ -359,7 +359,8 @@ void psmooth_fill(const DCsr& af, const int* agg, const double* dabs, double ome
                   double* v_p, hipStream_t s);
 
 // C = A B with in-order accumulation; allocates C's arrays from pool
-void spgemm(const DCsr& a, const DCsr& b, DCsr& c, Pool& pool, hipStream_t s);
+// (longest: c.maxlen too)
+void spgemm(const DCsr& a, const DCsr& b, DCsr& c, Pool& pool, hipStream_t s, bool longest = false);
 // kernel path of every product row (tests): 0 by row size, 1 one wavefront
 // per row, 2 numeric rows one block each, 3 global-memory tables
 void set_spgemm_route(int route);

@@ -114,9 +114,16 @@ static int row_lanes(int64_t n, int64_t nnz) {
 // pass over 1M rows of 7 entries, four fields side by side: 130-190 us, one
 // thread per row 36-63; the strengths 172 -> 50, the filtered matrix 459 ->
 // 141, the prolongator 712 -> 162).
-static int scan_lanes(int64_t n, int64_t nnz) {
-  const int L = row_lanes(n, nnz);
-  return L == 8 ? 1 : L;
+// Where a few rows are long, one thread would hold up the rest (the
+// prolongator walks a row once per aggregate it meets): 262k rows of 5 entries
+// with 20 rows of 29 / 45 / 85 among them, aggregation and prolongator of the
+// whole hierarchy 2.47 / 3.60 / 5.94 ms with one thread, 2.45 / 3.42 / 5.22
+// with eight; with longest rows of 21, 1.90 against 1.91; with none, 1.27
+// against 1.37.
+constexpr int SCAN_LONG = 24;
+static int scan_lanes(const DCsr& a) {
+  const int L = row_lanes(a.n, a.nnz);
+  return L == 8 && a.maxlen <= SCAN_LONG ? 1 : L;
 }
 // entries per lane requested together
 constexpr int row_regs(int L) { return L == 1 ? 8 : 1; }
@@ -680,7 +687,7 @@ __global__ void k_strength(int n, const int* rp, const int* ci, const double* v,
   }
 }
 void strength(const DCsr& a, const double* d, double theta, char* strong, char* excluded, hipStream_t s) {
-  const int L = scan_lanes(a.n, a.nnz);
+  const int L = scan_lanes(a);
   LAUNCH_ROW_GROUPS(k_strength, L, a.n, s, a.n, a.rp, a.ci, a.v, d, theta * theta, strong, excluded);
 }
 
@@ -790,7 +797,7 @@ void mis2_init(int n, const char* excluded, char* state, hipStream_t s) {
 
 void mis2_round(const DCsr& a, const char* strong, uint64_t salt, char* state, uint64_t* m1, char* r1,
                 bool first, int* undecided, hipStream_t s) {
-  const int L = scan_lanes(a.n, a.nnz);
+  const int L = scan_lanes(a);
   LAUNCH_ROW_GROUPS(k_mis2_max1, L, a.n, s, a.n, a.rp, a.ci, strong, salt, state, m1, first, undecided);
   LAUNCH_ROW_GROUPS(k_mis2_max2, L, a.n, s, a.n, a.rp, a.ci, strong, salt, m1, state);
   LAUNCH_ROW_GROUPS(k_mis2_near1, L, a.n, s, a.n, a.rp, a.ci, strong, state, m1, r1, first);
@@ -861,7 +868,7 @@ __global__ void k_agg_phase3(int n, const int* single_flag, const int64_t* singl
 void agg_phase12(const DCsr& a, const char* strong, uint64_t salt, const char* state, const int64_t* root_rank,
                  int* agg, int* single_flag, hipStream_t s) {
   Tmp<int> p1(a.n);
-  const int L = scan_lanes(a.n, a.nnz);
+  const int L = scan_lanes(a);
   LAUNCH_ROW_GROUPS(k_agg_phase1, L, a.n, s, a.n, a.rp, a.ci, strong, state, root_rank, p1.p);
   LAUNCH_ROW_GROUPS(k_agg_phase2, L, a.n, s, a.n, a.rp, a.ci, strong, salt, state, p1.p, agg, single_flag);
 }
@@ -954,12 +961,12 @@ __global__ void k_filter_fill(int n, const int* rp, const int* ci, const double*
   }
 }
 void filter_count(const DCsr& a, const char* strong, int* cnt, hipStream_t s) {
-  const int L = scan_lanes(a.n, a.nnz);
+  const int L = scan_lanes(a);
   LAUNCH_ROW_GROUPS(k_filter_count, L, a.n, s, a.n, a.rp, a.ci, strong, cnt);
 }
 void filter_fill(const DCsr& a, const char* strong, const int* rp_f, int* ci_f, double* v_f, double* dabs,
                  hipStream_t s) {
-  const int L = scan_lanes(a.n, a.nnz);
+  const int L = scan_lanes(a);
   LAUNCH_ROW_GROUPS(k_filter_fill, L, a.n, s, a.n, a.rp, a.ci, a.v, strong, rp_f, ci_f, v_f, dabs);
 }
 
@@ -1258,12 +1265,12 @@ __global__ void k_psmooth_fill(int n, const int* rp, const int* ci, const double
   }
 }
 void psmooth_count(const DCsr& af, const int* agg, int* cnt, hipStream_t s) {
-  const int L = scan_lanes(af.n, af.nnz);
+  const int L = scan_lanes(af);
   LAUNCH_ROW_GROUPS(k_psmooth_count, L, af.n, s, af.n, af.rp, af.ci, agg, cnt);
 }
 void psmooth_fill(const DCsr& af, const int* agg, const double* dabs, double omega, const int* rp_p, int* ci_p,
                   double* v_p, hipStream_t s) {
-  const int L = scan_lanes(af.n, af.nnz);
+  const int L = scan_lanes(af);
   LAUNCH_ROW_GROUPS(k_psmooth_fill, L, af.n, s, af.n, af.rp, af.ci, af.v, agg, dabs, omega, rp_p, ci_p, v_p);
 }
 
@@ -1741,11 +1748,13 @@ __global__ void k_spgemm_tsize_sym(int n, int bm, const int64_t* ub, const int* 
 }
 // rows beyond the wave kernels (more than wave_max entries) are listed for
 // the one-block-per-row kernel; rows beyond it (block_max) get a global table
-// (*any: some row does)
+// (*any: some row does).  *longest (where given): the longest row, mostly
+// found by the first blocks, so that the others only look
 __global__ void k_spgemm_tsize_num(int n, const int* crp, int64_t wave_max, int64_t block_max, int64_t* ts,
-                                   int* nmid, int* mid, int* any) {
+                                   int* nmid, int* mid, int* any, int* longest) {
   GRID_STRIDE(i, n) {
     const int64_t cnt = crp[i + 1] - crp[i];
+    if (longest && (int)cnt > *(volatile int*)longest) atomicMax(longest, (int)cnt);
     ts[i] = 0;
     if (cnt <= wave_max) continue;
     if (cnt <= block_max)
@@ -1826,7 +1835,7 @@ static int64_t batch_rows(const std::vector<int64_t>& off, int n, std::vector<in
 static std::atomic<int> g_spgemm_route{0};
 void set_spgemm_route(int route) { g_spgemm_route.store(route); }
 
-void spgemm(const DCsr& a, const DCsr& b, DCsr& c, Pool& pool, hipStream_t s) {
+void spgemm(const DCsr& a, const DCsr& b, DCsr& c, Pool& pool, hipStream_t s, bool longest) {
   const int n = a.n;
   // route: 0 by row size; 1 every row to the one-row-per-wavefront kernels;
   // 2 numeric rows to the one-block-per-row kernel; 3 every row to the
@@ -1836,8 +1845,8 @@ void spgemm(const DCsr& a, const DCsr& b, DCsr& c, Pool& pool, hipStream_t s) {
   c.m = b.m;
   Tmp<int64_t> ub(n), ts(n), toff(n + 1);
   // counters: accumulator overflow, rows with global tables (symbolic,
-  // numeric), wide rows (symbolic, numeric), one-block rows
-  enum { OVF, ANY_SYM, ANY_NUM, WIDE_SYM, WIDE_NUM, MID, NFLAGS };
+  // numeric), wide rows (symbolic, numeric), one-block rows, longest row
+  enum { OVF, ANY_SYM, ANY_NUM, WIDE_SYM, WIDE_NUM, MID, LONGEST, NFLAGS };
   Tmp<int> cnt(n), flags(NFLAGS);
   int* overflow = flags.p + OVF;
   HBGS_HIP(hipMemsetAsync(flags.p, 0, NFLAGS * sizeof(int), s));
@@ -1918,7 +1927,7 @@ void spgemm(const DCsr& a, const DCsr& b, DCsr& c, Pool& pool, hipStream_t s) {
   HBGS_HIP(hipGetLastError());
   Tmp<int> mid(n);
   k_spgemm_tsize_num<<<grid_for(n, BLK), BLK, 0, s>>>(n, c.rp, num_w, num_b, ts.p, flags.p + MID, mid.p,
-                                                      flags.p + ANY_NUM);
+                                                      flags.p + ANY_NUM, longest ? flags.p + LONGEST : nullptr);
   HBGS_HIP(hipGetLastError());
   if (b.m > num_w) {  // a row can have more entries than the wave kernel takes
     k_spgemm_num_block<<<grid_for(n, 1, 1024), BLK, 0, s>>>(flags.p + MID, mid.p, a.rp, a.ci, a.v, b.rp, b.ci, b.v,
@@ -1927,6 +1936,7 @@ void spgemm(const DCsr& a, const DCsr& b, DCsr& c, Pool& pool, hipStream_t s) {
   }
   int h_flags[NFLAGS];
   read_back(h_flags, flags.p, sizeof(h_flags), s);
+  c.maxlen = h_flags[LONGEST];
   if (h_flags[ANY_NUM]) {
     scan_i64(ts.p, toff.p, n, s);
     h_off.resize(n + 1);
