@@ -120,9 +120,11 @@ typedef struct {
   int32_t rows[HBGS_MAX_FIELDS][HBGS_MAX_LEVELS];    /* rows per level */
   int64_t nnz_a[HBGS_MAX_FIELDS][HBGS_MAX_LEVELS];   /* nnz(A_l) per level */
   int64_t nnz_p[HBGS_MAX_FIELDS][HBGS_MAX_LEVELS];   /* nnz(P_l) per level */
-  double vcycle_bytes[2];   /* algorithmic HBM bytes of one preconditioner apply
-                               (all field V-cycles + couplings), [0] FP64, [1] mixed */
-  double spmv_bytes[2];     /* algorithmic bytes of one outer SpMV, [0] FP64 x, [1] FP32 x */
+  double vcycle_bytes[2];   /* algorithmic HBM bytes of one preconditioner apply (all
+                               field V-cycles + couplings: each pass reads and writes its
+                               matrix, in the form it is held in, and its vectors once),
+                               [0] FP64, [1] mixed */
+  double spmv_bytes[2];     /* the same of one outer SpMV, [0] FP64 x, [1] FP32 x */
   double setup_seconds;     /* wall time of the last setup */
   double setup_field_seconds[HBGS_MAX_FIELDS]; /* wall time of each field's block
                                extraction and hierarchy build in the last setup */

@@ -871,9 +871,34 @@ static void build_hierarchy(hbgs_ctx* c, Field& F, hipStream_t s) {
   setup::build_tiles(pool, mats.data(), rb.data(), (int)mats.size(), s);
 }
 
+// Bytes of a product with a: what the kernel that its layout selects reads of
+// the matrix, the operand and the result once, and extra_vec vectors of its rows
 static double spmv_bytes(const DCsr& a, int tv, int tx, int ty, int extra_vec) {
-  return (double)a.nnz * (tv + 4) + 4.0 * (a.n + 1) + (double)a.m * tx + (double)a.n * ty +
-         (double)extra_vec * a.n * tv;
+  return solve::matrix_bytes(a, tv, tx) + (double)a.m * tx + (double)a.n * ty + (double)extra_vec * a.n * tv;
+}
+
+// a field's part of a sweep in precision T (4 or 8 bytes): the bytes that its
+// passes are charged when they are timed one by one
+static double field_bytes(const hbgs_ctx* c, const Field& F, int T) {
+  const double n = F.n();
+  const bool d0 = F.leaf == 0 && smoothed_level(F, 0) && F.lv[0].cc.degree == 2;
+  const int more = F.leaf == 1 || d0 ? 2 : 0;
+  double b = F.lower.nnz ? spmv_bytes(F.lower, T, 0, T, more) + 8.0 * n + (double)std::min<int64_t>(F.lower.nnz, c->n) * T
+                         : (8.0 + T * (1 + more)) * n;
+  if (F.leaf == 2) return b + 2.0 * spmv_bytes(F.ilu.F, T, T, T, 1);
+  if (F.leaf == 1) return b;
+  for (size_t l = 0; l < F.lv.size(); ++l) {
+    const Level& L = F.lv[l];
+    const int deg = L.cc.degree;
+    if (!smoothed_level(F, l)) return b + 8.0 * L.A.n * L.A.n + 2.0 * L.A.n * T;
+    b += deg == 2 ? spmv_bytes(L.A, T, T, T, 2) : 4.0 * T * L.A.n + (deg - 1) * spmv_bytes(L.A, T, T, 3 * T, 2);
+    if (l + 1 == F.lv.size()) return b;  // smoothed coarsest: the polynomial from zero only
+    const bool d0c = smoothed_level(F, l + 1) && F.lv[l + 1].cc.degree == 2;
+    b += spmv_bytes(L.A, T, T, T, 1) + spmv_bytes(L.R, T, T, T, d0c ? 2 : 0);
+    b += L.Q.n ? spmv_bytes(L.Q, T, T, T, 2) : spmv_bytes(L.P, T, T, T, 1) + spmv_bytes(L.A, T, T, 2 * T, 2);
+    b += deg == 1 ? 3.0 * T * L.A.n : (deg - 1) * spmv_bytes(L.A, T, T, T, 3);
+  }
+  return b;
 }
 
 static void compute_stats(hbgs_ctx* c) {
@@ -886,32 +911,7 @@ static void compute_stats(hbgs_ctx* c) {
     double b = 0;
     for (int f : c->leaf_order) {
       Field& F = c->F[f];
-      double fb = 0;
-      if (F.lower.nnz) fb += spmv_bytes(F.lower, T, T, T, 0) + 8.0 * F.n();
-      if (F.leaf == 1) {
-        fb += 3.0 * T * F.n();
-      } else if (F.leaf == 2) {
-        fb += 2.0 * spmv_bytes(F.ilu.F, T, T, T, 1);
-      } else {
-        for (size_t l = 0; l + 1 < F.lv.size(); ++l) {
-          const Level& L = F.lv[l];
-          const DCsr& A = L.A;
-          fb += spmv_bytes(A, T, T, T, 1);          // pre (b, dinv gathered; x written)
-          fb += spmv_bytes(A, T, T, T, 1);          // residual
-          fb += spmv_bytes(L.R, T, T, T, 0);        // restriction
-          fb += spmv_bytes(L.P, T, T, T, 1);        // prolongation (x read+write)
-          fb += spmv_bytes(A, T, T, 2 * T, 2);      // post start
-          fb += spmv_bytes(A, T, T, T, 3);          // post step
-        }
-        const Level& C = F.lv.back();
-        const int nc = C.A.n;
-        if (F.inv)
-          fb += 8.0 * nc * nc + 2.0 * nc * T;
-        else  // smoothed coarsest: the pre-smoothing polynomial only
-          fb += (C.cc.degree - 1) * spmv_bytes(C.A, T, T, T, 3) + 4.0 * T * nc;
-      }
-      F.bytes[p] = fb;
-      b += fb;
+      b += F.bytes[p] = field_bytes(c, F, T);
     }
     st.vcycle_bytes[p] = b;
     st.spmv_bytes[p] = spmv_bytes(c->Ap, 8, T, 8, 0);

@@ -419,6 +419,9 @@ constexpr int ROWS_CAP_F32 = 4096, ROWS_CAP_F64 = 2048;
 // never (tests)
 void set_tiles(bool on);
 bool tiles_on();
+// bytes of the matrix itself that a product with values of tv and an operand of
+// tx bytes reads, in the form that its kernel takes it in
+double matrix_bytes(const DCsr& a, int tv, int tx);
 // kernel classes tracked by the optional profiler
 enum Kind {
   K_SPMV_OUTER = 0,

@@ -486,6 +486,8 @@ int rows_per_block(const DCsr& a, int cap, bool vec) {
   return rb;
 }
 
+static unsigned cdiv(int64_t a, int64_t b) { return (unsigned)((a + b - 1) / b); }
+
 // one job of a CSR launch: the matrix, the operand, the rows' epilogue
 template <class TX, class Epi>
 struct Pass {
@@ -559,6 +561,24 @@ static Shape shape_of(const DCsr& a) {
   return sh;
 }
 
+double matrix_bytes(const DCsr& a, int tv, int tx) {
+  const Shape sh = tv == 4   ? shape_of<float, float, float>(a)
+                   : tx == 4 ? shape_of<double, double, float>(a)
+                             : shape_of<double, double, double>(a);
+  const double rows = a.n, entries = (double)a.nnz;
+  switch (sh.kind) {
+    case Shape::EMPTY: return 0.0;
+    case Shape::SLICES: {  // values of all places, the rows' masks, the slices' tables
+      const double places = (double)a.dia_places, slices = (a.n + DIA_ROWS - 1) / DIA_ROWS;
+      return places * tv + rows * (sh.flag ? 2 : 4) + 4.0 * (DIA_DIAG * slices + places / DIA_ROWS);
+    }
+    case Shape::TILED:
+      return entries * (tv + 2) + 4.0 * (rows + 1) + 4.0 * a.tile_cnt * cdiv(a.n, sh.par);
+    default:
+      return entries * (tv + (sh.flag ? 2 : 4)) + 4.0 * (rows + 1) + (sh.flag ? 4.0 * cdiv(a.nnz, COL_CHUNK) : 0.0);
+  }
+}
+
 // e0/e1 (optional): events that the dispatch itself stamps with the
 // kernel's start and end (no extra packets in the stream), for timing one
 // class of launches inside a timed run
@@ -583,7 +603,6 @@ static unsigned batch_blocks(B& b, int nj, bool rev, F blocks) {
   b.rev = rev ? grid / 8 : 0;
   return grid;
 }
-static unsigned cdiv(int64_t a, int64_t b) { return (unsigned)((a + b - 1) / b); }
 
 template <class TM, class TV, class TACC, class TX, class Epi>
 static void launch_slices(const Pass<TX, Epi>* const* p, int nj, bool rev, int rb, hipStream_t s, hipEvent_t e0,
