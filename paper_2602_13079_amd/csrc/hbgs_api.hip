@@ -2028,12 +2028,11 @@ hbgs_status hbgs_setup(hbgs_ctx** out, int32_t n, int64_t nnz, const int32_t* ro
     c->Ap.rp = c->pool.make<int>(n + 1);
     c->Ap.nnz = setup::counts_to_rowptr(len.p, c->Ap.rp, n, s);
     c->Ap.ci = c->pool.make<int>(nnz);
-    c->Ap.v = c->pool.make<double>(nnz);
     c->src = c->pool.make<int>(nnz);
-    setup::permute_fill(n, c->rp0, c->ci0, val, c->perm, c->iperm, c->Ap.rp, c->Ap.ci, c->Ap.v, c->src, s);
+    setup::permute_pattern(n, c->rp0, c->ci0, c->perm, c->iperm, c->Ap.rp, c->Ap.ci, c->src, s);
   }
-  // A_p^T, and for each of its entries the caller's value index (so that a
-  // value update is two gathers)
+  // A_p^T's pattern, and for each of its entries its value's position in A_p's
+  // (so that a value update is two gathers)
   {
     Tmp<double> pos(nnz);
     k_iota_f64<<<grid_for(nnz, 256), 256, 0, s>>>(nnz, pos.p);
@@ -2048,12 +2047,11 @@ hbgs_status hbgs_setup(hbgs_ctx** out, int32_t n, int64_t nnz, const int32_t* ro
   for (DCsr* a : {&c->Ap, &c->ApT}) {
     setup::row_stats(*a, s);
     solve_layout(c->pool, *a, solve::ROWS_CAP_F64, s);
-    if (a->dia_w) {  // the slices' values replace those in row order
+    if (a->v) {  // the transpose's positions, read by now
       HBGS_HIP(hipStreamSynchronize(s));
       c->pool.release(a->v);
-      a->v = nullptr;
-      setup::alloc_slice_values(c->pool, *a, false);
     }
+    make_values(c->pool, *a, false);
   }
   setup::load_values(c->Ap, val, c->src, s);
   Tmp<int> place;

@@ -316,13 +316,11 @@ int64_t counts_to_rowptr(const int* counts, int* rp, int n, hipStream_t s);  // 
 void validate(int n, int64_t nnz, const int* rp, const int* ci, const double* v, int nf, const int* field,
               int* flags, hipStream_t s);
 void field_histogram(int n, const int* field, int nf, int* counts, hipStream_t s);
-void field_ranks(int n, const int* field, int f, const int* f_lo_dev, int* perm, hipStream_t s);
 void field_ranks_all(int n, const int* field, int nf, const int* f_lo_host, int* perm, hipStream_t s);
 void invert_perm(int n, const int* perm, int* iperm, hipStream_t s);
 void permuted_lengths(int n, const int* rp, const int* perm, int* len, hipStream_t s);
-void permute_fill(int n, const int* rp, const int* ci, const double* v, const int* perm, const int* iperm,
-                  const int* rp_p, int* ci_p, double* v_p, int* pos_p, hipStream_t s);
-void scatter_values(int64_t nnz, const double* v, const int* pos, double* v_p, hipStream_t s);
+void permute_pattern(int n, const int* rp, const int* ci, const int* perm, const int* iperm, const int* rp_p,
+                     int* ci_p, int* pos_p, hipStream_t s);
 
 // transpose: t must have rp (m+1), ci, v allocated with a.nnz entries
 void transpose(const DCsr& a, DCsr& t, hipStream_t s);

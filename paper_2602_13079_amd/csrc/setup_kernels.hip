@@ -377,47 +377,29 @@ void permuted_lengths(int n, const int* rp, const int* perm, int* len, hipStream
   HBGS_HIP(hipGetLastError());
 }
 
-// row p of P A P^T: old row iperm[p] with columns mapped and re-sorted
-// (insertion sort carrying value and source position)
-__global__ void k_permute_fill(int n, const int* rp, const int* ci, const double* v, const int* perm,
-                               const int* iperm, const int* rp_p, int* ci_p, double* v_p, int* pos_p) {
+// the pattern of row p of P A P^T: old row iperm[p] with columns mapped and
+// re-sorted (insertion sort), and each entry's position in A
+__global__ void k_permute_pattern(int n, const int* rp, const int* ci, const int* perm, const int* iperm,
+                                  const int* rp_p, int* ci_p, int* pos_p) {
   GRID_STRIDE(p, n) {
     int i = iperm[p];
     int s = rp[i], e = rp[i + 1], o = rp_p[p];
     for (int k = s; k < e; ++k) {
       int c = perm[ci[k]];
-      double x = v[k];
-      int src = k;
       int q = o + (k - s) - 1;
       while (q >= o && ci_p[q] > c) {
         ci_p[q + 1] = ci_p[q];
-        v_p[q + 1] = v_p[q];
         pos_p[q + 1] = pos_p[q];
         --q;
       }
       ci_p[q + 1] = c;
-      v_p[q + 1] = x;
-      pos_p[q + 1] = src;
+      pos_p[q + 1] = k;
     }
   }
 }
-
-// pos_p[q] holds the source entry of permuted entry q; invert it
-__global__ void k_invert_pos(int64_t nnz, int* pos_p, int* tmp) {
-  GRID_STRIDE(q, nnz) tmp[pos_p[q]] = (int)q;
-}
-
-void permute_fill(int n, const int* rp, const int* ci, const double* v, const int* perm, const int* iperm,
-                  const int* rp_p, int* ci_p, double* v_p, int* pos_p, hipStream_t s) {
-  k_permute_fill<<<grid_for(n, BLK), BLK, 0, s>>>(n, rp, ci, v, perm, iperm, rp_p, ci_p, v_p, pos_p);
-  HBGS_HIP(hipGetLastError());
-}
-
-__global__ void k_scatter_values(int64_t nnz, const double* v, const int* pos, double* v_p) {
-  GRID_STRIDE(k, nnz) v_p[pos[k]] = v[k];
-}
-void scatter_values(int64_t nnz, const double* v, const int* pos, double* v_p, hipStream_t s) {
-  k_scatter_values<<<grid_for(nnz, BLK), BLK, 0, s>>>(nnz, v, pos, v_p);
+void permute_pattern(int n, const int* rp, const int* ci, const int* perm, const int* iperm, const int* rp_p,
+                     int* ci_p, int* pos_p, hipStream_t s) {
+  k_permute_pattern<<<grid_for(n, BLK), BLK, 0, s>>>(n, rp, ci, perm, iperm, rp_p, ci_p, pos_p);
   HBGS_HIP(hipGetLastError());
 }
 
