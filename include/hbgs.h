@@ -288,6 +288,17 @@ hbgs_status hbgs_debug_spgemm_route(int32_t route);
  * Returns HBGS_EINVAL for any other value. */
 hbgs_status hbgs_debug_spmv_tiles(int32_t on);
 
+/* Test query: the form in which products read a matrix, out4 = {form, its
+ * parameter, index bits, diagonals}: form 0 no entries, 1 diagonal slices
+ * (parameter: the row-block size whose sums they reproduce; index bits: of a
+ * row's mask; diagonals: most in a slice), 2 row blocks with the operand in
+ * LDS, 3 row blocks, 4 lane groups (parameter: rows per block or lanes per
+ * row; index bits: of a column).  which: 0 the outer operator, 1 its
+ * transpose (field ignored); of field `field`: 2 its finest diagonal block, 3
+ * its couplings, 4 its transposed couplings.  precision: 0 FP64, 1 the mixed
+ * mode.  HBGS_EINVAL for other values. */
+hbgs_status hbgs_debug_layout(hbgs_ctx *ctx, int32_t field, int32_t which, int32_t precision, int32_t *out4);
+
 void hbgs_destroy(hbgs_ctx *ctx);
 const char *hbgs_last_error(void);
 

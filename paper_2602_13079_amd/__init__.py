@@ -73,6 +73,7 @@ EXPORTS = {
     "hbgs_set_allocator": ("i32", ["p", "p", "p"]),
     "hbgs_debug_spgemm_route": ("i32", ["i32"]),
     "hbgs_debug_spmv_tiles": ("i32", ["i32"]),
+    "hbgs_debug_layout": ("i32", ["p", "i32", "i32", "i32", "p"]),
     "hbgs_destroy": (None, ["p"]),
     "hbgs_last_error": ("str", []),
 }
@@ -318,6 +319,14 @@ class Solver:
                                        rp.ctypes.data_as(ctypes.c_void_p), ci.ctypes.data_as(ctypes.c_void_p),
                                        v.ctypes.data_as(ctypes.c_void_p)))
         return rp, ci, v, nc.value
+
+    def debug_layout(self, which, field=0, precision=1):
+        """Test query: (form, parameter, index bits, diagonals) in which products read a matrix; which is "A" or "AT"
+        (outer operator), "block", "couplings" or "couplings_T" (of a field)."""
+        w = {"A": 0, "AT": 1, "block": 2, "couplings": 3, "couplings_T": 4}[which]
+        out = (ctypes.c_int32 * 4)()
+        _check(self.lib.hbgs_debug_layout(self.h, field, w, precision, out))
+        return ("none", "slices", "tiled", "rows", "lanes")[out[0]], out[1], out[2], out[3]
 
     def aggregates(self, field, level):
         nrows = self.get_level(field, level, "A")[0].shape[0] - 1

@@ -2359,6 +2359,27 @@ hbgs_status hbgs_debug_spmv_tiles(int32_t on) {
   return HBGS_OK;
 }
 
+hbgs_status hbgs_debug_layout(hbgs_ctx* c, int32_t field, int32_t which, int32_t precision, int32_t* out4) {
+  if (!c || !out4) {
+    set_error("NULL argument");
+    return HBGS_EINVAL;
+  }
+  HBGS_API_BEGIN
+  require_built(c);
+  if (which < 0 || which > 4 || (which > 1 && (field < 0 || field >= c->nf)) || (precision != 0 && precision != 1))
+    HBGS_FAIL(HBGS_EINVAL, "invalid field/which/precision");
+  if (which == 1 || which == 4) ensure_transpose(c, nullptr);
+  const int t = precision == 1 ? 4 : 8;
+  if (which < 2) {
+    solve::layout_of(which == 0 ? c->Ap : c->ApT, 8, t, out4);
+  } else {
+    const Field& F = c->F[field];
+    solve::layout_of(which == 2 ? F.lv[0].A : which == 3 ? F.lower : F.upperT, t, t, out4);
+  }
+  return HBGS_OK;
+  HBGS_API_END
+}
+
 hbgs_status hbgs_set_allocator(void* (*alloc)(size_t, void*), void (*free_fn)(void*, void*), void* user) {
   if ((alloc == nullptr) != (free_fn == nullptr)) {
     set_error("hbgs_set_allocator: give both functions or neither");

@@ -420,6 +420,8 @@ bool tiles_on();
 // bytes of the matrix itself that a product with values of tv and an operand of
 // tx bytes reads, in the form that its kernel takes it in
 double matrix_bytes(const DCsr& a, int tv, int tx);
+// {form, parameter, index bits, diagonals} of that form (see hbgs_debug_layout)
+void layout_of(const DCsr& a, int tv, int tx, int32_t* out4);
 // kernel classes tracked by the optional profiler
 enum Kind {
   K_SPMV_OUTER = 0,

@@ -561,10 +561,19 @@ static Shape shape_of(const DCsr& a) {
   return sh;
 }
 
+static Shape shape_for(const DCsr& a, int tv, int tx) {
+  if (tv == 4) return shape_of<float, float, float>(a);
+  return tx == 4 ? shape_of<double, double, float>(a) : shape_of<double, double, double>(a);
+}
+void layout_of(const DCsr& a, int tv, int tx, int32_t* out4) {
+  const Shape sh = shape_for(a, tv, tx);
+  out4[0] = (int32_t)sh.kind;
+  out4[1] = sh.par;
+  out4[2] = sh.kind == Shape::EMPTY ? 0 : sh.flag || sh.kind == Shape::TILED ? 16 : 32;
+  out4[3] = sh.kind == Shape::SLICES ? a.dia_w : 0;
+}
 double matrix_bytes(const DCsr& a, int tv, int tx) {
-  const Shape sh = tv == 4   ? shape_of<float, float, float>(a)
-                   : tx == 4 ? shape_of<double, double, float>(a)
-                             : shape_of<double, double, double>(a);
+  const Shape sh = shape_for(a, tv, tx);
   const double rows = a.n, entries = (double)a.nnz;
   switch (sh.kind) {
     case Shape::EMPTY: return 0.0;
