@@ -299,8 +299,9 @@ inline unsigned grid_for(int64_t work, int block, int64_t cap = 1 << 20) {
 // (setup_kernels.hip, compiled without floating-point contraction so that
 // every value matches a sequential, rounded-product-then-add evaluation)
 namespace setup {
-// bytes (a multiple of 4) of device memory to the host, after the work
-// enqueued on s so far: through the thread's mail when it has a scratch
+// bytes (a multiple of 4, at most Mail::kBytes) of device memory to the host,
+// after the work enqueued on s so far: through the thread's mail when it has a
+// scratch
 void read_back(void* dst, const void* src, size_t bytes, hipStream_t s);
 template <class T>
 T read_one(const T* src, hipStream_t s) {

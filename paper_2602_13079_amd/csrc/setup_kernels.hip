@@ -153,9 +153,12 @@ __global__ __launch_bounds__(BLK) void k_mail(const uint32_t* __restrict__ src, 
   for (int t = threadIdx.x; t < words; t += BLK) dst[t] = src[t];
   mail_flag(m);
 }
+// most matrices whose layouts are built together: A, P, R and [A P; P] of
+// every level of a field
+constexpr int MATRICES = 4 * HBGS_MAX_LEVELS;
 void read_back(void* dst, const void* src, size_t bytes, hipStream_t s) {
   Scratch* sc = tmp_scratch();
-  if (!sc || bytes > Mail::kBytes || bytes % 4) {
+  if (!sc) {
     HBGS_HIP(hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s));
     HBGS_HIP(hipStreamSynchronize(s));
     return;
@@ -3003,6 +3006,7 @@ void build_tiles(Pool& pool, DCsr* const* a, const int* rb, int count, hipStream
     HBGS_HIP(hipGetLastError());
   }
   if (!any) return;
+  static_assert(2 * MATRICES * sizeof(int) <= Mail::kBytes, "one message");
   std::vector<int> h(2 * (size_t)count);
   read_back(h.data(), flags.p, h.size() * sizeof(int), s);
   for (int k = 0; k < count; ++k) {
@@ -3432,6 +3436,7 @@ void pack_columns(Pool& pool, DCsr& a, hipStream_t s) {
 void stats_and_columns(Pool& pool, DCsr* const* a, int count, hipStream_t s) {
   if (count <= 0) return;
   constexpr int W = STATS + 1;
+  static_assert(W * MATRICES * sizeof(int) <= Mail::kBytes, "one message");
   Tmp<int> part(W * (size_t)count);
   HBGS_HIP(hipMemsetAsync(part.p, 0, W * (size_t)count * sizeof(int), s));
   for (int k = 0; k < count; ++k) {
