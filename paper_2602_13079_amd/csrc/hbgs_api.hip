@@ -105,14 +105,6 @@ MailArg Mail::next() {
   }
   return {dev_, ++seq_};
 }
-// One turn of a wait that polls: a pause, and now and then the core for
-// another thread (the other fields' launch from threads of their own, and
-// there may be fewer cores than those)
-static inline void poll_pause(unsigned spins) {
-  __builtin_ia32_pause();
-  if ((spins & 127u) == 0) std::this_thread::yield();
-}
-
 const void* Mail::wait(hipStream_t s) {
   const volatile uint64_t* flag = host_;
   for (unsigned spins = 1; *flag != seq_; ++spins) {
@@ -123,7 +115,10 @@ const void* Mail::wait(hipStream_t s) {
       if (e == hipSuccess && *flag != seq_) HBGS_FAIL(HBGS_EHIP, "a setup kernel ended without its result");
       if (e != hipSuccess && e != hipErrorNotReady) HBGS_HIP(e);
     }
-    poll_pause(spins);
+    __builtin_ia32_pause();
+    // the other fields launch from threads of their own, and there may be fewer
+    // cores than those
+    if ((spins & 127u) == 0) std::this_thread::yield();
   }
   std::atomic_thread_fence(std::memory_order_acquire);
   return host_ + 8;
@@ -1611,8 +1606,9 @@ static void wait_estimate(const double* host, hipStream_t s) {
         HBGS_FAIL(HBGS_EHIP, "a GMRES step or norm ended without its result");
       }
       if (e != hipErrorNotReady) HBGS_HIP(e);
+      std::this_thread::yield();
     }
-    poll_pause(spins);
+    __builtin_ia32_pause();
   }
 }
 

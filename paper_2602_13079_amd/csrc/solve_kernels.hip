@@ -1,12 +1,13 @@
 // Solve-phase kernels (gfx950, wave64): everything here is sparse or
 // vector work bound by HBM bandwidth, so no matrix cores are used.
 //
-// CSR kernels process one row per group of LPR lanes (LPR = 1..64 chosen
-// from the mean row length): the value and column streams of consecutive
-// rows are read by consecutive lanes, so a wavefront's loads are coalesced;
-// the partial products are combined with cross-lane shuffles and the row's
-// epilogue (residual, Chebyshev update, transfer accumulation) is fused into
-// the same kernel, so each vector is read and written once per step.
+// A product takes the form of its matrix: diagonal slices, one row per thread
+// (k_slices); row blocks whose entries are streamed and whose products are
+// summed from LDS, the operand staged there too (k_csr_rows_tiled) or gathered
+// (k_csr_rows); a group of lanes per row for what fits neither (k_csr).  Each
+// fuses the row's epilogue (residual, Chebyshev update, transfer accumulation),
+// so each vector is read and written once per step, and each takes the same
+// step of several independent fields in one launch.
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
@@ -47,7 +48,6 @@ struct ColPlain {
     c[2] = t.z;
     c[3] = t.w;
   }
-  bool aligned() const { return reinterpret_cast<uintptr_t>(ci) % 16 == 0; }
 };
 struct ColPacked {
   const uint16_t* __restrict__ cd;
@@ -61,7 +61,6 @@ struct ColPacked {
     c[2] = b + (int)t.z;
     c[3] = b + (int)t.w;
   }
-  bool aligned() const { return reinterpret_cast<uintptr_t>(cd) % 8 == 0; }
 };
 static_assert(COL_CHUNK % 4 == 0, "a group of four entries shares one packed base");
 // values of entries k..k+3 (16-byte loads)
